@@ -521,13 +521,17 @@ tdp_status tdp_profile_read(tdp_graph, double *ms, int32_t *calls);
  *  sweep_mode 2: self-test of those bounded waits: as 1, but the start
  *    points are never published, so every wait gives up.
  *  sweep_mode 3: arrivals one launch per level, required times on a
- *    resident grid (the default where the resident grid is possible).
+ *    resident grid.
+ *  A new graph takes mode 1 where it is possible, otherwise a resident grid
+ *  for each sweep that its precision, max_k and nets allow, until a mode is set.
  *  flow_waves: 64-lane waves per workgroup of the resident grids (1, 2 or
  *    4; 0 keeps; default 4);
  *  flow_per_cu: workgroups per compute unit of the resident grids (1..4,
- *    capped by the kernel's occupancy; 0 keeps; default 1).  The grids must
- *    fit on the GPU beside whatever runs concurrently on other streams; two
- *    such sweeps from different graphs may run at once within 4 per CU.
+ *    capped by the kernel's occupancy; 0 keeps; default 1): the forward grid
+ *    takes that many for the arrivals and three times as many for the
+ *    deviation lists, the backward grid twice as many.  The grids must
+ *    fit on the GPU beside whatever runs concurrently on other streams; at
+ *    the default two such sweeps from different graphs may run at once.
  *  spin_log2: log2 of the poll budget per wait (0 keeps, 1..30).
  * Results do not depend on the tuning: both sweep forms compute every value
  * with the same operations in the same order. */

@@ -195,23 +195,29 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
   ok = ok && dalloc(g, g->load, T.M, es) && dalloc(g, g->dnet, T.S, es) && dalloc(g, g->at, T.P, es) &&
        dalloc(g, g->slew, T.M, es) && dalloc(g, g->rat, T.P, es) &&
        dalloc(g, g->dnet_nm, (size_t)T.n_nm_chunks * CHUNK, es) && dalloc(g, g->drv_as, (size_t)2 * T.M, es) &&
-       dalloc(g, g->fw_a, (size_t)T.n_fw_chunks * CHUNK, es) &&
-       dalloc(g, g->darc, T.A, es) && dalloc(g, g->crit, T.n_comb) && dalloc(g, g->hop, (size_t)T.n_comb * 4) &&
-       dalloc(g, g->hop4, (size_t)T.n_comb * 16) &&
-       dalloc(g, g->cdep, T.M) && dalloc(g, g->ep_slack, T.E, es) &&
+       dalloc(g, g->fw_a, T.A, es) &&
+       dalloc(g, g->darc, T.A, es) && dalloc(g, g->crit, T.n_comb) &&
+       dalloc(g, g->node, (size_t)T.n_comb * (es == 8 ? node_words<double>(g->side_k) : node_words<float>(g->side_k))) &&
+       dalloc(g, g->cdep, T.M) && dalloc(g, g->d_tag, 2) && dalloc(g, g->ep_slack, T.E, es) &&
        dalloc(g, g->red_ep, (size_t)3 * T.num_inst * g->ep_chunks) && dalloc(g, g->red_loss, 4096) &&
        dalloc(g, g->red_wa, 4096) && dalloc(g, g->summary, (size_t)4 * T.num_inst) &&
        dalloc(g, g->inst_nfail, T.num_inst) && dalloc(g, g->d_err, 4) && dalloc(g, g->consts, 4) &&
        upload(g, g->d_inst_req, g->h_inst_req);
-  if (ok && g->side_k > 1)
-    ok = dalloc(g, g->side_cost, (size_t)T.n_comb * g->side_k, es) &&
-         dalloc(g, g->side_pin, (size_t)T.n_comb * g->side_k);
-  // dataflow sweeps: single precision, every net fits one 64-lane chunk
+  // dataflow sweeps: forward in single precision or without deviation lists,
+  // backward where every net fits one 64-lane chunk
+  g->fw_flow_ok = prec == TDP_F32 || g->side_k == 1;
+  g->bw_flow_ok = T.n_big == 0;
   g->flow_ok = prec == TDP_F32 && T.n_big == 0;
-  g->sweep_mode = g->flow_ok ? 3 : 0;
-  if (ok && g->flow_ok) {
-    ok = dalloc(g, g->flow_w, T.M) && dalloc(g, g->flow_r, T.M) && dalloc(g, g->flow_cd, T.M) &&
-         dalloc(g, g->flow_se, (size_t)T.n_comb * g->side_k);
+  g->sweep_mode = g->flow_ok ? 1 : (g->fw_flow_ok || g->bw_flow_ok ? 4 : 0);
+  if (ok && g->bw_flow_ok) ok = dalloc(g, g->flow_r, T.M, es);
+  if (ok && g->fw_flow_ok) {
+    std::vector<int2> turns;
+    const int ng = CHUNK / list_lanes(g->side_k);
+    for (int l = 1; l <= T.D; ++l)
+      for (int c = H.lv.lvl[l - 1]; c < H.lv.lvl[l]; c += ng) turns.push_back(make_int2(c, std::min(ng, H.lv.lvl[l] - c)));
+    g->n_turns = (int32_t)turns.size();
+    ok = upload(g, g->list_turn, turns) && dalloc(g, g->flow_w, (size_t)T.M * (es / 4)) &&
+         (g->side_k == 1 || dalloc(g, g->flow_a, T.A));
   }
   if (ok) {
     const double one[4] = {1.0, 0.0, 0.0, 0.0};
@@ -1092,7 +1098,7 @@ tdp_status tdp_autotune(tdp_graph g, const float *x, const float *y, int32_t n, 
       g->flow_waves = it->second.waves;
       g->flow_per_cu = it->second.per_cu;
       if (choice) {
-        choice[0] = it->second.mode;
+        choice[0] = it->second.mode == 4 ? 0 : it->second.mode;
         choice[1] = it->second.waves;
         choice[2] = it->second.per_cu;
         choice[3] = it->second.us;
@@ -1105,7 +1111,7 @@ tdp_status tdp_autotune(tdp_graph g, const float *x, const float *y, int32_t n, 
   struct Cand {
     int mode, waves, per_cu;
   };
-  std::vector<Cand> cands = {{0, g->flow_waves, g->flow_per_cu}};
+  std::vector<Cand> cands = {{g->flow_ok ? 0 : g->sweep_mode, g->flow_waves, g->flow_per_cu}};
   if (g->flow_ok)
     for (int w : {1, 2, 4})
       for (int pc : {1, 2, 4})
@@ -1161,7 +1167,7 @@ tdp_status tdp_autotune(tdp_graph g, const float *x, const float *y, int32_t n, 
   if (st != TDP_OK) return st;
   const int us = std::isfinite(best) ? (int32_t)std::lround(best * 1000.0f) : -1;
   if (choice) {
-    choice[0] = best_c.mode;
+    choice[0] = best_c.mode == 4 ? 0 : best_c.mode;
     choice[1] = best_c.waves;
     choice[2] = best_c.per_cu;
     choice[3] = us;

@@ -47,8 +47,10 @@ struct Nodes {
 
 template <typename T>
 struct Ctx {
-  const T *at, *darc, *side_cost, *ep_slack, *theta;
-  const int32_t *crit, *side_pin, *cdep;
+  const T *at, *darc, *ep_slack, *theta;
+  const int32_t *crit;
+  const uint64_t *node;
+  const uint32_t *cdep;
   T limit;
 };
 
@@ -79,7 +81,7 @@ __global__ void k_gt_root_flags(Topo tp, const T *__restrict__ ep_slack, const T
 // the roots: each endpoint's critical path
 template <typename T>
 __global__ void k_gt_roots(Topo tp, const int32_t *__restrict__ flag, const int32_t *__restrict__ pos,
-                           const T *__restrict__ ep_slack, const int32_t *__restrict__ cdep, int cap, Nodes<T> nd) {
+                           const T *__restrict__ ep_slack, const uint32_t *__restrict__ cdep, int cap, Nodes<T> nd) {
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= tp.E || !flag[f]) return;
   const int i = pos[f];
@@ -89,7 +91,7 @@ __global__ void k_gt_roots(Topo tp, const int32_t *__restrict__ flag, const int3
   nd.dev[i] = -1;
   nd.par[i] = -1;
   nd.ep[i] = f;
-  nd.cells[i] = cdep[tp.snk_drv[tp.A + f]];
+  nd.cells[i] = (int)(cdep[tp.snk_drv[tp.A + f]] & ID_MASK);
   nd.ndev[i] = 0;
 }
 
@@ -119,21 +121,25 @@ __device__ int gt_children(const Topo &tp, const Ctx<T> &cx, const Nodes<T> &nd,
     nd.dev[o] = t;
     nd.par[o] = i;
     nd.ep[o] = f;
-    nd.cells[o] = cells + 1 - cx.cdep[tp.n_start + tp.snk_comb[t]] + cx.cdep[tp.snk_drv[t]];
+    nd.cells[o] = cells + 1 - (int)(cx.cdep[tp.n_start + tp.snk_comb[t]] & ID_MASK) +
+                  (int)(cx.cdep[tp.snk_drv[t]] & ID_MASK);
     nd.ndev[o] = ndv + 1;
   };
   if constexpr (KM > 1) {
-    const size_t lb = (size_t)(u - tp.n_start) * KM;
+    const int uc = u - tp.n_start;
     int j = 0;
     for (; j < KM; ++j) {
-      const T d = cx.side_cost[lb + j];
+      const T d = list_entry<T, KM>(cx.node, uc, j).cost;
       if (!(d < inf_of<T>())) break;
       const T key = se + (cost + d);
       if (!(key <= th && key < lim)) break;
     }
     if (j < KM) {
       if constexpr (EMIT)
-        for (int q = 0; q < j; ++q) put(out + q, cx.side_pin[lb + q], cost + cx.side_cost[lb + q]);
+        for (int q = 0; q < j; ++q) {
+          const Dev<T> d = list_entry<T, KM>(cx.node, uc, q);
+          put(out + q, d.sink, cost + d.cost);
+        }
       return j;
     }
   }
@@ -257,7 +263,8 @@ __global__ void k_gt_index(int n, int f32, const uint64_t *__restrict__ keys, co
 template <typename T>
 __global__ void __launch_bounds__(128) k_walk_nodes(Topo tp, const int32_t *__restrict__ d_num_paths,
                                                      const int32_t *__restrict__ out_slot, Nodes<T> nd,
-                                                     const int4 *__restrict__ hop4, const int32_t *__restrict__ path_ptr,
+                                                     const uint64_t *__restrict__ recs, int words,
+                                                     const int32_t *__restrict__ path_ptr,
                                                      int32_t *__restrict__ path_pins, int32_t *__restrict__ path_int,
                                                      int32_t *__restrict__ path_ep, int32_t *__restrict__ path_epi,
                                                      T *__restrict__ path_slack, int32_t *__restrict__ err,
@@ -286,7 +293,7 @@ __global__ void __launch_bounds__(128) k_walk_nodes(Topo tp, const int32_t *__re
   ds.nb = 0;
   ds.bi = 0;
   RevWriter w{path_pins, path_int, stage + threadIdx.x * WALK_ROW, live ? hi - 1 : -1, live ? lo : 0, live ? hi : 0};
-  const bool ok = walk_path(tp, hop4, w, f, live, [&]() { return ds.next(); });
+  const bool ok = walk_path(tp, recs, words, w, f, live, [&]() { return ds.next(); });
   if (!live) return;
   if (!ok) atomicOr(err, 1);
   path_ep[q] = tp.snk_ext[tp.A + f];
@@ -376,8 +383,8 @@ tdp_status report_impl(tdp_graph g, const GtStore &st, int K, float slack_limit,
   const Topo &tp = g->topo;
   const int cap = st.cap;
   Nodes<T> nd{(T *)st.gt_cost, (T *)st.gt_key, st.gt_dev, st.gt_par, st.gt_ep, st.gt_cells, st.gt_nd};
-  Ctx<T> cx{(const T *)g->at, (const T *)g->darc, (const T *)g->side_cost, (const T *)g->ep_slack,
-            (const T *)st.gt_theta, g->crit, g->side_pin, g->cdep, (T)slack_limit};
+  Ctx<T> cx{(const T *)g->at, (const T *)g->darc, (const T *)g->ep_slack, (const T *)st.gt_theta, g->crit,
+            g->node, g->cdep, (T)slack_limit};
   int total = 0;
   if (K > 0 && tp.E > 0) {
     // bound from the per-endpoint search at the K worst endpoints
@@ -441,7 +448,7 @@ tdp_status report_impl(tdp_graph g, const GtStore &st, int K, float slack_limit,
   scan_exclusive(g->out_len, g->path_ptr, g->max_out, g->d_num_paths, nullptr, g->scan_tmp, s);
   ptr_tail(g->d_num_paths, g->out_len, g->path_ptr, s);
   hipLaunchKernelGGL(k_walk_nodes<T>, dim3(nb(g->max_out, 128)), dim3(128), 0, s, tp, g->d_num_paths, g->out_slot,
-                     nd, (const int4 *)g->hop4, g->path_ptr, g->path_pins, g->path_int, g->path_ep, g->path_epi,
+                     nd, (const uint64_t *)g->node, node_words<T>(g->side_k), g->path_ptr, g->path_pins, g->path_int, g->path_ep, g->path_epi,
                      (T *)g->path_slack, g->d_err, g->pin_cap);
   // ranks per endpoint (the node store is free again: its arrays serve as scratch)
   const int mo = g->max_out;

@@ -176,6 +176,65 @@ struct Topo {
 
 constexpr int CHUNK = 64;
 
+// Node record of a combinational cell, 64-bit words:
+//   0..7   four hops up its critical chain, two words each: {critical sink,
+//          its driver}, {their external pin ids}; hops past a start point are
+//          {-1, -1}, {0, 0}
+//   8..    with deviation lists, the side_k cheapest deviations along that
+//          chain, ascending: {cost, sink} (single precision: one word; double:
+//          two), padded with {+inf, -1}
+// A list of eight and its hops share one 128-byte line, the unit a random
+// read brings in.  Ids are below 2^30; bits 30-31 of a word's id half (of its
+// first id for the hop words, of the sink for a list entry) and of a chain
+// depth hold a tag, the number of the arrival pass modulo 4: every full pass
+// writes every word, so a word is of this pass exactly if its tag is, and the
+// dataflow sweep's readers wait on the words themselves with nothing cleared
+// between passes.
+constexpr int HOP_WORDS = 8;
+constexpr uint32_t ID_MASK = 0x3FFFFFFFu;
+// lanes per cell where node records are made: one per hop word and list entry
+__host__ __device__ constexpr int list_lanes(int km) { return km < HOP_WORDS ? HOP_WORDS : km; }
+template <typename T>
+__host__ __device__ constexpr int list_words() { return (int)sizeof(T) / 4; }
+template <typename T>
+__host__ __device__ constexpr int node_words(int km) { return HOP_WORDS + (km > 1 ? km * list_words<T>() : 0); }
+__device__ __forceinline__ uint64_t pack_ids(int a, int b, uint32_t tag) {
+  return (uint64_t)(((uint32_t)a & ID_MASK) | tag << 30) | (uint64_t)(uint32_t)b << 32;
+}
+__device__ __forceinline__ uint32_t tag_lo(uint64_t w) { return (uint32_t)w >> 30; }
+__device__ __forceinline__ uint32_t tag_hi(uint64_t w) { return (uint32_t)(w >> 62); }
+// an id of 30 bits, sign-extended (-1 stays -1)
+__device__ __forceinline__ int id30(uint32_t v) { return (int)(v << 2) >> 2; }
+
+// a deviation of a list
+template <typename T> struct Dev { T cost; int32_t sink; };
+__device__ __forceinline__ uint64_t pack_dev(float cost, int sink, uint32_t tag) {
+  return (uint64_t)__float_as_uint(cost) | (uint64_t)(((uint32_t)sink & ID_MASK) | tag << 30) << 32;
+}
+__device__ __forceinline__ Dev<float> unpack_dev(uint64_t w) {
+  return Dev<float>{__uint_as_float((uint32_t)w), id30((uint32_t)(w >> 32))};
+}
+// entry j of the list of combinational cell c
+template <typename T, int KM>
+__device__ __forceinline__ Dev<T> list_entry(const uint64_t *__restrict__ node, int c, int j) {
+  const uint64_t *p = node + (size_t)c * node_words<T>(KM) + HOP_WORDS;
+  if constexpr (sizeof(T) == 4) {
+    return unpack_dev(p[j]);
+  } else {
+    return Dev<T>{__longlong_as_double((long long)p[2 * j]), id30((uint32_t)(p[2 * j + 1] >> 32))};
+  }
+}
+template <typename T, int KM>
+__device__ __forceinline__ void store_entry(uint64_t *__restrict__ node, int c, int j, Dev<T> e, uint32_t tag) {
+  uint64_t *p = node + (size_t)c * node_words<T>(KM) + HOP_WORDS;
+  if constexpr (sizeof(T) == 4) {
+    p[j] = pack_dev(e.cost, e.sink, tag);
+  } else {
+    p[2 * j] = (uint64_t)__double_as_longlong(e.cost);
+    p[2 * j + 1] = pack_dev(0.f, e.sink, tag);
+  }
+}
+
 struct HostLevels {
   std::vector<int32_t> fw_lvl;    // [D+1]: level l input chunks are [fw_lvl[l-1], fw_lvl[l])
   std::vector<int32_t> nm_lvl;    // [D+2]: level l net chunks are [nm_lvl[l], nm_lvl[l+1]) (0 = start points)
@@ -258,22 +317,23 @@ struct tdp_graph_s {
   void *load = nullptr, *dnet = nullptr, *at = nullptr, *slew = nullptr, *rat = nullptr, *darc = nullptr,
        *dnet_nm = nullptr, *drv_as = nullptr, *fw_a = nullptr;
   int32_t *crit = nullptr;       // [n_comb] arc index of the critical input
-  int32_t *hop = nullptr;        // [n_comb][4] {critical sink, its driver, their external ids}
-  int32_t *hop4 = nullptr;       // [n_comb][4][4] the hop records of a cell and of the next three up its chain
-  int32_t *cdep = nullptr;       // [M] combinational cells on the critical chain
-  void *side_cost = nullptr;     // [n_comb][side_k] cheapest deviations along the chain
-  int32_t *side_pin = nullptr;   // [n_comb][side_k]
+  // node records and chain depths, as tagged words (see NodeRec below)
+  uint64_t *node = nullptr;      // [n_comb][node_words]
+  uint32_t *cdep = nullptr;      // [M] combinational cells on the critical chain
+  uint32_t *d_tag = nullptr;     // [2] arrival passes so far; the last dataflow sweep gave up
   void *ep_slack = nullptr;      // [E]
-  // dataflow sweeps (single precision): published words polled by consumers
-  uint64_t *flow_w = nullptr;    // [M] {arrival, transition} of a driver; all ones = not yet
-  uint32_t *flow_r = nullptr;    // [M] required time of a driver; all ones = not yet
-  uint32_t *flow_cd = nullptr;   // [M] chain depth + 1 of a driver; 0 = not yet
-  uint64_t *flow_se = nullptr;   // [n_comb][side_k] deviation entries {cost, sink}; all ones = not yet
+  // dataflow sweeps: published words polled by consumers
+  uint64_t *flow_w = nullptr;    // [M] {arrival, transition} of a driver (double: two words); all ones = not yet
+  uint64_t *flow_a = nullptr;    // [A] {arrival through an input's arc, tag}, with deviation lists
+  int2 *list_turn = nullptr;     // [n_turns] {first cell, cells} of a list wave's turns, level by level
+  int32_t n_turns = 0;
+  void *flow_r = nullptr;        // [M] required time of a driver (its bits, 4 or 8 bytes); all ones = not yet
   int32_t flow_waves = 4, spin_limit = 1 << 20;
   int32_t flow_per_cu = 1;       // workgroups per compute unit of the resident dataflow grids
   int32_t num_cu = 0;            // compute units of the device
   int32_t occ_fw[3] = {-1, -1, -1}, occ_bw[3] = {-1, -1, -1};  // occupancy per 1 / 2 / 4 waves, -1 = not yet
-  bool flow_ok = false;          // the graph can use the dataflow sweeps
+  bool fw_flow_ok = false, bw_flow_ok = false;  // the graph can use the forward / backward dataflow sweep
+  bool flow_ok = false;          // the graph can use sweep modes 1-3
   int32_t pos_gen = 0;           // arrival passes so far; d_err[1] == pos_gen: a position was not finite
   bool flow_r_clear = false;     // flow_r holds no published word (the last net pass reset it)
   bool drv_as_stale = false;     // drv_as (combinational drivers) and fw_a predate the last forward sweep

@@ -113,8 +113,8 @@ __global__ void __launch_bounds__(256) k_valid_counts(const int32_t *__restrict_
 template <typename T, int KM>
 __global__ void __launch_bounds__(64) k_search(Topo tp, int k, T slack_limit, const int32_t *__restrict__ d_nsel,
                                                 const int32_t *__restrict__ sel, const T *__restrict__ ep_slack,
-                                                const int32_t *__restrict__ cdep, const T *__restrict__ side_cost,
-                                                const int32_t *__restrict__ side_pin, T *__restrict__ slot_key,
+                                                const uint32_t *__restrict__ cdep, const uint64_t *__restrict__ node,
+                                                T *__restrict__ slot_key,
                                                 int32_t *__restrict__ slot_dev, int32_t *__restrict__ slot_par,
                                                 int32_t *__restrict__ slot_len, int32_t *__restrict__ slot_cells,
                                                 int32_t *__restrict__ npop_out) {
@@ -167,12 +167,14 @@ __global__ void __launch_bounds__(64) k_search(Topo tp, int k, T slack_limit, co
       const bool more = r + 1 < k && u >= tp.n_start;
       if constexpr (KM > 1) {
         if (more) {
-          d = side_cost[(size_t)(u - tp.n_start) * KM + j];
-          p = side_pin[(size_t)(u - tp.n_start) * KM + j];
+          const Dev<T> e = list_entry<T, KM>(node, u - tp.n_start, j);
+          d = e.cost;
+          p = e.sink;
         }
       }
-      cells = cdep[u];
-      if (dev >= 0) cells += pc + 1 - cdep[tp.n_start + dc];
+      cells = (int)(cdep[u] & ID_MASK);
+      if (dev >= 0) cells += pc + 1 - (int)(cdep[tp.n_start + dc] & ID_MASK);
+      cells = min(max(cells, 0), tp.D);  // (out of range only after a failed update)
     }
     if (live && j == r) {
       okey = sk;
@@ -279,8 +281,8 @@ template <typename T>
 __global__ void __launch_bounds__(128) k_walk(Topo tp, int k, const int32_t *__restrict__ d_num_paths,
                                                const int32_t *__restrict__ out_slot, const int32_t *__restrict__ sel,
                                                const int32_t *__restrict__ slot_dev, const int32_t *__restrict__ slot_par,
-                                               const T *__restrict__ slot_key, const int4 *__restrict__ hop4,
-                                               const int32_t *__restrict__ path_ptr, int32_t *__restrict__ path_pins,
+                                               const T *__restrict__ slot_key, const uint64_t *__restrict__ node,
+                                               int words, const int32_t *__restrict__ path_ptr, int32_t *__restrict__ path_pins,
                                                int32_t *__restrict__ path_int, int32_t *__restrict__ path_ep,
                                                int32_t *__restrict__ path_epi, int32_t *__restrict__ path_rank,
                                                T *__restrict__ path_slack, int32_t *__restrict__ err, int pin_cap) {
@@ -313,7 +315,7 @@ __global__ void __launch_bounds__(128) k_walk(Topo tp, int k, const int32_t *__r
   }
   int di = nd - 1;
   RevWriter w{path_pins, path_int, stage + threadIdx.x * WALK_ROW, live ? hi - 1 : -1, live ? lo : 0, live ? hi : 0};
-  const bool ok = walk_path(tp, hop4, w, f, live, [&]() { return di >= 0 ? devs[di--] : -1; });
+  const bool ok = walk_path(tp, node, words, w, f, live, [&]() { return di >= 0 ? devs[di--] : -1; });
   if (!live) return;
   if (!ok) atomicOr(err, 1);
   const int et = tp.A + f;
@@ -337,7 +339,7 @@ template <typename T, int KM>
 static void launch_search(tdp_graph g, int k, T limit, hipStream_t s) {
   const Topo &tp = g->topo;
   hipLaunchKernelGGL((k_search<T, KM>), dim3(nb(tp.E, 64 / KM)), dim3(64), 0, s, tp, k, limit, g->d_nsel, g->sel_list,
-                     (const T *)g->ep_slack, g->cdep, (const T *)g->side_cost, g->side_pin, (T *)g->slot_key,
+                     (const T *)g->ep_slack, g->cdep, g->node, (T *)g->slot_key,
                      g->slot_dev, g->slot_par, g->slot_len, g->slot_cells, g->sel_npop);
 }
 
@@ -419,7 +421,7 @@ void extract_impl(tdp_graph g, int n, int k, int K, float slack_limit, hipStream
   // walk
   prof_begin(g, TDP_STAGE_WALK, s);
   hipLaunchKernelGGL(k_walk<T>, dim3(nb(g->max_out, 128)), dim3(128), 0, s, tp, k, g->d_num_paths, g->out_slot,
-                     g->sel_list, g->slot_dev, g->slot_par, (const T *)g->slot_key, (const int4 *)g->hop4,
+                     g->sel_list, g->slot_dev, g->slot_par, (const T *)g->slot_key, g->node, node_words<T>(g->side_k),
                      g->path_ptr, g->path_pins, g->path_int, g->path_ep, g->path_epi, g->path_rank,
                      (T *)g->path_slack, g->d_err, g->pin_cap);
   prof_end(g, TDP_STAGE_WALK, s);

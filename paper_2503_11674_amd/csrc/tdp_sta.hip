@@ -34,7 +34,19 @@ namespace tdp {
 // published words of the dataflow sweeps (relaxed device-scope atomics; a
 // consumer polls one word, so no fences are needed)
 constexpr uint64_t W_EMPTY = ~0ull;
-constexpr uint32_t R_EMPTY = ~0u;
+// a published required time: its bits, all ones = not yet (no computed value,
+// NaN included, has that pattern)
+template <typename T> struct ReqWord;
+template <> struct ReqWord<float> {
+  using type = uint32_t;
+  static __device__ __forceinline__ uint32_t bits(float v) { return __float_as_uint(v); }
+  static __device__ __forceinline__ float value(uint32_t w) { return __uint_as_float(w); }
+};
+template <> struct ReqWord<double> {
+  using type = uint64_t;
+  static __device__ __forceinline__ uint64_t bits(double v) { return (uint64_t)__double_as_longlong(v); }
+  static __device__ __forceinline__ double value(uint64_t w) { return __longlong_as_double((long long)w); }
+};
 
 __device__ __forceinline__ uint64_t pub_ld(const uint64_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -100,10 +112,12 @@ __device__ __forceinline__ U load_or_wait(const U *base, int idx, bool want, U e
 
 struct FlowInit {
   uint64_t *w = nullptr;
-  uint32_t *r = nullptr, *cd = nullptr;
-  uint64_t *se = nullptr;
+  void *r = nullptr;
   int32_t *err = nullptr;  // cleared at the start of every update
-  int km = 0;
+  const uint32_t *tag = nullptr;  // the graph's pass counter and whether the last sweep gave up
+  uint64_t *node = nullptr;
+  uint32_t *cd = nullptr;
+  int words = 0;                  // of a node record
   int seed = 1;  // 0: start points are never published (self-test of the bounded waits)
   int reset_blocks = 0;  // trailing workgroups of the net pass that reset the words
 };
@@ -146,32 +160,45 @@ __device__ __forceinline__ void fill_u32(uint32_t *p, size_t n, uint32_t x, size
 // The words the dataflow sweeps poll return to "not yet published" at the
 // start of every update (the start points' words are seeded by the net pass
 // itself, so they are left out here): streaming stores in workgroups of their
-// own beside the net pass's gathers.
+// own beside the net pass's gathers.  The tagged words need this only after a
+// sweep that gave up, which leaves some of them of an older pass.
+template <typename T>
 __device__ __forceinline__ void flow_reset(const FlowInit &fl, const Topo &tp, int b) {
+  constexpr int N = sizeof(T) / 4;
   const size_t nth = (size_t)fl.reset_blocks * blockDim.x, tid = (size_t)b * blockDim.x + threadIdx.x;
   const size_t nc = (size_t)(tp.M - tp.n_start);
-  if (fl.w) {
-    fill_u32((uint32_t *)(fl.w + tp.n_start), 2 * nc, ~0u, tid, nth);
-    fill_u32(fl.cd + tp.n_start, nc, 0u, tid, nth);
-    if (fl.km) fill_u32((uint32_t *)fl.se, 2 * (size_t)tp.n_comb * fl.km, ~0u, tid, nth);
+  if (fl.w) fill_u32((uint32_t *)(fl.w + (size_t)N * tp.n_start), 2 * N * nc, ~0u, tid, nth);
+  if (fl.r) fill_u32((uint32_t *)fl.r, (size_t)tp.M * N, ~0u, tid, nth);
+  if (fl.w && fl.tag[1]) {
+    // id 0 in both halves (a sweep that gives up again reads them as ids)
+    // under the previous pass's tag, where a hop word or a list entry has it
+    const uint32_t old = (fl.tag[0] - 1) << 30;
+    for (size_t i = tid; i < nc * fl.words; i += nth)
+      fl.node[i] = i % fl.words < HOP_WORDS ? (uint64_t)old : (uint64_t)old << 32;
+    fill_u32(fl.cd + tp.n_start, nc, old, tid, nth);
   }
-  if (fl.r) fill_u32(fl.r, (size_t)tp.M, R_EMPTY, tid, nth);
 }
 
 template <typename T>
 __device__ __forceinline__ void start_point(const Topo &tp, const LutView &L, int v, T ld, T in_slew, T clk_slew,
                                             T *__restrict__ at, T *__restrict__ slew, V2<T> *__restrict__ as,
-                                            int32_t *__restrict__ cdep, const FlowInit &fl) {
+                                            uint32_t *__restrict__ cdep, const FlowInit &fl) {
   T a = 0, s = in_slew;
   if (v >= tp.n_pi && v < tp.n_start) lut_pair<T>(L, tp.ff_type[v - tp.n_pi], clk_slew, ld, a, s);
   if (v < tp.n_start) {
     at[v] = a;
     slew[v] = s;
     as[v] = v2<T>(a, s);
-    cdep[v] = 0;
-    if (fl.w) {  // seed the start points' words of the dataflow sweeps
-      fl.w[v] = fl.seed ? pack2((float)a, (float)s) : W_EMPTY;
-      fl.cd[v] = fl.seed ? 1 : 0;
+    // (an incremental pass, without a tag, leaves the depths as they are)
+    if (fl.tag) cdep[v] = (fl.tag[0] - (fl.seed ? 0 : 1)) << 30;
+    // seed the start points' words of the dataflow sweeps
+    if (fl.w) {
+      if constexpr (sizeof(T) == 4) {
+        fl.w[v] = fl.seed ? pack2(a, s) : W_EMPTY;
+      } else {
+        fl.w[2 * (size_t)v] = fl.seed ? (uint64_t)__double_as_longlong(a) : W_EMPTY;
+        fl.w[2 * (size_t)v + 1] = fl.seed ? (uint64_t)__double_as_longlong(s) : W_EMPTY;
+      }
     }
   }
 }
@@ -183,7 +210,7 @@ __device__ __forceinline__ void netpass_chunk(const Topo &tp, const LutView &L, 
                                               const NetModel<T> &nm, T cw, T in_slew, T clk_slew,
                                               T *__restrict__ load, T *__restrict__ dnet, T *__restrict__ dnet_nm,
                                               float2 *__restrict__ cxy_nm, T *__restrict__ at, T *__restrict__ slew,
-                                              V2<T> *__restrict__ as, int32_t *__restrict__ cdep, const FlowInit &fl,
+                                              V2<T> *__restrict__ as, uint32_t *__restrict__ cdep, const FlowInit &fl,
                                               const IncFlags &inc) {
   const int lane = wave_lane();
   const int k = chunk * CHUNK + lane;
@@ -236,11 +263,11 @@ __global__ void __launch_bounds__(256) k_netpass(Topo tp, LutView L, const float
                                                   T clk_slew, T *__restrict__ load, T *__restrict__ dnet,
                                                   T *__restrict__ dnet_nm, float2 *__restrict__ cxy_nm,
                                                   T *__restrict__ at, T *__restrict__ slew,
-                                                  V2<T> *__restrict__ as, int32_t *__restrict__ cdep, FlowInit fl) {
+                                                  V2<T> *__restrict__ as, uint32_t *__restrict__ cdep, FlowInit fl) {
   if (blockIdx.x == 0 && threadIdx.x == 0 && fl.err) *fl.err = 0;
   const int main_blocks = (int)gridDim.x - fl.reset_blocks;
   if ((int)blockIdx.x >= main_blocks) {
-    flow_reset(fl, tp, (int)blockIdx.x - main_blocks);
+    flow_reset<T>(fl, tp, (int)blockIdx.x - main_blocks);
     return;
   }
   const int chunk = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -257,7 +284,7 @@ __global__ void __launch_bounds__(256) k_netpass_marked(Topo tp, LutView L, cons
                                                          T *__restrict__ load, T *__restrict__ dnet,
                                                          T *__restrict__ dnet_nm, float2 *__restrict__ cxy_nm,
                                                          T *__restrict__ at, T *__restrict__ slew,
-                                                         V2<T> *__restrict__ as, int32_t *__restrict__ cdep,
+                                                         V2<T> *__restrict__ as, uint32_t *__restrict__ cdep,
                                                          IncFlags inc) {
   const int chunk = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (chunk >= tp.n_nm_chunks || inc.nm[chunk] != inc.epoch) return;
@@ -272,7 +299,7 @@ __global__ void k_netpass_big(Topo tp, LutView L, const float *__restrict__ x, c
                               const T *__restrict__ tree_wl, T cw, T in_slew, T clk_slew, T *__restrict__ load,
                               T *__restrict__ dnet,
                               T *__restrict__ at, T *__restrict__ slew, V2<T> *__restrict__ as,
-                              int32_t *__restrict__ cdep) {
+                              uint32_t *__restrict__ cdep, FlowInit fl) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= tp.n_big) return;
   const int v = tp.big_net[i];
@@ -290,25 +317,7 @@ __global__ void k_netpass_big(Topo tp, LutView L, const float *__restrict__ x, c
   }
   const T ld = (T)tp.net_cpin[v] + cw * wl;
   load[v] = ld;
-  start_point<T>(tp, L, v, ld, in_slew, clk_slew, at, slew, as, cdep, FlowInit{});
-}
-
-// insert (c, p) into the ascending list (kc, kp); an entry equal to existing
-// ones goes in front of them; the last entry falls off
-template <typename T, int KM>
-__device__ __forceinline__ void insert_front(T (&kc)[KM], int32_t (&kp)[KM], T c, int32_t p) {
-  bool moving = false;
-#pragma unroll
-  for (int j = 0; j < KM; ++j) {
-    const bool go = moving || c <= kc[j];
-    const T oc = kc[j];
-    const int32_t op = kp[j];
-    kc[j] = go ? c : oc;
-    kp[j] = go ? p : op;
-    c = go ? oc : c;
-    p = go ? op : p;
-    moving = go;
-  }
+  start_point<T>(tp, L, v, ld, in_slew, clk_slew, at, slew, as, cdep, fl);
 }
 
 // -------------------------------------------------------------- forward
@@ -318,19 +327,42 @@ __device__ __forceinline__ void insert_front(T (&kc)[KM], int32_t (&kp)[KM], T c
 // launch settled.  A cell's list extends its critical input's driver's list,
 // a dependent load; running it beside the next level's arrivals keeps that
 // round trip off the arrival chain.  fw_a keeps each input's arrival through
-// its arc (per chunk slot) for the list job.
+// its arc (by input) for the list job.
+// a cell's maximum arrival, worst transition and the lane of its first input
+// attaining the maximum (the head when none does, e.g. NaN), from its inputs'
+// a and o; w: the lane's record's last word
+template <typename T>
+__device__ __forceinline__ void cell_max(T a, T o, bool valid, int w, int lane, T &best, T &so, int &argl) {
+  const int head = w & 63, tail = (w >> 8) & 63;
+  if (((w >> 24) & 127) <= 4) {  // every cell of the chunk has <= 4 inputs
+    T ua[4], uo[4];
+    seg_fetch<4>(a, head, tail, ua);
+    seg_fetch<4>(o, head, tail, uo);
+    int aj, oj;
+    best = max_first<4>(ua, aj);
+    so = max_first<4>(uo, oj);
+    argl = head + aj;
+  } else {
+    best = seg_max(a, lane, head, tail);
+    so = seg_max(o, lane, head, tail);
+    const int arg0 = seg_min((valid && a == best) ? lane : 64, lane, head, tail);
+    argl = arg0 <= tail ? arg0 : head;
+  }
+}
+
 template <typename T>
 __device__ __forceinline__ void fw_arrivals(const Topo &tp, const LutView &L, float *s_lut, int chunk, int ch1,
                                             const T *__restrict__ load, const T *__restrict__ dnet,
                                             T *__restrict__ at, T *__restrict__ slew, V2<T> *__restrict__ as,
                                             T *__restrict__ darc, int32_t *__restrict__ crit, T *__restrict__ fw_a,
+                                            uint64_t *__restrict__ node, int words, uint32_t tag,
                                             const IncFlags &inc) {
   const int lane = wave_lane();
-  const int k = chunk * CHUNK + lane;
   // the record and the inputs' loads are issued before the tables are
   // staged, so the latencies overlap (a wave past the level's last chunk
   // reads that chunk's records again and then leaves)
   const int4 rec = tp.fw_rec[(chunk < ch1 ? chunk : ch1 - 1) * CHUNK + lane];
+  const int2 ex = tp.fw_ext[(chunk < ch1 ? chunk : ch1 - 1) * CHUNK + lane];
   const int t = rec.x, s = rec.y, c = rec.z;
   const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
   const bool valid = t >= 0 && chunk < ch1;
@@ -362,27 +394,14 @@ __device__ __forceinline__ void fw_arrivals(const Topo &tp, const LutView &L, fl
     at[tp.M + t] = a_in;
     darc[t] = d;
     a = a_in + d;
+    fw_a[t] = a;  // for the list job
   }
-  fw_a[k] = a;  // -inf in padding slots
-  // the cell's maximum arrival, worst transition and first input attaining
-  // the maximum (the head when none does, e.g. NaN)
   T best, so;
   int argl;
-  if (((rec.w >> 24) & 127) <= 4) {  // every cell of the chunk has <= 4 inputs
-    T ua[4], uo[4];
-    seg_fetch<4>(a, head, tail, ua);
-    seg_fetch<4>(o, head, tail, uo);
-    int aj, oj;
-    best = max_first<4>(ua, aj);
-    so = max_first<4>(uo, oj);
-    argl = head + aj;
-  } else {
-    best = seg_max(a, lane, head, tail);
-    so = seg_max(o, lane, head, tail);
-    const int arg0 = seg_min((valid && a == best) ? lane : 64, lane, head, tail);
-    argl = arg0 <= tail ? arg0 : head;
-  }
-  if (valid && lane == head) {  // (the list job records the critical input's hop)
+  cell_max<T>(a, o, valid, rec.w, lane, best, so, argl);
+  const uint64_t h0 = pack_ids(__shfl(t, argl & 63, 64), __shfl(s, argl & 63, 64), tag);
+  const uint64_t h1 = pack_ids(__shfl(ex.x, argl & 63, 64), __shfl(ex.y, argl & 63, 64), tag);
+  if (valid && lane == head) {
     const int v = tp.n_start + c;
     if (inc.arr && (!same_bits(old.x, best) || !same_bits(old.y, so)))
       inc.drv_chg[v] = inc.epoch;  // a changed output re-times the cells it drives
@@ -390,149 +409,130 @@ __device__ __forceinline__ void fw_arrivals(const Topo &tp, const LutView &L, fl
     slew[v] = so;
     as[v] = v2<T>(best, so);
     crit[c] = argl - head;
+    ulonglong2 *hop = reinterpret_cast<ulonglong2 *>(node + (size_t)c * words);
+    if (inc.arr) {  // the records above copy this hop (the tag is the last full pass's)
+      const ulonglong2 o = *hop;
+      if (o.x != h0 || o.y != h1) inc.drv_lchg[v] = inc.epoch;
+    }
+    *hop = make_ulonglong2(h0, h1);
   }
 }
 
-// hop4 of a cell: its own hop record followed by the first three of its
-// critical input's driver's hop4 (terminal records {-1, -1, 0, 0} past a
-// start point), so a path walk reads four hops per load
+// Lists of cells [.., lc1), LG lanes per cell: the rest of a cell's node
+// record (the arrival job wrote its own hop): the first three hops of its
+// critical input's driver, its chain depth, and its deviation list: the
+// driver's list merged with the cell's own deviations.  Lane j holds entry j
+// of the driver's list and deviation j of the cell; every value's place in the
+// merged list is its rank (own deviations in front of equal entries, in arc
+// order among themselves), counted from broadcasts and ballots, and is stored
+// there directly.  Two dependent loads (the own hop, then everything else) and
+// a few dozen instructions, whatever KM; one lane inserting into a list in
+// registers took a chain of several hundred at KM = 16.
+// ranks of a group's values in the merged list: `shift` own deviations go in
+// front of lane j's entry e, and lane j's own deviation d (index i0 of the
+// cell's inputs, +inf for none) goes to `rank`.  dev(i) gives every lane of
+// the group the cell's deviation i (+inf for the critical input and past the
+// last one), i < nmax; `base`: the group's first lane, `group`: its lanes.
+template <typename T, class F>
+__device__ __forceinline__ void list_ranks(T e, T d, int i0, int nmax, unsigned long long group, F &&dev, int &shift,
+                                           int &rank) {
+  shift = 0;
+  rank = 0;
+  for (int i = 0; i < nmax; ++i) {
+    const T di = dev(i);
+    const bool own = di < pos_inf<T>();
+    shift += own && di <= e;
+    const int less = __popcll(__ballot(e < di) & group);
+    rank += i == i0 ? less : (own && (di < d || (di == d && i < i0)));
+  }
+}
+
 template <typename T, int KM>
-__device__ __forceinline__ void fw_lists(const Topo &tp, int chunk, int lc1, const T *__restrict__ fw_a,
-                                         int32_t *__restrict__ cdep, T *__restrict__ side_cost,
-                                         int32_t *__restrict__ side_pin, int4 *__restrict__ hop4,
-                                         const IncFlags &inc) {
-  if (chunk >= lc1) return;
-  const int lane = wave_lane();
-  const int k = chunk * CHUNK + lane;
-  const int4 rec = tp.fw_rec[k];
-  const int2 ex = tp.fw_ext[k];
-  const int t = rec.x, s = rec.y, c = rec.z;
-  const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
-  const bool valid = t >= 0;
-  const T a = fw_a[k];
-  if (inc.lst) {  // incremental: the chunk was re-timed or an input's driver's list changed
-    const bool mark = (valid && inc.drv_lchg[s] == inc.epoch) || inc.lst[chunk] == inc.epoch;
-    if (__ballot(mark) == 0) return;
+__device__ __forceinline__ void fw_lists(const Topo &tp, int c, int lc1, const T *__restrict__ at,
+                                         const T *__restrict__ fw_a, uint32_t *__restrict__ cdep,
+                                         uint64_t *__restrict__ node, uint32_t tag, const IncFlags &inc) {
+  constexpr int LG = list_lanes(KM), W = node_words<T>(KM);
+  const int lane = wave_lane(), j = lane & (LG - 1), base = lane & ~(LG - 1);
+  bool live = c < lc1;
+  const int cc = live ? c : lc1 - 1;  // (spare groups read the last cell's record and store nothing)
+  const uint64_t own = node[(size_t)cc * W];
+  const int t0 = tp.comb_inptr[cc], n = tp.comb_inptr[cc + 1] - t0;
+  const int pred = (int)(uint32_t)(own >> 32), arg = id30((uint32_t)own) - t0;
+  if (inc.lst) {  // incremental: the cell was re-timed or its critical driver's record changed
+    const bool mark = inc.drv_lchg[pred] == inc.epoch || inc.lst[inc.snk_chunk[t0]] == inc.epoch;
+    live = live && mark;
   }
-  // the same maximum and critical input as the arrival job found
-  const bool narrow = ((rec.w >> 24) & 127) <= 4;  // wave-uniform
-  T ua[4];
-  int ut[4], aj = 0;
-  T best;
-  int argl, pred, tc;
-  int2 exc;
-  if (narrow) {
-    seg_fetch<4>(a, head, tail, ua);
-    seg_fetch<4>(t, head, tail, ut);
-    best = max_first<4>(ua, aj);
-    argl = head + aj;
-  } else {
-    best = seg_max(a, lane, head, tail);
-    const int arg0 = seg_min((valid && a == best) ? lane : 64, lane, head, tail);
-    argl = arg0 <= tail ? arg0 : head;
-  }
-  pred = __shfl(s, argl & 63, 64);
-  tc = __shfl(t, argl & 63, 64);
-  exc = make_int2(__shfl(ex.x, argl & 63, 64), __shfl(ex.y, argl & 63, 64));
-  const bool is_head = valid && lane == head;
-  // Every load from the critical input's driver (its deviation list, hop
-  // records and chain depth) comes before the first store in program order,
-  // so the three share one memory latency (loads are not moved above the
-  // stores).
-  constexpr int KL = KM > 1 ? KM : 1;
-  T kc[KL];
-  int32_t kp[KL];
-#pragma unroll
-  for (int j = 0; j < KL; ++j) {
-    kc[j] = pos_inf<T>();
-    kp[j] = -1;
-  }
+  const bool chain = pred >= tp.n_start;
+  const int pc = chain ? pred - tp.n_start : 0;
+  const T best = at[tp.n_start + cc];
+  const uint32_t cd = ((cdep[pred] + 1) & ID_MASK) | tag << 30;
+  const T a0 = j < n ? fw_a[t0 + j] : pos_inf<T>();
+  uint64_t hw = j & 1 ? pack_ids(0, 0, tag) : pack_ids(-1, -1, tag);
+  if (chain && j < HOP_WORDS - 2) hw = node[(size_t)pc * W + j];
+  Dev<T> e{pos_inf<T>(), -1};
   if constexpr (KM > 1) {
-    if (is_head && pred >= tp.n_start) {
-      const size_t pb = (size_t)(pred - tp.n_start) * KM;
-      load_list<KM>(side_cost + pb, kc);
-      load_list<KM>(side_pin + pb, kp);
-    }
+    if (chain && j < KM) e = list_entry<T, KM>(node, pc, j);
   }
-  // incremental: whether this cell's list, hop records or chain depth change
   bool changed = false;
-  if (is_head) {
-    const int4 none = make_int4(-1, -1, 0, 0);
-    int4 up0 = none, up1 = none, up2 = none;
-    if (pred >= tp.n_start) {
-      const int4 *ph = hop4 + (size_t)(pred - tp.n_start) * 4;
-      up0 = ph[0];
-      up1 = ph[1];
-      up2 = ph[2];
-    }
-    const int32_t cd = cdep[pred];
-    int4 *h = hop4 + (size_t)c * 4;
-    const int4 h0 = make_int4(tc, pred, exc.x, exc.y);
-    if (inc.lst) {
-      auto ne = [](int4 a, int4 b) { return a.x != b.x || a.y != b.y || a.z != b.z || a.w != b.w; };
-      changed = cdep[tp.n_start + c] != cd + 1 || ne(h[0], h0) || ne(h[1], up0) || ne(h[2], up1) || ne(h[3], up2);
-    }
-    cdep[tp.n_start + c] = cd + 1;
-    h[0] = h0;
-    h[1] = up0;
-    h[2] = up1;
-    h[3] = up2;
+  if (inc.lst) {
+    if (live && j < HOP_WORDS - 2) changed = node[(size_t)cc * W + 2 + j] != hw;
+    if (live && j == 0) changed = changed || cdep[tp.n_start + cc] != cd;
   }
+  if (live && j < HOP_WORDS - 2) node[(size_t)cc * W + 2 + j] = hw;
+  if (live && j == 0) cdep[tp.n_start + cc] = cd;
+  const unsigned long long group = ((1ull << LG) - 1) << base;
   if constexpr (KM > 1) {
-    // own deviations, last arc first so that equal costs keep arc order
-    if (narrow) {
-      if (is_head) {
-#pragma unroll
-        for (int j = 3; j >= 0; --j) {
-          const T dj = best - ua[j];
-          if (j <= tail - head && j != aj && dj < pos_inf<T>()) insert_front<T, KM>(kc, kp, dj, ut[j]);
-        }
-      }
-    } else {
-      const T dl = (valid && lane != argl) ? best - a : pos_inf<T>();
-      const int width = wave_max_int(valid ? tail - head + 1 : 0);
-      for (int r = 0; r < width; ++r) {
-        const int j = tail - r;
-        const T dj = __shfl(dl, j & 63, 64);
-        const int tj = __shfl(t, j & 63, 64);
-        if (is_head && j >= head && dj < pos_inf<T>()) insert_front<T, KM>(kc, kp, dj, tj);
-      }
-    }
-    if (is_head) {
-      const size_t cb = (size_t)c * KM;
+    auto place = [&](int pos, Dev<T> v) {
+      if (!live || pos >= KM) return;
       if (inc.lst) {
-        T oc[KM];
-        int32_t op[KM];
-        load_list<KM>(side_cost + cb, oc);
-        load_list<KM>(side_pin + cb, op);
-#pragma unroll
-        for (int j = 0; j < KM; ++j) changed = changed || !same_bits(oc[j], kc[j]) || op[j] != kp[j];
+        const Dev<T> o = list_entry<T, KM>(node, cc, pos);
+        changed = changed || !same_bits(o.cost, v.cost) || o.sink != v.sink;
       }
-      store_list<KM>(side_cost + cb, kc);
-      store_list<KM>(side_pin + cb, kp);
+      store_entry<T, KM>(node, cc, pos, v, tag);
+    };
+    const int nmax = wave_max_int(n);
+    int shift = 0, rank;
+    if (nmax <= LG) {
+      const T d = j < n && j != arg ? best - a0 : pos_inf<T>();
+      list_ranks(e.cost, d, j, nmax, group, [&](int i) { return __shfl(d, base + i, 64); }, shift, rank);
+      if (d < pos_inf<T>()) place(rank, Dev<T>{d, t0 + j});
+    } else {  // a cell with more inputs than lanes
+      auto dev = [&](int i) { return i < n && i != arg ? best - fw_a[t0 + i] : pos_inf<T>(); };
+      for (int b = 0; b < nmax; b += LG) {
+        const T d = dev(b + j);
+        list_ranks(e.cost, d, b + j, nmax, group, dev, shift, rank);
+        if (d < pos_inf<T>()) place(rank, Dev<T>{d, t0 + b + j});
+      }
     }
+    if (j < KM) place(j + shift, e);
   }
-  // the cells this one drives may take it as their critical input
-  if (changed) inc.drv_lchg[tp.n_start + c] = inc.epoch;
+  if (inc.lst) {
+    const unsigned long long any = __ballot(changed);
+    // the cells this one drives may take it as their critical input
+    if (live && j == 0 && (any & group)) inc.drv_lchg[tp.n_start + cc] = inc.epoch;
+  }
 }
 
-// arrival chunks [ch0, ch1) in workgroups [0, n_arr); list chunks [lc0, lc1)
+// arrival chunks [ch0, ch1) in workgroups [0, n_arr); lists of cells [lc0, lc1)
 // in the rest
 template <typename T, int KM>
 __global__ void __launch_bounds__(256) k_forward(Topo tp, LutView L, int ch0, int ch1, int n_arr, int lc0, int lc1,
                                                   const T *__restrict__ load, const T *__restrict__ dnet,
                                                   T *__restrict__ at, T *__restrict__ slew, V2<T> *__restrict__ as,
                                                   T *__restrict__ darc, int32_t *__restrict__ crit,
-                                                  int32_t *__restrict__ cdep,
-                                                  T *__restrict__ side_cost, int32_t *__restrict__ side_pin,
-                                                  T *__restrict__ fw_a, int4 *__restrict__ hop4, IncFlags inc) {
+                                                  uint32_t *__restrict__ cdep, uint64_t *__restrict__ node,
+                                                  T *__restrict__ fw_a, const uint32_t *__restrict__ d_tag,
+                                                  IncFlags inc) {
   extern __shared__ float4 s_lut4[];
   float *s_lut = (float *)s_lut4;
   const int wave = threadIdx.x >> 6;
+  const uint32_t tag = *d_tag & 3u;
   if ((int)blockIdx.x < n_arr)
-    fw_arrivals<T>(tp, L, s_lut, ch0 + blockIdx.x * 4 + wave, ch1, load, dnet, at, slew, as, darc, crit, fw_a, inc);
+    fw_arrivals<T>(tp, L, s_lut, ch0 + blockIdx.x * 4 + wave, ch1, load, dnet, at, slew, as, darc, crit, fw_a, node,
+                   node_words<T>(KM), tag, inc);
   else
-    fw_lists<T, KM>(tp, lc0 + (blockIdx.x - n_arr) * 4 + wave, lc1, fw_a, cdep, side_cost, side_pin, hop4, inc);
+    fw_lists<T, KM>(tp, lc0 + ((blockIdx.x - n_arr) * 256 + threadIdx.x) / list_lanes(KM), lc1, at, fw_a, cdep, node,
+                    tag, inc);
 }
 
 // ------------------------------------------------------------- endpoints
@@ -678,197 +678,289 @@ __global__ void k_backward_big(Topo tp, int i0, int i1, const T *__restrict__ dn
 // to see published last) before the others load theirs, which keeps the
 // polling traffic of the waiting waves off the frontier's way.
 //
-// Forward.  Arrival phase of a chunk: a lane loads its driver's {arrival,
-// transition} word, waiting only if it is not out yet, and the cell's head
-// lane publishes the output's word before anything else.  List phase (head
-// lanes): the chain depth and the deviation list follow the critical input,
-// every entry its own word, loaded at once and waited for only where still
-// empty.  A wave runs the list phase of a chunk after the arrival phase of
-// its next chunk: the list chain trails the arrival chain, and a list phase
-// run at once would hold the wave (and its next arrivals) until the lists
-// below it are out.  Deferral keeps the sweep deadlock-free: give the
-// arrival phase of chunk c the key c and its list phase the key c + W; a
-// phase waits only on phases of smaller keys, and every wave runs its phases
-// in increasing key order (the arrival phase of chunk c, then the list phase
-// of chunk c - W, whose key is also c), so the phase of smallest key not yet
-// done always has its inputs and its wave at it.
-struct FwPend {
-  int4 rec;   // the chunk's record (rec.x = -1: nothing pending)
-  float a;    // arrival through the lane's arc
-  float best; // the cell's arrival
-  int argl;   // lane of the critical input
-  int pred;   // driver of the critical input
-};
-
-template <int KM>
-__device__ __forceinline__ void fw_flow_lists(const Topo &tp, const FwPend &q, int32_t *__restrict__ cdep,
-                                              float *__restrict__ side_cost, int32_t *__restrict__ side_pin,
-                                              uint32_t *__restrict__ fcd, uint64_t *__restrict__ fse,
-                                              int32_t *__restrict__ err, int limit) {
-  const int lane = wave_lane();
-  const int t = q.rec.x, c = q.rec.z;
-  const int head = q.rec.w & 63, tail = (q.rec.w >> 8) & 63;
-  const bool valid = t >= 0;
-  const bool is_head = valid && lane == head;
-  const int pred = q.pred;
-  const int v = tp.n_start + c;
-  // chain depth (+1 in the published word) and deviation list of the
-  // critical input's driver
-  constexpr int KL = KM > 1 ? KM : 1;
-  const bool chain = is_head && pred >= tp.n_start;
-  const size_t pb = chain ? (size_t)(pred - tp.n_start) * KM : 0;
-  uint32_t cdp = is_head ? pub_ld(&fcd[pred]) : 1u;
-  uint64_t pe[KL];
-  bool miss = cdp == 0u;
+// Forward.  Two kinds of workgroups share the launch.  Arrival waves take the
+// chunks: a lane loads its driver's {arrival, transition} word, waiting only if
+// it is not out yet; the cell's head lane publishes the output's word before
+// anything else, then its cell's own hop, and with deviation lists every lane
+// its input's arrival through its arc.  List waves take the cells in order,
+// list_lanes lanes per cell as in the per-level list job: they wait for the
+// cell's own hop (its arrival is out), then for the record of its critical
+// input's driver, and publish the rest of the cell's record.  Every record word
+// says by its tag whether it is this pass's, so each is waited for by itself
+// and no fence is needed.  Arrivals never wait for lists, so the arrival chain
+// runs at its own pace and the list chain trails it; in one wave that did
+// both (lists of a chunk after the arrivals of its next) each level took the
+// time of the slower of the two (200k cells, k = 10: 517 us against 152).
+// Both kinds wait only on lower-numbered chunks or cells and take theirs in
+// increasing order, so the lowest one not yet done can always run.
+// Words idx * N .. idx * N + N - 1 of every lane that wants them.  If some are
+// not out yet, one lane first polls the last word of the highest-numbered
+// missing driver (likely to be published last), so that a waiting wave polls
+// one address rather than 64; then all missing words are loaded again
+// together, one round trip per poll.  Bounded as wait_pub.
+template <int N>
+__device__ __forceinline__ void load_words(const uint64_t *base, int idx, bool want, uint64_t (&w)[N], int32_t *err,
+                                           int limit) {
+  bool miss = false;
 #pragma unroll
-  for (int j = 0; j < KL; ++j) {
-    pe[j] = (KM > 1 && chain) ? pub_ld(&fse[pb + j]) : 0ull;
-    miss = miss || pe[j] == W_EMPTY;
+  for (int q = 0; q < N; ++q) {
+    w[q] = want ? pub_ld(base + (size_t)idx * N + q) : 0ull;
+    miss = miss || w[q] == W_EMPTY;
   }
-  if (__ballot(miss)) {
-    const int p_rep = wave_max_int(miss ? pred : -1);
-    if (lane == 0) (void)wait_pub(&fcd[p_rep], 0u, err, limit);
-    // then every word still missing is loaded again, all at once (one round
-    // trip per poll, not one per word)
-    int it = 0;
-    while (__ballot(miss)) {
-      if (miss) {
-        if (cdp == 0u) cdp = pub_ld(&fcd[pred]);
-#pragma unroll
-        for (int j = 0; j < KL; ++j)
-          if (pe[j] == W_EMPTY) pe[j] = pub_ld(&fse[pb + j]);
-        miss = cdp == 0u;
-#pragma unroll
-        for (int j = 0; j < KL; ++j) miss = miss || pe[j] == W_EMPTY;
-      }
-      if (++it > limit) {
-        if (lane == 0) atomicOr(err, 2);
-        break;
-      }
-      if ((it & 31) == 0 && __ballot(__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) break;
-      if (__ballot(miss)) __builtin_amdgcn_s_sleep(1);
+  if (!__ballot(miss)) return;
+  const int rep = wave_max_int(miss ? idx : -1);
+  wait_rep(base + (size_t)rep * N + N - 1, W_EMPTY, err, limit);
+  for (int it = 0; __ballot(miss); ++it) {
+    if (it > limit) {
+      if (wave_lane() == 0) atomicOr(err, 2);
+      return;
     }
-  }
-  if (is_head) cdep[v] = (int32_t)cdp;
-  if constexpr (KM > 1) {
-    const float dl = (valid && lane != q.argl) ? q.best - q.a : __builtin_huge_valf();
-    const int width = wave_max_int(valid ? tail - head + 1 : 0);
-    float kc[KM];
-    int32_t kp[KM];
+    if ((it & 31) == 31 && __ballot(__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) return;
+    if (miss) {
+      miss = false;
 #pragma unroll
-    for (int j = 0; j < KM; ++j) {
-      kc[j] = chain ? __uint_as_float((uint32_t)pe[j]) : __builtin_huge_valf();
-      kp[j] = chain ? (int32_t)(uint32_t)(pe[j] >> 32) : -1;
-    }
-    // own deviations, last arc first so that equal costs keep arc order
-    for (int r = 0; r < width; ++r) {
-      const int j = tail - r;
-      const float dj = __shfl(dl, j & 63, 64);
-      const int tj = __shfl(t, j & 63, 64);
-      if (is_head && j >= head && dj < __builtin_huge_valf()) insert_front<float, KM>(kc, kp, dj, tj);
-    }
-    if (is_head) {
-      const size_t cb = (size_t)c * KM;
-#pragma unroll
-      for (int j = 0; j < KM; ++j) {
-        pub_st(&fse[cb + j], (uint64_t)__float_as_uint(kc[j]) | ((uint64_t)(uint32_t)kp[j] << 32));
-        side_cost[cb + j] = kc[j];
-        side_pin[cb + j] = kp[j];
+      for (int q = 0; q < N; ++q) {
+        if (w[q] == W_EMPTY) w[q] = pub_ld(base + (size_t)idx * N + q);
+        miss = miss || w[q] == W_EMPTY;
       }
     }
   }
-  if (is_head) pub_st(&fcd[v], cdp + 1);
 }
 
-template <int KM>
-__global__ void __launch_bounds__(256) k_forward_flow(Topo tp, LutView L, const float *__restrict__ load,
-                                                       const float *__restrict__ dnet, float *__restrict__ at,
-                                                       float *__restrict__ slew, float *__restrict__ darc,
-                                                       int32_t *__restrict__ crit, int4 *__restrict__ hop,
-                                                       int32_t *__restrict__ cdep, float *__restrict__ side_cost,
-                                                       int32_t *__restrict__ side_pin, uint64_t *__restrict__ fw,
-                                                       uint32_t *__restrict__ fcd, uint64_t *__restrict__ fse,
-                                                       int32_t *__restrict__ err,
-                                                       int limit) {
-  extern __shared__ float4 s_lut4[];
-  float *s_lut = (float *)s_lut4;
+// arrivals of chunks w0, w0 + W, ...
+template <typename T>
+__device__ __forceinline__ void flow_arrivals(const Topo &tp, const LutView &L, float *s_lut, int w0, int W,
+                                              const T *__restrict__ load, const T *__restrict__ dnet,
+                                              T *__restrict__ at, T *__restrict__ slew, T *__restrict__ darc,
+                                              int32_t *__restrict__ crit, uint64_t *__restrict__ node, int words,
+                                              uint64_t *__restrict__ fa, uint64_t *__restrict__ fw, uint32_t tag,
+                                              int32_t *__restrict__ err, int limit) {
+  constexpr int N = sizeof(T) / 4;  // words of a driver's {arrival, transition}
   const int lane = wave_lane();
-  const int wpb = blockDim.x >> 6;
-  const int W = gridDim.x * wpb;
   const int nch = tp.n_fw_chunks;
-  int chunk = blockIdx.x * wpb + (threadIdx.x >> 6);
-  int4 nrec = make_int4(-1, 0, 0, 0);
-  int2 nex = make_int2(0, 0);
+  int chunk = w0;
+  const int4 norec = make_int4(-1, 0, 0, 0);
+  int4 rec1 = norec, rec2 = norec;  // records of this wave's next two chunks
+  int2 ex1 = make_int2(0, 0);
+  T ld1 = 0, dn1 = 0;
   if (chunk < nch) {
-    nrec = tp.fw_rec[chunk * CHUNK + lane];
-    nex = tp.fw_ext[chunk * CHUNK + lane];
+    rec1 = tp.fw_rec[chunk * CHUNK + lane];
+    ex1 = tp.fw_ext[chunk * CHUNK + lane];
   }
+  if (chunk + W < nch) rec2 = tp.fw_rec[(chunk + W) * CHUNK + lane];
   stage_lut(L, s_lut);
-  FwPend pend;
-  bool pending = false;
+  if (rec1.x >= 0) {
+    ld1 = load[tp.n_start + rec1.z];
+    dn1 = dnet[rec1.x];
+  }
   for (; chunk < nch; chunk += W) {
-    const int4 rec = nrec;
-    const int2 ex = nex;
-    if (chunk + W < nch) {  // the next chunk's static data, in flight while this one waits
-      nrec = tp.fw_rec[(chunk + W) * CHUNK + lane];
-      nex = tp.fw_ext[(chunk + W) * CHUNK + lane];
-    }
+    const int4 rec = rec1;
+    const int2 ex = ex1;
+    const T ld = ld1, dn = dn1;
     const int t = rec.x, s = rec.y, c = rec.z, ty = (rec.w >> 16) & 255;
-    const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
+    const int head = rec.w & 63;
     const bool valid = t >= 0;
-    float a = -__builtin_huge_valf(), o = 0.f;
-    float ld = 0.f, dn = 0.f;
-    if (valid) {
-      ld = load[tp.n_start + c];
-      dn = dnet[t];
+    uint64_t w[N];
+    load_words<N>(fw, s, valid, w, err, limit);
+    // the next chunks' static data, in flight behind this one
+    rec1 = rec2;
+    rec2 = norec;
+    if (rec1.x >= 0) {
+      ld1 = load[tp.n_start + rec1.z];
+      dn1 = dnet[rec1.x];
     }
-    const uint64_t w = load_or_wait(fw, valid ? s : 0, valid, W_EMPTY, err, limit);
+    if (chunk + W < nch) ex1 = tp.fw_ext[(chunk + W) * CHUNK + lane];
+    if (chunk + 2 * W < nch) rec2 = tp.fw_rec[(chunk + 2 * W) * CHUNK + lane];
+    T a = -pos_inf<T>(), o = 0, a_in = 0, d = 0;
     if (valid) {
-      const float a_in = __uint_as_float((uint32_t)w) + dn;
-      float d;
-      lut_lds<float>(s_lut, L.nt, L.ns, L.nl, ty, sink_slew<float>(L.net_model, __uint_as_float((uint32_t)(w >> 32)), dn),
-                     ld, d, o);
-      at[tp.M + t] = a_in;
-      darc[t] = d;
+      T wa, ws;
+      if constexpr (N == 1) {
+        wa = __uint_as_float((uint32_t)w[0]);
+        ws = __uint_as_float((uint32_t)(w[0] >> 32));
+      } else {
+        wa = __longlong_as_double((long long)w[0]);
+        ws = __longlong_as_double((long long)w[N - 1]);
+      }
+      a_in = wa + dn;
+      lut_lds<T>(s_lut, L.nt, L.ns, L.nl, ty, sink_slew<T>(L.net_model, ws, dn), ld, d, o);
       a = a_in + d;
     }
-    const float best = seg_max(a, lane, head, tail);
-    const float so = seg_max(o, lane, head, tail);
-    // first input attaining the maximum (the head when none does, e.g. NaN)
-    const int arg0 = seg_min((valid && a == best) ? lane : 64, lane, head, tail);
-    const int argl = arg0 <= tail ? arg0 : head;
+    T best, so;
+    int argl;
+    cell_max<T>(a, o, valid, rec.w, lane, best, so, argl);
     const bool is_head = valid && lane == head;
     const int v = tp.n_start + c;
-    if (is_head) pub_st(&fw[v], pack2(best, so));
-    const int tc = __shfl(t, argl & 63, 64);
-    const int pred = __shfl(s, argl & 63, 64);
-    const int2 exc = make_int2(__shfl(ex.x, argl & 63, 64), __shfl(ex.y, argl & 63, 64));
     if (is_head) {
+      if constexpr (N == 1) {
+        pub_st(&fw[v], pack2(best, so));
+      } else {
+        pub_st(&fw[2 * (size_t)v], (uint64_t)__double_as_longlong(best));
+        pub_st(&fw[2 * (size_t)v + 1], (uint64_t)__double_as_longlong(so));
+      }
+    }
+    const uint64_t h0 = pack_ids(__shfl(t, argl & 63, 64), __shfl(s, argl & 63, 64), tag);
+    const uint64_t h1 = pack_ids(__shfl(ex.x, argl & 63, 64), __shfl(ex.y, argl & 63, 64), tag);
+    if constexpr (N == 1) {
+      if (fa && valid) pub_st(&fa[t], pack_dev(a, 0, tag));
+    }
+    if (is_head) {
+      pub_st(node + (size_t)c * words, h0);
+      pub_st(node + (size_t)c * words + 1, h1);
       at[v] = best;
       slew[v] = so;
       crit[c] = argl - head;
-      hop[c] = make_int4(tc, pred, exc.x, exc.y);
     }
-    if (pending) fw_flow_lists<KM>(tp, pend, cdep, side_cost, side_pin, fcd, fse, err, limit);
-    pend.rec = rec;
-    pend.a = a;
-    pend.best = best;
-    pend.argl = argl;
-    pend.pred = pred;
-    pending = true;
+    if (valid) {
+      at[tp.M + t] = a_in;
+      darc[t] = d;
+    }
   }
-  if (pending) fw_flow_lists<KM>(tp, pend, cdep, side_cost, side_pin, fcd, fse, err, limit);
+}
+
+// node records of the cells of turns w0, w0 + W, ...: turn q takes turn[q].y
+// cells from turn[q].x on, at most 64 / list_lanes, of one level (two cells of
+// one turn never wait for each other)
+template <typename T, int KM>
+__device__ __forceinline__ void flow_lists(const Topo &tp, const int2 *__restrict__ turn, int turns, int w0, int W,
+                                           uint32_t *__restrict__ cdep,
+                                           uint64_t *__restrict__ node, const uint64_t *__restrict__ fa, uint32_t tag,
+                                           int32_t *__restrict__ err, int limit) {
+  static_assert(KM == 1 || sizeof(T) == 4, "double-precision lists are not published");
+  constexpr int LG = list_lanes(KM), NG = 64 / LG, NW = node_words<T>(KM);
+  const int lane = wave_lane(), j = lane & (LG - 1), base = lane & ~(LG - 1), g = lane / LG;
+  const unsigned long long group = ((1ull << LG) - 1) << base;
+  const uint64_t none = j & 1 ? pack_ids(0, 0, tag) : pack_ids(-1, -1, tag);
+  const uint64_t pad = pack_dev(__builtin_huge_valf(), -1, tag);
+  // (spare groups repeat the turn's last cell and store nothing)
+  auto cell = [&](int2 u) { return u.x + min(g, u.y - 1); };
+  int q = w0;
+  int2 u1 = make_int2(0, 1), u2 = u1;  // this wave's next two turns
+  int nt0 = 0, nt1 = 0;                // the next turn's cells' input ranges
+  if (q < turns) u1 = turn[q];
+  if (q + W < turns) u2 = turn[q + W];
+  if (q < turns) {
+    nt0 = tp.comb_inptr[cell(u1)];
+    nt1 = tp.comb_inptr[cell(u1) + 1];
+  }
+  for (; q < turns; q += W) {
+    const int c = cell(u1);
+    const bool on = g < u1.y;
+    const int last_c = u1.x + u1.y - 1;
+    const int t0 = nt0, n = nt1 - nt0;
+    u1 = u2;
+    if (q + W < turns) {
+      nt0 = tp.comb_inptr[cell(u1)];
+      nt1 = tp.comb_inptr[cell(u1) + 1];
+    }
+    if (q + 2 * W < turns) u2 = turn[q + 2 * W];
+    uint64_t *rec = node + (size_t)c * NW;
+    int it = 0;
+    // bounded waits: false once the polls run out or another wave gave up
+    auto again = [&](bool miss) {
+      if (!__ballot(miss)) return false;
+      if (++it > limit) {
+        if (lane == 0) atomicOr(err, 2);
+        return false;
+      }
+      if ((it & 31) == 0 && __ballot(__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) return false;
+      __builtin_amdgcn_s_sleep(1);
+      return true;
+    };
+    // own hop: lanes 0 and 1 of the group; arrivals through the arcs: lane j's
+    // input.  Where some are missing, one lane first polls the own hop of the
+    // turn's last cell, then all missing words are loaded together
+    uint64_t ow = j < 2 ? pub_ld(rec + j) : none;
+    const bool own_a = KM > 1 && j < n;
+    uint64_t aw = own_a ? pub_ld(fa + t0 + j) : pad;
+    if (__ballot(tag_lo(ow) != tag || tag_hi(aw) != tag)) {
+      const uint64_t *last = node + (size_t)last_c * NW + 1;
+      uint64_t lastw = lane == 0 ? pub_ld(last) : none;
+      while (again(tag_lo(lastw) != tag)) {
+        if (lane == 0) lastw = pub_ld(last);
+      }
+      do {
+        if (tag_lo(ow) != tag) ow = pub_ld(rec + j);
+        if (tag_hi(aw) != tag) aw = pub_ld(fa + t0 + j);
+      } while (again(tag_lo(ow) != tag || tag_hi(aw) != tag));
+    }
+    const int pred = __shfl((int)(uint32_t)(ow >> 32), base, 64);
+    const bool chain = pred >= tp.n_start;
+    const uint64_t *p = node + (size_t)(chain ? pred - tp.n_start : 0) * NW;
+    uint64_t hw = chain && j < HOP_WORDS - 2 ? pub_ld(p + j) : none;
+    uint64_t lw = KM > 1 && chain && j < KM ? pub_ld(p + HOP_WORDS + j) : pad;
+    uint32_t cd = j == 0 ? pub_ld(cdep + pred) : tag << 30;
+    while (again(tag_lo(hw) != tag || tag_hi(lw) != tag || cd >> 30 != tag)) {
+      if (tag_lo(hw) != tag) hw = pub_ld(p + j);
+      if (tag_hi(lw) != tag) lw = pub_ld(p + HOP_WORDS + j);
+      if (cd >> 30 != tag) cd = pub_ld(cdep + pred);
+    }
+    if (on && j < HOP_WORDS - 2) pub_st(rec + 2 + j, hw);
+    if (on && j == 0) pub_st(cdep + tp.n_start + c, ((cd + 1) & ID_MASK) | tag << 30);
+    if constexpr (KM > 1) {
+      const Dev<float> e = unpack_dev(lw);
+      const int arg = __shfl(id30((uint32_t)ow), base, 64) - t0;
+      const int nmax = wave_max_int(n);
+      int shift = 0, rank;
+      if (nmax <= LG) {
+        const float a = unpack_dev(aw).cost;
+        const float best = __shfl(a, base + arg, 64);
+        const float d = j < n && j != arg && best - a < __builtin_huge_valf() ? best - a : __builtin_huge_valf();
+        list_ranks(e.cost, d, j, nmax, group, [&](int i) { return __shfl(d, base + i, 64); }, shift, rank);
+        if (on && d < __builtin_huge_valf() && rank < KM) pub_st(rec + HOP_WORDS + rank, pack_dev(d, t0 + j, tag));
+      } else {  // a cell with more inputs than lanes: its arrivals one by one
+        auto arc = [&](int i) {
+          uint64_t w = pub_ld(fa + t0 + i);
+          while (again(tag_hi(w) != tag)) w = pub_ld(fa + t0 + i);
+          return unpack_dev(w).cost;
+        };
+        const float best = arc(arg);
+        auto dev = [&](int i) {
+          const float d = best - arc(min(i, n - 1));
+          return i < n && i != arg && d < __builtin_huge_valf() ? d : __builtin_huge_valf();
+        };
+        for (int b = 0; b < nmax; b += LG) {
+          const float d = dev(b + j);
+          list_ranks(e.cost, d, b + j, nmax, group, dev, shift, rank);
+          if (on && d < __builtin_huge_valf() && rank < KM) pub_st(rec + HOP_WORDS + rank, pack_dev(d, t0 + b + j, tag));
+        }
+      }
+      if (on && j < KM && j + shift < KM) pub_st(rec + HOP_WORDS + j + shift, lw);
+    }
+  }
+}
+
+// n_arr workgroups of arrival waves, the rest list waves
+template <typename T, int KM>
+__global__ void __launch_bounds__(256) k_forward_flow(Topo tp, LutView L, int n_arr, const int2 *__restrict__ turn,
+                                                       int turns, const T *__restrict__ load,
+                                                       const T *__restrict__ dnet, T *__restrict__ at,
+                                                       T *__restrict__ slew, T *__restrict__ darc,
+                                                       int32_t *__restrict__ crit, uint32_t *__restrict__ cdep,
+                                                       uint64_t *__restrict__ node, uint64_t *__restrict__ fa,
+                                                       uint64_t *__restrict__ fw, const uint32_t *__restrict__ d_tag,
+                                                       int32_t *__restrict__ err, int limit) {
+  extern __shared__ float4 s_lut4[];
+  const int wpb = blockDim.x >> 6, wave = threadIdx.x >> 6;
+  const uint32_t tag = *d_tag & 3u;
+  if ((int)blockIdx.x < n_arr)
+    flow_arrivals<T>(tp, L, (float *)s_lut4, blockIdx.x * wpb + wave, n_arr * wpb, load, dnet, at, slew, darc, crit,
+                     node, node_words<T>(KM), KM > 1 ? fa : nullptr, fw, tag, err, limit);
+  else
+    flow_lists<T, KM>(tp, turn, turns, (blockIdx.x - n_arr) * wpb + wave, ((int)gridDim.x - n_arr) * wpb, cdep, node,
+                      fa, tag, err, limit);
 }
 
 // Backward: chunks from the last; a sink lane loads the required time of its
 // cell's output (the D pin of a flip-flop needs nothing), waiting only if it
 // is not out yet; the driver lane publishes its own.
-__global__ void __launch_bounds__(256) k_backward_flow(Topo tp, const float *__restrict__ dnet_nm,
-                                                        const float *__restrict__ darc, float *__restrict__ rat,
-                                                        uint32_t *__restrict__ fr, int32_t *__restrict__ err,
-                                                        int limit) {
+template <typename T>
+__global__ void __launch_bounds__(256) k_backward_flow(Topo tp, const T *__restrict__ dnet_nm,
+                                                        const T *__restrict__ darc, T *__restrict__ rat,
+                                                        typename ReqWord<T>::type *__restrict__ fr,
+                                                        int32_t *__restrict__ err, int limit) {
+  using RW = typename ReqWord<T>::type;
   const int lane = wave_lane();
-  const float inf = __builtin_huge_valf();
+  const T inf = pos_inf<T>();
   const int wpb = blockDim.x >> 6;
   const int W = gridDim.x * wpb;
   const int nch = tp.n_nm_chunks;
@@ -884,36 +976,21 @@ __global__ void __launch_bounds__(256) k_backward_flow(Topo tp, const float *__r
     const bool sink = p >= 0 && lane != head;
     const int t = p - tp.M;
     const bool comb_in = sink && vo >= 0;
-    const float dn = sink ? dnet_nm[k] : 0.f, da = comb_in ? darc[t] : 0.f;
-    const float rq = sink && !comb_in ? rat[p] : 0.f;  // a D pin's, set at the endpoint
+    const T dn = sink ? dnet_nm[k] : (T)0, da = comb_in ? darc[t] : (T)0;
+    const T rq = sink && !comb_in ? rat[p] : (T)0;  // a D pin's, set at the endpoint
     // outputs are numbered in production order of the forward sweep, so the
     // backward sweep publishes the lowest one last
-    const uint32_t wr = load_or_wait<true>(fr, comb_in ? vo : 0, comb_in, R_EMPTY, err, limit);
-    float r = inf;
+    const RW wr = load_or_wait<true>(fr, comb_in ? vo : 0, comb_in, (RW)~(RW)0, err, limit);
+    T r = inf;
     if (sink) {
-      const float rt = comb_in ? sink_required<float>(p, __uint_as_float(wr), da, rat) : rq;
+      const T rt = comb_in ? sink_required<T>(p, ReqWord<T>::value(wr), da, rat) : rq;
       if (rt != inf) r = rt - dn;
     }
     r = seg_min(r, lane, head, tail);
     if (p >= 0 && lane == head) {
-      pub_st(&fr[p], __float_as_uint(r));
+      pub_st(&fr[p], ReqWord<T>::bits(r));
       rat[p] = r;
     }
-  }
-}
-
-// hop4 from the hop records, for the dataflow forward sweep (the per-level
-// one builds it as it goes): three dependent gathers per cell
-__global__ void __launch_bounds__(256) k_hop4_fill(Topo tp, const int4 *__restrict__ hop, int4 *__restrict__ hop4) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= tp.n_comb) return;
-  int4 cur = hop[c];
-  int4 *h = hop4 + (size_t)c * 4;
-  h[0] = cur;
-  for (int j = 1; j < 4; ++j) {
-    if (cur.x >= 0 && cur.y >= tp.n_start) cur = hop[cur.y - tp.n_start];
-    else cur = make_int4(-1, -1, 0, 0);
-    h[j] = cur;
   }
 }
 
@@ -955,15 +1032,16 @@ template <typename T, int KM>
 static void launch_forward(tdp_graph g, int ch0, int ch1, int lc0, int lc1, const IncFlags &inc, hipStream_t s) {
   const Topo &tp = g->topo;
   const int n_arr = ch1 > ch0 ? nblk(ch1 - ch0, 4) : 0;
-  const int n_lst = lc1 > lc0 ? nblk(lc1 - lc0, 4) : 0;
+  const int n_lst = lc1 > lc0 ? nblk((long long)(lc1 - lc0) * list_lanes(KM), 256) : 0;
   if (n_arr + n_lst == 0) return;
   hipLaunchKernelGGL((k_forward<T, KM>), dim3(n_arr + n_lst), dim3(256), n_arr ? lut_bytes(g->lut) : 0, s, tp,
                      g->lut, ch0, ch1, n_arr, lc0, lc1, (const T *)g->load, (const T *)g->dnet, (T *)g->at,
-                     (T *)g->slew, (V2<T> *)g->drv_as, (T *)g->darc, g->crit, g->cdep,
-                     (T *)g->side_cost, g->side_pin, (T *)g->fw_a, (int4 *)g->hop4, inc);
+                     (T *)g->slew, (V2<T> *)g->drv_as, (T *)g->darc, g->crit, g->cdep, g->node, (T *)g->fw_a,
+                     g->d_tag, inc);
 }
 
-// arrivals of chunks [ch0, ch1) and the lists of [lc0, lc1), the level before
+// arrivals of chunks [ch0, ch1) and the lists of cells [lc0, lc1), the level
+// before
 template <typename T>
 static void forward_level(tdp_graph g, int ch0, int ch1, int lc0, int lc1, const IncFlags &inc, hipStream_t s) {
   switch (g->side_k) {
@@ -980,64 +1058,79 @@ static void forward_level(tdp_graph g, int ch0, int ch1, int lc0, int lc1, const
 template <typename T>
 static void forward_levels(tdp_graph g, const IncFlags &inc, hipStream_t s) {
   const Topo &tp = g->topo;
-  int lc0 = 0, lc1 = 0;  // the previous non-empty level, whose lists are due
+  int lc0 = 0, lc1 = 0;  // cells of the previous non-empty level, whose lists are due
   for (int l = 1; l <= tp.D; ++l) {
     const int ch0 = g->lv.fw_lvl[l - 1], ch1 = g->lv.fw_lvl[l];
     if (ch1 <= ch0) continue;
     forward_level<T>(g, ch0, ch1, lc0, lc1, inc, s);
-    lc0 = ch0;
-    lc1 = ch1;
+    lc0 = g->lv.lvl[l - 1];
+    lc1 = g->lv.lvl[l];
   }
   forward_level<T>(g, 0, 0, lc0, lc1, inc, s);
 }
 
-// workgroups of a resident grid of `waves`-wave workgroups over nch chunks:
-// flow_per_cu per compute unit, within the kernel's occupancy (cached per
-// wave count), and no more than the chunks need
-static int resident_blocks(tdp_graph g, const void *kern, int32_t *occ_cache, int waves, size_t lds, int nch) {
+// workgroups of `waves` waves of a kernel that a compute unit holds (cached per wave count)
+static int occupancy(const void *kern, int32_t *occ_cache, int waves, size_t lds) {
   const int wi = waves == 1 ? 0 : (waves == 2 ? 1 : 2);
   if (occ_cache[wi] < 0) {
     int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * waves, lds) != hipSuccess || occ < 1) occ = 1;
     occ_cache[wi] = occ;
   }
-  const long long per = std::min(occ_cache[wi], g->flow_per_cu);
-  const long long need = nblk(nch, waves);
-  return (int)std::max(1LL, std::min(per * std::max(1, g->num_cu), need));
+  return occ_cache[wi];
 }
 
-template <int KM>
+// `per` resident workgroups per compute unit, but no more than `units` of work (one per wave) need
+static int resident_blocks(tdp_graph g, int per, int waves, int units) {
+  return (int)std::max(1LL, std::min((long long)std::max(1, per) * std::max(1, g->num_cu), (long long)nblk(units, waves)));
+}
+
+// Arrival workgroups: flow_per_cu per compute unit; list workgroups: three
+// times that (a turn of a list wave waits longer and holds fewer cells than a
+// chunk).  With 1 + 3 per compute unit the sweep takes 152 us at 200k cells
+// (k = 10), 329 at 1M (k = 10), 465 at 2M (k = 8); with 1 + 2, 153, 385 and 571;
+// with 1 + 4, 190, 385 and 480 (the waiting waves' polls get in the way); with
+// 2 + 3, 154, 330 and 561.
+constexpr int LIST_PER_ARR = 3;
+
+template <typename T, int KM>
 static void launch_forward_flow(tdp_graph g, hipStream_t s) {
   const Topo &tp = g->topo;
   const int w = g->flow_waves;
-  const int nb = resident_blocks(g, reinterpret_cast<const void *>(&k_forward_flow<KM>), g->occ_fw, w,
-                                 lut_bytes(g->lut), tp.n_fw_chunks);
-  hipLaunchKernelGGL((k_forward_flow<KM>), dim3(nb), dim3(64 * w), lut_bytes(g->lut), s, tp, g->lut,
-                     (const float *)g->load, (const float *)g->dnet, (float *)g->at, (float *)g->slew,
-                     (float *)g->darc, g->crit, (int4 *)g->hop, g->cdep, (float *)g->side_cost, g->side_pin,
-                     g->flow_w, g->flow_cd, g->flow_se, g->d_err, g->spin_limit);
+  const int occ = occupancy(reinterpret_cast<const void *>(&k_forward_flow<T, KM>), g->occ_fw, w, lut_bytes(g->lut));
+  const int pa = std::max(1, std::min(occ / (1 + LIST_PER_ARR), g->flow_per_cu));
+  const int na = resident_blocks(g, pa, w, tp.n_fw_chunks);
+  const int nl = resident_blocks(g, std::min(occ - pa, LIST_PER_ARR * pa), w, g->n_turns);
+  hipLaunchKernelGGL((k_forward_flow<T, KM>), dim3(na + nl), dim3(64 * w), lut_bytes(g->lut), s, tp, g->lut, na,
+                     g->list_turn, g->n_turns,
+                     (const T *)g->load, (const T *)g->dnet, (T *)g->at, (T *)g->slew, (T *)g->darc, g->crit, g->cdep,
+                     g->node, g->flow_a, g->flow_w, g->d_tag, g->d_err, g->spin_limit);
 }
 
+template <typename T>
 static void forward_flow(tdp_graph g, hipStream_t s) {
+  if constexpr (sizeof(T) == 8) return launch_forward_flow<double, 1>(g, s);
   switch (g->side_k) {
-    case 1: launch_forward_flow<1>(g, s); break;
-    case 2: launch_forward_flow<2>(g, s); break;
-    case 4: launch_forward_flow<4>(g, s); break;
-    case 8: launch_forward_flow<8>(g, s); break;
-    case 16: launch_forward_flow<16>(g, s); break;
-    default: launch_forward_flow<32>(g, s); break;
+    case 1: launch_forward_flow<float, 1>(g, s); break;
+    case 2: launch_forward_flow<float, 2>(g, s); break;
+    case 4: launch_forward_flow<float, 4>(g, s); break;
+    case 8: launch_forward_flow<float, 8>(g, s); break;
+    case 16: launch_forward_flow<float, 16>(g, s); break;
+    default: launch_forward_flow<float, 32>(g, s); break;
   }
 }
 
 // net pass: pin positions, net delays, driver loads, start points (and the
-// reset of the dataflow words in trailing workgroups)
+// reset of the dataflow words in trailing workgroups).  sweep: an arrival sweep
+// that writes every node record follows (a new tag)
 template <typename T>
-static void netpass_launch(tdp_graph g, const float *x, const float *y, const FlowInit &fl, hipStream_t s) {
+static void netpass_launch(tdp_graph g, const float *x, const float *y, const FlowInit &fl, bool sweep,
+                           hipStream_t s) {
   const Topo &tp = g->topo;
   const NetModel<T> nm = net_model<T>(g);
   const bool tree = g->lut.net_model == 2;
   const T *tree_wl = tree ? (const T *)g->tree.wl : nullptr;
-  pack_xy(x, y, g->xy, tp.N, s, g->d_err + 1, ++g->pos_gen);
+  pack_xy(x, y, g->xy, tp.N, s, g->d_err + 1, ++g->pos_gen, g->d_err, sweep ? g->d_tag : nullptr);
   const auto k_np = tree ? k_netpass<T, true> : k_netpass<T, false>;
   hipLaunchKernelGGL(k_np, dim3(nblk(tp.n_nm_chunks, 4) + fl.reset_blocks),
                      dim3(256), 0, s, tp, g->lut, g->xy, nm,
@@ -1048,7 +1141,7 @@ static void netpass_launch(tdp_graph g, const float *x, const float *y, const Fl
   if (tp.n_big > 0)
     hipLaunchKernelGGL(k_netpass_big<T>, dim3(nblk(tp.n_big, 64)), dim3(64), 0, s, tp, g->lut, x, y, nm, tree_wl,
                        (T)g->c, (T)g->input_slew, (T)g->clock_slew, (T *)g->load, (T *)g->dnet, (T *)g->at,
-                       (T *)g->slew, (V2<T> *)g->drv_as, g->cdep);
+                       (T *)g->slew, (V2<T> *)g->drv_as, g->cdep, fl);
 }
 
 template <typename T>
@@ -1064,7 +1157,24 @@ template <typename T>
 void netpass_impl(tdp_graph g, const float *x, const float *y, hipStream_t s) {
   FlowInit fl;
   fl.err = g->d_err;
-  netpass_launch<T>(g, x, y, fl, s);
+  fl.tag = g->d_tag;
+  netpass_launch<T>(g, x, y, fl, false, s);
+}
+
+// Which sweeps run as resident dataflow grids.  sweep_mode 1 and 2: both; 3:
+// the backward one only; 4 (the choice for graphs that modes 1-3 do not take:
+// double precision, or a net wider than a chunk): each that the graph allows.
+// A published deviation is one word, so lists in double precision stay with
+// the per-level launches; so do required times where a net is wider than a
+// chunk.  The grids win at every size measured (forward / backward us: 2k
+// cells, k = 10, 48 / 28 against 81 / 58; 200k 152 / 99 against 268 / 199; 2M,
+// k = 8, 465 / 346 against 682 / 557): no kernel boundary per level, static data
+// loaded ahead, and lists off the arrivals' way.
+static bool flow_forward(const tdp_graph_s *g) {
+  return g->sweep_mode == 1 || g->sweep_mode == 2 || (g->sweep_mode == 4 && g->fw_flow_ok);
+}
+static bool flow_backward(const tdp_graph_s *g) {
+  return (g->sweep_mode >= 1 && g->sweep_mode <= 3) || (g->sweep_mode == 4 && g->bw_flow_ok);
 }
 
 // arrivals: net pass, forward sweep, endpoint slacks and WNS / TNS
@@ -1072,34 +1182,27 @@ template <typename T>
 void sta_arrivals_impl(tdp_graph g, const float *x, const float *y, hipStream_t s) {
   const Topo &tp = g->topo;
   const NetModel<T> nm = net_model<T>(g);
-  // sweep_mode 1 and 2: both sweeps as resident dataflow grids; 3: the
-  // backward one only
-  const bool flow = sizeof(T) == 4 && g->flow_ok && (g->sweep_mode == 1 || g->sweep_mode == 2);
-  const bool bflow = sizeof(T) == 4 && g->flow_ok && g->sweep_mode >= 1;
+  const bool flow = flow_forward(g), bflow = flow_backward(g);
   FlowInit fl;
   fl.err = g->d_err;
+  fl.tag = g->d_tag;
   if (flow) {
     fl.w = g->flow_w;
-    fl.cd = g->flow_cd;
-    fl.se = g->flow_se;
-    fl.km = g->side_k > 1 ? g->side_k : 0;
+    fl.node = g->node;
+    fl.words = node_words<T>(g->side_k);
+    fl.cd = g->cdep;
     fl.seed = g->sweep_mode == 2 ? 0 : 1;
   }
-  if (bflow) {
-    fl.r = g->flow_r;
-    fl.reset_blocks = flow ? 1024 : 64;
-  }
+  if (bflow) fl.r = g->flow_r;
+  fl.reset_blocks = flow ? 1024 : (bflow ? 64 : 0);
   prof_begin(g, TDP_STAGE_NETPASS, s);
-  netpass_launch<T>(g, x, y, fl, s);
+  netpass_launch<T>(g, x, y, fl, true, s);
   g->flow_r_clear = bflow;
   prof_end(g, TDP_STAGE_NETPASS, s);
   prof_begin(g, TDP_STAGE_FORWARD, s);
   g->drv_as_stale = flow;  // the dataflow sweep publishes through its own words
   if (flow) {
-    forward_flow(g, s);
-    if (tp.n_comb > 0)
-      hipLaunchKernelGGL(k_hop4_fill, dim3(nblk(tp.n_comb, 256)), dim3(256), 0, s, tp, (const int4 *)g->hop,
-                         (int4 *)g->hop4);
+    forward_flow<T>(g, s);
   } else {
     forward_levels<T>(g, IncFlags{}, s);
   }
@@ -1128,7 +1231,7 @@ __global__ void k_inc_maps(Topo tp, int32_t *__restrict__ snk_chunk, int32_t *__
 }
 
 // {arrival, transition} pairs of the combinational drivers from the two
-// arrays, and each forward slot's arrival through its arc (the same sum the
+// arrays, and each input's arrival through its arc (the same sum the
 // arrival job forms), after a forward sweep that kept neither
 template <typename T>
 __global__ void k_pack_as(Topo tp, const T *__restrict__ at, const T *__restrict__ slew, const T *__restrict__ darc,
@@ -1136,10 +1239,7 @@ __global__ void k_pack_as(Topo tp, const T *__restrict__ at, const T *__restrict
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const int v = tp.n_start + (int)i;
   if (v < tp.M) as[v] = v2<T>(at[v], slew[v]);
-  if (i < (long long)tp.n_fw_chunks * CHUNK) {
-    const int t = tp.fw_rec[i].x;
-    fw_a[i] = t >= 0 ? at[tp.M + t] + darc[t] : -pos_inf<T>();
-  }
+  if (i < tp.A) fw_a[i] = at[tp.M + i] + darc[i];
 }
 
 // the net chunks that hold a moved cell's pins: its output's net and the nets
@@ -1180,7 +1280,7 @@ void sta_arrivals_incremental_impl(tdp_graph g, const float *x, const float *y, 
   inc.nm = g->inc_nm;
   prof_begin(g, TDP_STAGE_NETPASS, s);
   if (g->drv_as_stale && tp.n_comb > 0)
-    hipLaunchKernelGGL(k_pack_as<T>, dim3(nblk(std::max<long long>(tp.n_comb, (long long)tp.n_fw_chunks * CHUNK), 256)),
+    hipLaunchKernelGGL(k_pack_as<T>, dim3(nblk(std::max(tp.n_comb, tp.A), 256)),
                        dim3(256), 0, s, tp, (const T *)g->at, (const T *)g->slew, (const T *)g->darc,
                        (V2<T> *)g->drv_as, (T *)g->fw_a);
   g->drv_as_stale = false;
@@ -1217,19 +1317,20 @@ void inc_maps(tdp_graph g, hipStream_t s) {
 template <typename T>
 void sta_required_impl(tdp_graph g, hipStream_t s) {
   const Topo &tp = g->topo;
-  const bool flow = sizeof(T) == 4 && g->flow_ok && g->sweep_mode >= 1;  // modes 1-3
+  const bool flow = flow_backward(g);
   prof_begin(g, TDP_STAGE_BACKWARD, s);
   if (flow) {
     // the words are reset by a full arrival pass that plans this sweep; after
     // any other (incremental, per-level, or none since the last sweep) they
     // are reset here
-    if (!g->flow_r_clear) fill_i32(reinterpret_cast<int32_t *>(g->flow_r), tp.M, (int32_t)R_EMPTY, s);
+    if (!g->flow_r_clear) fill_i32(reinterpret_cast<int32_t *>(g->flow_r), tp.M * (int)(sizeof(T) / 4), -1, s);
     g->flow_r_clear = false;
+    // twice flow_per_cu: 346 us against 379 at 2M cells, no difference at 200k
     const int w = g->flow_waves;
-    const int nb = resident_blocks(g, reinterpret_cast<const void *>(&k_backward_flow), g->occ_bw, w, 0,
-                                   tp.n_nm_chunks);
-    hipLaunchKernelGGL(k_backward_flow, dim3(nb), dim3(64 * w), 0, s, tp,
-                       (const float *)g->dnet_nm, (const float *)g->darc, (float *)g->rat, g->flow_r, g->d_err,
+    const int occ = occupancy(reinterpret_cast<const void *>(&k_backward_flow<T>), g->occ_bw, w, 0);
+    const int nb = resident_blocks(g, std::min(occ, 2 * g->flow_per_cu), w, tp.n_nm_chunks);
+    hipLaunchKernelGGL(k_backward_flow<T>, dim3(nb), dim3(64 * w), 0, s, tp, (const T *)g->dnet_nm,
+                       (const T *)g->darc, (T *)g->rat, (typename ReqWord<T>::type *)g->flow_r, g->d_err,
                        g->spin_limit);
     prof_end(g, TDP_STAGE_BACKWARD, s);
     return;

@@ -107,8 +107,8 @@ struct LinkDevs {
 // four cells along it; a deviation cell leaves the chain and ends the lane's
 // step early.
 template <class Next>
-__device__ __forceinline__ bool walk_path(const Topo &tp, const int4 *__restrict__ hop4, RevWriter &w, int f,
-                                          bool live, Next &&next) {
+__device__ __forceinline__ bool walk_path(const Topo &tp, const uint64_t *__restrict__ node, int words, RevWriter &w,
+                                          int f, bool live, Next &&next) {
   const int lo = w.lo;
   int v = 0, dt = -1, dc = -1;
   bool done = !live;
@@ -125,7 +125,7 @@ __device__ __forceinline__ bool walk_path(const Topo &tp, const int4 *__restrict
   w.flush();
   for (int step = 1; __ballot(!done && w.pos >= lo); ++step) {
     if (!done && w.pos >= lo) {
-      const int4 *hp = hop4 + (size_t)(v - tp.n_start) * 4;
+      const int4 *hp = reinterpret_cast<const int4 *>(node + (size_t)(v - tp.n_start) * words);
       const int4 g0 = hp[0], g1 = hp[1], g2 = hp[2], g3 = hp[3];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -141,9 +141,9 @@ __device__ __forceinline__ bool walk_path(const Topo &tp, const int4 *__restrict
           dc = dt >= 0 ? tp.snk_comb[dt] : -1;
         } else {
           const int4 h = i == 0 ? g0 : (i == 1 ? g1 : (i == 2 ? g2 : g3));
-          t = h.x;
+          t = id30((uint32_t)h.x);
           nv = h.y;
-          text = h.z;
+          text = (int)((uint32_t)h.z & ID_MASK);
           nvext = h.w;
         }
         if (w.pos < lo) {
