@@ -92,6 +92,12 @@ static double required_time(tdp_precision prec, float period, float setup) {
   return prec == TDP_F32 ? (double)(period - setup) : (double)period - (double)setup;
 }
 
+// state words of the one-launch prefix sums: the most tiles any of them has, times its values
+static size_t look_words(const Topo &T, int slots) {
+  const size_t t = 4096;
+  return 2 * (std::max({(size_t)T.S, (size_t)T.N, (size_t)T.E, 2 * (size_t)slots}) / t + 2) + T.num_inst;
+}
+
 // host-side copies kept for export / import
 struct HostSide {
   std::vector<int32_t> snk_ext;
@@ -225,15 +231,16 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
   }
   // extraction
   const int sc = g->slot_cap, mo = g->max_out, ni = T.num_inst;
-  const int scan_cap = std::max({T.S, T.N, T.E, mo, sc, sort_hist_size(sc)});
+  const int scan_cap = std::max({T.S, T.N, T.E, mo, sc});
   ok = ok && dalloc(g, g->sel_flag, T.E) && dalloc(g, g->sel_pos, T.E) && dalloc(g, g->sel_list, T.E) &&
-       dalloc(g, g->d_nsel, 1) && dalloc(g, g->inst_nsel, ni) && dalloc(g, g->inst_nvalid, ni) &&
-       dalloc(g, g->inst_seg, ni) && dalloc(g, g->inst_outb, ni) && dalloc(g, g->inst_kept, ni) &&
-       dalloc(g, g->inst_selb, ni) && dalloc(g, g->sel_npop, T.E) &&
+       dalloc(g, g->d_nsel, 1) && dalloc(g, g->sel_cut, (size_t)4 * ni) &&
+       dalloc(g, g->inst_outb, ni) && dalloc(g, g->inst_kept, ni) && dalloc(g, g->inst_selb, (size_t)ni + 1) &&
+       dalloc(g, g->look_st, look_words(T, sc)) && dalloc(g, g->look_ctr, 4) &&
+       dalloc(g, g->order_hist, (size_t)64 << 8) && dalloc(g, g->order_total, 64) && dalloc(g, g->order_flags, 65) &&
        dalloc(g, g->slot_key, sc, es) && dalloc(g, g->slot_dev, sc) && dalloc(g, g->slot_par, sc) &&
-       dalloc(g, g->slot_len, sc) && dalloc(g, g->slot_out, std::max(sc, mo)) && dalloc(g, g->slot_cells, sc) && dalloc(g, g->d_nslots, 1) &&
+       dalloc(g, g->slot_len, sc) && dalloc(g, g->slot_out, std::max(sc, mo)) && dalloc(g, g->d_nslots, 1) &&
        dalloc(g, g->sort_k0, sc) && dalloc(g, g->sort_k1, sc) && dalloc(g, g->sort_v0, sc) &&
-       dalloc(g, g->sort_v1, sc) && dalloc(g, g->sort_hist, sort_hist_size(sc)) &&
+       dalloc(g, g->sort_v1, sc) && dalloc(g, g->sort_hist, sort_hist_size(sc, 11)) &&
        dalloc(g, g->scan_tmp, scan_tmp_size(scan_cap)) && dalloc(g, g->out_slot, mo) &&
        dalloc(g, g->out_len, mo) && dalloc(g, g->path_ptr, (size_t)mo + 1) && dalloc(g, g->path_pins, g->pin_cap) &&
        dalloc(g, g->path_int, g->pin_cap) && dalloc(g, g->path_ep, mo) && dalloc(g, g->path_epi, mo) &&
@@ -600,14 +607,13 @@ tdp_status ensure_global(tdp_graph g) {
   const Topo &T = g->topo;
   const int cap = report_node_cap(g);
   const size_t es = g->esz;
-  const int scan_cap = std::max(cap, sort_hist_size(cap));
   const bool ok = dalloc(g, g->gt_cost, cap, es) && dalloc(g, g->gt_key, cap, es) &&
                   dalloc(g, g->gt_theta, T.num_inst, es) && dalloc(g, g->gt_dev, cap) && dalloc(g, g->gt_par, cap) &&
                   dalloc(g, g->gt_ep, cap) && dalloc(g, g->gt_cells, cap) && dalloc(g, g->gt_nd, cap) &&
                   dalloc(g, g->gt_cnt, cap) && dalloc(g, g->gt_off, cap) && dalloc(g, g->gt_start, T.num_inst) &&
                   dalloc(g, g->gt_end, T.num_inst) && dalloc(g, g->gt_misc, 4) && dalloc(g, g->gt_k0, cap) &&
                   dalloc(g, g->gt_k1, cap) && dalloc(g, g->gt_v0, cap) && dalloc(g, g->gt_v1, cap) &&
-                  dalloc(g, g->gt_hist, sort_hist_size(cap)) && dalloc(g, g->gt_scan, scan_tmp_size(scan_cap));
+                  dalloc(g, g->gt_hist, sort_hist_size(cap, GT_DIGIT_BITS)) && dalloc(g, g->gt_scan, scan_tmp_size(cap));
   if (!ok) return fail(g, TDP_E_NOMEM, "report_timing: device allocation failed");
   g->gcap = cap;
   return TDP_OK;
@@ -661,7 +667,6 @@ tdp_status scratch_address(tdp_graph g, unsigned char **out) {
 // the bytes it needs (more than limit: nothing carved)
 size_t carve_store(const tdp_graph_s *g, int cap, unsigned char *base, size_t limit, GtStore &st) {
   const size_t es = g->esz, ni = (size_t)g->topo.num_inst;
-  const int scan_cap = std::max(cap, sort_hist_size(cap));
   size_t off = 0;
   auto take = [&](size_t bytes) -> void * {
     void *p = base + off;
@@ -687,8 +692,8 @@ size_t carve_store(const tdp_graph_s *g, int cap, unsigned char *base, size_t li
   st.gt_k1 = (uint64_t *)take(c * 8);
   st.gt_v0 = (uint32_t *)take(c * 4);
   st.gt_v1 = (uint32_t *)take(c * 4);
-  st.gt_hist = (int32_t *)take((size_t)sort_hist_size(cap) * 4);
-  st.gt_scan = (int32_t *)take((size_t)scan_tmp_size(scan_cap) * 4);
+  st.gt_hist = (int32_t *)take((size_t)sort_hist_size(cap, GT_DIGIT_BITS) * 4);
+  st.gt_scan = (int32_t *)take((size_t)scan_tmp_size(cap) * 4);
   if (off > limit) st = GtStore{};
   return off;
 }
@@ -965,10 +970,9 @@ tdp_status tdp_density_setup(tdp_graph g, const tdp_density_grid *grid, const fl
   const int bins = q.bins_x * q.bins_y, K = 2 * q.radius + 1;
   bool ok = true;
   if (!g->dn_area) {
-    const int scan_cap = std::max(std::max(N, 1), sort_hist_size(std::max(N, 1)));
     ok = dalloc(g, g->dn_area, N) && dalloc(g, g->dn_k0, N) && dalloc(g, g->dn_k1, N) && dalloc(g, g->dn_v0, N) &&
-         dalloc(g, g->dn_v1, N) && dalloc(g, g->dn_hist, sort_hist_size(std::max(N, 1))) &&
-         dalloc(g, g->dn_scan, scan_tmp_size(scan_cap)) && dalloc(g, g->dn_part, 2 * density_parts()) &&
+         dalloc(g, g->dn_v1, N) && dalloc(g, g->dn_hist, sort_hist_size(std::max(N, 1), 11)) &&
+         dalloc(g, g->dn_part, 2 * density_parts()) &&
          dalloc(g, g->nest_part, 2 * density_parts()) && dalloc(g, g->nest_alpha, 1) && dalloc(g, g->dn_nheavy, 1);
   }
   if (ok && bins > g->dn_alloc_bins) {  // a smaller grid reuses the buffers
@@ -984,7 +988,7 @@ tdp_status tdp_density_setup(tdp_graph g, const tdp_density_grid *grid, const fl
     return fail(g, TDP_E_DEVICE, "density: area upload failed");
   int bits = 0;
   while (bits < 62 && ((int64_t)1 << bits) < (int64_t)bins) ++bits;
-  g->dn_key_bits = std::max(8, (bits + 7) / 8 * 8);
+  g->dn_key_bits = std::max(1, bits);
   g->dn = DensityGrid{q.x0, q.y0, q.bin_w, q.bin_h, q.target, q.bins_x, q.bins_y, q.radius};
   g->dn_total_area = total;
   g->dn_ready = true;

@@ -58,14 +58,11 @@ struct Ctx {
 // (sorted by (instance, slack); unfound slots are +inf and sort last), or
 // +inf when fewer than K were found
 template <typename T>
-__global__ void k_gt_theta0(int num_inst, int k, int K, const int32_t *__restrict__ inst_nsel,
-                            const int32_t *__restrict__ inst_nvalid, const uint32_t *__restrict__ perm,
-                            const T *__restrict__ slot_key, T *__restrict__ theta) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  int s = 0;
-  for (int i = 0; i < num_inst; ++i) {
-    theta[i] = inst_nvalid[i] >= K ? slot_key[perm[s + K - 1]] : inf_of<T>();
-    s += inst_nsel[i] * k;
+__global__ void k_gt_theta0(int num_inst, int k, int K, const int32_t *__restrict__ inst_selb,
+                            const uint32_t *__restrict__ perm, const T *__restrict__ slot_key, T *__restrict__ theta) {
+  for (int i = threadIdx.x; i < num_inst; i += blockDim.x) {
+    const int s = inst_selb[i] * k, n = inst_selb[i + 1] * k - s;
+    theta[i] = n >= K ? slot_key[perm[s + K - 1]] : inf_of<T>();
   }
 }
 
@@ -362,18 +359,18 @@ bool read_i32(const int32_t *d, int32_t *h, hipStream_t s) {
   return hipStreamSynchronize(s) == hipSuccess && hipMemcpy(h, d, 4, hipMemcpyDeviceToHost) == hipSuccess;
 }
 
-// sort nodes [0, n) by (instance, slack) into gt_k0 / gt_v0 and find each
-// instance's range
+// sort nodes [0, n) by (instance, slack) and find each instance's range
 template <typename T>
-void sort_nodes(tdp_graph g, const GtStore &st, const Nodes<T> &nd, int n, hipStream_t s) {
+Sorted<uint64_t> sort_nodes(tdp_graph g, const GtStore &st, const Nodes<T> &nd, int n, hipStream_t s) {
   const Topo &tp = g->topo;
   hipLaunchKernelGGL(k_gt_keys<T>, dim3(nb(n, 256)), dim3(256), 0, s, tp, n, nd.ep, nd.key, st.gt_k0, st.gt_v0);
-  radix_sort(st.gt_k0, st.gt_v0, st.gt_k1, st.gt_v1, n, nullptr, sizeof(T) == 4 ? g->key_bits32 : 64, st.gt_hist,
-             st.gt_scan, s);
+  const Sorted<uint64_t> so = radix_sort(st.gt_k0, st.gt_v0, st.gt_k1, st.gt_v1, n, nullptr,
+                                         sizeof(T) == 4 ? g->key_bits32 : 64, GT_DIGIT_BITS, st.gt_hist, s);
   fill_i32(st.gt_start, tp.num_inst, 0, s);
   fill_i32(st.gt_end, tp.num_inst, 0, s);
-  hipLaunchKernelGGL(k_gt_segments, dim3(nb(n, 256)), dim3(256), 0, s, n, sizeof(T) == 4 ? 1 : 0, st.gt_k0,
+  hipLaunchKernelGGL(k_gt_segments, dim3(nb(n, 256)), dim3(256), 0, s, n, sizeof(T) == 4 ? 1 : 0, so.keys,
                      st.gt_start, st.gt_end);
+  return so;
 }
 
 }  // namespace
@@ -391,9 +388,9 @@ tdp_status report_impl(tdp_graph g, const GtStore &st, int K, float slack_limit,
     const int k = g->max_k;
     select_stage<T>(g, K, s);
     search_stage<T>(g, k, slack_limit, s);
-    slot_sort_stage<T>(g, k, s);
-    hipLaunchKernelGGL(k_gt_theta0<T>, dim3(1), dim3(1), 0, s, tp.num_inst, k, K, g->inst_nsel, g->inst_nvalid,
-                       g->sort_v0, (const T *)g->slot_key, (T *)st.gt_theta);
+    const Sorted<uint64_t> so = slot_sort_stage<T>(g, k, s);
+    hipLaunchKernelGGL(k_gt_theta0<T>, dim3(1), dim3(256), 0, s, tp.num_inst, k, K, g->inst_selb, so.vals,
+                       (const T *)g->slot_key, (T *)st.gt_theta);
     constexpr int kMaxRestarts = 64;
     for (int attempt = 0;; ++attempt) {
       if (attempt == kMaxRestarts)
@@ -423,8 +420,8 @@ tdp_status report_impl(tdp_graph g, const GtStore &st, int K, float slack_limit,
       total = fe;
       if (!over) break;
       // the store is full of real paths: tighten the bound and start again
-      sort_nodes<T>(g, st, nd, cap, s);
-      hipLaunchKernelGGL(k_gt_refine<T>, dim3(1), dim3(1), 0, s, tp.num_inst, K, st.gt_start, st.gt_end, st.gt_v0,
+      const Sorted<uint64_t> so = sort_nodes<T>(g, st, nd, cap, s);
+      hipLaunchKernelGGL(k_gt_refine<T>, dim3(1), dim3(1), 0, s, tp.num_inst, K, st.gt_start, st.gt_end, so.vals,
                          (const T *)st.gt_key, (T *)st.gt_theta, st.gt_misc);
       int32_t moved = 0;
       if (!read_i32(st.gt_misc + 2, &moved, s)) return gt_fail(g, TDP_E_DEVICE, "report_timing: count copy failed");
@@ -433,8 +430,9 @@ tdp_status report_impl(tdp_graph g, const GtStore &st, int K, float slack_limit,
     }
   }
   // order, cut to K per instance, walk
+  Sorted<uint64_t> so{st.gt_k0, st.gt_v0};
   if (total > 0) {
-    sort_nodes<T>(g, st, nd, total, s);
+    so = sort_nodes<T>(g, st, nd, total, s);
   } else {
     fill_i32(st.gt_start, tp.num_inst, 0, s);
     fill_i32(st.gt_end, tp.num_inst, 0, s);
@@ -443,7 +441,7 @@ tdp_status report_impl(tdp_graph g, const GtStore &st, int K, float slack_limit,
                      g->inst_kept, g->d_num_paths, g->d_nslots);
   if (total > 0)
     hipLaunchKernelGGL(k_gt_index<T>, dim3(nb(total, 256)), dim3(256), 0, s, total, sizeof(T) == 4 ? 1 : 0,
-                       st.gt_k0, st.gt_v0, st.gt_start, g->inst_outb, g->inst_kept, st.gt_cells, g->out_slot,
+                       so.keys, so.vals, st.gt_start, g->inst_outb, g->inst_kept, st.gt_cells, g->out_slot,
                        g->out_len, g->slot_out);
   scan_exclusive(g->out_len, g->path_ptr, g->max_out, g->d_num_paths, nullptr, g->scan_tmp, s);
   ptr_tail(g->d_num_paths, g->out_len, g->path_ptr, s);
@@ -454,13 +452,13 @@ tdp_status report_impl(tdp_graph g, const GtStore &st, int K, float slack_limit,
   const int mo = g->max_out;
   hipLaunchKernelGGL(k_gt_rank_keys, dim3(nb(mo, 256)), dim3(256), 0, s, g->d_num_paths, g->path_epi, st.gt_k0,
                      st.gt_v0);
-  radix_sort(st.gt_k0, st.gt_v0, st.gt_k1, st.gt_v1, mo, g->d_num_paths, 32, st.gt_hist, st.gt_scan, s);
-  hipLaunchKernelGGL(k_gt_rank_heads, dim3(nb(mo, 256)), dim3(256), 0, s, g->d_num_paths, st.gt_k0, st.gt_cnt);
+  so = radix_sort(st.gt_k0, st.gt_v0, st.gt_k1, st.gt_v1, mo, g->d_num_paths, 32, GT_DIGIT_BITS, st.gt_hist, s);
+  hipLaunchKernelGGL(k_gt_rank_heads, dim3(nb(mo, 256)), dim3(256), 0, s, g->d_num_paths, so.keys, st.gt_cnt);
   scan_exclusive(st.gt_cnt, st.gt_off, mo, g->d_num_paths, nullptr, st.gt_scan, s);
   hipLaunchKernelGGL(k_gt_rank_starts, dim3(nb(mo, 256)), dim3(256), 0, s, g->d_num_paths, st.gt_cnt, st.gt_off,
                      st.gt_dev);
   hipLaunchKernelGGL(k_gt_rank_write, dim3(nb(mo, 256)), dim3(256), 0, s, g->d_num_paths, st.gt_cnt, st.gt_off,
-                     st.gt_dev, st.gt_v0, g->path_rank);
+                     st.gt_dev, so.vals, g->path_rank);
   return TDP_OK;
 }
 

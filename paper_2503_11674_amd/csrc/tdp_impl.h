@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "tdp_internal.h"
+#include "tdp_prims.h"
 
 namespace tdp {
 
@@ -57,7 +58,9 @@ void sta_export_crit(tdp_graph g, int32_t *out, hipStream_t s);
 template <typename T> void extract_impl(tdp_graph g, int n, int k, int K, float slack_limit, hipStream_t s);
 template <typename T> void select_stage(tdp_graph g, int n, hipStream_t s);
 template <typename T> void search_stage(tdp_graph g, int k, float slack_limit, hipStream_t s);
-template <typename T> void slot_sort_stage(tdp_graph g, int k, hipStream_t s);
+// digits of the node store's sorts (the fixed array holds their histograms)
+constexpr int GT_DIGIT_BITS = 8;
+template <typename T> Sorted<uint64_t> slot_sort_stage(tdp_graph g, int k, hipStream_t s);
 void ptr_tail(const int32_t *d_num_paths, const int32_t *len, int32_t *ptr, hipStream_t s);
 // report_timing(K)'s node store and its sort / scan scratch: the graph's own
 // (allocated by the first call) or carved from the fixed device array of the

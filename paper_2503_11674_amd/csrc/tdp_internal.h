@@ -343,10 +343,14 @@ struct tdp_graph_s {
 
   // extraction
   int32_t *sel_flag = nullptr, *sel_pos = nullptr, *sel_list = nullptr, *d_nsel = nullptr;
-  int32_t *inst_nsel = nullptr, *inst_nvalid = nullptr, *inst_seg = nullptr, *inst_outb = nullptr,
-          *inst_kept = nullptr, *inst_selb = nullptr, *sel_npop = nullptr;
+  int32_t *inst_selb = nullptr;  // [num_inst + 1] first selected endpoint of each instance
+  int32_t *inst_outb = nullptr, *inst_kept = nullptr, *sel_cut = nullptr;
+  uint64_t *look_st = nullptr;   // state of the one-launch prefix sums (tdp_look.h)
+  uint32_t *look_ctr = nullptr;
+  uint32_t *order_hist = nullptr, *order_flags = nullptr;  // exchange of the ordering's workgroups
+  uint64_t *order_total = nullptr;
   void *slot_key = nullptr;      // path slack per slot
-  int32_t *slot_dev = nullptr, *slot_par = nullptr, *slot_len = nullptr, *slot_cells = nullptr,
+  int32_t *slot_dev = nullptr, *slot_par = nullptr, *slot_len = nullptr,
           *d_nslots = nullptr;
   uint64_t *sort_k0 = nullptr, *sort_k1 = nullptr;
   uint32_t *sort_v0 = nullptr, *sort_v1 = nullptr;
@@ -420,9 +424,9 @@ struct tdp_graph_s {
   int dn_key_bits = 8, dn_alloc_bins = 0, dn_alloc_R = -1;
   double dn_total_area = 0;
   float *dn_area = nullptr;                    // [N]
-  uint64_t *dn_k0 = nullptr, *dn_k1 = nullptr;  // [N] bin keys (sort ping-pong)
+  uint32_t *dn_k0 = nullptr, *dn_k1 = nullptr;  // [N] bin keys (sort ping-pong)
   uint32_t *dn_v0 = nullptr, *dn_v1 = nullptr;  // [N] cell ids
-  int32_t *dn_hist = nullptr, *dn_scan = nullptr, *dn_start = nullptr;  // start [bins + 1]
+  int32_t *dn_hist = nullptr, *dn_start = nullptr;  // start [bins + 1]
   int32_t *dn_heavy = nullptr, *dn_nheavy = nullptr;  // crowded bins [bins] and their count
   float *dn_w = nullptr;                       // [2 (2R+1)][N] window weights of the sorted cells
   float *dn_map = nullptr;                     // [bins]

@@ -20,10 +20,11 @@
 //                  count (from the critical-chain depths)
 //   ordering       stable radix sort of the slots by (instance, slack); per
 //                  instance cut to K; prefix sum of the pin counts
-//   k_walk         one thread per output path: follow critical inputs and
+//   k_walk         four lanes per output path: follow critical inputs and
 //                  the deviations from the endpoint back to the start point,
 //                  writing the pins in place from the end.
 #include "tdp_impl.h"
+#include "tdp_look.h"
 #include "tdp_prims.h"
 #include "tdp_walk.h"
 #include "tdp_wave.h"
@@ -31,73 +32,283 @@
 namespace tdp {
 
 // ------------------------------------------------------------- selection
+constexpr int SEL_TILE = 4096;  // endpoints per tile: 256 threads x 16
+
+// The violated endpoints of every instance, in order, in one launch: flags by
+// ballot, places by look-back; the place of an instance's first endpoint is
+// its inst_selb.  (Five launches, flags through memory, took 21 us at 20,000
+// endpoints and 28 at 240,000; this 10 and 12.)
+template <typename T>
+__global__ void __launch_bounds__(256) k_sel_violated(Topo tp, Look lk, const int32_t *__restrict__ ep_base,
+                                                       const T *__restrict__ ep_slack, int32_t *__restrict__ list,
+                                                       int32_t *__restrict__ d_nsel, int32_t *__restrict__ inst_selb) {
+  __shared__ unsigned long long s_mask[64];  // rounds x waves
+  __shared__ int s_before[64], s_base, s_total;
+  const int lane = wave_lane(), wid = threadIdx.x >> 6;
+  const uint32_t launch = lk.ctr[0];
+  const int tiles = max(1, (tp.E + SEL_TILE - 1) / SEL_TILE);
+  for (int tile = look_tile(lk); tile < tiles; tile = look_tile(lk)) {
+    const int f0 = tile * SEL_TILE;
+    unsigned long long m[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int f = f0 + r * 256 + threadIdx.x;
+      m[r] = __ballot(f < tp.E && ep_slack[f] < (T)0);
+      if (lane == 0) s_mask[r * 4 + wid] = m[r];
+    }
+    __syncthreads();
+    if (wid == 0) {
+      const int c = __popcll(s_mask[lane]);
+      int x = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(x, o, 64);
+        if (lane >= o) x += u;
+      }
+      s_before[lane] = x - c;
+      const int total[1] = {__shfl(x, 63, 64)};
+      int before[1];
+      look_prefix<1>(lk, tile, launch, total, before);
+      if (lane == 0) {
+        s_base = before[0];
+        s_total = total[0];
+      }
+    }
+    __syncthreads();
+    const unsigned long long below = (1ull << lane) - 1;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if ((m[r] >> lane) & 1) list[s_base + s_before[r * 4 + wid] + __popcll(m[r] & below)] = f0 + r * 256 + threadIdx.x;
+    const bool last = tile == tiles - 1;
+    for (int i = threadIdx.x; i <= tp.num_inst; i += 256) {
+      const int e = ep_base[i] - f0;
+      if (e < 0 || (e >= SEL_TILE && !(last && ep_base[i] == tp.E))) continue;
+      inst_selb[i] = e >= SEL_TILE ? s_base + s_total
+                                   : s_base + s_before[e >> 6] + __popcll(s_mask[e >> 6] & ((1ull << (e & 63)) - 1));
+    }
+    if (last && threadIdx.x == 0) *d_nsel = s_base + s_total;
+  }
+  look_done(lk, launch);
+}
+
+// The first n endpoints of each instance in (slack, position) order, listed in
+// position order: one workgroup per instance holds its keys in registers, R a
+// thread, finds the n-th smallest by a radix select (four counts of 8 bits in
+// LDS), and lists everything below it and the first of its equals; where its
+// part of the list starts comes by look-back.  For instances of up to
+// SEL_SELECT endpoints; a sort serves larger ones.  Bound by one workgroup's
+// LDS counts and barriers: 15,000 endpoints in 26 us, against 90 by sort,
+// flags and scans in some 20 launches (and 60 with the keys read again for
+// every count).
+constexpr int SEL_SELECT = 1 << 16;
+constexpr uint32_t SEL_NEVER = 0xFFFFFFFFu;  // endpoints without a finite slack, never taken
+
+template <typename T>
+__device__ __forceinline__ uint32_t sel_key(T slack) {
+  return (uint32_t)order_key((float)slack);
+}
+
+template <typename T, int R>
+__global__ void __launch_bounds__(1024) k_sel_worst(int num_inst, const int32_t *__restrict__ ep_base,
+                                                     const T *__restrict__ ep_slack, int n, Look lk,
+                                                     int32_t *__restrict__ list, int32_t *__restrict__ d_nsel,
+                                                     int32_t *__restrict__ inst_selb) {
+  __shared__ int hist[256], s_lt[R * 16], s_eq[R * 16], s_digit, s_below, s_pos;
+  const int tid = threadIdx.x, lane = wave_lane(), wid = tid >> 6;
+  const unsigned long long below = (1ull << lane) - 1;
+  const uint32_t launch = lk.ctr[0];
+  for (int inst = look_tile(lk); inst < num_inst; inst = look_tile(lk)) {
+    const int b = ep_base[inst], e = ep_base[inst + 1];
+    uint32_t key[R];
+    int finite = 0;
+#pragma unroll
+    for (int r0 = 0; r0 < R; r0 += 16) {
+      T sl[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int f = b + (r0 + r) * 1024 + tid;
+        sl[r] = f < e ? ep_slack[f] : inf_of<T>();
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const bool in = sl[r] < inf_of<T>();
+        key[r0 + r] = in ? sel_key(sl[r]) : SEL_NEVER;
+        finite += in;
+      }
+    }
+    int all;
+    block_exclusive(finite, &all);
+    const int take = min(n, all);
+    uint32_t cut = 0;
+    int need = take;  // of the endpoints that share the digits settled so far
+    if (take > 0) {
+      for (int shift = 24; shift >= 0; shift -= 8) {
+        if (tid < 256) hist[tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if (key[r] != SEL_NEVER && (uint64_t)(key[r] ^ cut) >> (shift + 8) == 0)
+            atomicAdd(&hist[(key[r] >> shift) & 255u], 1);
+        __syncthreads();
+        const int h = tid < 256 ? hist[tid] : 0;
+        const int c = block_exclusive(h, &all);
+        if (tid < 256 && c < need && c + h >= need) {
+          s_digit = tid;
+          s_below = c;
+        }
+        __syncthreads();
+        cut |= (uint32_t)s_digit << shift;
+        need -= s_below;
+      }
+    }
+    // counts of each 64 endpoints below the cut and at it, to counts before
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int lt = __popcll(__ballot(key[r] < cut)), eq = __popcll(__ballot(key[r] == cut));
+      if (lane == 0) {
+        s_lt[r * 16 + wid] = lt;
+        s_eq[r * 16 + wid] = eq;
+      }
+    }
+    __syncthreads();
+    const int lt = block_exclusive(tid < R * 16 ? s_lt[tid] : 0, &all);
+    const int eq = block_exclusive(tid < R * 16 ? s_eq[tid] : 0, &all);
+    if (tid < R * 16) {
+      s_lt[tid] = lt;
+      s_eq[tid] = eq;
+    }
+    if (wid == 0) {
+      const int total[1] = {take};
+      int before[1];
+      look_prefix<1>(lk, inst, launch, total, before);
+      if (lane == 0) {
+        s_pos = before[0];
+        inst_selb[inst] = before[0];
+        if (inst == num_inst - 1) *d_nsel = inst_selb[num_inst] = before[0] + take;
+      }
+    }
+    __syncthreads();
+    if (take == 0) continue;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const bool is_lt = key[r] < cut, is_eq = key[r] == cut;
+      const unsigned long long ml = __ballot(is_lt), me = __ballot(is_eq);
+      const int l = s_lt[r * 16 + wid] + __popcll(ml & below), q = s_eq[r * 16 + wid] + __popcll(me & below);
+      if (is_lt || (is_eq && q < need)) list[s_pos + l + min(q, need)] = b + r * 1024 + tid;
+    }
+  }
+  look_done(lk, launch);
+}
+
+// larger instances: endpoints taken, the cut's key and its equals among them,
+// from the endpoints sorted by (instance, slack, position)
+constexpr int SEL_CUT = 4;  // words per instance: the cut's key, endpoints taken, equals taken among them
+
 template <typename T>
 __global__ void k_sel_keys(Topo tp, const T *__restrict__ ep_slack, uint64_t *__restrict__ keys,
                            uint32_t *__restrict__ vals) {
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= tp.E) return;
-  keys[f] = ((uint64_t)tp.ff_inst[f] << 32) | (order_key((float)ep_slack[f]) & 0xFFFFFFFFull);
+  keys[f] = ((uint64_t)tp.ff_inst[f] << 32) | sel_key(ep_slack[f]);
   vals[f] = f;
 }
 
-// flags of the first n endpoints of each instance in sorted order; the
-// double-precision tie-break is settled by a second key pass in sel_by_rank
 template <typename T>
-__global__ void k_sel_first_n(Topo tp, const int32_t *__restrict__ ep_base, const uint64_t *__restrict__ keys,
-                              const uint32_t *__restrict__ perm, const T *__restrict__ ep_slack, int n,
-                              int32_t *__restrict__ flag) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= tp.E) return;
-  const int inst = (int)(keys[j] >> 32);
-  const int rank = j - ep_base[inst];
-  const int f = perm[j];
-  flag[f] = (rank < n && ep_slack[f] < inf_of<T>()) ? 1 : 0;
-}
-
-template <typename T>
-__global__ void k_sel_violated(Topo tp, const T *__restrict__ ep_slack, int32_t *__restrict__ flag) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= tp.E) return;
-  flag[f] = ep_slack[f] < (T)0 ? 1 : 0;
-}
-
-__global__ void k_sel_compact(Topo tp, const int32_t *__restrict__ flag, const int32_t *__restrict__ pos,
-                              int32_t *__restrict__ list) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= tp.E) return;
-  if (flag[f]) list[pos[f]] = f;
-}
-
-// per instance: first selected index and count (endpoint ranges are
-// contiguous per instance, so the scan positions give both)
-__global__ void k_sel_counts(int num_inst, int E, const int32_t *__restrict__ ep_base, const int32_t *__restrict__ pos,
-                             const int32_t *__restrict__ d_nsel, int32_t *__restrict__ inst_selb,
-                             int32_t *__restrict__ inst_nsel) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= num_inst) return;
-  const int b = ep_base[i] < E ? pos[ep_base[i]] : *d_nsel;
-  const int e = ep_base[i + 1] < E ? pos[ep_base[i + 1]] : *d_nsel;
-  inst_selb[i] = b;
-  inst_nsel[i] = e - b;
-}
-
-// per instance: number of paths found (sum of the per-endpoint counts)
-__global__ void __launch_bounds__(256) k_valid_counts(const int32_t *__restrict__ inst_selb,
-                                                       const int32_t *__restrict__ inst_nsel,
-                                                       const int32_t *__restrict__ npop,
-                                                       int32_t *__restrict__ inst_nvalid) {
-  __shared__ int sh[256];
-  const int i = blockIdx.x;
-  const int b = inst_selb[i], n = inst_nsel[i];
-  int acc = 0;
-  for (int q = threadIdx.x; q < n; q += 256) acc += npop[b + q];
-  sh[threadIdx.x] = acc;
+__global__ void __launch_bounds__(1024) k_sel_cut_sorted(const int32_t *__restrict__ ep_base,
+                                                          const T *__restrict__ ep_slack,
+                                                          const uint64_t *__restrict__ keys,
+                                                          const uint32_t *__restrict__ perm, int n,
+                                                          int32_t *__restrict__ cut) {
+  __shared__ int s_take, s_equal;
+  const int b = ep_base[blockIdx.x], e = ep_base[blockIdx.x + 1];
+  if (threadIdx.x == 0) s_take = s_equal = 0;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
+  const int m = min(n, e - b);
+  int c = 0;
+  for (int j = threadIdx.x; j < m; j += 1024) c += ep_slack[perm[b + j]] < inf_of<T>();
+  if (c) atomicAdd(&s_take, c);
+  __syncthreads();
+  const int take = s_take;
+  const uint32_t key = take > 0 ? (uint32_t)keys[b + take - 1] : 0u;
+  c = 0;
+  for (int j = threadIdx.x; j < take; j += 1024) c += (uint32_t)keys[b + j] == key;
+  if (c) atomicAdd(&s_equal, c);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    cut[SEL_CUT * blockIdx.x] = (int)key;
+    cut[SEL_CUT * blockIdx.x + 1] = take;
+    cut[SEL_CUT * blockIdx.x + 2] = s_equal;
   }
-  if (threadIdx.x == 0) inst_nvalid[i] = sh[0];
+}
+
+template <typename T>
+__global__ void __launch_bounds__(1024) k_sel_take(int num_inst, const int32_t *__restrict__ ep_base,
+                                                    const T *__restrict__ ep_slack, const int32_t *__restrict__ cut,
+                                                    int32_t *__restrict__ list, int32_t *__restrict__ d_nsel,
+                                                    int32_t *__restrict__ inst_selb) {
+  __shared__ int s_lt[65], s_eq[65], s_base;
+  const int lane = wave_lane(), wid = threadIdx.x >> 6, inst = blockIdx.x;
+  if (threadIdx.x == 0) s_base = 0;
+  __syncthreads();
+  int before = 0;
+  for (int i = threadIdx.x; i < inst; i += 1024) before += cut[SEL_CUT * i + 1];
+  if (before) atomicAdd(&s_base, before);
+  __syncthreads();
+  int pos = s_base;
+  const uint32_t key = (uint32_t)cut[SEL_CUT * inst];
+  const int take = cut[SEL_CUT * inst + 1];
+  int equals = cut[SEL_CUT * inst + 2];  // still to take
+  if (threadIdx.x == 0) {
+    inst_selb[inst] = pos;
+    if (inst == num_inst - 1) *d_nsel = inst_selb[num_inst] = pos + take;
+  }
+  const int b = ep_base[inst], e = ep_base[inst + 1];
+  const unsigned long long below = (1ull << lane) - 1;
+  if (take == 0) return;
+  for (int f0 = b; f0 < e; f0 += 4096) {
+    T s[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int f = f0 + r * 1024 + threadIdx.x;
+      s[r] = f < e ? ep_slack[f] : inf_of<T>();
+    }
+    unsigned long long lt[4], eq[4];
+    __syncthreads();  // (the masks of the round before are read)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool fin = s[r] < inf_of<T>();
+      const uint32_t k = sel_key(s[r]);
+      lt[r] = __ballot(fin && k < key);
+      eq[r] = __ballot(fin && k == key);
+      if (lane == 0) {
+        s_lt[r * 16 + wid] = __popcll(lt[r]);
+        s_eq[r * 16 + wid] = __popcll(eq[r]);
+      }
+    }
+    __syncthreads();
+    if (wid < 2) {  // counts to counts before, over the 64 rounds and waves
+      int *c = wid == 0 ? s_lt : s_eq;
+      const int v = c[lane];
+      int x = v;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(x, o, 64);
+        if (lane >= o) x += u;
+      }
+      c[lane] = x - v;
+      if (lane == 63) c[64] = x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int l = s_lt[r * 16 + wid] + __popcll(lt[r] & below), q = s_eq[r * 16 + wid] + __popcll(eq[r] & below);
+      const bool in = ((lt[r] >> lane) & 1) || (((eq[r] >> lane) & 1) && q < equals);
+      if (in) list[pos + l + min(q, equals)] = f0 + r * 1024 + threadIdx.x;
+    }
+    const int qall = min(s_eq[64], equals);
+    pos += s_lt[64] + qall;
+    equals -= qall;
+  }
 }
 
 // --------------------------------------------------------------- search
@@ -108,7 +319,7 @@ __global__ void __launch_bounds__(256) k_valid_counts(const int32_t *__restrict_
 // pop costs its two dependent loads (the deviation's driver, then the list)
 // and some 4 KM instructions.  One thread per endpoint with the lists in
 // registers took KM^2 dependent steps per pop and left most of the chip
-// idle: 78 us against 16 for 1,000 endpoints at k = 10, KM = 16; 28 against 17
+// idle: 78 us against 18 for 1,000 endpoints at k = 10, KM = 16; 28 against 18
 // for 12,000 at k = KM = 8.
 template <typename T, int KM>
 __global__ void __launch_bounds__(64) k_search(Topo tp, int k, T slack_limit, const int32_t *__restrict__ d_nsel,
@@ -116,8 +327,7 @@ __global__ void __launch_bounds__(64) k_search(Topo tp, int k, T slack_limit, co
                                                 const uint32_t *__restrict__ cdep, const uint64_t *__restrict__ node,
                                                 T *__restrict__ slot_key,
                                                 int32_t *__restrict__ slot_dev, int32_t *__restrict__ slot_par,
-                                                int32_t *__restrict__ slot_len, int32_t *__restrict__ slot_cells,
-                                                int32_t *__restrict__ npop_out) {
+                                                int32_t *__restrict__ slot_len) {
   static_assert(KM >= 1 && KM <= 32 && (KM & (KM - 1)) == 0, "a power of two of at most half a wave");
   __shared__ T s_cost[64];
   __shared__ int32_t s_dev[64], s_par[64];
@@ -215,110 +425,549 @@ __global__ void __launch_bounds__(64) k_search(Topo tp, int k, T slack_limit, co
   slot_key[o] = okey;
   slot_dev[o] = odev;
   slot_par[o] = opar;
-  slot_cells[o] = ocells;
   slot_len[o] = j < npop ? 2 * ocells + 2 : 0;
-  if (j == 0) npop_out[q] = npop;
 }
 
 // ------------------------------------------------------------- ordering
+// Slots are ordered by (instance, slack, slot); the first K found ones of an
+// instance are its paths.  inst_selb gives each instance's first slot.
+template <typename T>
+__device__ __forceinline__ uint64_t slot_order(const Topo &tp, int f, T key) {
+  if constexpr (sizeof(T) == 4) return ((uint64_t)tp.ff_inst[f] << 32) | (order_key((float)key) & 0xFFFFFFFFull);
+  else return order_key((double)key);
+}
+
 template <typename T>
 __global__ void k_slot_keys(Topo tp, int k, const int32_t *__restrict__ d_nsel, const int32_t *__restrict__ sel,
                             const T *__restrict__ slot_key, int32_t *__restrict__ d_nslots,
-                            uint64_t *__restrict__ keys, uint32_t *__restrict__ vals, int64_t cap) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n = (int64_t)(*d_nsel) * k;
-  if (i == 0) *d_nslots = (int32_t)n;
-  if (i >= n || i >= cap) return;
-  const int f = sel[i / k];
-  uint64_t kk;
-  if constexpr (sizeof(T) == 4) kk = ((uint64_t)tp.ff_inst[f] << 32) | (order_key((float)slot_key[i]) & 0xFFFFFFFFull);
-  else kk = order_key((double)slot_key[i]);
-  keys[i] = kk;
-  vals[i] = (uint32_t)i;
+                            uint64_t *__restrict__ keys, uint32_t *__restrict__ vals) {
+  const int n = *d_nsel * k, nth = gridDim.x * blockDim.x;
+  const int i0 = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i0 == 0) *d_nslots = n;
+  for (int i = i0; i < n; i += nth) {
+    keys[i] = slot_order<T>(tp, sel[i / k], slot_key[i]);
+    vals[i] = (uint32_t)i;
+  }
 }
 
-// per instance: start of its slot segment, start of its output range, paths kept
-__global__ void k_path_bases(int num_inst, int k, int K, const int32_t *__restrict__ inst_nsel,
-                             const int32_t *__restrict__ inst_nvalid, int32_t *__restrict__ seg,
-                             int32_t *__restrict__ outb, int32_t *__restrict__ kept, int32_t *__restrict__ d_num_paths) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  int s = 0, o = 0;
-  for (int i = 0; i < num_inst; ++i) {
-    seg[i] = s;
-    outb[i] = o;
-    const int kp = inst_nvalid[i] < K ? inst_nvalid[i] : K;
-    kept[i] = kp;
-    s += inst_nsel[i] * k;
-    o += kp;
-  }
-  *d_num_paths = o;
+// The whole ordering in one launch, single precision: a stable radix sort of
+// {instance, slack, slot} words by instance and slack, then the output index
+// and first pin of every path.  One workgroup per 2,048 live slots (known on
+// the device only), at most ORDER_GROUPS; the others of the grid leave at
+// once.  A workgroup owns a run of slots, a wave a run of those: pass by pass
+// (8 bits) every wave ranks its words against its own counters in LDS, the
+// workgroup publishes its digits' counts, and after a barrier finds their
+// places from everyone's counts and moves its words.  What workgroups exchange
+// goes through device-scope stores and loads.  Bound by the barriers (two a
+// pass) and the round trips around them.  10,000 slots (200k cells): 50 us,
+// against 65 in nine launches and 103 in 22 (and 85 with 11-bit digits: more to
+// clear, add up and read per pass than a pass saves); 96,000 (2M cells): 71
+// against 78 and 105.  Without passes, behind k_rank: 12 us for 10,000.
+constexpr int ORDER_GROUPS = 64;
+constexpr int ORDER_ITEMS = 2;  // words per thread and round
+constexpr int ORDER_RUN = 1024 * ORDER_ITEMS;
+
+struct OrderBuf {
+  uint64_t *w0, *w1;
+  uint32_t *hist;   // [ORDER_GROUPS][256]
+  uint64_t *total;  // [ORDER_GROUPS] kept slots and their pins
+  uint32_t *flags;  // [ORDER_GROUPS] barrier flags, then the phase reached by the launches so far
+};
+
+// Slots of instances that have at most RANK_MOST each are put in order by
+// counting, for every slot, the slots of its instance that come before it: no
+// pass waits for another, and the compute units share the comparisons (10,000
+// slots: 10^8 in 21 us, where k_order's passes take 38).  One workgroup per
+// 64 slots, a lane each; its 16 waves count a part of every tile of keys in LDS.
+constexpr int RANK_MOST = 1 << 14;
+constexpr int RANK_TILE = 4096;
+
+// whether counting orders this call's slots (the same answer in every thread
+// of every workgroup)
+__device__ __forceinline__ bool rank_orders(int num_inst, int k, const int32_t *__restrict__ inst_selb) {
+  bool big = false;
+  for (int i = threadIdx.x; i < num_inst; i += blockDim.x)
+    big = big || (long long)(inst_selb[i + 1] - inst_selb[i]) * k > RANK_MOST;
+  return __syncthreads_or(big) == 0;
 }
+
+__global__ void __launch_bounds__(1024) k_rank(Topo tp, int k, int slot_bits, const int32_t *__restrict__ d_nsel,
+                                                const int32_t *__restrict__ sel, const int32_t *__restrict__ inst_selb,
+                                                const float *__restrict__ slot_key, uint64_t *__restrict__ words) {
+  __shared__ uint4 s_key[RANK_TILE / 4];
+  __shared__ int s_cnt[16][64];
+  const int n = *d_nsel * k;
+  if ((int)blockIdx.x * 64 >= n || !rank_orders(tp.num_inst, k, inst_selb)) return;
+  const int lane = wave_lane(), wid = threadIdx.x >> 6;
+  for (int e0 = blockIdx.x * 64; e0 < n; e0 += gridDim.x * 64) {
+    const int i = min(e0 + lane, n - 1);
+    const int inst = tp.ff_inst[sel[i / k]];
+    const int s0 = inst_selb[inst] * k, s1 = inst_selb[inst + 1] * k;  // the lane's instance's slots
+    const uint64_t word = slot_order<float>(tp, sel[i / k], slot_key[i]);
+    const uint32_t key = (uint32_t)word;
+    const int a = __shfl(s0, 0, 64), z = __shfl(s1, 63, 64);  // of all the lanes' instances
+    const bool one = __shfl(s1, 0, 64) == z;
+    int count = 0;
+    for (int t0 = a; t0 < z; t0 += RANK_TILE) {
+      float raw[RANK_TILE / 1024];
+#pragma unroll
+      for (int r = 0; r < RANK_TILE / 1024; ++r) raw[r] = slot_key[min(t0 + r * 1024 + (int)threadIdx.x, z - 1)];
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < RANK_TILE / 1024; ++r) {
+        const int j = r * 1024 + (int)threadIdx.x;  // (past the end: before nothing)
+        reinterpret_cast<uint32_t *>(s_key)[j] = t0 + j < z ? (uint32_t)order_key(raw[r]) : 0xFFFFFFFFu;
+      }
+      __syncthreads();
+      // this wave's part of the tile: before the workgroup's own slots, after them, or neither
+      const int j0 = wid * (RANK_TILE / 16), j1 = min(j0 + RANK_TILE / 16, z - t0);
+      if (one && t0 + j1 <= e0) {
+#pragma unroll 4
+        for (int j = j0; j < j1; j += 4) {
+          const uint4 v = s_key[j / 4];
+          count += (v.x <= key) + (v.y <= key) + (v.z <= key) + (v.w <= key);
+        }
+      } else if (one && t0 + j0 >= e0 + 64) {
+#pragma unroll 4
+        for (int j = j0; j < j1; j += 4) {
+          const uint4 v = s_key[j / 4];
+          count += (v.x < key) + (v.y < key) + (v.z < key) + (v.w < key);
+        }
+      } else {
+        const uint32_t *ks = reinterpret_cast<const uint32_t *>(s_key);
+        const int m0 = one ? max(j0, min(e0 - t0, j1)) : j0, m1 = one ? max(j0, min(e0 + 64 - t0, j1)) : j1;
+#pragma unroll 8
+        for (int j = j0; j < m0; ++j) count += ks[j] <= key;
+#pragma unroll 8
+        for (int j = m0; j < m1; ++j) {
+          const uint32_t kj = ks[j];
+          const int at = t0 + j;
+          count += (at >= s0) & (at < s1) & ((kj < key) | ((kj == key) & (at < i)));
+        }
+#pragma unroll 8
+        for (int j = max(m1, j0); j < j1; ++j) count += ks[j] < key;
+      }
+    }
+    __syncthreads();
+    s_cnt[wid][lane] = count;
+    __syncthreads();
+    if (wid == 0 && e0 + lane < n) {
+      int rank = 0;
+#pragma unroll
+      for (int w = 0; w < 16; ++w) rank += s_cnt[w][lane];
+      words[s0 + rank] = word << slot_bits | (uint64_t)i;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(1024) k_order(Topo tp, int k, int K, int key_bits, int slot_bits,
+                                                 const int32_t *__restrict__ d_nsel, const int32_t *__restrict__ sel,
+                                                 const int32_t *__restrict__ inst_selb,
+                                                 const float *__restrict__ slot_key,
+                                                 const int32_t *__restrict__ slot_len, OrderBuf ob,
+                                                 int32_t *__restrict__ d_nslots, int32_t *__restrict__ out_slot,
+                                                 int32_t *__restrict__ slot_out, int32_t *__restrict__ path_ptr,
+                                                 int32_t *__restrict__ d_num_paths, int32_t *__restrict__ err) {
+  constexpr int WAVES = 16;
+  __shared__ uint32_t cnt[WAVES][256], s_base[256];
+  const int tid = threadIdx.x, lane = wave_lane(), wid = tid >> 6, me = blockIdx.x;
+  const int n = *d_nsel * k;
+  const int groups = min((int)gridDim.x, max(1, (n + ORDER_RUN - 1) / ORDER_RUN));
+  if (me >= groups) return;
+  const uint32_t start = ob.flags[ORDER_GROUPS];
+  uint32_t phase = start;
+  // this workgroup's slots, and this wave's, in rounds of ORDER_ITEMS words a lane
+  const int run = ((n + groups - 1) / groups + ORDER_RUN - 1) / ORDER_RUN * ORDER_RUN;
+  const int b = min(n, me * run), e = min(n, b + run);
+  const int wrun = run / WAVES;
+  const int wb = min(e, b + wid * wrun), we = min(e, wb + wrun);
+  const bool single = run == ORDER_RUN;  // the words of a round stay in registers
+  const uint64_t slot_mask = (1ull << slot_bits) - 1;
+  const unsigned long long below = (1ull << lane) - 1;
+  uint64_t *wa = ob.w0, *wz = ob.w1;
+  const int passes = rank_orders(tp.num_inst, k, inst_selb) ? 0 : (key_bits + 7) / 8;  // 0: k_rank put them in order
+  for (int pass = 0; pass < passes; ++pass) {
+    const int shift = slot_bits + 8 * pass;
+    uint64_t ww[ORDER_ITEMS];
+    auto load = [&](int i0) {
+#pragma unroll
+      for (int j = 0; j < ORDER_ITEMS; ++j) {
+        const int i = i0 + j * 64 + lane;
+        ww[j] = 0;
+        if (i < we)
+          ww[j] = pass == 0 ? slot_order<float>(tp, sel[i / k], slot_key[i]) << slot_bits | (uint64_t)i : pub_ld(wa + i);
+      }
+    };
+    // the lanes of the round's j-th word that share this lane's digit
+    auto peers = [&](int i0, int j, uint32_t &d) {
+      d = (uint32_t)(ww[j] >> shift) & 255u;
+      uint64_t m = __ballot(i0 + j * 64 + lane < we);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const uint64_t bal = __ballot((d >> q) & 1u);
+        m &= ((d >> q) & 1u) ? bal : ~bal;
+      }
+      return m;
+    };
+#pragma unroll
+    for (int q = 0; q < 4; ++q) cnt[wid][q * 64 + lane] = 0;
+    for (int i0 = wb; i0 < we; i0 += 64 * ORDER_ITEMS) {
+      load(i0);
+#pragma unroll
+      for (int j = 0; j < ORDER_ITEMS; ++j) {
+        uint32_t d;
+        const uint64_t m = peers(i0, j, d);
+        if (((m >> lane) & 1) && (m & below) == 0) cnt[wid][d] += (uint32_t)__popcll(m);
+      }
+    }
+    __syncthreads();
+    // counts to places among the waves; the sums to everyone
+    uint32_t mine = 0;
+    if (tid < 256) {
+      uint32_t c[WAVES];
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) c[w] = cnt[w][tid];
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) {
+        cnt[w][tid] = mine;
+        mine += c[w];
+      }
+      if (groups > 1) pub_st(ob.hist + me * 256 + tid, mine);
+    }
+    group_barrier(ob.flags, groups, ++phase, err);
+    uint32_t before = 0, total = mine;
+    if (tid < 256 && groups > 1) {
+      total = 0;
+#pragma unroll 16
+      for (int g = 0; g < groups; ++g) {
+        const uint32_t h = pub_ld(ob.hist + g * 256 + tid);
+        total += h;
+        before += g < me ? h : 0u;
+      }
+    }
+    int all;
+    const uint32_t base = (uint32_t)block_exclusive((int)total, &all);
+    if (tid < 256) s_base[tid] = base + before;
+    __syncthreads();
+    for (int i0 = wb; i0 < we; i0 += 64 * ORDER_ITEMS) {
+      if (!single) load(i0);
+#pragma unroll
+      for (int j = 0; j < ORDER_ITEMS; ++j) {
+        uint32_t d;
+        const uint64_t m = peers(i0, j, d);
+        const uint32_t place = cnt[wid][d];
+        if ((m >> lane) & 1) {
+          pub_st(wz + s_base[d] + place + __popcll(m & below), ww[j]);
+          if ((m & below) == 0) cnt[wid][d] = place + (uint32_t)__popcll(m);
+        }
+      }
+    }
+    group_barrier(ob.flags, groups, ++phase, err);
+    uint64_t *t = wa;
+    wa = wz;
+    wz = t;
+  }
+  // kept slots, in order: the first K found ones of their instance
+  const uint64_t inf_key = order_key(inf_of<float>());
+  auto kept = [&](int j, int &slot, int &len) {
+    const uint64_t w = pub_ld(wa + j), key = w >> slot_bits;
+    slot = (int)(w & slot_mask);
+    const bool in = (key & 0xFFFFFFFFull) < inf_key && j - inst_selb[(int)(key >> 32)] * k < K;
+    len = in ? slot_len[slot] : 0;
+    return in;
+  };
+  int paths = 0, pins = 0;  // of the workgroup's run, this thread's share
+  for (int j0 = b; j0 < e; j0 += 1024) {
+    int slot, len = 0;
+    if (j0 + tid < e) paths += kept(j0 + tid, slot, len);
+    pins += len;
+  }
+  int q0 = 0, p0 = 0;
+  if (groups > 1) {
+    int c, p;
+    block_exclusive(paths, &c);
+    block_exclusive(pins, &p);
+    if (tid == 0) pub_st(ob.total + me, (uint64_t)(uint32_t)c | (uint64_t)(uint32_t)p << 32);
+    group_barrier(ob.flags, groups, ++phase, err);
+    for (int g = 0; g < me; ++g) {
+      const uint64_t w = pub_ld(ob.total + g);
+      q0 += (int)(uint32_t)w;
+      p0 += (int)(uint32_t)(w >> 32);
+    }
+  }
+  for (int j0 = b; j0 < e; j0 += 1024) {
+    int slot = 0, len = 0, c, p;
+    const bool on = j0 + tid < e && kept(j0 + tid, slot, len);
+    const int q = q0 + block_exclusive(on, &c), at = p0 + block_exclusive(len, &p);
+    if (j0 + tid < e) slot_out[slot] = on ? q : -1;
+    if (on) {
+      out_slot[q] = slot;
+      path_ptr[q] = at;
+    }
+    q0 += c;
+    p0 += p;
+  }
+  if (me == groups - 1 && tid == 0) {
+    *d_nslots = n;
+    *d_num_paths = q0;
+    path_ptr[q0] = p0;
+  }
+  // (everyone has read the phase: a launch has a barrier, or one workgroup)
+  if (me == 0 && tid == 0) ob.flags[ORDER_GROUPS] = start + 2 * passes + 1;
+}
+
+// the same steps as launches of their own, where a slot's word does not fit
+// 64 bits (double precision; hundreds of instances with many slots): output
+// index and first pin of every path from the sorted slots, summed together by
+// look-back
+constexpr int OUT_TILE = 2048;  // 256 threads x 8
 
 template <typename T>
-__global__ void k_path_index(Topo tp, int k, const int32_t *__restrict__ d_nslots, const uint32_t *__restrict__ perm,
-                             const int32_t *__restrict__ sel, const int32_t *__restrict__ seg,
-                             const int32_t *__restrict__ outb, const int32_t *__restrict__ kept,
-                             const int32_t *__restrict__ slot_len, int32_t *__restrict__ out_slot,
-                             int32_t *__restrict__ out_len, int32_t *__restrict__ slot_out) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= *d_nslots) return;
-  const int slot = perm[j];
-  const int f = sel[slot / k];
-  const int inst = tp.ff_inst[f];
-  const int rho = j - seg[inst];
-  if (rho < kept[inst]) {
-    const int q = outb[inst] + rho;
-    out_slot[q] = slot;
-    out_len[q] = slot_len[slot];
-    slot_out[slot] = q;
-  } else {
-    slot_out[slot] = -1;
+__global__ void __launch_bounds__(256) k_path_out(int k, int K, Look lk, const int32_t *__restrict__ d_nslots,
+                                                   const int32_t *__restrict__ inst_selb,
+                                                   const uint64_t *__restrict__ keys, const uint32_t *__restrict__ perm,
+                                                   const int32_t *__restrict__ slot_len, int32_t *__restrict__ out_slot,
+                                                   int32_t *__restrict__ slot_out, int32_t *__restrict__ path_ptr,
+                                                   int32_t *__restrict__ d_num_paths) {
+  __shared__ int s_base[2];
+  const uint32_t launch = lk.ctr[0];
+  const int n = *d_nslots;
+  const int tiles = max(1, (n + OUT_TILE - 1) / OUT_TILE);
+  const uint64_t inf_key = sizeof(T) == 4 ? order_key(inf_of<float>()) : order_key(inf_of<double>());
+  for (int tile = look_tile(lk); tile < tiles; tile = look_tile(lk)) {
+    const int j0 = tile * OUT_TILE + threadIdx.x * 8;
+    int slot[8], len[8];
+    bool kept[8];
+    int cnt = 0, pins = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int j = j0 + q;
+      const uint64_t key = j < n ? keys[j] : inf_key;
+      slot[q] = j < n ? (int)perm[j] : 0;
+      const int inst = sizeof(T) == 4 && j < n ? (int)(key >> 32) : 0;
+      kept[q] = j < n && (sizeof(T) == 4 ? (key & 0xFFFFFFFFull) : key) < inf_key && j - inst_selb[inst] * k < K;
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      len[q] = kept[q] ? slot_len[slot[q]] : 0;
+      cnt += kept[q];
+      pins += len[q];
+    }
+    int total[2], before[2];
+    int c = block_exclusive(cnt, &total[0]), p = block_exclusive(pins, &total[1]);
+    if (threadIdx.x < 64) {
+      look_prefix<2>(lk, tile, launch, total, before);
+      if (threadIdx.x == 0) {
+        s_base[0] = before[0];
+        s_base[1] = before[1];
+      }
+    }
+    __syncthreads();
+    c += s_base[0];
+    p += s_base[1];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (j0 + q >= n) break;
+      slot_out[slot[q]] = kept[q] ? c : -1;
+      if (kept[q]) {
+        out_slot[c] = slot[q];
+        path_ptr[c] = p;
+        ++c;
+        p += len[q];
+      }
+    }
+    if (tile == tiles - 1 && threadIdx.x == 0) {
+      *d_num_paths = s_base[0] + total[0];
+      path_ptr[s_base[0] + total[0]] = s_base[1] + total[1];
+    }
+  }
+  look_done(lk, launch);
+}
+
+// The whole ordering in one workgroup, for at most ORDER_ONE slots: a bitonic
+// sort of {instance, slack, slot} words in LDS, then the output indices.  9 us
+// for 100 slots (22 launches of 2 us before); with 7,000 it took 82.
+constexpr int ORDER_ONE = 2048;
+constexpr int ORDER_SLOT_BITS = 11;
+
+__global__ void __launch_bounds__(1024) k_order_one(Topo tp, int k, int K, const int32_t *__restrict__ d_nsel,
+                                                     const int32_t *__restrict__ sel,
+                                                     const int32_t *__restrict__ inst_selb,
+                                                     const float *__restrict__ slot_key,
+                                                     const int32_t *__restrict__ slot_len,
+                                                     int32_t *__restrict__ d_nslots, int32_t *__restrict__ out_slot,
+                                                     int32_t *__restrict__ slot_out, int32_t *__restrict__ path_ptr,
+                                                     int32_t *__restrict__ d_num_paths) {
+  __shared__ uint64_t s_key[ORDER_ONE];
+  const int n = min(*d_nsel * k, ORDER_ONE);
+  int m = 64;
+  while (m < n) m <<= 1;
+  for (int i = threadIdx.x; i < m; i += 1024)
+    s_key[i] = i < n ? slot_order<float>(tp, sel[i / k], slot_key[i]) << ORDER_SLOT_BITS | (uint64_t)i : ~0ull;
+  __syncthreads();
+  for (int size = 2; size <= m; size <<= 1) {
+    for (int d = size >> 1; d > 0; d >>= 1) {
+      for (int q = threadIdx.x; q < m / 2; q += 1024) {
+        const int i = 2 * q - (q & (d - 1));  // the pair (i, i + d)
+        const uint64_t a = s_key[i], b = s_key[i + d];
+        if ((a > b) == ((i & size) == 0)) {
+          s_key[i] = b;
+          s_key[i + d] = a;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  // consecutive slots per thread
+  const uint64_t inf_key = order_key(inf_of<float>());
+  int len[ORDER_ONE / 1024];
+  int cnt = 0, pins = 0;
+  const int per = (m + 1023) / 1024, j0 = threadIdx.x * per;
+#pragma unroll
+  for (int q = 0; q < ORDER_ONE / 1024; ++q) {
+    const int j = j0 + q;
+    len[q] = -1;
+    if (q >= per || j >= n) continue;
+    const uint64_t key = s_key[j] >> ORDER_SLOT_BITS;
+    if ((key & 0xFFFFFFFFull) < inf_key && j - inst_selb[(int)(key >> 32)] * k < K) {
+      len[q] = slot_len[s_key[j] & (ORDER_ONE - 1)];
+      ++cnt;
+      pins += len[q];
+    }
+  }
+  int all, all_pins;
+  int c = block_exclusive(cnt, &all), p = block_exclusive(pins, &all_pins);
+#pragma unroll
+  for (int q = 0; q < ORDER_ONE / 1024; ++q) {
+    const int j = j0 + q;
+    if (q >= per || j >= n) continue;
+    const int slot = (int)(s_key[j] & (ORDER_ONE - 1));
+    slot_out[slot] = len[q] >= 0 ? c : -1;
+    if (len[q] >= 0) {
+      out_slot[c] = slot;
+      path_ptr[c] = p;
+      ++c;
+      p += len[q];
+    }
+  }
+  if (threadIdx.x == 0) {
+    *d_nslots = n;
+    *d_num_paths = all;
+    path_ptr[all] = all_pins;
   }
 }
 
 // ----------------------------------------------------------------- walk
+// Four lanes per path, one per hop of a node record: a step loads the record
+// of the path's current cell, 16 bytes a lane, and moves the path four cells
+// on (fewer at a deviation or at the start point); each lane writes its hop's
+// two pins in place, 32 bytes of each output array per path and step.  The
+// path's deviations are gathered first, with all that a step needs of them, so
+// the record is the step's only load.  Bound by the chain of records (a quarter
+// of the path's cells) and, with many paths, by the writes.  A lane per path
+// that staged its pins in LDS spent most of a step on its eight pins one
+// after another: 53 us against 18 for 10,000 paths at 200k cells, 105 against
+// 95 for 96,000 at 2M.
+constexpr int WALK_PATHS = 32;  // per workgroup of 128
+
 template <typename T>
 __global__ void __launch_bounds__(128) k_walk(Topo tp, int k, const int32_t *__restrict__ d_num_paths,
                                                const int32_t *__restrict__ out_slot, const int32_t *__restrict__ sel,
                                                const int32_t *__restrict__ slot_dev, const int32_t *__restrict__ slot_par,
                                                const T *__restrict__ slot_key, const uint64_t *__restrict__ node,
-                                               int words, const int32_t *__restrict__ path_ptr, int32_t *__restrict__ path_pins,
-                                               int32_t *__restrict__ path_int, int32_t *__restrict__ path_ep,
-                                               int32_t *__restrict__ path_epi, int32_t *__restrict__ path_rank,
-                                               T *__restrict__ path_slack, int32_t *__restrict__ err, int pin_cap) {
-  __shared__ int32_t stage[128 * WALK_ROW];
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  // every lane stays to the end: the wave shares the walk's flush points
-  bool live = q < *d_num_paths;
-  int slot = 0, r = 0, f = 0, lo = 0, hi = 0;
-  int devs[TDP_MAX_K];
-  int nd = 0;
+                                               int words, const int32_t *__restrict__ path_ptr,
+                                               int32_t *__restrict__ path_pins, int32_t *__restrict__ path_int,
+                                               int32_t *__restrict__ path_ep, int32_t *__restrict__ path_epi,
+                                               int32_t *__restrict__ path_rank, T *__restrict__ path_slack,
+                                               int32_t *__restrict__ err, int pin_cap) {
+  // a deviation: its sink, cell, driver and both external ids
+  __shared__ int32_t s_dev[WALK_PATHS][TDP_MAX_K][5];
+  const int lane = wave_lane(), h = lane & 3, first = lane & ~3, mine = threadIdx.x >> 2;
+  const int q = blockIdx.x * WALK_PATHS + mine;
+  const int n = *d_num_paths;
+  if ((int)blockIdx.x * WALK_PATHS >= n) return;
+  bool live = q < n;
+  int slot = 0, r = 0, f = 0, lo = 0, hi = 0, nd = 0;
   if (live) {
     slot = out_slot[q];
     const int qs = slot / k;
     r = slot - qs * k;
-    const int base = qs * k;
     f = sel[qs];
-    // deviations, upstream-most first (the walk meets them last to first)
-    for (int a = r; a >= 0 && nd < TDP_MAX_K;) {
-      const int d = slot_dev[base + a];
-      if (d < 0) break;
-      devs[nd++] = d;
-      a = slot_par[base + a];
-    }
     lo = path_ptr[q];
     hi = path_ptr[q + 1];
+    // deviations, upstream-most first (the walk meets them last to first)
+    for (int a = r; a >= 0 && nd < TDP_MAX_K;) {
+      const int d = slot_dev[qs * k + a];
+      if (d < 0) break;
+      if (h == 0) s_dev[mine][nd][0] = d;
+      ++nd;
+      a = slot_par[qs * k + a];
+    }
     if (lo < 0 || hi > pin_cap || hi - lo < 2) {  // only after a failed update
-      atomicOr(err, 1);
+      if (h == 0) atomicOr(err, 1);
       live = false;
     }
   }
-  int di = nd - 1;
-  RevWriter w{path_pins, path_int, stage + threadIdx.x * WALK_ROW, live ? hi - 1 : -1, live ? lo : 0, live ? hi : 0};
-  const bool ok = walk_path(tp, node, words, w, f, live, [&]() { return di >= 0 ? devs[di--] : -1; });
-  if (!live) return;
-  if (!ok) atomicOr(err, 1);
+  __syncthreads();
+  if (live) {
+    for (int i = h; i < nd; i += 4) {
+      const int d = s_dev[mine][i][0], drv = tp.snk_drv[d];
+      s_dev[mine][i][1] = tp.snk_comb[d];
+      s_dev[mine][i][2] = drv;
+      s_dev[mine][i][3] = tp.snk_ext[d];
+      s_dev[mine][i][4] = tp.drv_ext[drv];
+    }
+  }
+  __syncthreads();
   const int et = tp.A + f;
+  int v = 0, pos = 0, di = nd - 1;
+  // two pins at pos - 1 (driver) and pos (sink); path ranges start at even positions
+  auto put = [&](int at, int drv, int drv_ext, int snk, int snk_ext) {
+    *(int2 *)(path_pins + at - 1) = make_int2(drv_ext, snk_ext);
+    *(int2 *)(path_int + at - 1) = make_int2(drv, tp.M + snk);
+  };
+  if (live) {
+    v = tp.snk_drv[et];
+    pos = hi - 1;
+    if (h == 0) put(pos, v, tp.drv_ext[v], et, tp.snk_ext[et]);
+    pos -= 2;
+  }
+  for (;;) {
+    const bool go = live && v >= tp.n_start && pos > lo;
+    if (!__ballot(go)) break;
+    int4 rec = make_int4(0, -1, 0, 0);
+    if (go) rec = reinterpret_cast<const int4 *>(node + (size_t)(v - tp.n_start) * words)[h];
+    // the driver this lane's hop starts at, and whether the chain gets there
+    const int up = __shfl_up(rec.y, 1, 4);
+    const int at = h == 0 ? v : up;
+    const bool there = go && at >= tp.n_start;
+    const unsigned on = (unsigned)(__ballot(there) >> first) & 15u;
+    const int dc = di >= 0 ? s_dev[mine][di][1] : -1;
+    const unsigned hit = (unsigned)(__ballot(there && at - tp.n_start == dc) >> first) & 15u;
+    // hops before the first one the chain does not reach, up to and with a deviation
+    int hops = __ffs(~on & 31u) - 1;
+    const int dev = hit ? __ffs(hit) - 1 : 4;
+    const bool turn = dev < hops;
+    if (turn) hops = dev + 1;
+    int snk = id30((uint32_t)rec.x), drv = rec.y, snk_ext = (int)((uint32_t)rec.z & ID_MASK), drv_ext = rec.w;
+    if (turn && h == dev) {
+      const int32_t *s = s_dev[mine][di];
+      snk = s[0];
+      drv = s[2];
+      snk_ext = s[3];
+      drv_ext = s[4];
+    }
+    const int p = pos - 2 * h;
+    if (go && h < hops && p > lo) put(p, drv, drv_ext, snk, snk_ext);
+    const int nv = __shfl(drv, first + (hops > 0 ? hops - 1 : 0), 64);
+    if (go) {
+      v = nv;
+      pos -= 2 * hops;
+      if (turn) --di;
+    }
+  }
+  if (!live || h != 0) return;
+  if (pos != lo - 1 || v >= tp.n_start || di >= 0) atomicOr(err, 1);
   path_ep[q] = tp.snk_ext[et];
   path_epi[q] = f;
   path_rank[q] = r;
@@ -340,34 +989,44 @@ static void launch_search(tdp_graph g, int k, T limit, hipStream_t s) {
   const Topo &tp = g->topo;
   hipLaunchKernelGGL((k_search<T, KM>), dim3(nb(tp.E, 64 / KM)), dim3(64), 0, s, tp, k, limit, g->d_nsel, g->sel_list,
                      (const T *)g->ep_slack, g->cdep, g->node, (T *)g->slot_key,
-                     g->slot_dev, g->slot_par, g->slot_len, g->slot_cells, g->sel_npop);
+                     g->slot_dev, g->slot_par, g->slot_len);
 }
 
 // endpoints of each instance: the first n in (slack, pin) order, or the
-// violated ones (n < 0); fills sel_list, d_nsel, inst_selb, inst_nsel
+// violated ones (n < 0); fills sel_list, d_nsel and inst_selb
 template <typename T>
 void select_stage(tdp_graph g, int n, hipStream_t s) {
   const Topo &tp = g->topo;
   const int E = tp.E;
+  const Look lk{g->look_st, g->look_ctr, g->d_err};
   if (n < 0) {
-    hipLaunchKernelGGL(k_sel_violated<T>, dim3(nb(E, 256)), dim3(256), 0, s, tp, (const T *)g->ep_slack,
-                       g->sel_flag);
-  } else {
-    hipLaunchKernelGGL(k_sel_keys<T>, dim3(nb(E, 256)), dim3(256), 0, s, tp, (const T *)g->ep_slack, g->sort_k0,
-                       g->sort_v0);
-    radix_sort(g->sort_k0, g->sort_v0, g->sort_k1, g->sort_v1, E, nullptr, g->key_bits32, g->sort_hist,
-               g->scan_tmp, s);
-    hipLaunchKernelGGL(k_sel_first_n<T>, dim3(nb(E, 256)), dim3(256), 0, s, tp, g->d_ep_base, g->sort_k0,
-                       g->sort_v0, (const T *)g->ep_slack, n, g->sel_flag);
+    hipLaunchKernelGGL(k_sel_violated<T>, dim3(std::min(512, nb(E, SEL_TILE))), dim3(256), 0, s, tp, lk, g->d_ep_base,
+                       (const T *)g->ep_slack, g->sel_list, g->d_nsel, g->inst_selb);
+    return;
   }
-  scan_exclusive(g->sel_flag, g->sel_pos, E, nullptr, g->d_nsel, g->scan_tmp, s);
-  hipLaunchKernelGGL(k_sel_compact, dim3(nb(E, 256)), dim3(256), 0, s, tp, g->sel_flag, g->sel_pos, g->sel_list);
-  hipLaunchKernelGGL(k_sel_counts, dim3(nb(tp.num_inst, 64)), dim3(64), 0, s, tp.num_inst, E, g->d_ep_base,
-                     g->sel_pos, g->d_nsel, g->inst_selb, g->inst_nsel);
+  int most = 0;
+  for (int i = 0; i < tp.num_inst; ++i) most = std::max(most, g->lv.ep_base[i + 1] - g->lv.ep_base[i]);
+  if (most <= SEL_SELECT) {
+    const dim3 grid(std::min(256, tp.num_inst));
+    if (most <= 16 * 1024)
+      hipLaunchKernelGGL((k_sel_worst<T, 16>), grid, dim3(1024), 0, s, tp.num_inst, g->d_ep_base,
+                         (const T *)g->ep_slack, n, lk, g->sel_list, g->d_nsel, g->inst_selb);
+    else
+      hipLaunchKernelGGL((k_sel_worst<T, 64>), grid, dim3(1024), 0, s, tp.num_inst, g->d_ep_base,
+                         (const T *)g->ep_slack, n, lk, g->sel_list, g->d_nsel, g->inst_selb);
+    return;
+  }
+  hipLaunchKernelGGL(k_sel_keys<T>, dim3(nb(E, 256)), dim3(256), 0, s, tp, (const T *)g->ep_slack, g->sort_k0,
+                     g->sort_v0);
+  const Sorted<uint64_t> so = radix_sort(g->sort_k0, g->sort_v0, g->sort_k1, g->sort_v1, E, nullptr, g->key_bits32, 11,
+                                         g->sort_hist, s);
+  hipLaunchKernelGGL(k_sel_cut_sorted<T>, dim3(tp.num_inst), dim3(1024), 0, s, g->d_ep_base, (const T *)g->ep_slack,
+                     so.keys, so.vals, n, g->sel_cut);
+  hipLaunchKernelGGL(k_sel_take<T>, dim3(tp.num_inst), dim3(1024), 0, s, tp.num_inst, g->d_ep_base,
+                     (const T *)g->ep_slack, g->sel_cut, g->sel_list, g->d_nsel, g->inst_selb);
 }
 
-// up to k paths per selected endpoint, in slots q * k + r; per instance the
-// number found (inst_nvalid)
+// up to k paths per selected endpoint, in slots q * k + r
 template <typename T>
 void search_stage(tdp_graph g, int k, float slack_limit, hipStream_t s) {
   const T limit = (T)slack_limit;
@@ -379,19 +1038,16 @@ void search_stage(tdp_graph g, int k, float slack_limit, hipStream_t s) {
     case 16: launch_search<T, 16>(g, k, limit, s); break;
     default: launch_search<T, 32>(g, k, limit, s); break;
   }
-  hipLaunchKernelGGL(k_valid_counts, dim3(g->topo.num_inst), dim3(256), 0, s, g->inst_selb, g->inst_nsel,
-                     g->sel_npop, g->inst_nvalid);
 }
 
-// slots sorted by (instance, path slack), stable: sort_v0 holds the slot
-// order, sort_k0 the keys
+// the slots sorted by (instance, path slack), stable
 template <typename T>
-void slot_sort_stage(tdp_graph g, int k, hipStream_t s) {
+Sorted<uint64_t> slot_sort_stage(tdp_graph g, int k, hipStream_t s) {
   const int cap = g->slot_cap;
-  hipLaunchKernelGGL(k_slot_keys<T>, dim3(nb(cap, 256)), dim3(256), 0, s, g->topo, k, g->d_nsel, g->sel_list,
-                     (const T *)g->slot_key, g->d_nslots, g->sort_k0, g->sort_v0, (int64_t)cap);
-  radix_sort(g->sort_k0, g->sort_v0, g->sort_k1, g->sort_v1, cap, g->d_nslots,
-             sizeof(T) == 4 ? g->key_bits32 : 64, g->sort_hist, g->scan_tmp, s);
+  hipLaunchKernelGGL(k_slot_keys<T>, dim3(std::min(1024, nb(cap, 256))), dim3(256), 0, s, g->topo, k, g->d_nsel,
+                     g->sel_list, (const T *)g->slot_key, g->d_nslots, g->sort_k0, g->sort_v0);
+  return radix_sort(g->sort_k0, g->sort_v0, g->sort_k1, g->sort_v1, cap, g->d_nslots,
+                    sizeof(T) == 4 ? g->key_bits32 : 64, 11, g->sort_hist, s);
 }
 
 void ptr_tail(const int32_t *d_num_paths, const int32_t *len, int32_t *ptr, hipStream_t s) {
@@ -409,18 +1065,33 @@ void extract_impl(tdp_graph g, int n, int k, int K, float slack_limit, hipStream
   prof_end(g, TDP_STAGE_SEARCH, s);
   // ordering
   prof_begin(g, TDP_STAGE_ORDER, s);
-  const int cap = g->slot_cap;
-  slot_sort_stage<T>(g, k, s);
-  hipLaunchKernelGGL(k_path_bases, dim3(1), dim3(1), 0, s, tp.num_inst, k, K, g->inst_nsel, g->inst_nvalid,
-                     g->inst_seg, g->inst_outb, g->inst_kept, g->d_num_paths);
-  hipLaunchKernelGGL(k_path_index<T>, dim3(nb(cap, 256)), dim3(256), 0, s, tp, k, g->d_nslots, g->sort_v0,
-                     g->sel_list, g->inst_seg, g->inst_outb, g->inst_kept, g->slot_len, g->out_slot, g->out_len, g->slot_out);
-  scan_exclusive(g->out_len, g->path_ptr, g->max_out, g->d_num_paths, nullptr, g->scan_tmp, s);
-  ptr_tail(g->d_num_paths, g->out_len, g->path_ptr, s);
+  // the most slots the call can have: the endpoints selected times k
+  const long long most = (n < 0 ? (long long)tp.E : std::min((long long)tp.E, (long long)n * tp.num_inst)) * k;
+  int slot_bits = 1;
+  while ((1ll << slot_bits) < most) ++slot_bits;
+  if (sizeof(T) == 4 && most <= ORDER_ONE) {
+    hipLaunchKernelGGL(k_order_one, dim3(1), dim3(1024), 0, s, tp, k, K, g->d_nsel, g->sel_list, g->inst_selb,
+                       (const float *)g->slot_key, g->slot_len, g->d_nslots, g->out_slot, g->slot_out, g->path_ptr,
+                       g->d_num_paths);
+  } else if (sizeof(T) == 4 && g->key_bits32 + slot_bits <= 64) {
+    const OrderBuf ob{g->sort_k0, g->sort_k1, g->order_hist, g->order_total, g->order_flags};
+    hipLaunchKernelGGL(k_rank, dim3((int)std::min<long long>(1024, (most + 63) / 64)), dim3(1024), 0, s, tp, k, slot_bits,
+                       g->d_nsel, g->sel_list, g->inst_selb, (const float *)g->slot_key, ob.w0);
+    hipLaunchKernelGGL(k_order, dim3((int)std::min<long long>(ORDER_GROUPS, (most + ORDER_RUN - 1) / ORDER_RUN)),
+                       dim3(1024), 0, s, tp, k, K, g->key_bits32, slot_bits, g->d_nsel, g->sel_list, g->inst_selb,
+                       (const float *)g->slot_key, g->slot_len, ob, g->d_nslots, g->out_slot, g->slot_out, g->path_ptr,
+                       g->d_num_paths, g->d_err);
+  } else {
+    const Sorted<uint64_t> so = slot_sort_stage<T>(g, k, s);
+    const Look lk{g->look_st, g->look_ctr, g->d_err};
+    hipLaunchKernelGGL(k_path_out<T>, dim3(std::min(256, nb(g->slot_cap, OUT_TILE))), dim3(256), 0, s, k, K, lk,
+                       g->d_nslots, g->inst_selb, so.keys, so.vals, g->slot_len, g->out_slot, g->slot_out, g->path_ptr,
+                       g->d_num_paths);
+  }
   prof_end(g, TDP_STAGE_ORDER, s);
   // walk
   prof_begin(g, TDP_STAGE_WALK, s);
-  hipLaunchKernelGGL(k_walk<T>, dim3(nb(g->max_out, 128)), dim3(128), 0, s, tp, k, g->d_num_paths, g->out_slot,
+  hipLaunchKernelGGL(k_walk<T>, dim3(nb(g->max_out, WALK_PATHS)), dim3(4 * WALK_PATHS), 0, s, tp, k, g->d_num_paths, g->out_slot,
                      g->sel_list, g->slot_dev, g->slot_par, (const T *)g->slot_key, g->node, node_words<T>(g->side_k),
                      g->path_ptr, g->path_pins, g->path_int, g->path_ep, g->path_epi, g->path_rank,
                      (T *)g->path_slack, g->d_err, g->pin_cap);
@@ -433,7 +1104,7 @@ template void select_stage<float>(tdp_graph, int, hipStream_t);
 template void select_stage<double>(tdp_graph, int, hipStream_t);
 template void search_stage<float>(tdp_graph, int, float, hipStream_t);
 template void search_stage<double>(tdp_graph, int, float, hipStream_t);
-template void slot_sort_stage<float>(tdp_graph, int, hipStream_t);
-template void slot_sort_stage<double>(tdp_graph, int, hipStream_t);
+template Sorted<uint64_t> slot_sort_stage<float>(tdp_graph, int, hipStream_t);
+template Sorted<uint64_t> slot_sort_stage<double>(tdp_graph, int, hipStream_t);
 
 }  // namespace tdp

@@ -77,27 +77,27 @@ __device__ __forceinline__ void axis_weight(int b, float f, int g, int R, int i,
 }
 
 __global__ void __launch_bounds__(DN_BLOCK) k_dn_keys(int n, const float *__restrict__ x, const float *__restrict__ y,
-                                                       DensityGrid gr, uint64_t *__restrict__ key,
+                                                       DensityGrid gr, uint32_t *__restrict__ key,
                                                        uint32_t *__restrict__ val) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n) return;
   float fx, fy;
   const int bx = dn_bin(x[c], gr.x0, gr.bw, gr.gx, fx);
   const int by = dn_bin(y[c], gr.y0, gr.bh, gr.gy, fy);
-  key[c] = (uint64_t)by * (uint64_t)gr.gx + (uint64_t)bx;
+  key[c] = (uint32_t)by * (uint32_t)gr.gx + (uint32_t)bx;
   val[c] = (uint32_t)c;
 }
 
 // start[b] = first sorted position with key >= b, for b in [0, G]: a binary
 // search per bin (balanced however crowded the bins are)
-__global__ void __launch_bounds__(DN_BLOCK) k_dn_starts(int n, int G, const uint64_t *__restrict__ key,
+__global__ void __launch_bounds__(DN_BLOCK) k_dn_starts(int n, int G, const uint32_t *__restrict__ key,
                                                          int32_t *__restrict__ start) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b > G) return;
   int lo = 0, hi = n;  // the answer lies in [lo, hi]
   while (lo < hi) {
     const int mid = lo + ((hi - lo) >> 1);
-    if (key[mid] < (uint64_t)b) lo = mid + 1;
+    if (key[mid] < (uint32_t)b) lo = mid + 1;
     else hi = mid;
   }
   start[b] = lo;
@@ -161,14 +161,14 @@ __device__ __forceinline__ void window_row(const DensityGrid &gr, const int32_t 
 }
 
 // the product a_c Wx_c(i) Wy_c(j) of sorted cell s in row sj = j - dj
-__device__ __forceinline__ double dn_term(const DensityGrid &gr, const uint64_t *__restrict__ key,
+__device__ __forceinline__ double dn_term(const DensityGrid &gr, const uint32_t *__restrict__ key,
                                           const float *__restrict__ w, int n, int K, int i, int sj, int dj, int s) {
-  const int di = i - (int)(key[s] - (uint64_t)sj * (uint64_t)gr.gx);
+  const int di = i - (int)(key[s] - (uint32_t)sj * (uint32_t)gr.gx);
   return (double)(w[(size_t)(di + gr.R) * n + s] * w[(size_t)(K + dj + gr.R) * n + s]);
 }
 
 __global__ void __launch_bounds__(DN_BLOCK) k_dn_bins(int n, DensityGrid gr, const int32_t *__restrict__ start,
-                                                       const uint64_t *__restrict__ key, const float *__restrict__ w,
+                                                       const uint32_t *__restrict__ key, const float *__restrict__ w,
                                                        float *__restrict__ map, int32_t *__restrict__ heavy,
                                                        int32_t *__restrict__ n_heavy) {
   const int G = gr.gx * gr.gy, R = gr.R, K = 2 * R + 1;
@@ -214,7 +214,7 @@ __device__ __forceinline__ double block_sum1(double a) {
 
 // one workgroup per listed bin (grid-stride over the list)
 __global__ void __launch_bounds__(DN_BLOCK) k_dn_heavy(int n, DensityGrid gr, const int32_t *__restrict__ start,
-                                                        const uint64_t *__restrict__ key, const float *__restrict__ w,
+                                                        const uint32_t *__restrict__ key, const float *__restrict__ w,
                                                         const int32_t *__restrict__ heavy,
                                                         const int32_t *__restrict__ n_heavy, float *__restrict__ map) {
   const int R = gr.R, K = 2 * R + 1;
@@ -337,20 +337,21 @@ void density_impl(tdp_graph g, const float *x, const float *y, float scale, doub
   const DensityGrid &gr = g->dn;
   const int G = gr.gx * gr.gy;
   prof_begin(g, TDP_STAGE_DENSITY, s);
+  Sorted<uint32_t> so{g->dn_k0, g->dn_v0};
   if (n > 0) {
     hipLaunchKernelGGL(k_dn_keys, dim3(nbk(n, DN_BLOCK)), dim3(DN_BLOCK), 0, s, n, x, y, gr, g->dn_k0, g->dn_v0);
-    radix_sort(g->dn_k0, g->dn_v0, g->dn_k1, g->dn_v1, n, nullptr, g->dn_key_bits, g->dn_hist, g->dn_scan, s);
-    hipLaunchKernelGGL(k_dn_weights, dim3(nbk(n, DN_BLOCK)), dim3(DN_BLOCK), 0, s, n, (const uint32_t *)g->dn_v0,
+    so = radix_sort(g->dn_k0, g->dn_v0, g->dn_k1, g->dn_v1, n, nullptr, g->dn_key_bits, 11, g->dn_hist, s);
+    hipLaunchKernelGGL(k_dn_weights, dim3(nbk(n, DN_BLOCK)), dim3(DN_BLOCK), 0, s, n, (const uint32_t *)so.vals,
                        x, y, (const float *)g->dn_area, gr, g->dn_w);
   }
   hipLaunchKernelGGL(k_dn_starts, dim3(nbk((long long)G + 1, DN_BLOCK)), dim3(DN_BLOCK), 0, s, n, G,
-                     (const uint64_t *)g->dn_k0, g->dn_start);
+                     (const uint32_t *)so.keys, g->dn_start);
   float *map = map_out ? map_out : g->dn_map;
   fill_i32(g->dn_nheavy, 1, 0, s);
   hipLaunchKernelGGL(k_dn_bins, dim3(nbk(G, DN_BLOCK)), dim3(DN_BLOCK), 0, s, n, gr, (const int32_t *)g->dn_start,
-                     (const uint64_t *)g->dn_k0, (const float *)g->dn_w, map, g->dn_heavy, g->dn_nheavy);
+                     (const uint32_t *)so.keys, (const float *)g->dn_w, map, g->dn_heavy, g->dn_nheavy);
   hipLaunchKernelGGL(k_dn_heavy, dim3(DN_PARTS), dim3(DN_BLOCK), 0, s, n, gr, (const int32_t *)g->dn_start,
-                     (const uint64_t *)g->dn_k0, (const float *)g->dn_w, (const int32_t *)g->dn_heavy,
+                     (const uint32_t *)so.keys, (const float *)g->dn_w, (const int32_t *)g->dn_heavy,
                      (const int32_t *)g->dn_nheavy, map);
   hipLaunchKernelGGL(k_dn_reduce, dim3(DN_PARTS), dim3(DN_BLOCK), 0, s, gr, (const float *)map, g->dn_part);
   hipLaunchKernelGGL(k_dn_final, dim3(1), dim3(DN_BLOCK), 0, s, (const double *)g->dn_part,
@@ -358,7 +359,7 @@ void density_impl(tdp_graph g, const float *x, const float *y, float scale, doub
   if (gx && gy && n > 0) {
     const float *area = g->dn_area;
     const uint8_t *fixed = g->topo.cell_fixed;
-    const uint32_t *order = g->dn_v0;  // cell ids in bin order (this call's sort)
+    const uint32_t *order = so.vals;  // cell ids in bin order (this call's sort)
     switch (gr.R) {
       case 0: launch_grad<0>(n, order, x, y, area, fixed, gr, map, scale, gx, gy, s); break;
       case 1: launch_grad<1>(n, order, x, y, area, fixed, gr, map, scale, gx, gy, s); break;

@@ -10,12 +10,15 @@ namespace tdp {
 void scan_exclusive(const int32_t *in, int32_t *out, int cap, const int32_t *d_n, int32_t *d_total,
                     int32_t *tmp, hipStream_t s);
 int scan_tmp_size(int cap);
-// Stable sort of 64-bit keys (low `bits` bits, a multiple of 8) carrying
-// 32-bit values; the result is left in k0/v0.  hist needs sort_hist_size(cap)
-// ints; scan_tmp needs scan_tmp_size(sort_hist_size(cap)).
-void radix_sort(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, int cap, const int32_t *d_n, int bits,
-                int32_t *hist, int32_t *scan_tmp, hipStream_t s);
-int sort_hist_size(int cap);
+// Stable sort of the low `bits` bits of 32- or 64-bit keys carrying 32-bit
+// values, by digits of at most digit_bits (<= 11) bits; the result is in one of
+// the two pairs of buffers.  n = min(cap, *d_n) when d_n is given.  hist needs
+// sort_hist_size(cap, digit_bits) ints.
+template <typename Key> struct Sorted { Key *keys; uint32_t *vals; };
+template <typename Key>
+Sorted<Key> radix_sort(Key *k0, uint32_t *v0, Key *k1, uint32_t *v1, int cap, const int32_t *d_n, int bits,
+                       int digit_bits, int32_t *hist, hipStream_t s);
+int sort_hist_size(int cap, int digit_bits);
 void fill_i32(int32_t *p, int n, int32_t v, hipStream_t s);
 // xy[i] = (x[i], y[i]): one 8-byte gather per random position lookup; where
 // a coordinate is NaN or infinite, *bad = gen (if bad is given); tag (if

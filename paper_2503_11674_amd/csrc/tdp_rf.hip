@@ -431,14 +431,14 @@ void rf_extract_impl(tdp_graph g, int n, int K, hipStream_t s) {
   select_stage<T>(g, n, s);
   hipLaunchKernelGGL(k_rf_sel_keys<T>, dim3(nb(tp.E, 256)), dim3(256), 0, s, g->d_nsel, g->sel_list,
                      (const T *)g->ep_slack, g->sort_k0, g->sort_v0);
-  radix_sort(g->sort_k0, g->sort_v0, g->sort_k1, g->sort_v1, tp.E, g->d_nsel, sizeof(T) == 4 ? 32 : 64,
-             g->sort_hist, g->scan_tmp, s);
+  const Sorted<uint64_t> so = radix_sort(g->sort_k0, g->sort_v0, g->sort_k1, g->sort_v1, tp.E, g->d_nsel,
+                                         sizeof(T) == 4 ? 32 : 64, 11, g->sort_hist, s);
   const int cap = std::min(K, g->max_out);
-  hipLaunchKernelGGL(k_rf_path_len<T>, dim3(nb(cap, 256)), dim3(256), 0, s, tp, cap, g->d_nsel, g->sort_v0,
+  hipLaunchKernelGGL(k_rf_path_len<T>, dim3(nb(cap, 256)), dim3(256), 0, s, tp, cap, g->d_nsel, so.vals,
                      (const T *)g->rf_at, g->rf_crit, g->out_len, g->d_num_paths);
   scan_exclusive(g->out_len, g->path_ptr, g->max_out, g->d_num_paths, nullptr, g->scan_tmp, s);
   ptr_tail(g->d_num_paths, g->out_len, g->path_ptr, s);
-  hipLaunchKernelGGL(k_rf_walk<T>, dim3(nb(cap, 256)), dim3(256), 0, s, tp, g->d_num_paths, g->sort_v0,
+  hipLaunchKernelGGL(k_rf_walk<T>, dim3(nb(cap, 256)), dim3(256), 0, s, tp, g->d_num_paths, so.vals,
                      (const T *)g->rf_at, (const T *)g->ep_slack, g->rf_crit, g->path_ptr, g->path_pins, g->path_int,
                      g->rf_path_tran, g->path_ep, g->path_epi, g->path_rank, (T *)g->path_slack, g->slot_out, g->d_err,
                      g->pin_cap);

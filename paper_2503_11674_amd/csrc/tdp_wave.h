@@ -29,6 +29,20 @@ template <> __device__ __forceinline__ double pos_inf<double>() { return __built
 
 __device__ __forceinline__ int wave_lane() { return threadIdx.x & 63; }
 
+// words that waves of one launch exchange (relaxed device-scope accesses)
+__device__ __forceinline__ uint64_t pub_ld(const uint64_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t pub_ld(const uint32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void pub_st(uint64_t *p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void pub_st(uint32_t *p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Segmented reductions over the 64 lanes of a wave (segment [head, tail],
 // the result broadcast to every lane).  These shuffle forms combine lane L
 // with lane L - d for d = 1, 2, 4, ..., so the order of the operations
