@@ -198,42 +198,6 @@ template <typename T>
 __host__ __device__ constexpr int list_words() { return (int)sizeof(T) / 4; }
 template <typename T>
 __host__ __device__ constexpr int node_words(int km) { return HOP_WORDS + (km > 1 ? km * list_words<T>() : 0); }
-__device__ __forceinline__ uint64_t pack_ids(int a, int b, uint32_t tag) {
-  return (uint64_t)(((uint32_t)a & ID_MASK) | tag << 30) | (uint64_t)(uint32_t)b << 32;
-}
-__device__ __forceinline__ uint32_t tag_lo(uint64_t w) { return (uint32_t)w >> 30; }
-__device__ __forceinline__ uint32_t tag_hi(uint64_t w) { return (uint32_t)(w >> 62); }
-// an id of 30 bits, sign-extended (-1 stays -1)
-__device__ __forceinline__ int id30(uint32_t v) { return (int)(v << 2) >> 2; }
-
-// a deviation of a list
-template <typename T> struct Dev { T cost; int32_t sink; };
-__device__ __forceinline__ uint64_t pack_dev(float cost, int sink, uint32_t tag) {
-  return (uint64_t)__float_as_uint(cost) | (uint64_t)(((uint32_t)sink & ID_MASK) | tag << 30) << 32;
-}
-__device__ __forceinline__ Dev<float> unpack_dev(uint64_t w) {
-  return Dev<float>{__uint_as_float((uint32_t)w), id30((uint32_t)(w >> 32))};
-}
-// entry j of the list of combinational cell c
-template <typename T, int KM>
-__device__ __forceinline__ Dev<T> list_entry(const uint64_t *__restrict__ node, int c, int j) {
-  const uint64_t *p = node + (size_t)c * node_words<T>(KM) + HOP_WORDS;
-  if constexpr (sizeof(T) == 4) {
-    return unpack_dev(p[j]);
-  } else {
-    return Dev<T>{__longlong_as_double((long long)p[2 * j]), id30((uint32_t)(p[2 * j + 1] >> 32))};
-  }
-}
-template <typename T, int KM>
-__device__ __forceinline__ void store_entry(uint64_t *__restrict__ node, int c, int j, Dev<T> e, uint32_t tag) {
-  uint64_t *p = node + (size_t)c * node_words<T>(KM) + HOP_WORDS;
-  if constexpr (sizeof(T) == 4) {
-    p[j] = pack_dev(e.cost, e.sink, tag);
-  } else {
-    p[2 * j] = (uint64_t)__double_as_longlong(e.cost);
-    p[2 * j + 1] = pack_dev(0.f, e.sink, tag);
-  }
-}
 
 struct HostLevels {
   std::vector<int32_t> fw_lvl;    // [D+1]: level l input chunks are [fw_lvl[l-1], fw_lvl[l])

@@ -4,7 +4,7 @@
 // critical input of every cell except where a deviation names another input.
 #pragma once
 
-#include "tdp_internal.h"
+#include "tdp_wave.h"
 
 namespace tdp {
 
