@@ -161,7 +161,7 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
   g->key_bits32 = T.num_inst <= 1 ? 32 : (T.num_inst <= 256 ? 40 : 48);
   int max_inst_e = 1;
   for (int i = 0; i < T.num_inst; ++i) max_inst_e = std::max(max_inst_e, H.lv.ep_base[i + 1] - H.lv.ep_base[i]);
-  g->ep_chunks = std::min(64, std::max(1, (max_inst_e + 4095) / 4096));
+  g->ep_chunks = std::min(256, std::max(1, (max_inst_e + 1023) / 1024));
 
   bool ok = true;
   // library
@@ -205,9 +205,9 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
        dalloc(g, g->darc, T.A, es) && dalloc(g, g->crit, T.n_comb) &&
        dalloc(g, g->node, (size_t)T.n_comb * (es == 8 ? node_words<double>(g->side_k) : node_words<float>(g->side_k))) &&
        dalloc(g, g->cdep, T.M) && dalloc(g, g->d_tag, 2) && dalloc(g, g->ep_slack, T.E, es) &&
-       dalloc(g, g->red_ep, (size_t)3 * T.num_inst * g->ep_chunks) && dalloc(g, g->red_loss, 4096) &&
+       dalloc(g, g->red_ep, (size_t)3 * T.num_inst * g->ep_chunks) && dalloc(g, g->red_loss, 4096) && dalloc(g, g->red_p2p, 1024) &&
        dalloc(g, g->red_wa, 4096) && dalloc(g, g->summary, (size_t)4 * T.num_inst) &&
-       dalloc(g, g->inst_nfail, T.num_inst) && dalloc(g, g->d_err, 4) && dalloc(g, g->consts, 4) &&
+       dalloc(g, g->d_err, 4) && dalloc(g, g->consts, 4) &&
        upload(g, g->d_inst_req, g->h_inst_req);
   // dataflow sweeps: forward in single precision or without deviation lists,
   // backward where every net fits one 64-lane chunk
@@ -235,7 +235,7 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
   ok = ok && dalloc(g, g->sel_flag, T.E) && dalloc(g, g->sel_pos, T.E) && dalloc(g, g->sel_list, T.E) &&
        dalloc(g, g->d_nsel, 1) && dalloc(g, g->sel_cut, (size_t)4 * ni) &&
        dalloc(g, g->inst_outb, ni) && dalloc(g, g->inst_kept, ni) && dalloc(g, g->inst_selb, (size_t)ni + 1) &&
-       dalloc(g, g->look_st, look_words(T, sc)) && dalloc(g, g->look_ctr, 4) &&
+       dalloc(g, g->look_st, look_words(T, sc)) && dalloc(g, g->look_ctr, 8) &&
        dalloc(g, g->order_hist, (size_t)64 << 8) && dalloc(g, g->order_total, 64) && dalloc(g, g->order_flags, 65) &&
        dalloc(g, g->slot_key, sc, es) && dalloc(g, g->slot_dev, sc) && dalloc(g, g->slot_par, sc) &&
        dalloc(g, g->slot_len, sc) && dalloc(g, g->slot_out, std::max(sc, mo)) && dalloc(g, g->d_nslots, 1) &&
@@ -247,11 +247,11 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
        dalloc(g, g->path_rank, mo) && dalloc(g, g->d_num_paths, 1) && dalloc(g, g->path_slack, mo, es);
   // pairs
   ok = ok && dalloc(g, g->pw, T.S) && dalloc(g, g->pin_p, T.S) && dalloc(g, g->pacc, T.S) &&
-       dalloc(g, g->pfirst, T.S, sizeof(int32_t), 0x7F) && dalloc(g, g->pflag, T.S) && dalloc(g, g->d_npairs, 1) &&
+       dalloc(g, g->pfirst, T.S, sizeof(int32_t), 0x7F) && dalloc(g, g->d_npairs, 1) &&
        dalloc(g, g->pair_sink, T.S) && dalloc(g, g->pair_cs, T.S) && dalloc(g, g->pair_ct, T.S) &&
        dalloc(g, g->pair_dox, T.S) && dalloc(g, g->pair_doy, T.S) && dalloc(g, g->pair_w, T.S) &&
-       dalloc(g, g->cell_cnt, T.N) && dalloc(g, g->cell_ptr, (size_t)T.N + 1) && dalloc(g, g->cell_cur, T.N) &&
-       dalloc(g, g->cell_flag, T.N) && dalloc(g, g->touched, T.N) && dalloc(g, g->d_ntouched, 1) &&
+       dalloc(g, g->cell_cnt, T.N) && dalloc(g, g->cell_ptr, T.N) && dalloc(g, g->cell_cur, T.N) &&
+       dalloc(g, g->touched, T.N) && dalloc(g, g->touched_ptr, (size_t)T.N + 1) && dalloc(g, g->d_ntouched, 1) &&
        dalloc(g, g->inc_other, (size_t)2 * T.S) && dalloc(g, g->inc_key, (size_t)2 * T.S) &&
        dalloc(g, g->inc_dx, (size_t)2 * T.S) && dalloc(g, g->inc_dy, (size_t)2 * T.S) &&
        dalloc(g, g->inc_w, (size_t)2 * T.S);

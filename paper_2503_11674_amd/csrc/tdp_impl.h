@@ -80,7 +80,6 @@ int report_node_cap(const tdp_graph_s *g);
 template <typename T> tdp_status report_impl(tdp_graph g, const GtStore &st, int K, float slack_limit, hipStream_t s);
 template <typename T> void pairs_update_impl(tdp_graph g, int rule, float w0, float w1, hipStream_t s);
 void pairs_rebuild(tdp_graph g, hipStream_t s);
-void pairs_compact(tdp_graph g, hipStream_t s);
 template <typename T>
 void p2p_fwd_impl(tdp_graph g, int kind, const float *x, const float *y, double *loss, hipStream_t s);
 template <typename T>

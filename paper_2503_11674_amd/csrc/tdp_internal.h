@@ -301,16 +301,18 @@ struct tdp_graph_s {
   int32_t pos_gen = 0;           // arrival passes so far; d_err[1] == pos_gen: a position was not finite
   bool flow_r_clear = false;     // flow_r holds no published word (the last net pass reset it)
   bool drv_as_stale = false;     // drv_as (combinational drivers) and fw_a predate the last forward sweep
-  double *red_ep = nullptr, *red_loss = nullptr, *red_wa = nullptr;
+  double *red_ep = nullptr, *red_loss = nullptr, *red_p2p = nullptr, *red_wa = nullptr;
   double *summary = nullptr;     // [4 * num_inst]: wns, tns, n_fail, 0
-  int32_t *inst_nfail = nullptr, *d_ep_base = nullptr;
+  int32_t *d_ep_base = nullptr;
 
   // extraction
   int32_t *sel_flag = nullptr, *sel_pos = nullptr, *sel_list = nullptr, *d_nsel = nullptr;
   int32_t *inst_selb = nullptr;  // [num_inst + 1] first selected endpoint of each instance
   int32_t *inst_outb = nullptr, *inst_kept = nullptr, *sel_cut = nullptr;
   uint64_t *look_st = nullptr;   // state of the one-launch prefix sums (tdp_look.h)
-  uint32_t *look_ctr = nullptr;
+  // counters of launches whose workgroups meet: the main chain's, and the pair
+  // losses' (which a caller may run beside it on another stream)
+  uint32_t *look_ctr = nullptr;  // [2][4]
   uint32_t *order_hist = nullptr, *order_flags = nullptr;  // exchange of the ordering's workgroups
   uint64_t *order_total = nullptr;
   void *slot_key = nullptr;      // path slack per slot
@@ -342,12 +344,11 @@ struct tdp_graph_s {
   uint8_t *pin_p = nullptr;            // [S] membership in P
   unsigned long long *pacc = nullptr;  // [S] fixed-point accumulator
   int32_t *pfirst = nullptr;           // [S] first occurrence (path index)
-  int32_t *pflag = nullptr;            // [S] compaction positions
   int32_t *d_npairs = nullptr;
   int32_t *pair_sink = nullptr, *pair_cs = nullptr, *pair_ct = nullptr;
   float *pair_dox = nullptr, *pair_doy = nullptr, *pair_w = nullptr;
-  int32_t *cell_cnt = nullptr, *cell_ptr = nullptr, *cell_cur = nullptr, *cell_flag = nullptr,
-          *touched = nullptr, *d_ntouched = nullptr;
+  int32_t *cell_cnt = nullptr, *cell_ptr = nullptr, *cell_cur = nullptr,
+          *touched = nullptr, *touched_ptr = nullptr, *d_ntouched = nullptr;
   int32_t *inc_other = nullptr, *inc_key = nullptr;
   float *inc_dx = nullptr, *inc_dy = nullptr, *inc_w = nullptr;
 

@@ -17,6 +17,7 @@
 // a per-cell incidence list in a fixed order so that every cell sums its terms
 // in the same order on every run (no floating-point atomics).
 #include "tdp_impl.h"
+#include "tdp_look.h"
 #include "tdp_prims.h"
 
 namespace tdp {
@@ -164,37 +165,114 @@ __global__ void __launch_bounds__(256) k_pairs_acc_lds(Topo tp, int rule, int pe
   }
 }
 
-// every sink pin: apply this round's sum to the pairs it touched (the first
-// occurrence inserts under Eq. 9), clear the accumulators, flag P's members
-template <typename T>
-__global__ void k_pairs_apply(Topo tp, int rule, float w0, float w1, int max_out, const int32_t *__restrict__ path_epi,
-                              const T *__restrict__ path_slack, const double *__restrict__ summary,
-                              unsigned long long *__restrict__ acc, int32_t *__restrict__ first,
-                              float *__restrict__ w, uint8_t *__restrict__ in_p, int32_t *__restrict__ flag) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= tp.S) return;
-  const int q = first[t];
-  const unsigned long long sum = acc[t];
-  // a pair already in P (Eq. 9) only sums; its first occurrence is not kept
-  const bool member = rule == 0 && in_p[t];
-  if (member && sum != 0ull) {
-    w[t] = (float)((double)w[t] + (double)w1 * ((double)sum / FIX_ONE));
-    acc[t] = 0ull;
-  } else if (!member && q >= 0 && q < max_out) {
-    const double wns = summary[4 * tp.ff_inst[path_epi[q]]];
-    unsigned long long v = 0;
-    pair_contrib<T>(rule, path_slack[q], wns, v);
-    if (rule == 0) {  // inserted by its first occurrence, which adds no weight
-      w[t] = (float)((double)w0 + (double)w1 * ((double)(sum - v) / FIX_ONE));
-      in_p[t] = 1;
-    } else {
-      w[t] = (float)((double)sum / FIX_ONE);
-      in_p[t] = 1;
+// P's members after this round, in pin order: those that were, and (APPLY)
+// those that a path touched; places by look-back.  R consecutive sinks a
+// thread: 4, and 16 where that would take more than 512 tiles, which count
+// themselves at one address (17 ns each).  Bound by one read of the flags and
+// first occurrences, 5 bytes a sink.  With k_pairs_records 16 us at 200k cells
+// and 51 at 2M; the same in four launches over all sinks (update, two of a
+// scan, records) took 19 and 65, and in one launch 28 and 216, since the
+// members are few and their gathers filled no wave.
+template <bool APPLY, int R>
+__global__ void __launch_bounds__(1024) k_pairs_find(int S, int max_out, const uint8_t *__restrict__ in_p,
+                                                      const int32_t *__restrict__ first, Look lk,
+                                                      int32_t *__restrict__ d_npairs,
+                                                      int32_t *__restrict__ pair_sink) {
+  __shared__ int s_base;
+  const uint32_t launch = lk.ctr[0];
+  const int tiles = max(1, (S + 1024 * R - 1) / (1024 * R));
+  for (int tile = look_tile(lk); tile < tiles; tile = look_next(lk, tiles)) {
+    const int b = (tile * 1024 + (int)threadIdx.x) * R;
+    uint32_t in[R / 4];
+    int4 q[R / 4];
+#pragma unroll
+    for (int r = 0; r < R / 4; ++r) {
+      const int t = b + 4 * r;
+      in[r] = 0;
+      q[r] = make_int4(-1, -1, -1, -1);
+      if (t + 4 <= S) {
+        in[r] = *(const uint32_t *)(in_p + t);
+        if constexpr (APPLY) q[r] = *(const int4 *)(first + t);
+      } else {
+        for (int j = 0; t + j < S; ++j) {
+          in[r] |= (uint32_t)in_p[t + j] << (8 * j);
+          if constexpr (APPLY) (j == 0 ? q[r].x : j == 1 ? q[r].y : q[r].z) = first[t + j];
+        }
+      }
     }
-    acc[t] = 0ull;
-    first[t] = 0x7fffffff;
+    uint32_t member = 0;
+#pragma unroll
+    for (int r = 0; r < R / 4; ++r) {
+      const uint32_t m = (uint32_t)((in[r] & 0xFFu) || (uint32_t)q[r].x < (uint32_t)max_out) |
+                         (uint32_t)((in[r] & 0xFF00u) || (uint32_t)q[r].y < (uint32_t)max_out) << 1 |
+                         (uint32_t)((in[r] & 0xFF0000u) || (uint32_t)q[r].z < (uint32_t)max_out) << 2 |
+                         (uint32_t)((in[r] & 0xFF000000u) || (uint32_t)q[r].w < (uint32_t)max_out) << 3;
+      member |= m << (4 * r);
+    }
+    int total[1], before[1];
+    int place = block_exclusive(__popc(member), &total[0]);
+    if (threadIdx.x < 64) {
+      look_prefix<1>(lk, tile, launch, total, before);
+      if (threadIdx.x == 0) {
+        s_base = before[0];
+        if (tile == tiles - 1) *d_npairs = before[0] + total[0];
+      }
+    }
+    __syncthreads();
+    place += s_base;
+    for (; member; member &= member - 1) pair_sink[place++] = b + __ffs(member) - 1;
   }
-  flag[t] = in_p[t] ? 1 : 0;
+  look_done(lk, launch);
+}
+
+// every member: apply this round's sum (the first occurrence inserts under
+// Eq. 9) and clear its accumulators (APPLY); the record that the loss reads;
+// incidence counts per cell
+template <typename T, bool APPLY>
+__global__ void __launch_bounds__(256) k_pairs_records(
+    Topo tp, int rule, float w0, float w1, int max_out, const int32_t *__restrict__ path_epi,
+    const T *__restrict__ path_slack, const double *__restrict__ summary, unsigned long long *__restrict__ acc,
+    int32_t *__restrict__ first, float *__restrict__ w, uint8_t *__restrict__ in_p,
+    const int32_t *__restrict__ d_npairs, const int32_t *__restrict__ pair_sink, int32_t *__restrict__ pair_cs,
+    int32_t *__restrict__ pair_ct, float *__restrict__ pair_dox, float *__restrict__ pair_doy,
+    float *__restrict__ pair_w, int32_t *__restrict__ cell_cnt) {
+  const int n = *d_npairs;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const int t = pair_sink[i];
+    const int s = tp.snk_drv[t], ct = tp.snk_cell[t];
+    const float tox = tp.snk_ox[t], toy = tp.snk_oy[t];
+    float wt = w[t];
+    if constexpr (APPLY) {
+      const int q = first[t];
+      const unsigned long long sum = acc[t];
+      // a pair already in P (Eq. 9) only sums; its first occurrence is not kept
+      const bool member = rule == 0 && in_p[t];
+      if (member && sum != 0ull) {
+        w[t] = wt = (float)((double)wt + (double)w1 * ((double)sum / FIX_ONE));
+        acc[t] = 0ull;
+      } else if (!member && q >= 0 && q < max_out) {
+        const double wns = summary[4 * tp.ff_inst[path_epi[q]]];
+        unsigned long long v = 0;
+        pair_contrib<T>(rule, path_slack[q], wns, v);
+        if (rule == 0)  // inserted by its first occurrence, which adds no weight
+          wt = (float)((double)w0 + (double)w1 * ((double)(sum - v) / FIX_ONE));
+        else
+          wt = (float)((double)sum / FIX_ONE);
+        w[t] = wt;
+        in_p[t] = 1;
+        acc[t] = 0ull;
+        first[t] = 0x7fffffff;
+      }
+    }
+    const int cs = tp.drv_cell[s];
+    pair_cs[i] = cs;
+    pair_ct[i] = ct;
+    pair_dox[i] = tp.drv_ox[s] - tox;
+    pair_doy[i] = tp.drv_oy[s] - toy;
+    pair_w[i] = wt;
+    if (!tp.cell_fixed[ct]) atomicAdd(&cell_cnt[ct], 1);
+    if (cs >= 0 && !tp.cell_fixed[cs]) atomicAdd(&cell_cnt[cs], 1);
+  }
 }
 
 // stateless rule: drop the previous round's pairs
@@ -207,76 +285,109 @@ __global__ void k_pairs_clear_list(const int32_t *__restrict__ d_npairs, const i
   in_p[t] = 0;
 }
 
-__global__ void k_pairs_flags(int S, const uint8_t *__restrict__ in_p, int32_t *__restrict__ flag) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < S) flag[t] = in_p[t] ? 1 : 0;
-}
+// The cells with incidences, in cell order: their list (touched), where each
+// one's incidences start (touched_ptr, and cell_ptr by cell), counters ready
+// for filling them.  Both sums by one look-back: 9 us at 200k cells, 24 at 2M
+// (two scans, flags and their compaction: 28 and 37 in six launches).
+constexpr int CELL_TILE = 4096;  // 1024 threads x 4
 
-// compact list + per-pair loss record + incidence counts per cell
-__global__ void k_pairs_records(Topo tp, const uint8_t *__restrict__ in_p, const int32_t *__restrict__ pos,
-                                const float *__restrict__ w, int32_t *__restrict__ pair_sink,
-                                int32_t *__restrict__ pair_cs, int32_t *__restrict__ pair_ct,
-                                float *__restrict__ pair_dox, float *__restrict__ pair_doy,
-                                float *__restrict__ pair_w, int32_t *__restrict__ cell_cnt) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= tp.S || !in_p[t]) return;
-  const int q = pos[t];
-  const int s = tp.snk_drv[t];
-  const int cs = tp.drv_cell[s], ct = tp.snk_cell[t];
-  pair_sink[q] = t;
-  pair_cs[q] = cs;
-  pair_ct[q] = ct;
-  pair_dox[q] = tp.drv_ox[s] - tp.snk_ox[t];
-  pair_doy[q] = tp.drv_oy[s] - tp.snk_oy[t];
-  pair_w[q] = w[t];
-  if (!tp.cell_fixed[ct]) atomicAdd(&cell_cnt[ct], 1);
-  if (cs >= 0 && !tp.cell_fixed[cs]) atomicAdd(&cell_cnt[cs], 1);
-}
-
-__global__ void k_cell_flags(int N, const int32_t *__restrict__ cnt, int32_t *__restrict__ flag) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < N) flag[c] = cnt[c] > 0 ? 1 : 0;
-}
-
-__global__ void k_cell_touched(int N, const int32_t *__restrict__ cnt, const int32_t *__restrict__ tpos,
-                               int32_t *__restrict__ touched) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < N && cnt[c] > 0) touched[tpos[c]] = c;
+__global__ void __launch_bounds__(1024) k_pairs_cells(int N, Look lk, int32_t *__restrict__ cnt,
+                                                       int32_t *__restrict__ cell_ptr, int32_t *__restrict__ cell_cur,
+                                                       int32_t *__restrict__ touched,
+                                                       int32_t *__restrict__ touched_ptr,
+                                                       int32_t *__restrict__ d_ntouched) {
+  __shared__ int s_base[2];
+  const uint32_t launch = lk.ctr[0];
+  const int tiles = max(1, (N + CELL_TILE - 1) / CELL_TILE);
+  for (int tile = look_tile(lk); tile < tiles; tile = look_next(lk, tiles)) {
+    const int c0 = tile * CELL_TILE + threadIdx.x * 4;
+    int4 x{0, 0, 0, 0};
+    if (c0 + 4 <= N) {
+      x = *(const int4 *)(cnt + c0);
+    } else {
+      if (c0 < N) x.x = cnt[c0];
+      if (c0 + 1 < N) x.y = cnt[c0 + 1];
+      if (c0 + 2 < N) x.z = cnt[c0 + 2];
+    }
+    const int v[4] = {x.x, x.y, x.z, x.w};
+    int cells = 0, inc = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      cells += v[q] > 0;
+      inc += v[q];
+    }
+    int total[2], before[2];
+    int i = block_exclusive(cells, &total[0]), p = block_exclusive(inc, &total[1]);
+    if (threadIdx.x < 64) {
+      look_prefix<2>(lk, tile, launch, total, before);
+      if (threadIdx.x == 0) {
+        s_base[0] = before[0];
+        s_base[1] = before[1];
+        if (tile == tiles - 1) {
+          *d_ntouched = before[0] + total[0];
+          touched_ptr[before[0] + total[0]] = before[1] + total[1];
+        }
+      }
+    }
+    __syncthreads();
+    i += s_base[0];
+    p += s_base[1];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (v[q] <= 0) continue;
+      touched[i] = c0 + q;
+      touched_ptr[i++] = p;
+      cell_ptr[c0 + q] = p;
+      cell_cur[c0 + q] = 0;
+      cnt[c0 + q] = 0;
+      p += v[q];
+    }
+  }
+  look_done(lk, launch);
 }
 
 // incidences of pair q, first pass: a slot in each of its two cells' lists
 // (arbitrary order within a list) holding only the key that orders the list,
 // 2q at the sink's cell and 2q + 1 at the driver's
-__global__ void k_inc_fill(Topo tp, const int32_t *__restrict__ d_npairs, const int32_t *__restrict__ pair_cs,
-                           const int32_t *__restrict__ pair_ct, const int32_t *__restrict__ cell_ptr,
-                           int32_t *__restrict__ cell_cur, int32_t *__restrict__ inc_key) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= *d_npairs) return;
-  const int cs = pair_cs[q], ct = pair_ct[q];
-  if (!tp.cell_fixed[ct]) inc_key[cell_ptr[ct] + atomicAdd(&cell_cur[ct], 1)] = 2 * q;
-  if (cs >= 0 && !tp.cell_fixed[cs]) inc_key[cell_ptr[cs] + atomicAdd(&cell_cur[cs], 1)] = 2 * q + 1;
+__global__ void __launch_bounds__(256) k_inc_fill(Topo tp, const int32_t *__restrict__ d_npairs,
+                                                   const int32_t *__restrict__ pair_cs,
+                                                   const int32_t *__restrict__ pair_ct,
+                                                   const int32_t *__restrict__ cell_ptr,
+                                                   int32_t *__restrict__ cell_cur, int32_t *__restrict__ inc_key) {
+  const int n = *d_npairs;
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) {
+    const int cs = pair_cs[q], ct = pair_ct[q];
+    if (!tp.cell_fixed[ct]) inc_key[cell_ptr[ct] + atomicAdd(&cell_cur[ct], 1)] = 2 * q;
+    if (cs >= 0 && !tp.cell_fixed[cs]) inc_key[cell_ptr[cs] + atomicAdd(&cell_cur[cs], 1)] = 2 * q + 1;
+  }
 }
 
 // second pass, one thread per slot: the slot's place in its cell's list is
 // the number of smaller keys in the list (keys are distinct), so every list
 // ends up in key order whatever order the first pass filled it in; writes
 // the incidence there (the other cell, -1 for a port; this pin's offset
-// minus the other pin's; the weight) and resets the cell's counters.  Only
-// loads precede the stores, so no load waits behind a store.
-__global__ void k_inc_rank(const int32_t *__restrict__ cell_ptr, int N, const int32_t *__restrict__ inc_key,
-                           const int32_t *__restrict__ pair_cs, const int32_t *__restrict__ pair_ct,
-                           const float *__restrict__ pair_dox, const float *__restrict__ pair_doy,
-                           const float *__restrict__ pair_w, int32_t *__restrict__ cell_cnt,
-                           int32_t *__restrict__ cell_cur, int32_t *__restrict__ inc_other,
-                           float *__restrict__ inc_dx, float *__restrict__ inc_dy, float *__restrict__ inc_w) {
-  const int total = cell_ptr[N];
+// minus the other pin's; the weight).  Only loads precede the stores, so no
+// load waits behind a store.
+__global__ void __launch_bounds__(256) k_inc_rank(const int32_t *__restrict__ cell_ptr,
+                                                   const int32_t *__restrict__ cell_cur,
+                                                   const int32_t *__restrict__ d_ntouched,
+                                                   const int32_t *__restrict__ touched_ptr,
+                                                   const int32_t *__restrict__ inc_key,
+                                                   const int32_t *__restrict__ pair_cs,
+                                                   const int32_t *__restrict__ pair_ct,
+                                                   const float *__restrict__ pair_dox,
+                                                   const float *__restrict__ pair_doy,
+                                                   const float *__restrict__ pair_w, int32_t *__restrict__ inc_other,
+                                                   float *__restrict__ inc_dx, float *__restrict__ inc_dy,
+                                                   float *__restrict__ inc_w) {
+  const int total = touched_ptr[*d_ntouched];
   for (int a = blockIdx.x * blockDim.x + threadIdx.x; a < total; a += gridDim.x * blockDim.x) {
     const int key = inc_key[a];
     const int q = key >> 1;
     const bool drv = key & 1;  // this cell drives the pair
     const int cs = pair_cs[q], ct = pair_ct[q];
     const int c = drv ? cs : ct;
-    const int b = cell_ptr[c], e = cell_ptr[c + 1];
+    const int b = cell_ptr[c], e = b + cell_cur[c];
     int rank = 0;
     for (int z = b; z < e; ++z) rank += inc_key[z] < key;
     const float dox = pair_dox[q], doy = pair_doy[q];
@@ -285,10 +396,6 @@ __global__ void k_inc_rank(const int32_t *__restrict__ cell_ptr, int N, const in
     inc_dx[d] = drv ? dox : -dox;
     inc_dy[d] = drv ? doy : -doy;
     inc_w[d] = pair_w[q];
-    if (rank == 0) {
-      cell_cnt[c] = 0;
-      cell_cur[c] = 0;
-    }
   }
 }
 
@@ -333,7 +440,8 @@ __global__ void __launch_bounds__(256) k_p2p_fwd(const int32_t *__restrict__ d_n
                                                   const float *__restrict__ pair_dox,
                                                   const float *__restrict__ pair_doy,
                                                   const float *__restrict__ pair_w, const float *__restrict__ x,
-                                                  const float *__restrict__ y, double *__restrict__ part) {
+                                                  const float *__restrict__ y, double *__restrict__ part,
+                                                  uint32_t *__restrict__ ctr, double *__restrict__ out) {
   __shared__ double sh[256];
   const int n = *d_npairs;
   double acc = 0.0;
@@ -350,26 +458,14 @@ __global__ void __launch_bounds__(256) k_p2p_fwd(const int32_t *__restrict__ d_n
     if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-
-__global__ void __launch_bounds__(256) k_sum_parts(int n, const double *__restrict__ part, double *__restrict__ out) {
-  __shared__ double sh[256];
-  double a = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) a += part[i];
-  sh[threadIdx.x] = a;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = sh[0];
+  if (threadIdx.x == 0) pub_st(part + blockIdx.x, sh[0]);
+  last_sum(ctr, gridDim.x, part, out);
 }
 
 template <typename T, int KIND>
 __global__ void __launch_bounds__(256) k_p2p_bwd(const int32_t *__restrict__ d_ntouched,
                                                   const int32_t *__restrict__ touched,
-                                                  const int32_t *__restrict__ cell_ptr,
+                                                  const int32_t *__restrict__ touched_ptr,
                                                   const int32_t *__restrict__ inc_other,
                                                   const float *__restrict__ inc_dx, const float *__restrict__ inc_dy,
                                                   const float *__restrict__ inc_w, const float *__restrict__ x,
@@ -381,7 +477,7 @@ __global__ void __launch_bounds__(256) k_p2p_bwd(const int32_t *__restrict__ d_n
     const int c = touched[i];
     const T xc = (T)x[c], yc = (T)y[c];
     T ax = 0, ay = 0;
-    for (int a = cell_ptr[c]; a < cell_ptr[c + 1]; ++a) {
+    for (int a = touched_ptr[i]; a < touched_ptr[i + 1]; ++a) {
       const int o = inc_other[a];
       const T xo = o >= 0 ? (T)x[o] : (T)0, yo = o >= 0 ? (T)y[o] : (T)0;
       T gx1, gy1;
@@ -396,6 +492,37 @@ __global__ void __launch_bounds__(256) k_p2p_bwd(const int32_t *__restrict__ d_n
 
 // ------------------------------------------------------------- launchers
 static inline int nb(long long n, int b) { return n > 0 ? (int)((n + b - 1) / b) : 1; }
+
+// P's list, and its members' records
+template <typename T, bool APPLY>
+static void list_launch(tdp_graph g, int rule, float w0, float w1, hipStream_t s) {
+  const Topo &tp = g->topo;
+  const Look lk{g->look_st, g->look_ctr, g->d_err};
+  if (tp.S <= 512 * 4096)
+    hipLaunchKernelGGL((k_pairs_find<APPLY, 4>), dim3(nb(tp.S, 4096)), dim3(1024), 0, s, tp.S, g->max_out, g->pin_p,
+                       g->pfirst, lk, g->d_npairs, g->pair_sink);
+  else
+    hipLaunchKernelGGL((k_pairs_find<APPLY, 16>), dim3(std::min(512, nb(tp.S, 16384))), dim3(1024), 0, s, tp.S,
+                       g->max_out, g->pin_p, g->pfirst, lk, g->d_npairs, g->pair_sink);
+  hipLaunchKernelGGL((k_pairs_records<T, APPLY>), dim3(std::min(1024, nb(tp.S, 256))), dim3(256), 0, s, tp, rule, w0,
+                     w1, g->max_out, g->path_epi, (const T *)g->path_slack, g->summary, g->pacc, g->pfirst, g->pw,
+                     g->pin_p, g->d_npairs, g->pair_sink, g->pair_cs, g->pair_ct, g->pair_dox, g->pair_doy, g->pair_w,
+                     g->cell_cnt);
+}
+
+// per-cell incidence lists of the pair list
+static void pairs_incidences(tdp_graph g, hipStream_t s) {
+  const Topo &tp = g->topo;
+  const Look lk{g->look_st, g->look_ctr, g->d_err};
+  hipLaunchKernelGGL(k_pairs_cells, dim3(std::min(512, nb(tp.N, CELL_TILE))), dim3(1024), 0, s, tp.N, lk, g->cell_cnt,
+                     g->cell_ptr, g->cell_cur, g->touched, g->touched_ptr, g->d_ntouched);
+  hipLaunchKernelGGL(k_inc_fill, dim3(std::min(1024, nb(tp.S, 256))), dim3(256), 0, s, tp, g->d_npairs, g->pair_cs,
+                     g->pair_ct, g->cell_ptr, g->cell_cur, g->inc_key);
+  hipLaunchKernelGGL(k_inc_rank, dim3(std::min(1024, nb(2ll * tp.S, 256))), dim3(256), 0, s, g->cell_ptr, g->cell_cur,
+                     g->d_ntouched, g->touched_ptr, g->inc_key, g->pair_cs, g->pair_ct, g->pair_dox, g->pair_doy,
+                     g->pair_w, g->inc_other, g->inc_dx, g->inc_dy, g->inc_w);
+  g->pairs_built = true;
+}
 
 template <typename T>
 void pairs_update_impl(tdp_graph g, int rule, float w0, float w1, hipStream_t s) {
@@ -415,60 +542,38 @@ void pairs_update_impl(tdp_graph g, int rule, float w0, float w1, hipStream_t s)
     hipLaunchKernelGGL(k_pairs_acc<T>, dim3(std::min(2048, nb(g->max_out, 4))), dim3(256), 0, s, tp, rule,
                        g->d_num_paths, g->path_ptr, g->path_int, g->path_epi, (const T *)g->path_slack, g->summary,
                        g->pacc, g->pfirst);
-  hipLaunchKernelGGL(k_pairs_apply<T>, dim3(nb(tp.S, 256)), dim3(256), 0, s, tp, rule, w0, w1, g->max_out,
-                     g->path_epi, (const T *)g->path_slack, g->summary, g->pacc, g->pfirst, g->pw, g->pin_p,
-                     g->pflag);
-  pairs_compact(g, s);
+  list_launch<T, true>(g, rule, w0, w1, s);
+  pairs_incidences(g, s);
   prof_end(g, TDP_STAGE_PAIRS, s);
 }
 
+// the pair list and the per-cell lists from the memberships alone
 void pairs_rebuild(tdp_graph g, hipStream_t s) {
-  const Topo &tp = g->topo;
-  hipLaunchKernelGGL(k_pairs_flags, dim3(nb(tp.S, 256)), dim3(256), 0, s, tp.S, g->pin_p, g->pflag);
-  pairs_compact(g, s);
-}
-
-// pflag holds the membership flags; build the pair list and the per-cell lists
-void pairs_compact(tdp_graph g, hipStream_t s) {
-  const Topo &tp = g->topo;
-  scan_exclusive(g->pflag, g->pflag, tp.S, nullptr, g->d_npairs, g->scan_tmp, s);
-  hipLaunchKernelGGL(k_pairs_records, dim3(nb(tp.S, 256)), dim3(256), 0, s, tp, g->pin_p, g->pflag, g->pw,
-                     g->pair_sink, g->pair_cs, g->pair_ct, g->pair_dox, g->pair_doy, g->pair_w, g->cell_cnt);
-  // cell_ptr = exclusive scan of counts; touched list = compaction of cells with any
-  scan_exclusive(g->cell_cnt, g->cell_ptr, tp.N, nullptr, g->cell_ptr + tp.N, g->scan_tmp, s);
-  hipLaunchKernelGGL(k_cell_flags, dim3(nb(tp.N, 256)), dim3(256), 0, s, tp.N, g->cell_cnt, g->cell_flag);
-  scan_exclusive(g->cell_flag, g->cell_flag, tp.N, nullptr, g->d_ntouched, g->scan_tmp, s);
-  hipLaunchKernelGGL(k_cell_touched, dim3(nb(tp.N, 256)), dim3(256), 0, s, tp.N, g->cell_cnt, g->cell_flag,
-                     g->touched);
-  hipLaunchKernelGGL(k_inc_fill, dim3(nb(tp.S, 256)), dim3(256), 0, s, tp, g->d_npairs, g->pair_cs, g->pair_ct,
-                     g->cell_ptr, g->cell_cur, g->inc_key);
-  hipLaunchKernelGGL(k_inc_rank, dim3(1024), dim3(256), 0, s, g->cell_ptr, tp.N, g->inc_key, g->pair_cs, g->pair_ct,
-                     g->pair_dox, g->pair_doy, g->pair_w, g->cell_cnt, g->cell_cur, g->inc_other, g->inc_dx,
-                     g->inc_dy, g->inc_w);
-  g->pairs_built = true;
+  list_launch<float, false>(g, 0, 0.f, 0.f, s);
+  pairs_incidences(g, s);
 }
 
 template <typename T, int KIND>
-static void launch_pair_fwd(tdp_graph g, const float *x, const float *y, hipStream_t s) {
-  hipLaunchKernelGGL((k_p2p_fwd<T, KIND>), dim3(LOSS_BLOCKS), dim3(256), 0, s, g->d_npairs, g->pair_cs, g->pair_ct,
-                     g->pair_dox, g->pair_doy, g->pair_w, x, y, g->red_loss);
+static void launch_pair_fwd(tdp_graph g, const float *x, const float *y, double *loss, hipStream_t s) {
+  hipLaunchKernelGGL((k_p2p_fwd<T, KIND>), dim3(std::min(256, nb(g->topo.S, 256))), dim3(256), 0, s,
+                     g->d_npairs, g->pair_cs, g->pair_ct, g->pair_dox, g->pair_doy, g->pair_w, x, y, g->red_p2p,
+                     g->look_ctr + 4, loss);
 }
 
 template <typename T>
 void p2p_fwd_impl(tdp_graph g, int kind, const float *x, const float *y, double *loss, hipStream_t s) {
   prof_begin(g, TDP_STAGE_P2P_FWD, s);
-  if (kind == 1) launch_pair_fwd<T, 1>(g, x, y, s);
-  else if (kind == 2) launch_pair_fwd<T, 2>(g, x, y, s);
-  else launch_pair_fwd<T, 0>(g, x, y, s);
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, LOSS_BLOCKS, g->red_loss, loss);
+  if (kind == 1) launch_pair_fwd<T, 1>(g, x, y, loss, s);
+  else if (kind == 2) launch_pair_fwd<T, 2>(g, x, y, loss, s);
+  else launch_pair_fwd<T, 0>(g, x, y, loss, s);
   prof_end(g, TDP_STAGE_P2P_FWD, s);
 }
 
 template <typename T, int KIND>
 static void launch_pair_bwd(tdp_graph g, const float *x, const float *y, const double *gout, float *gx, float *gy,
                             hipStream_t s) {
-  hipLaunchKernelGGL((k_p2p_bwd<T, KIND>), dim3(LOSS_BLOCKS * 2), dim3(256), 0, s, g->d_ntouched, g->touched,
-                     g->cell_ptr, g->inc_other, g->inc_dx, g->inc_dy, g->inc_w, x, y, gout, gx, gy);
+  hipLaunchKernelGGL((k_p2p_bwd<T, KIND>), dim3(std::min(LOSS_BLOCKS * 2, nb(g->topo.N, 256))), dim3(256), 0, s, g->d_ntouched, g->touched,
+                     g->touched_ptr, g->inc_other, g->inc_dx, g->inc_dy, g->inc_w, x, y, gout, gx, gy);
 }
 
 template <typename T>

@@ -32,29 +32,34 @@
 namespace tdp {
 
 // ------------------------------------------------------------- selection
-constexpr int SEL_TILE = 4096;  // endpoints per tile: 256 threads x 16
+constexpr int SEL_TILE = 4096;  // endpoints per tile: 1024 threads x 4
 
 // The violated endpoints of every instance, in order, in one launch: flags by
 // ballot, places by look-back; the place of an instance's first endpoint is
 // its inst_selb.  (Five launches, flags through memory, took 21 us at 20,000
 // endpoints and 28 at 240,000; this 10 and 12.)
 template <typename T>
-__global__ void __launch_bounds__(256) k_sel_violated(Topo tp, Look lk, const int32_t *__restrict__ ep_base,
-                                                       const T *__restrict__ ep_slack, int32_t *__restrict__ list,
-                                                       int32_t *__restrict__ d_nsel, int32_t *__restrict__ inst_selb) {
+__global__ void __launch_bounds__(1024) k_sel_violated(Topo tp, Look lk, const int32_t *__restrict__ ep_base,
+                                                        const T *__restrict__ ep_slack, int32_t *__restrict__ list,
+                                                        int32_t *__restrict__ d_nsel, int32_t *__restrict__ inst_selb) {
   __shared__ unsigned long long s_mask[64];  // rounds x waves
   __shared__ int s_before[64], s_base, s_total;
   const int lane = wave_lane(), wid = threadIdx.x >> 6;
   const uint32_t launch = lk.ctr[0];
   const int tiles = max(1, (tp.E + SEL_TILE - 1) / SEL_TILE);
-  for (int tile = look_tile(lk); tile < tiles; tile = look_tile(lk)) {
+  for (int tile = look_tile(lk); tile < tiles; tile = look_next(lk, tiles)) {
     const int f0 = tile * SEL_TILE;
-    unsigned long long m[16];
+    T sl[4];
+    unsigned long long m[4];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int f = f0 + r * 256 + threadIdx.x;
-      m[r] = __ballot(f < tp.E && ep_slack[f] < (T)0);
-      if (lane == 0) s_mask[r * 4 + wid] = m[r];
+    for (int r = 0; r < 4; ++r) {
+      const int f = f0 + r * 1024 + threadIdx.x;
+      sl[r] = f < tp.E ? ep_slack[f] : (T)0;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      m[r] = __ballot(sl[r] < (T)0);
+      if (lane == 0) s_mask[r * 16 + wid] = m[r];
     }
     __syncthreads();
     if (wid == 0) {
@@ -77,10 +82,11 @@ __global__ void __launch_bounds__(256) k_sel_violated(Topo tp, Look lk, const in
     __syncthreads();
     const unsigned long long below = (1ull << lane) - 1;
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if ((m[r] >> lane) & 1) list[s_base + s_before[r * 4 + wid] + __popcll(m[r] & below)] = f0 + r * 256 + threadIdx.x;
+    for (int r = 0; r < 4; ++r)
+      if ((m[r] >> lane) & 1)
+        list[s_base + s_before[r * 16 + wid] + __popcll(m[r] & below)] = f0 + r * 1024 + threadIdx.x;
     const bool last = tile == tiles - 1;
-    for (int i = threadIdx.x; i <= tp.num_inst; i += 256) {
+    for (int i = threadIdx.x; i <= tp.num_inst; i += 1024) {
       const int e = ep_base[i] - f0;
       if (e < 0 || (e >= SEL_TILE && !(last && ep_base[i] == tp.E))) continue;
       inst_selb[i] = e >= SEL_TILE ? s_base + s_total
@@ -117,7 +123,7 @@ __global__ void __launch_bounds__(1024) k_sel_worst(int num_inst, const int32_t 
   const int tid = threadIdx.x, lane = wave_lane(), wid = tid >> 6;
   const unsigned long long below = (1ull << lane) - 1;
   const uint32_t launch = lk.ctr[0];
-  for (int inst = look_tile(lk); inst < num_inst; inst = look_tile(lk)) {
+  for (int inst = look_tile(lk); inst < num_inst; inst = look_next(lk, num_inst)) {
     const int b = ep_base[inst], e = ep_base[inst + 1];
     uint32_t key[R];
     int finite = 0;
@@ -734,7 +740,7 @@ __global__ void __launch_bounds__(256) k_path_out(int k, int K, Look lk, const i
   const int n = *d_nslots;
   const int tiles = max(1, (n + OUT_TILE - 1) / OUT_TILE);
   const uint64_t inf_key = sizeof(T) == 4 ? order_key(inf_of<float>()) : order_key(inf_of<double>());
-  for (int tile = look_tile(lk); tile < tiles; tile = look_tile(lk)) {
+  for (int tile = look_tile(lk); tile < tiles; tile = look_next(lk, tiles)) {
     const int j0 = tile * OUT_TILE + threadIdx.x * 8;
     int slot[8], len[8];
     bool kept[8];
@@ -1000,7 +1006,7 @@ void select_stage(tdp_graph g, int n, hipStream_t s) {
   const int E = tp.E;
   const Look lk{g->look_st, g->look_ctr, g->d_err};
   if (n < 0) {
-    hipLaunchKernelGGL(k_sel_violated<T>, dim3(std::min(512, nb(E, SEL_TILE))), dim3(256), 0, s, tp, lk, g->d_ep_base,
+    hipLaunchKernelGGL(k_sel_violated<T>, dim3(std::min(512, nb(E, SEL_TILE))), dim3(1024), 0, s, tp, lk, g->d_ep_base,
                        (const T *)g->ep_slack, g->sel_list, g->d_nsel, g->inst_selb);
     return;
   }

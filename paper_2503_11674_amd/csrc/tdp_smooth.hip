@@ -403,9 +403,12 @@ void wa_impl(tdp_graph g, const float *x, const float *y, float gamma, double *w
     xy = g->xy_wa;
     cxy = nullptr;
   }
-  hipLaunchKernelGGL(k_wa_net, dim3(WB), dim3(256), 0, s, tp, xy, cxy, gamma, g->wa_gpin, g->red_wa);
-  hipLaunchKernelGGL(k_wa_big, dim3(BB), dim3(64), 0, s, tp, xy, gamma, g->wa_gpin, g->red_wa + WB);
-  hipLaunchKernelGGL(k_sum_parts2, dim3(1), dim3(256), 0, s, WB + BB, g->red_wa, wl);
+  // (no launch for wide nets where the design has none)
+  const int wb = std::min(WB, nb(tp.n_nm_chunks, 4)), bb = tp.n_big > 0 ? BB : 0;
+  hipLaunchKernelGGL(k_wa_net, dim3(wb), dim3(256), 0, s, tp, xy, cxy, gamma, g->wa_gpin, g->red_wa);
+  if (bb)
+    hipLaunchKernelGGL(k_wa_big, dim3(bb), dim3(64), 0, s, tp, xy, gamma, g->wa_gpin, g->red_wa + wb);
+  hipLaunchKernelGGL(k_sum_parts2, dim3(1), dim3(256), 0, s, wb + bb, g->red_wa, wl);
   hipLaunchKernelGGL(k_wa_cell, dim3(nb(tp.N, 256)), dim3(256), 0, s, tp, g->wa_gpin, gx, gy);
   prof_end(g, TDP_STAGE_WA, s);
 }
