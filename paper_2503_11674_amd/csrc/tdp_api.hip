@@ -235,7 +235,7 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
   ok = ok && dalloc(g, g->sel_flag, T.E) && dalloc(g, g->sel_pos, T.E) && dalloc(g, g->sel_list, T.E) &&
        dalloc(g, g->d_nsel, 1) && dalloc(g, g->sel_cut, (size_t)4 * ni) &&
        dalloc(g, g->inst_outb, ni) && dalloc(g, g->inst_kept, ni) && dalloc(g, g->inst_selb, (size_t)ni + 1) &&
-       dalloc(g, g->look_st, look_words(T, sc)) && dalloc(g, g->look_ctr, 8) &&
+       dalloc(g, g->look_st, look_words(T, sc)) && dalloc(g, g->look_ctr, 12) &&
        dalloc(g, g->order_hist, (size_t)64 << 8) && dalloc(g, g->order_total, 64) && dalloc(g, g->order_flags, 65) &&
        dalloc(g, g->slot_key, sc, es) && dalloc(g, g->slot_dev, sc) && dalloc(g, g->slot_par, sc) &&
        dalloc(g, g->slot_len, sc) && dalloc(g, g->slot_out, std::max(sc, mo)) && dalloc(g, g->d_nslots, 1) &&
@@ -257,7 +257,7 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
        dalloc(g, g->inc_w, (size_t)2 * T.S);
   // smoothed TNS, WA
   ok = ok && dalloc(g, g->st_at, T.P, es) && dalloc(g, g->st_adj, T.P, es) && dalloc(g, g->st_dnet, T.S, es) &&
-       dalloc(g, g->st_gp, (size_t)2 * T.P, es) &&
+       dalloc(g, g->st_gp, (size_t)2 * T.P, es) && dalloc(g, g->st_adj_nm, (size_t)T.n_nm_chunks * CHUNK, es) &&
        dalloc(g, g->wa_gpin, (size_t)2 * T.P) && dalloc(g, g->xy, T.N) &&
        dalloc(g, g->xy_wa, T.N) && dalloc(g, g->xy_st, T.N) && dalloc(g, g->cxy_nm, (size_t)T.n_nm_chunks * CHUNK);
   // spanning-tree net model: scratch of the net pass and of the smoothed TNS

@@ -38,7 +38,7 @@ void st_net_fwd_impl(tdp_graph g, const float *x, const float *y, T *dnl, hipStr
 // of the net delays, at the positions of the last st_net_fwd_impl call (its
 // packed copy; x and y serve the nets wider than a chunk)
 template <typename T>
-void st_net_grad_impl(tdp_graph g, const float *x, const float *y, const T *adj, hipStream_t s);
+void st_net_grad_impl(tdp_graph g, const float *x, const float *y, const T *adj, const T *adj_nm, hipStream_t s);
 // WNS / TNS / violated count per instance from the endpoint slacks
 template <typename T> void ep_reduce_impl(tdp_graph g, hipStream_t s);
 template <typename T> void rf_update_impl(tdp_graph g, const float *x, const float *y, hipStream_t s);

@@ -295,7 +295,8 @@ struct tdp_graph_s {
   int32_t flow_waves = 4, spin_limit = 1 << 20;
   int32_t flow_per_cu = 1;       // workgroups per compute unit of the resident dataflow grids
   int32_t num_cu = 0;            // compute units of the device
-  int32_t occ_fw[3] = {-1, -1, -1}, occ_bw[3] = {-1, -1, -1};  // occupancy per 1 / 2 / 4 waves, -1 = not yet
+  int32_t occ_fw[3] = {-1, -1, -1}, occ_bw[3] = {-1, -1, -1},
+          occ_st[2][3] = {{-1, -1, -1}, {-1, -1, -1}};  // occupancy per 1 / 2 / 4 waves, -1 = not yet
   bool fw_flow_ok = false, bw_flow_ok = false;  // the graph can use the forward / backward dataflow sweep
   bool flow_ok = false;          // the graph can use sweep modes 1-3
   int32_t pos_gen = 0;           // arrival passes so far; d_err[1] == pos_gen: a position was not finite
@@ -311,8 +312,9 @@ struct tdp_graph_s {
   int32_t *inst_outb = nullptr, *inst_kept = nullptr, *sel_cut = nullptr;
   uint64_t *look_st = nullptr;   // state of the one-launch prefix sums (tdp_look.h)
   // counters of launches whose workgroups meet: the main chain's, and the pair
-  // losses' (which a caller may run beside it on another stream)
-  uint32_t *look_ctr = nullptr;  // [2][4]
+  // losses' and the smoothed sum's (which a caller may run beside it on other
+  // streams)
+  uint32_t *look_ctr = nullptr;  // [3][4]
   uint32_t *order_hist = nullptr, *order_flags = nullptr;  // exchange of the ordering's workgroups
   uint64_t *order_total = nullptr;
   void *slot_key = nullptr;      // path slack per slot
@@ -354,6 +356,7 @@ struct tdp_graph_s {
 
   // smoothed TNS (st_gp: the gradient per pin and axis [2P])
   void *st_at = nullptr, *st_adj = nullptr, *st_dnet = nullptr, *st_gp = nullptr;
+  void *st_adj_nm = nullptr;     // [n_nm_chunks * 64] the sinks' adjoints, by net chunk lane
   float st_gamma = 0;
   const float *st_x = nullptr, *st_y = nullptr;
 

@@ -13,8 +13,8 @@
 //   value:           -g * sum_e softplus(-s(e)/g)
 // The adjoint runs the levels top-down: dv/dA(e) = -sigmoid(-s(e)/g); an
 // output passes its adjoint to input j in proportion to softmax_j(a/g); a
-// driver collects the adjoints of its sinks (per level over the net chunks,
-// as the required-time pass runs).  dv/d dnet(t) is the adjoint at
+// driver collects the adjoints of its sinks (over the net chunks, as the
+// required-time pass runs).  dv/d dnet(t) is the adjoint at
 // t, and on a star net d dnet/dX_s = dnet'(L) sign(X_s - X_t) = -d dnet/dX_t
 // (the spanning-tree model differentiates through its tree).  The net delays
 // and the per-pin terms come from the net kernels of tdp_tree.hip.
@@ -22,7 +22,9 @@
 // Weighted-average wirelength (the smoothed WL of Eq. 1): per net and axis,
 // sum x e^{x/g} / sum e^{x/g} - sum x e^{-x/g} / sum e^{-x/g}, with the
 // exponents shifted by the net's max and min.
+#include "tdp_flow.h"
 #include "tdp_impl.h"
+#include "tdp_look.h"
 #include "tdp_prims.h"
 #include "tdp_wave.h"
 
@@ -30,20 +32,51 @@ namespace tdp {
 
 static inline int nb(long long n, int b) { return n > 0 ? (int)((n + b - 1) / b) : 1; }
 
+// the smoothed sweeps' own error word, behind d_err's
+constexpr int ST_ERR = 2;
+
 template <typename T>
 __device__ __forceinline__ T sgn(T v) {
   return (T)((v > (T)0) - (v < (T)0));
 }
 
+// a value as the word that the dataflow sweeps publish: all ones means not yet,
+// which no NaN made here has
 template <typename T>
-__global__ void k_st_start(Topo tp, const T *__restrict__ at, T *__restrict__ sa) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < tp.n_start) sa[v] = at[v];
+__device__ __forceinline__ typename ReqWord<T>::type pub_bits(T v) {
+  return ReqWord<T>::bits(v == v ? v : (T)__builtin_nan(""));
 }
 
-// one level's combinational cells on the forward chunks, a lane per input
-// (each cell a segment): the input's arrival, then the cell's log-sum-exp
-// over its inputs by segment reductions
+// start points' arrivals; every other driver's word, and every driver's
+// adjoint, not yet
+template <typename T>
+__global__ void __launch_bounds__(256) k_st_start(Topo tp, const T *__restrict__ at, T *__restrict__ sa,
+                                                   T *__restrict__ adj, int32_t *__restrict__ err) {
+  using RW = typename ReqWord<T>::type;
+  if (blockIdx.x == 0 && threadIdx.x == 0) err[0] = 0;
+  for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < tp.M; v += gridDim.x * blockDim.x) {
+    reinterpret_cast<RW *>(sa)[v] = v < tp.n_start ? pub_bits<T>(at[v]) : ~(RW)0;
+    reinterpret_cast<RW *>(adj)[v] = ~(RW)0;
+  }
+}
+
+// A chunk's combinational cells, a lane per input (each cell a segment): the
+// input's arrival through its arc (ai: its driver's arrival), the cell's
+// log-sum-exp over its inputs by segment reductions, and each input's share of
+// the output's adjoint, its softmax weight, for the backward sweep
+template <typename T>
+struct StCell {
+  T a, out;
+  __device__ __forceinline__ StCell(T ai, T dn, T da, bool valid, int lane, int head, int tail, T gam) {
+    a = valid ? (ai + dn) + da : -pos_inf<T>();
+    const T m = seg_max(a, lane, head, tail);
+    const T sum = seg_sum(valid ? exp((a - m) / gam) : (T)0, lane, head, tail);
+    out = m + gam * log(sum);
+  }
+  __device__ __forceinline__ T share(T gam) const { return exp((a - out) / gam); }
+};
+
+// one level's cells on the forward chunks
 template <typename T>
 __global__ void __launch_bounds__(256) k_st_fwd(Topo tp, int ch0, int ch1, T gam, const T *__restrict__ dnl,
                                                  const T *__restrict__ darc, T *__restrict__ sa) {
@@ -54,29 +87,52 @@ __global__ void __launch_bounds__(256) k_st_fwd(Topo tp, int ch0, int ch1, T gam
   const int t = rec.x;
   const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
   const bool valid = t >= 0;
-  T a = -pos_inf<T>();
-  if (valid) {
-    const T ai = sa[rec.y] + dnl[t];
-    sa[tp.M + t] = ai;
-    a = ai + darc[t];
-  }
-  const T m = seg_max(a, lane, head, tail);
-  const T sum = seg_sum(valid ? exp((a - m) / gam) : (T)0, lane, head, tail);
-  if (valid && lane == head) sa[tp.n_start + rec.z] = m + gam * log(sum);
+  const StCell<T> c(valid ? sa[rec.y] : (T)0, valid ? dnl[t] : (T)0, valid ? darc[t] : (T)0, valid, lane, head, tail,
+                    gam);
+  if (valid && lane == head) sa[tp.n_start + rec.z] = c.out;
+  if (valid) sa[tp.M + t] = c.share(gam);
 }
 
-// endpoint values and adjoint seeds; per-block partial sums of the value
+// The whole forward sweep on a resident grid (see the dataflow sweeps of the
+// timing pass): wave w takes chunks w, w + W, ... in level order, waits for its
+// drivers' words and publishes its cells'.  Bound by the chain of levels: 156 us
+// at 1M cells, 80 levels, against 312 with a launch per level.
+template <typename T>
+__global__ void __launch_bounds__(256) k_st_fwd_flow(Topo tp, T gam, const T *__restrict__ dnl,
+                                                      const T *__restrict__ darc, T *sa, int32_t *__restrict__ err,
+                                                      int limit) {
+  using RW = typename ReqWord<T>::type;
+  RW *words = reinterpret_cast<RW *>(sa);
+  const int lane = wave_lane(), wpb = blockDim.x >> 6;
+  const int W = gridDim.x * wpb, nch = tp.n_fw_chunks;
+  int q = blockIdx.x * wpb + (threadIdx.x >> 6);
+  int4 nrec = q < nch ? tp.fw_rec[q * CHUNK + lane] : make_int4(-1, 0, 0, 0);
+  for (; q < nch; q += W) {
+    const int4 rec = nrec;
+    if (q + W < nch) nrec = tp.fw_rec[(q + W) * CHUNK + lane];
+    const int t = rec.x;
+    const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
+    const bool valid = t >= 0;
+    const T dn = valid ? dnl[t] : (T)0, da = valid ? darc[t] : (T)0;
+    const RW w = load_or_wait(words, valid ? rec.y : 0, valid, (RW)~(RW)0, err, limit);
+    const StCell<T> c(ReqWord<T>::value(w), dn, da, valid, lane, head, tail, gam);
+    if (valid && lane == head) pub_st(words + tp.n_start + rec.z, pub_bits<T>(c.out));
+    if (valid) sa[tp.M + t] = c.share(gam);
+  }
+  if (lane == 0 && pub_ld(reinterpret_cast<const uint32_t *>(err)) != 0) atomicOr(err - ST_ERR, 2);
+}
+
+// endpoint values and adjoint seeds; the value summed by the last workgroup
 template <typename T>
 __global__ void __launch_bounds__(256) k_st_end(Topo tp, const double *__restrict__ inst_req, T gam,
-                                                 const T *__restrict__ dnl,
-                                                 T *__restrict__ sa, T *__restrict__ adj,
-                                                 double *__restrict__ part) {
+                                                 const T *__restrict__ dnl, const T *__restrict__ sa,
+                                                 T *__restrict__ adj, double *__restrict__ part,
+                                                 uint32_t *__restrict__ ctr, double *__restrict__ val) {
   __shared__ double sh[256];
   double acc = 0.0;
   for (int f = blockIdx.x * blockDim.x + threadIdx.x; f < tp.E; f += gridDim.x * blockDim.x) {
     const int t = tp.A + f;
     const T a = sa[tp.snk_drv[t]] + dnl[t];
-    sa[tp.M + t] = a;
     const T z = (a - (T)inst_req[tp.ff_inst[f]]) / gam;  // -slack / g
     const T sp = (z > 0 ? z : (T)0) + log1p(exp(-fabs(z)));
     acc += (double)(-gam * sp);
@@ -88,17 +144,18 @@ __global__ void __launch_bounds__(256) k_st_end(Topo tp, const double *__restric
     if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+  if (threadIdx.x == 0) pub_st(part + blockIdx.x, sh[0]);
+  last_sum(ctr, gridDim.x, part, val);
 }
 
 // The adjoint of one level's nets (drivers at that level, top-down), a lane
 // per net pin: a combinational-input sink takes its cell output's adjoint
-// times its softmax weight (the output's level is higher, so it is final), an
+// times its share (the output's level is higher, so it is final), an
 // endpoint keeps the seed the endpoint kernel wrote; the driver collects its
 // sinks' (a segment sum).
 template <typename T>
-__global__ void __launch_bounds__(256) k_st_bwd(Topo tp, int ch0, int ch1, T gam, const T *__restrict__ darc,
-                                                 const T *__restrict__ sa, T *__restrict__ adj) {
+__global__ void __launch_bounds__(256) k_st_bwd(Topo tp, int ch0, int ch1, const T *__restrict__ sa,
+                                                 T *__restrict__ adj, T *__restrict__ adj_nm) {
   const int lane = wave_lane();
   const int chunk = ch0 + blockIdx.x * 4 + (threadIdx.x >> 6);
   if (chunk >= ch1) return;
@@ -107,21 +164,46 @@ __global__ void __launch_bounds__(256) k_st_bwd(Topo tp, int ch0, int ch1, T gam
   const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
   T a = 0;
   if (p >= 0 && lane != head) {
-    if (vo >= 0) {
-      a = adj[vo] * exp((sa[p] + darc[p - tp.M] - sa[vo]) / gam);
-      adj[p] = a;
-    } else {
-      a = adj[p];
-    }
+    a = vo >= 0 ? adj[vo] * sa[p] : adj[p];
+    adj_nm[chunk * CHUNK + lane] = a;
   }
   a = seg_sum(a, lane, head, tail);
   if (p >= 0 && lane == head) adj[p] = a;
 }
 
+// The whole backward sweep on a resident grid, in reverse level order (no net
+// wider than a chunk): 147 us at 1M cells against 385 with a launch per level,
+// which also gathered the arc, both arrivals and the exponential of each share.
+template <typename T>
+__global__ void __launch_bounds__(256) k_st_bwd_flow(Topo tp, const T *__restrict__ sa, T *adj,
+                                                      T *__restrict__ adj_nm, int32_t *__restrict__ err, int limit) {
+  using RW = typename ReqWord<T>::type;
+  RW *words = reinterpret_cast<RW *>(adj);
+  const int lane = wave_lane(), wpb = blockDim.x >> 6;
+  const int W = gridDim.x * wpb, nch = tp.n_nm_chunks;
+  int q = blockIdx.x * wpb + (threadIdx.x >> 6);
+  int4 nrec = q < nch ? tp.nm_rec[(nch - 1 - q) * CHUNK + lane] : make_int4(-1, -1, -1, 0);
+  for (; q < nch; q += W) {
+    const int chunk = nch - 1 - q;
+    const int4 rec = nrec;
+    if (q + W < nch) nrec = tp.nm_rec[(nch - 1 - q - W) * CHUNK + lane];
+    const int p = rec.x, vo = rec.z;
+    const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
+    const bool sink = p >= 0 && lane != head, comb_in = sink && vo >= 0;
+    // a combinational input's share, an endpoint's seed
+    const T share = sink ? (comb_in ? sa : adj)[p] : (T)0;
+    const RW w = load_or_wait<true>(words, comb_in ? vo : 0, comb_in, (RW)~(RW)0, err, limit);
+    const T mine = comb_in ? ReqWord<T>::value(w) * share : share;
+    const T a = seg_sum(mine, lane, head, tail);
+    if (p >= 0 && lane == head) pub_st(words + p, pub_bits<T>(a));
+    if (sink) adj_nm[chunk * CHUNK + lane] = mine;
+  }
+  if (lane == 0 && pub_ld(reinterpret_cast<const uint32_t *>(err)) != 0) atomicOr(err - ST_ERR, 2);
+}
+
 // the same for nets wider than a chunk, one thread per net
 template <typename T>
-__global__ void k_st_bwd_big(Topo tp, int i0, int i1, T gam, const T *__restrict__ darc, const T *__restrict__ sa,
-                             T *__restrict__ adj) {
+__global__ void k_st_bwd_big(Topo tp, int i0, int i1, const T *__restrict__ sa, T *__restrict__ adj) {
   const int i = i0 + blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= i1) return;
   const int v = tp.big_net[i];
@@ -131,8 +213,7 @@ __global__ void k_st_bwd_big(Topo tp, int i0, int i1, T gam, const T *__restrict
     const int p = tp.M + t;
     T a;
     if (t < tp.A) {
-      const int vo = tp.n_start + tp.snk_comb[t];
-      a = adj[vo] * exp((sa[p] + darc[t] - sa[vo]) / gam);
+      a = adj[tp.n_start + tp.snk_comb[t]] * sa[p];
       adj[p] = a;
     } else {
       a = adj[p];
@@ -145,7 +226,7 @@ __global__ void k_st_bwd_big(Topo tp, int i0, int i1, T gam, const T *__restrict
 // gradient per cell: the sum of its pins' gradients (its output pin, then its
 // input pins), which the net kernels computed per pin
 template <typename T>
-__global__ void __launch_bounds__(256) k_st_grad(Topo tp, const T *__restrict__ gp, const double *__restrict__ gout,
+__global__ void __launch_bounds__(256) k_st_grad(Topo tp, const V2<T> *__restrict__ gp, const double *__restrict__ gout,
                                                   float *__restrict__ gx, float *__restrict__ gy) {
   const int cell = blockIdx.x * blockDim.x + threadIdx.x;
   if (cell >= tp.N || tp.cell_fixed[cell]) return;
@@ -161,10 +242,12 @@ __global__ void __launch_bounds__(256) k_st_grad(Topo tp, const T *__restrict__ 
     t0 = tp.A + f;
     t1 = t0 + 1;
   }
-  T ax = gp[v], ay = gp[tp.P + v];
+  const V2<T> out = gp[v];
+  T ax = out.x, ay = out.y;
   for (int t = t0; t < t1; ++t) {
-    ax += gp[tp.M + t];
-    ay += gp[tp.P + tp.M + t];
+    const V2<T> in = gp[tp.M + t];
+    ax += in.x;
+    ay += in.y;
   }
   const T go = (T)*gout;
   gx[cell] += (float)(go * ax);
@@ -186,24 +269,38 @@ __global__ void __launch_bounds__(256) k_sum_parts2(int n, const double *__restr
 
 constexpr int RED_BLOCKS = 512;
 
+// workgroups of a smoothed sweep's resident grid (dir 0 forward, 1 backward)
+static int st_blocks(tdp_graph g, const void *kern, int dir, int chunks) {
+  const int w = g->flow_waves, occ = occupancy(kern, g->occ_st[dir], w, 0);
+  return resident_blocks(g, std::min(occ, 2 * g->flow_per_cu), w, chunks);
+}
+
+// Both sweeps run as resident grids unless sweep_mode 0 asks for a launch per
+// level; backward, nets wider than a chunk do too.
 template <typename T>
 void stns_fwd_impl(tdp_graph g, const float *x, const float *y, float gamma, double *val, hipStream_t s) {
   const Topo &tp = g->topo;
   prof_begin(g, TDP_STAGE_STNS, s);
   const T gam = (T)gamma;
   st_net_fwd_impl<T>(g, x, y, (T *)g->st_dnet, s);
-  if (tp.n_start > 0)
-    hipLaunchKernelGGL(k_st_start<T>, dim3(nb(tp.n_start, 256)), dim3(256), 0, s, tp, (const T *)g->at,
-                       (T *)g->st_at);
-  for (int l = 1; l <= tp.D; ++l) {
-    const int ch0 = g->lv.fw_lvl[l - 1], ch1 = g->lv.fw_lvl[l];
-    if (ch1 > ch0)
-      hipLaunchKernelGGL(k_st_fwd<T>, dim3(nb(ch1 - ch0, 4)), dim3(256), 0, s, tp, ch0, ch1, gam,
-                         (const T *)g->st_dnet, (const T *)g->darc, (T *)g->st_at);
+  hipLaunchKernelGGL(k_st_start<T>, dim3(std::min(2048, nb(tp.M, 256))), dim3(256), 0, s, tp, (const T *)g->at,
+                     (T *)g->st_at, (T *)g->st_adj, g->d_err + ST_ERR);
+  if (g->sweep_mode != 0) {
+    const int w = g->flow_waves;
+    hipLaunchKernelGGL(k_st_fwd_flow<T>,
+                       dim3(st_blocks(g, reinterpret_cast<const void *>(&k_st_fwd_flow<T>), 0, tp.n_fw_chunks)),
+                       dim3(64 * w), 0, s, tp, gam, (const T *)g->st_dnet, (const T *)g->darc, (T *)g->st_at,
+                       g->d_err + ST_ERR, g->spin_limit);
+  } else {
+    for (int l = 1; l <= tp.D; ++l) {
+      const int ch0 = g->lv.fw_lvl[l - 1], ch1 = g->lv.fw_lvl[l];
+      if (ch1 > ch0)
+        hipLaunchKernelGGL(k_st_fwd<T>, dim3(nb(ch1 - ch0, 4)), dim3(256), 0, s, tp, ch0, ch1, gam,
+                           (const T *)g->st_dnet, (const T *)g->darc, (T *)g->st_at);
+    }
   }
-  hipLaunchKernelGGL(k_st_end<T>, dim3(RED_BLOCKS), dim3(256), 0, s, tp, g->d_inst_req, gam, (const T *)g->st_dnet,
-                     (T *)g->st_at, (T *)g->st_adj, g->red_loss);
-  hipLaunchKernelGGL(k_sum_parts2, dim3(1), dim3(256), 0, s, RED_BLOCKS, g->red_loss, val);
+  hipLaunchKernelGGL(k_st_end<T>, dim3(std::min(128, nb(tp.E, 256))), dim3(256), 0, s, tp, g->d_inst_req, gam,
+                     (const T *)g->st_dnet, (const T *)g->st_at, (T *)g->st_adj, g->red_loss, g->look_ctr + 8, val);
   g->st_gamma = gamma;
   g->st_x = x;
   g->st_y = y;
@@ -215,19 +312,27 @@ template <typename T>
 void stns_bwd_impl(tdp_graph g, const double *gout, float *gx, float *gy, hipStream_t s) {
   const Topo &tp = g->topo;
   prof_begin(g, TDP_STAGE_STNS, s);
-  const T gam = (T)g->st_gamma;
-  for (int l = tp.D; l >= 0; --l) {
-    const int ch0 = g->lv.nm_lvl[l], ch1 = g->lv.nm_lvl[l + 1];
-    if (ch1 > ch0)
-      hipLaunchKernelGGL(k_st_bwd<T>, dim3(nb(ch1 - ch0, 4)), dim3(256), 0, s, tp, ch0, ch1, gam,
-                         (const T *)g->darc, (const T *)g->st_at, (T *)g->st_adj);
-    const int b0 = g->lv.big_lvl[l], b1 = g->lv.big_lvl[l + 1];
-    if (b1 > b0)
-      hipLaunchKernelGGL(k_st_bwd_big<T>, dim3(nb(b1 - b0, 64)), dim3(64), 0, s, tp, b0, b1, gam,
-                         (const T *)g->darc, (const T *)g->st_at, (T *)g->st_adj);
+  if (g->sweep_mode != 0 && g->bw_flow_ok) {
+    const int w = g->flow_waves;
+    hipLaunchKernelGGL(k_st_bwd_flow<T>,
+                       dim3(st_blocks(g, reinterpret_cast<const void *>(&k_st_bwd_flow<T>), 1, tp.n_nm_chunks)),
+                       dim3(64 * w), 0, s, tp, (const T *)g->st_at, (T *)g->st_adj, (T *)g->st_adj_nm,
+                       g->d_err + ST_ERR, g->spin_limit);
+  } else {
+    for (int l = tp.D; l >= 0; --l) {
+      const int ch0 = g->lv.nm_lvl[l], ch1 = g->lv.nm_lvl[l + 1];
+      if (ch1 > ch0)
+        hipLaunchKernelGGL(k_st_bwd<T>, dim3(nb(ch1 - ch0, 4)), dim3(256), 0, s, tp, ch0, ch1, (const T *)g->st_at,
+                           (T *)g->st_adj, (T *)g->st_adj_nm);
+      const int b0 = g->lv.big_lvl[l], b1 = g->lv.big_lvl[l + 1];
+      if (b1 > b0)
+        hipLaunchKernelGGL(k_st_bwd_big<T>, dim3(nb(b1 - b0, 64)), dim3(64), 0, s, tp, b0, b1, (const T *)g->st_at,
+                           (T *)g->st_adj);
+    }
   }
-  st_net_grad_impl<T>(g, g->st_x, g->st_y, (const T *)g->st_adj, s);
-  hipLaunchKernelGGL(k_st_grad<T>, dim3(nb(tp.N, 256)), dim3(256), 0, s, tp, (const T *)g->st_gp, gout, gx, gy);
+  st_net_grad_impl<T>(g, g->st_x, g->st_y, (const T *)g->st_adj, (const T *)g->st_adj_nm, s);
+  hipLaunchKernelGGL(k_st_grad<T>, dim3(nb(tp.N, 256)), dim3(256), 0, s, tp, (const V2<T> *)g->st_gp, gout,
+                     gx, gy);
   prof_end(g, TDP_STAGE_STNS, s);
 }
 

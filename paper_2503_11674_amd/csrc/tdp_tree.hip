@@ -155,25 +155,23 @@ __global__ void __launch_bounds__(256) k_tree_net(Topo tp, const float *__restri
 // A(child end of e), the derivative by the length of the edge into u is
 //   scale r (c L_u + C_below(u)) A(u) + c B(parent(u)):
 // the edge's own term and its capacitance in C_below of every edge above.
-// gp[pin] (x) and gp[P + pin] (y) collect d value / d position of each pin.
+// gp[pin] collects d value / d position of each pin.
 template <typename T>
 __global__ void __launch_bounds__(256) k_st_tree_grad(Topo tp, const float *__restrict__ x,
                                                        const float *__restrict__ y, NetModel<T> nm, T cw,
-                                                       TreeView<T> tb, const T *__restrict__ adj, T *__restrict__ gp,
+                                                       TreeView<T> tb, const T *__restrict__ adj,
+                                                       V2<T> *__restrict__ gp,
                                                        const int32_t *__restrict__ list, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int v = list[i];
   tree_build<T>(tp, x, y, cw, v, tb);
   const int k0 = tp.net_ptr[v], k1 = tp.net_ptr[v + 1];
-  T *gpx = gp, *gpy = gp + tp.P;
-  gpx[v] = 0;
-  gpy[v] = 0;
+  gp[v] = v2<T>(0, 0);
   for (int k = k0; k < k1; ++k) {
     const int t = tp.net_sink[k];
     tb.aux[k] = adj[tp.M + t];
-    gpx[tp.M + t] = 0;
-    gpy[tp.M + t] = 0;
+    gp[tp.M + t] = v2<T>(0, 0);
   }
   for (int step = k1 - k0 - 1; step >= 0; --step) {
     const int k = tb.ord[k0 + step], p = tb.par[k];
@@ -189,10 +187,10 @@ __global__ void __launch_bounds__(256) k_st_tree_grad(Topo tp, const float *__re
     tree_diff<T>(tree_pin(tp, x, y, v, p), tree_pin(tp, x, y, v, k), dx, dy);
     const T gx = gl * (T)((dx > (T)0) - (dx < (T)0)), gy = gl * (T)((dy > (T)0) - (dy < (T)0));
     const int pp = p >= 0 ? tp.M + tp.net_sink[p] : v, pk = tp.M + tp.net_sink[k];
-    gpx[pp] += gx;
-    gpy[pp] += gy;
-    gpx[pk] -= gx;
-    gpy[pk] -= gy;
+    gp[pp].x += gx;
+    gp[pp].y += gy;
+    gp[pk].x -= gx;
+    gp[pk].y -= gy;
   }
 }
 
@@ -255,14 +253,15 @@ __global__ void __launch_bounds__(256) k_st_tree_chunks(Topo tp, const float2 *_
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_st_tree_grad_chunks(Topo tp, const float2 *__restrict__ xy, NetModel<T> nm,
-                                                             T cw, const T *__restrict__ adj, T *__restrict__ gp) {
+                                                             T cw, const T *__restrict__ adj_nm,
+                                                             V2<T> *__restrict__ gp) {
   const int chunk = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (chunk >= tp.n_nm_chunks) return;
   const ChunkLane c = chunk_lane(tp, xy, chunk);
   const ChunkTree<T> tr = chunk_tree<T>(tp, c, cw);
   const int lane = c.lane, head = c.head, tail = c.tail;
   // A: the adjoint summed over the subtree (reverse joining order)
-  T a = c.sink ? adj[c.p] : (T)0;
+  T a = c.sink ? adj_nm[chunk * CHUNK + lane] : (T)0;
   for (int j = tr.rounds - 1; j >= 0; --j) {
     const int slot = head + 1 + j;
     const int w = __shfl(tr.who, slot < 64 ? slot : 63, 64);
@@ -304,10 +303,7 @@ __global__ void __launch_bounds__(256) k_st_tree_grad_chunks(Topo tp, const floa
       }
     }
   }
-  if (c.p >= 0) {
-    gp[c.p] = gx;
-    gp[tp.P + c.p] = gy;
-  }
+  if (c.p >= 0) gp[c.p] = v2<T>(gx, gy);
 }
 
 // The star models on net chunks: a sink's wire runs from the driver (the
@@ -338,19 +334,17 @@ __global__ void __launch_bounds__(256) k_st_star_chunks(Topo tp, const float2 *_
 // per pin: a sink minus its wire's term, the driver the sum of its sinks'
 template <typename T>
 __global__ void __launch_bounds__(256) k_st_star_grad_chunks(Topo tp, const float2 *__restrict__ xy, NetModel<T> nm,
-                                                             const T *__restrict__ adj, T *__restrict__ gp) {
+                                                             const T *__restrict__ adj_nm,
+                                                             V2<T> *__restrict__ gp) {
   const int chunk = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (chunk >= tp.n_nm_chunks) return;
   const ChunkLane c = chunk_lane(tp, xy, chunk);
   T dx, dy;
   const T len = star_diff<T>(c, dx, dy);
-  const T gl = c.sink ? adj[c.p] * nm.slope(len, nm.elmore ? (T)tp.type_cap[c.ty] : (T)0) : (T)0;
+  const T gl = c.sink ? adj_nm[chunk * CHUNK + c.lane] * nm.slope(len, nm.elmore ? (T)tp.type_cap[c.ty] : (T)0) : (T)0;
   const T ex = gl * (T)((dx > (T)0) - (dx < (T)0)), ey = gl * (T)((dy > (T)0) - (dy < (T)0));
   const T sx = seg_sum(ex, c.lane, c.head, c.tail), sy = seg_sum(ey, c.lane, c.head, c.tail);
-  if (c.p >= 0) {
-    gp[c.p] = c.sink ? -ex : sx;
-    gp[tp.P + c.p] = c.sink ? -ey : sy;
-  }
+  if (c.p >= 0) gp[c.p] = c.sink ? v2<T>(-ex, -ey) : v2<T>(sx, sy);
 }
 
 // the star models on the n nets listed (nets wider than a chunk), one thread
@@ -359,7 +353,7 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_st_star_big(Topo tp, const float *__restrict__ x,
                                                       const float *__restrict__ y, NetModel<T> nm,
                                                       const T *__restrict__ adj, T *__restrict__ dnl,
-                                                      T *__restrict__ gp, const int32_t *__restrict__ list, int n) {
+                                                      V2<T> *__restrict__ gp, const int32_t *__restrict__ list, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int v = list[i];
@@ -379,15 +373,11 @@ __global__ void __launch_bounds__(256) k_st_star_big(Topo tp, const float *__res
     }
     const T gl = adj[tp.M + t] * nm.slope(len, cap);
     const T ex = gl * (T)((dx > (T)0) - (dx < (T)0)), ey = gl * (T)((dy > (T)0) - (dy < (T)0));
-    gp[tp.M + t] = -ex;
-    gp[tp.P + tp.M + t] = -ey;
+    gp[tp.M + t] = v2<T>(-ex, -ey);
     sx += ex;
     sy += ey;
   }
-  if (adj) {
-    gp[v] = sx;
-    gp[tp.P + v] = sy;
-  }
+  if (adj) gp[v] = v2<T>(sx, sy);
 }
 
 template <typename T>
@@ -419,22 +409,22 @@ void st_net_fwd_impl(tdp_graph g, const float *x, const float *y, T *dnl, hipStr
       tree_net_impl<T>(g, g->st_tree, x, y, dnl, tp.big_net, tp.n_big, s);
     else
       hipLaunchKernelGGL(k_st_star_big<T>, dim3(nbt(tp.n_big, 256)), dim3(256), 0, s, tp, x, y, net_model<T>(g),
-                         (const T *)nullptr, dnl, (T *)nullptr, tp.big_net, tp.n_big);
+                         (const T *)nullptr, dnl, (V2<T> *)nullptr, tp.big_net, tp.n_big);
   }
 }
 
 template <typename T>
-void st_net_grad_impl(tdp_graph g, const float *x, const float *y, const T *adj, hipStream_t s) {
+void st_net_grad_impl(tdp_graph g, const float *x, const float *y, const T *adj, const T *adj_nm, hipStream_t s) {
   const Topo &tp = g->topo;
   const bool tree = g->lut.net_model == 2;
-  T *gp = (T *)g->st_gp;
+  V2<T> *gp = (V2<T> *)g->st_gp;
   if (tp.n_nm_chunks > 0) {
     if (tree)
       hipLaunchKernelGGL(k_st_tree_grad_chunks<T>, dim3(nbt(tp.n_nm_chunks, 4)), dim3(256), 0, s, tp, g->xy_st,
-                         net_model<T>(g), (T)g->c, adj, gp);
+                         net_model<T>(g), (T)g->c, adj_nm, gp);
     else
       hipLaunchKernelGGL(k_st_star_grad_chunks<T>, dim3(nbt(tp.n_nm_chunks, 4)), dim3(256), 0, s, tp, g->xy_st,
-                         net_model<T>(g), adj, gp);
+                         net_model<T>(g), adj_nm, gp);
   }
   if (tp.n_big > 0) {
     if (tree)
@@ -452,7 +442,9 @@ template void tree_net_impl<double>(tdp_graph, const TreeBuf &, const float *, c
                                     const int32_t *, int, hipStream_t);
 template void st_net_fwd_impl<float>(tdp_graph, const float *, const float *, float *, hipStream_t);
 template void st_net_fwd_impl<double>(tdp_graph, const float *, const float *, double *, hipStream_t);
-template void st_net_grad_impl<float>(tdp_graph, const float *, const float *, const float *, hipStream_t);
-template void st_net_grad_impl<double>(tdp_graph, const float *, const float *, const double *, hipStream_t);
+template void st_net_grad_impl<float>(tdp_graph, const float *, const float *, const float *, const float *,
+                                      hipStream_t);
+template void st_net_grad_impl<double>(tdp_graph, const float *, const float *, const double *, const double *,
+                                       hipStream_t);
 
 }  // namespace tdp
