@@ -973,14 +973,15 @@ tdp_status tdp_density_setup(tdp_graph g, const tdp_density_grid *grid, const fl
     ok = dalloc(g, g->dn_area, N) && dalloc(g, g->dn_k0, N) && dalloc(g, g->dn_k1, N) && dalloc(g, g->dn_v0, N) &&
          dalloc(g, g->dn_v1, N) && dalloc(g, g->dn_hist, sort_hist_size(std::max(N, 1), 11)) &&
          dalloc(g, g->dn_part, 2 * density_parts()) &&
-         dalloc(g, g->nest_part, 2 * density_parts()) && dalloc(g, g->nest_alpha, 1) && dalloc(g, g->dn_nheavy, 1);
+         dalloc(g, g->nest_part, 2 * density_parts()) && dalloc(g, g->nest_alpha, 1) && dalloc(g, g->dn_nheavy, 1) &&
+         dalloc(g, g->dn_ctr, 4);
   }
   if (ok && bins > g->dn_alloc_bins) {  // a smaller grid reuses the buffers
     ok = dalloc(g, g->dn_start, (size_t)bins + 1) && dalloc(g, g->dn_map, bins) && dalloc(g, g->dn_heavy, bins);
     if (ok) g->dn_alloc_bins = bins;
   }
   if (ok && q.radius > g->dn_alloc_R) {
-    ok = dalloc(g, g->dn_w, (size_t)2 * K * std::max(N, 1));
+    ok = dalloc(g, g->dn_w, (size_t)(2 * K + 3) * std::max(N, 1));
     if (ok) g->dn_alloc_R = q.radius;
   }
   if (!ok) return fail(g, TDP_E_NOMEM, "density: device allocation failed");

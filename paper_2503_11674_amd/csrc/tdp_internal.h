@@ -396,7 +396,8 @@ struct tdp_graph_s {
   uint32_t *dn_v0 = nullptr, *dn_v1 = nullptr;  // [N] cell ids
   int32_t *dn_hist = nullptr, *dn_start = nullptr;  // start [bins + 1]
   int32_t *dn_heavy = nullptr, *dn_nheavy = nullptr;  // crowded bins [bins] and their count
-  float *dn_w = nullptr;                       // [2 (2R+1)][N] window weights of the sorted cells
+  float *dn_w = nullptr;                       // [2 (2R+1) + 3][N] window weights, area and bin fractions of the sorted cells
+  uint32_t *dn_ctr = nullptr;                  // [4] counters of its sums' launch
   float *dn_map = nullptr;                     // [bins]
   double *dn_part = nullptr, *nest_part = nullptr, *nest_alpha = nullptr;
 

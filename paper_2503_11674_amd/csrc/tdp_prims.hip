@@ -236,17 +236,24 @@ __global__ void __launch_bounds__(1024) k_rs_cols(int cap, const int32_t *d_n, i
   const bool on = d < R;
   const int per = (ntiles + 15) / 16, t0 = min(g * per, ntiles), t1 = min(t0 + per, ntiles);
   int sum = 0;
-  if (on)
+  if (on) {
+#pragma unroll 8
     for (int t = t0; t < t1; ++t) sum += hist[(size_t)t * R + d];
+  }
   s_run[g][threadIdx.x & 63] = sum;
   __syncthreads();
   int run = 0;
   for (int q = 0; q < g; ++q) run += s_run[q][threadIdx.x & 63];
   if (!on) return;
-  for (int t = t0; t < t1; ++t) {
-    const int h = hist[(size_t)t * R + d];
-    hist[(size_t)t * R + d] = run;
-    run += h;
+  for (int t = t0; t < t1; t += 8) {
+    int h[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) h[q] = t + q < t1 ? hist[(size_t)(t + q) * R + d] : 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (t + q < t1) hist[(size_t)(t + q) * R + d] = run;
+      run += h[q];
+    }
   }
   if (g == 15) tot[d] = run;
 }
@@ -287,14 +294,21 @@ __global__ void __launch_bounds__(RS_BLOCK) k_rs_scatter(const Key *__restrict__
   for (int q = 0; q < PER; ++q) before[q] = total[q] = 0;
   if (tid * PER < R) {
     if (ntiles <= RS_DIRECT) {
-      for (int t = 0; t < ntiles; ++t) {
+      // eight tiles' counts in flight at a time
+      for (int t0 = 0; t0 < ntiles; t0 += 8) {
+        int h[8][PER];
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
-          const int d = tid * PER + q;
-          const int h = d < R ? hist[(size_t)t * R + d] : 0;
-          total[q] += h;
-          before[q] += t < tile ? h : 0;
-        }
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+          for (int q = 0; q < PER; ++q)
+            h[t][q] = t0 + t < ntiles && tid * PER + q < R ? hist[(size_t)(t0 + t) * R + tid * PER + q] : 0;
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+          for (int q = 0; q < PER; ++q) {
+            total[q] += h[t][q];
+            before[q] += t0 + t < tile ? h[t][q] : 0;
+          }
       }
     } else {
 #pragma unroll
