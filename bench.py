@@ -35,7 +35,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_2m_cells.md")
 # per level, the dataflow sweeps once)
 STAGE_KERNEL = {
     "netpass": ("tdp::k_netpass<float, false>", "tdp::k_netpass<float, true>"), "forward": ("tdp::k_forward<float, 8>", "tdp::k_forward_flow<float, 8>"),
-    "backward": ("tdp::k_backward<float>", "tdp::k_backward_flow<float>"), "walk": ("tdp::k_walk<float>",),
+    "backward": ("tdp::k_backward<float>", "tdp::k_backward_flow<float, false>", "tdp::k_backward_flow<float, true>"), "walk": ("tdp::k_walk<float>",),
     "pairs": ("tdp::k_pairs_acc_lds<float>",), "wa": ("tdp::k_wa_net",), "search": ("tdp::k_search<float, 8>",),
 }
 

@@ -344,7 +344,7 @@ tdp_status tdp_sta_update(tdp_graph g, const float *x, const float *y, hipStream
   g->ea_ready = false;  // the hold results belong to the previous placement
   g->rf_updated = false;
   dispatch(g, [&](auto z) {
-    sta_arrivals_impl<decltype(z)>(g, x, y, s);
+    sta_arrivals_impl<decltype(z)>(g, x, y, true, s);
     sta_required_impl<decltype(z)>(g, s);
   });
   tdp_status st = check_launch(g, "sta_update");
@@ -390,7 +390,7 @@ tdp_status tdp_sta_update_arrivals(tdp_graph g, const float *x, const float *y, 
   if (!x || !y) return fail(g, TDP_E_INVALID, "positions are NULL");
   g->ea_ready = false;
   g->rf_updated = false;
-  dispatch(g, [&](auto z) { sta_arrivals_impl<decltype(z)>(g, x, y, s); });
+  dispatch(g, [&](auto z) { sta_arrivals_impl<decltype(z)>(g, x, y, false, s); });
   tdp_status st = check_launch(g, "sta_update_arrivals");
   if (st == TDP_OK) g->updated = true;
   return st;

@@ -428,7 +428,10 @@ tdp_status build_host_topology(const tdp_netlist *const *nls, int32_t count, con
         }
         if (lane % CHUNK + n > CHUNK) pad();
         const int head = (int)(lane % CHUNK);
-        H.nm_rec.push_back(make_int4(v, H.drv_cell[v], -1, seg(head, head + n - 1)));
+        // (a combinational driver's inputs are consecutive sinks)
+        const int t0 = v >= T.n_start ? H.comb_inptr[v - T.n_start] : 0;
+        const int nin = v >= T.n_start ? H.comb_inptr[v - T.n_start + 1] - t0 : 0;
+        H.nm_rec.push_back(make_int4(v, H.drv_cell[v], t0, seg(head, head + n - 1) | nin << 16));
         H.nm_ox.push_back(H.drv_ox[v]);
         H.nm_oy.push_back(H.drv_oy[v]);
         ++lane;

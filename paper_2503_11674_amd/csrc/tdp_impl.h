@@ -45,7 +45,8 @@ template <typename T> void rf_update_impl(tdp_graph g, const float *x, const flo
 template <typename T>
 void rf_export_impl(tdp_graph g, double *at, double *rat, double *slack, double *slew, hipStream_t s);
 template <typename T> void rf_extract_impl(tdp_graph g, int n, int K, hipStream_t s);
-template <typename T> void sta_arrivals_impl(tdp_graph g, const float *x, const float *y, hipStream_t s);
+// required: the same call's sta_required_impl follows
+template <typename T> void sta_arrivals_impl(tdp_graph g, const float *x, const float *y, bool required, hipStream_t s);
 template <typename T>
 void sta_arrivals_incremental_impl(tdp_graph g, const float *x, const float *y, const int32_t *cells, int n,
                                    hipStream_t s);

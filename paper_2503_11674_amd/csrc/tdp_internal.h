@@ -166,8 +166,9 @@ struct Topo {
   // than 63 sinks are "big" and handled one thread per net.
   // One record per lane: {internal pin (driver v or M + t; -1 = padding),
   // external cell (-1 for a port or padding), for a combinational-input sink
-  // the output driver of its cell (else -1), head lane | tail lane << 8 |
-  // for a sink, its cell's type << 16}.
+  // the output driver of its cell (-1 for another sink) and for a driver its
+  // cell's first input sink, head lane | tail lane << 8 | for a sink its cell's
+  // type << 16, for a driver the number of its cell's inputs << 16}.
   int32_t n_nm_chunks = 0, n_big = 0;
   int4 *nm_rec = nullptr;
   float *nm_ox = nullptr, *nm_oy = nullptr;
@@ -291,7 +292,7 @@ struct tdp_graph_s {
   uint64_t *flow_a = nullptr;    // [A] {arrival through an input's arc, tag}, with deviation lists
   int2 *list_turn = nullptr;     // [n_turns] {first cell, cells} of a list wave's turns, level by level
   int32_t n_turns = 0;
-  void *flow_r = nullptr;        // [M] required time of a driver (its bits, 4 or 8 bytes); all ones = not yet
+  void *flow_r = nullptr;        // [M] required time of a driver (its bits, 4 or 8 bytes); all ones = not yet (PULL sweeps)
   int32_t flow_waves = 4, spin_limit = 1 << 20;
   int32_t flow_per_cu = 1;       // workgroups per compute unit of the resident dataflow grids
   int32_t num_cu = 0;            // compute units of the device

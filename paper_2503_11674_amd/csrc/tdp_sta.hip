@@ -39,7 +39,8 @@ __device__ __forceinline__ uint64_t pack2(float lo, float hi) {
 
 struct FlowInit {
   uint64_t *w = nullptr;
-  void *r = nullptr;
+  void *r = nullptr;              // the backward sweep's published words and their count
+  int nr = 0;
   int32_t *err = nullptr;  // cleared at the start of every update
   const uint32_t *tag = nullptr;  // the graph's pass counter and whether the last sweep gave up
   uint64_t *node = nullptr;
@@ -95,7 +96,7 @@ __device__ __forceinline__ void flow_reset(const FlowInit &fl, const Topo &tp, i
   const size_t nth = (size_t)fl.reset_blocks * blockDim.x, tid = (size_t)b * blockDim.x + threadIdx.x;
   const size_t nc = (size_t)(tp.M - tp.n_start);
   if (fl.w) fill_u32((uint32_t *)(fl.w + (size_t)N * tp.n_start), 2 * N * nc, ~0u, tid, nth);
-  if (fl.r) fill_u32((uint32_t *)fl.r, (size_t)tp.M * N, ~0u, tid, nth);
+  if (fl.r) fill_u32((uint32_t *)fl.r, (size_t)fl.nr * N, ~0u, tid, nth);
   if (fl.w && fl.tag[1]) {
     // id 0 in both halves (a sweep that gives up again reads them as ids)
     // under the previous pass's tag, where a hop word or a list entry has it
@@ -883,15 +884,29 @@ __global__ void __launch_bounds__(256) k_forward_flow(Topo tp, LutView L, int n_
                       fa, tag, err, limit);
 }
 
-// Backward: chunks from the last; a sink lane loads the required time of its
-// cell's output (the D pin of a flip-flop needs nothing), waiting only if it
-// is not out yet; the driver lane publishes its own.
-template <typename T>
+// Backward: chunks from the last.  PULL: a sink lane loads the required time of
+// its cell's output (the D pin of a flip-flop needs nothing), waiting only if
+// it is not out yet, and stores its own; the driver lane publishes its own in
+// fr.  PUSH: a sink lane loads its own required time, waiting likewise, and
+// the driver lane publishes its cell's inputs', a consecutive run: one random
+// read a sink where PULL has two and a random write, but three times the
+// published words.  Many chunks per wave are bound by the random accesses and
+// take PUSH (2M cells: 277 us against 345; 1M: 168 against 175), few by the
+// chain and take PULL (200k: 97 against 105; 2k: 26 against 30).
+constexpr int FANIN_AHEAD = 4;         // PUSH: inputs whose arcs are loaded before the wait
+constexpr int PUSH_CHUNKS_PER_CU = 256;  // net chunks from which PUSH is taken
+
+static bool backward_pushes(const tdp_graph_s *g) {
+  return g->topo.n_nm_chunks >= (long long)PUSH_CHUNKS_PER_CU * std::max(1, g->num_cu);
+}
+
+template <typename T, bool PUSH>
 __global__ void __launch_bounds__(256) k_backward_flow(Topo tp, const T *__restrict__ dnet_nm,
-                                                        const T *__restrict__ darc, T *__restrict__ rat,
-                                                        typename ReqWord<T>::type *__restrict__ fr,
-                                                        int32_t *__restrict__ err, int limit) {
+                                                        const T *__restrict__ darc, T *rat,
+                                                        typename ReqWord<T>::type *fr, int32_t *__restrict__ err,
+                                                        int limit) {
   using RW = typename ReqWord<T>::type;
+  RW *const words = PUSH ? reinterpret_cast<RW *>(rat) : fr;
   const int lane = wave_lane();
   const T inf = pos_inf<T>();
   const int wpb = blockDim.x >> 6;
@@ -901,29 +916,51 @@ __global__ void __launch_bounds__(256) k_backward_flow(Topo tp, const T *__restr
   int4 nrec = q < nch ? tp.nm_rec[(nch - 1 - q) * CHUNK + lane] : make_int4(-1, -1, -1, 0);
   for (; q < nch; q += W) {
     const int chunk = nch - 1 - q;
-    const int k = chunk * CHUNK + lane;
     const int4 rec = nrec;
     if (q + W < nch) nrec = tp.nm_rec[(nch - 1 - q - W) * CHUNK + lane];
-    const int p = rec.x, vo = rec.z;
+    const int p = rec.x;
     const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
-    const bool sink = p >= 0 && lane != head;
-    const int t = p - tp.M;
-    const bool comb_in = sink && vo >= 0;
-    const T dn = sink ? dnet_nm[k] : (T)0, da = comb_in ? darc[t] : (T)0;
-    const T rq = sink && !comb_in ? rat[p] : (T)0;  // a D pin's, set at the endpoint
-    // outputs are numbered in production order of the forward sweep, so the
-    // backward sweep publishes the lowest one last
-    const RW wr = load_or_wait<true>(fr, comb_in ? vo : 0, comb_in, (RW)~(RW)0, err, limit);
+    const bool sink = p >= 0 && lane != head, driver = p >= 0 && lane == head;
+    const T dn = sink ? dnet_nm[chunk * CHUNK + lane] : (T)0;
     T r = inf;
-    if (sink) {
-      const T rt = comb_in ? sink_required<T>(p, ReqWord<T>::value(wr), da, rat) : rq;
-      if (rt != inf) r = rt - dn;
+    if constexpr (PUSH) {
+      const int nin = driver ? rec.w >> 16 : 0;
+      const int t0 = rec.z;
+      T da[FANIN_AHEAD];
+#pragma unroll
+      for (int j = 0; j < FANIN_AHEAD; ++j) da[j] = j < nin ? darc[t0 + j] : (T)0;
+      // input sinks are numbered in level order and published from the top,
+      // so the lowest one missing comes last
+      const RW w = load_or_wait<true>(words, sink ? p : 0, sink, (RW)~(RW)0, err, limit);
+      const T rt = ReqWord<T>::value(w);
+      if (sink && rt != inf) r = rt - dn;
+      r = seg_min(r, lane, head, tail);
+      if (driver) {
+        auto publish = [&](int j, T d) {
+          const T ri = r != inf ? r - d : inf;
+          pub_st(words + tp.M + t0 + j, ReqWord<T>::bits(ri == ri ? ri : (T)__builtin_nan("")));
+        };
+#pragma unroll
+        for (int j = 0; j < FANIN_AHEAD; ++j)
+          if (j < nin) publish(j, da[j]);
+        for (int j = FANIN_AHEAD; j < nin; ++j) publish(j, darc[t0 + j]);
+      }
+    } else {
+      const int t = p - tp.M, vo = rec.z;
+      const bool comb_in = sink && vo >= 0;
+      const T da = comb_in ? darc[t] : (T)0;
+      const T rq = sink && !comb_in ? rat[p] : (T)0;  // a D pin's, set at the endpoint
+      // outputs are numbered in production order of the forward sweep, so the
+      // backward sweep publishes the lowest one last
+      const RW wr = load_or_wait<true>(words, comb_in ? vo : 0, comb_in, (RW)~(RW)0, err, limit);
+      if (sink) {
+        const T rt = comb_in ? sink_required<T>(p, ReqWord<T>::value(wr), da, rat) : rq;
+        if (rt != inf) r = rt - dn;
+      }
+      r = seg_min(r, lane, head, tail);
+      if (driver) pub_st(&fr[p], ReqWord<T>::bits(r));
     }
-    r = seg_min(r, lane, head, tail);
-    if (p >= 0 && lane == head) {
-      pub_st(&fr[p], ReqWord<T>::bits(r));
-      rat[p] = r;
-    }
+    if (driver) rat[p] = r;
   }
 }
 
@@ -1098,12 +1135,21 @@ static bool flow_backward(const tdp_graph_s *g) {
   return (g->sweep_mode >= 1 && g->sweep_mode <= 3) || (g->sweep_mode == 4 && g->bw_flow_ok);
 }
 
+// the words that the backward sweep publishes: input sinks' required times in
+// place (PUSH), or drivers' in an array of their own
+template <typename T>
+static T *backward_words(tdp_graph g, int &n) {
+  const bool push = backward_pushes(g);
+  n = push ? g->topo.A : g->topo.M;
+  return push ? (T *)g->rat + g->topo.M : (T *)g->flow_r;
+}
+
 // arrivals: net pass, forward sweep, endpoint slacks and WNS / TNS
 template <typename T>
-void sta_arrivals_impl(tdp_graph g, const float *x, const float *y, hipStream_t s) {
+void sta_arrivals_impl(tdp_graph g, const float *x, const float *y, bool required, hipStream_t s) {
   const Topo &tp = g->topo;
   const NetModel<T> nm = net_model<T>(g);
-  const bool flow = flow_forward(g), bflow = flow_backward(g);
+  const bool flow = flow_forward(g), bflow = required && flow_backward(g);
   FlowInit fl;
   fl.err = g->d_err;
   fl.tag = g->d_tag;
@@ -1114,7 +1160,7 @@ void sta_arrivals_impl(tdp_graph g, const float *x, const float *y, hipStream_t 
     fl.cd = g->cdep;
     fl.seed = g->sweep_mode == 2 ? 0 : 1;
   }
-  if (bflow) fl.r = g->flow_r;
+  if (bflow) fl.r = backward_words<T>(g, fl.nr);
   fl.reset_blocks = flow ? 1024 : (bflow ? 64 : 0);
   prof_begin(g, TDP_STAGE_NETPASS, s);
   netpass_launch<T>(g, x, y, fl, true, s);
@@ -1235,18 +1281,26 @@ void sta_required_impl(tdp_graph g, hipStream_t s) {
   const bool flow = flow_backward(g);
   prof_begin(g, TDP_STAGE_BACKWARD, s);
   if (flow) {
-    // the words are reset by a full arrival pass that plans this sweep; after
-    // any other (incremental, per-level, or none since the last sweep) they
-    // are reset here
-    if (!g->flow_r_clear) fill_i32(reinterpret_cast<int32_t *>(g->flow_r), tp.M * (int)(sizeof(T) / 4), -1, s);
+    // the words are reset by the arrival pass of the same call; a call of its
+    // own resets them here
+    int nr = 0;
+    T *const words = backward_words<T>(g, nr);
+    if (!g->flow_r_clear) fill_i32(reinterpret_cast<int32_t *>(words), nr * (int)(sizeof(T) / 4), -1, s);
     g->flow_r_clear = false;
     // twice flow_per_cu: 346 us against 379 at 2M cells, no difference at 200k
     const int w = g->flow_waves;
-    const int occ = occupancy(reinterpret_cast<const void *>(&k_backward_flow<T>), g->occ_bw, w, 0);
-    const int nb = resident_blocks(g, std::min(occ, 2 * g->flow_per_cu), w, tp.n_nm_chunks);
-    hipLaunchKernelGGL(k_backward_flow<T>, dim3(nb), dim3(64 * w), 0, s, tp, (const T *)g->dnet_nm,
-                       (const T *)g->darc, (T *)g->rat, (typename ReqWord<T>::type *)g->flow_r, g->d_err,
-                       g->spin_limit);
+    const bool push = backward_pushes(g);
+    const void *const kern = push ? reinterpret_cast<const void *>(&k_backward_flow<T, true>)
+                                  : reinterpret_cast<const void *>(&k_backward_flow<T, false>);
+    const int nb = resident_blocks(g, std::min(occupancy(kern, g->occ_bw, w, 0), 2 * g->flow_per_cu), w,
+                                   tp.n_nm_chunks);
+    using RW = typename ReqWord<T>::type;
+    if (push)
+      hipLaunchKernelGGL((k_backward_flow<T, true>), dim3(nb), dim3(64 * w), 0, s, tp, (const T *)g->dnet_nm,
+                         (const T *)g->darc, (T *)g->rat, (RW *)nullptr, g->d_err, g->spin_limit);
+    else
+      hipLaunchKernelGGL((k_backward_flow<T, false>), dim3(nb), dim3(64 * w), 0, s, tp, (const T *)g->dnet_nm,
+                         (const T *)g->darc, (T *)g->rat, (RW *)g->flow_r, g->d_err, g->spin_limit);
     prof_end(g, TDP_STAGE_BACKWARD, s);
     return;
   }
@@ -1285,8 +1339,8 @@ template void sta_arrivals_incremental_impl<float>(tdp_graph, const float *, con
                                                    hipStream_t);
 template void sta_arrivals_incremental_impl<double>(tdp_graph, const float *, const float *, const int32_t *, int,
                                                     hipStream_t);
-template void sta_arrivals_impl<float>(tdp_graph, const float *, const float *, hipStream_t);
-template void sta_arrivals_impl<double>(tdp_graph, const float *, const float *, hipStream_t);
+template void sta_arrivals_impl<float>(tdp_graph, const float *, const float *, bool, hipStream_t);
+template void sta_arrivals_impl<double>(tdp_graph, const float *, const float *, bool, hipStream_t);
 template void sta_required_impl<float>(tdp_graph, hipStream_t);
 template void sta_required_impl<double>(tdp_graph, hipStream_t);
 template void sta_export_impl<float>(tdp_graph, double *, double *, double *, double *, double *, double *,
