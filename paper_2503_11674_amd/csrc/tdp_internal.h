@@ -271,7 +271,9 @@ struct tdp_graph_s {
   bool updated = false, extracted = false, pairs_built = false, stns_ready = false;
   std::vector<void *> allocs;  // every device allocation, freed at destroy
   std::vector<int32_t> h_snk_ext;  // host copy: external pin of each sink
-  int32_t *d_err = nullptr;    // device flag for internal consistency errors
+  // device words: internal consistency errors, the last pass with a position that
+  // was not finite, a smoothed sweep that gave up
+  int32_t *d_err = nullptr;
   double *consts = nullptr;    // [4] device constants: {1, 0, 0, 0}
 
   // timing state (element type per precision)
@@ -292,7 +294,7 @@ struct tdp_graph_s {
   uint64_t *flow_a = nullptr;    // [A] {arrival through an input's arc, tag}, with deviation lists
   int2 *list_turn = nullptr;     // [n_turns] {first cell, cells} of a list wave's turns, level by level
   int32_t n_turns = 0;
-  void *flow_r = nullptr;        // [M] required time of a driver (its bits, 4 or 8 bytes); all ones = not yet (PULL sweeps)
+  void *flow_r = nullptr;        // [M] required time of a driver (its bits, 4 or 8 bytes); all ones = not yet (PULL)
   int32_t flow_waves = 4, spin_limit = 1 << 20;
   int32_t flow_per_cu = 1;       // workgroups per compute unit of the resident dataflow grids
   int32_t num_cu = 0;            // compute units of the device
@@ -397,7 +399,7 @@ struct tdp_graph_s {
   uint32_t *dn_v0 = nullptr, *dn_v1 = nullptr;  // [N] cell ids
   int32_t *dn_hist = nullptr, *dn_start = nullptr;  // start [bins + 1]
   int32_t *dn_heavy = nullptr, *dn_nheavy = nullptr;  // crowded bins [bins] and their count
-  float *dn_w = nullptr;                       // [2 (2R+1) + 3][N] window weights, area and bin fractions of the sorted cells
+  float *dn_w = nullptr;                       // [2 (2R+1) + 3][N] sorted cells' window weights, areas, bin fractions
   uint32_t *dn_ctr = nullptr;                  // [4] counters of its sums' launch
   float *dn_map = nullptr;                     // [bins]
   double *dn_part = nullptr, *nest_part = nullptr, *nest_alpha = nullptr;

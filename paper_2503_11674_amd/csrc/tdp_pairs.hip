@@ -572,7 +572,8 @@ void p2p_fwd_impl(tdp_graph g, int kind, const float *x, const float *y, double 
 template <typename T, int KIND>
 static void launch_pair_bwd(tdp_graph g, const float *x, const float *y, const double *gout, float *gx, float *gy,
                             hipStream_t s) {
-  hipLaunchKernelGGL((k_p2p_bwd<T, KIND>), dim3(std::min(LOSS_BLOCKS * 2, nb(g->topo.N, 256))), dim3(256), 0, s, g->d_ntouched, g->touched,
+  hipLaunchKernelGGL((k_p2p_bwd<T, KIND>), dim3(std::min(LOSS_BLOCKS * 2, nb(g->topo.N, 256))), dim3(256), 0, s, g->d_ntouched,
+                     g->touched,
                      g->touched_ptr, g->inc_other, g->inc_dx, g->inc_dy, g->inc_w, x, y, gout, gx, gy);
 }
 

@@ -1081,8 +1081,10 @@ void extract_impl(tdp_graph g, int n, int k, int K, float slack_limit, hipStream
                        g->d_num_paths);
   } else if (sizeof(T) == 4 && g->key_bits32 + slot_bits <= 64) {
     const OrderBuf ob{g->sort_k0, g->sort_k1, g->order_hist, g->order_total, g->order_flags};
-    hipLaunchKernelGGL(k_rank, dim3((int)std::min<long long>(1024, (most + 63) / 64)), dim3(1024), 0, s, tp, k, slot_bits,
-                       g->d_nsel, g->sel_list, g->inst_selb, (const float *)g->slot_key, ob.w0);
+    // (no more workgroups than it can have slots for: with more slots they leave)
+    const long long ranked = std::min(most, (long long)tp.num_inst * RANK_MOST);
+    hipLaunchKernelGGL(k_rank, dim3((int)std::min<long long>(1024, (ranked + 63) / 64)), dim3(1024), 0, s, tp, k,
+                       slot_bits, g->d_nsel, g->sel_list, g->inst_selb, (const float *)g->slot_key, ob.w0);
     hipLaunchKernelGGL(k_order, dim3((int)std::min<long long>(ORDER_GROUPS, (most + ORDER_RUN - 1) / ORDER_RUN)),
                        dim3(1024), 0, s, tp, k, K, g->key_bits32, slot_bits, g->d_nsel, g->sel_list, g->inst_selb,
                        (const float *)g->slot_key, g->slot_len, ob, g->d_nslots, g->out_slot, g->slot_out, g->path_ptr,
@@ -1097,7 +1099,8 @@ void extract_impl(tdp_graph g, int n, int k, int K, float slack_limit, hipStream
   prof_end(g, TDP_STAGE_ORDER, s);
   // walk
   prof_begin(g, TDP_STAGE_WALK, s);
-  hipLaunchKernelGGL(k_walk<T>, dim3(nb(g->max_out, WALK_PATHS)), dim3(4 * WALK_PATHS), 0, s, tp, k, g->d_num_paths, g->out_slot,
+  hipLaunchKernelGGL(k_walk<T>, dim3(nb(g->max_out, WALK_PATHS)), dim3(4 * WALK_PATHS), 0, s, tp, k, g->d_num_paths,
+                     g->out_slot,
                      g->sel_list, g->slot_dev, g->slot_par, (const T *)g->slot_key, g->node, node_words<T>(g->side_k),
                      g->path_ptr, g->path_pins, g->path_int, g->path_ep, g->path_epi, g->path_rank,
                      (T *)g->path_slack, g->d_err, g->pin_cap);

@@ -1126,7 +1126,7 @@ void netpass_impl(tdp_graph g, const float *x, const float *y, hipStream_t s) {
 // the per-level launches; so do required times where a net is wider than a
 // chunk.  The grids win at every size measured (forward / backward us: 2k
 // cells, k = 10, 48 / 28 against 81 / 58; 200k 152 / 99 against 268 / 199; 2M,
-// k = 8, 465 / 346 against 682 / 557): no kernel boundary per level, static data
+// k = 8, 457 / 277 against 682 / 557): no kernel boundary per level, static data
 // loaded ahead, and lists off the arrivals' way.
 static bool flow_forward(const tdp_graph_s *g) {
   return g->sweep_mode == 1 || g->sweep_mode == 2 || (g->sweep_mode == 4 && g->fw_flow_ok);
