@@ -10,8 +10,8 @@
 //   existing pair: w = w  + w1 * (sum of slack/WNS)
 // where "first" is the smallest output index.  The sums are accumulated as
 // 2^-32 fixed point in 64-bit integer atomics, so the result is independent of
-// thread timing; a second pass, run by the first occurrence, applies the
-// update and clears the accumulators.
+// thread timing; a second pass over P's members applies the update and clears
+// the accumulators.
 //
 // The loss uses a compact pair list (ascending sink id) and, for the gradient,
 // a per-cell incidence list in a fixed order so that every cell sums its terms

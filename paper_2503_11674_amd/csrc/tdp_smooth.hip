@@ -174,9 +174,16 @@ __global__ void __launch_bounds__(256) k_st_bwd(Topo tp, int ch0, int ch1, const
 // The whole backward sweep on a resident grid, in reverse level order (no net
 // wider than a chunk): 147 us at 1M cells against 385 with a launch per level,
 // which also gathered the arc, both arrivals and the exponential of each share.
-template <typename T>
+// STAR: the pins' gradients under the star models as well, after the driver's
+// adjoint is out: the waves wait for most of a level's time, and part of the
+// gathers and the scatter fits in it (208 us at 1M cells against 147 + 82 in
+// two launches; 46 against 44 + 6 at 50,000).  Otherwise the sinks' adjoints go
+// to adj_nm for the spanning trees' launch.
+template <typename T, bool STAR>
 __global__ void __launch_bounds__(256) k_st_bwd_flow(Topo tp, const T *__restrict__ sa, T *adj,
-                                                      T *__restrict__ adj_nm, int32_t *__restrict__ err, int limit) {
+                                                      T *__restrict__ adj_nm, const float2 *__restrict__ xy,
+                                                      NetModel<T> nm, V2<T> *__restrict__ gp,
+                                                      int32_t *__restrict__ err, int limit) {
   using RW = typename ReqWord<T>::type;
   RW *words = reinterpret_cast<RW *>(adj);
   const int lane = wave_lane(), wpb = blockDim.x >> 6;
@@ -184,7 +191,7 @@ __global__ void __launch_bounds__(256) k_st_bwd_flow(Topo tp, const T *__restric
   int q = blockIdx.x * wpb + (threadIdx.x >> 6);
   int4 nrec = q < nch ? tp.nm_rec[(nch - 1 - q) * CHUNK + lane] : make_int4(-1, -1, -1, 0);
   for (; q < nch; q += W) {
-    const int chunk = nch - 1 - q;
+    const int k = (nch - 1 - q) * CHUNK + lane;
     const int4 rec = nrec;
     if (q + W < nch) nrec = tp.nm_rec[(nch - 1 - q - W) * CHUNK + lane];
     const int p = rec.x, vo = rec.z;
@@ -192,11 +199,32 @@ __global__ void __launch_bounds__(256) k_st_bwd_flow(Topo tp, const T *__restric
     const bool sink = p >= 0 && lane != head, comb_in = sink && vo >= 0;
     // a combinational input's share, an endpoint's seed
     const T share = sink ? (comb_in ? sa : adj)[p] : (T)0;
+    float2 pos = make_float2(0.f, 0.f), off = pos;
+    if constexpr (STAR) {
+      if (rec.y >= 0) pos = xy[rec.y];
+      off = make_float2(tp.nm_ox[k], tp.nm_oy[k]);
+    }
     const RW w = load_or_wait<true>(words, comb_in ? vo : 0, comb_in, (RW)~(RW)0, err, limit);
     const T mine = comb_in ? ReqWord<T>::value(w) * share : share;
     const T a = seg_sum(mine, lane, head, tail);
     if (p >= 0 && lane == head) pub_st(words + p, pub_bits<T>(a));
-    if (sink) adj_nm[chunk * CHUNK + lane] = mine;
+    if constexpr (STAR) {
+      // (driver - sink) per axis, a port's position as the base (see the net pass)
+      const bool port = rec.y < 0;
+      const T cx = port ? (T)off.x : (T)pos.x, cy = port ? (T)off.y : (T)pos.y;
+      const T ox = port ? (T)0 : (T)off.x, oy = port ? (T)0 : (T)off.y;
+      const T cxd = __shfl(cx, head, 64), cyd = __shfl(cy, head, 64);
+      const T oxd = __shfl(ox, head, 64), oyd = __shfl(oy, head, 64);
+      const T dx = (cxd - cx) + (oxd - ox), dy = (cyd - cy) + (oyd - oy);
+      const T len = sink ? fabs(dx) + fabs(dy) : (T)0;
+      const T gl =
+          sink ? mine * nm.slope(len, nm.elmore ? (T)tp.type_cap[(rec.w >> 16) & 255] : (T)0) : (T)0;
+      const T ex = gl * sgn(dx), ey = gl * sgn(dy);
+      const T sx = seg_sum(ex, lane, head, tail), sy = seg_sum(ey, lane, head, tail);
+      if (p >= 0) gp[p] = sink ? v2<T>(-ex, -ey) : v2<T>(sx, sy);
+    } else {
+      if (sink) adj_nm[k] = mine;
+    }
   }
   if (lane == 0 && pub_ld(reinterpret_cast<const uint32_t *>(err)) != 0) atomicOr(err - ST_ERR, 2);
 }
@@ -312,12 +340,19 @@ template <typename T>
 void stns_bwd_impl(tdp_graph g, const double *gout, float *gx, float *gy, hipStream_t s) {
   const Topo &tp = g->topo;
   prof_begin(g, TDP_STAGE_STNS, s);
-  if (g->sweep_mode != 0 && g->bw_flow_ok) {
-    const int w = g->flow_waves;
-    hipLaunchKernelGGL(k_st_bwd_flow<T>,
-                       dim3(st_blocks(g, reinterpret_cast<const void *>(&k_st_bwd_flow<T>), 1, tp.n_nm_chunks)),
-                       dim3(64 * w), 0, s, tp, (const T *)g->st_at, (T *)g->st_adj, (T *)g->st_adj_nm,
-                       g->d_err + ST_ERR, g->spin_limit);
+  const bool flow = g->sweep_mode != 0 && g->bw_flow_ok, star = g->lut.net_model != 2;
+  if (flow) {
+    const void *const kern = star ? reinterpret_cast<const void *>(&k_st_bwd_flow<T, true>)
+                                  : reinterpret_cast<const void *>(&k_st_bwd_flow<T, false>);
+    const dim3 grid(st_blocks(g, kern, 1, tp.n_nm_chunks)), block(64 * g->flow_waves);
+    if (star)
+      hipLaunchKernelGGL((k_st_bwd_flow<T, true>), grid, block, 0, s, tp, (const T *)g->st_at, (T *)g->st_adj,
+                         (T *)nullptr, g->xy_st, net_model<T>(g), (V2<T> *)g->st_gp, g->d_err + ST_ERR,
+                         g->spin_limit);
+    else
+      hipLaunchKernelGGL((k_st_bwd_flow<T, false>), grid, block, 0, s, tp, (const T *)g->st_at, (T *)g->st_adj,
+                         (T *)g->st_adj_nm, g->xy_st, net_model<T>(g), (V2<T> *)nullptr, g->d_err + ST_ERR,
+                         g->spin_limit);
   } else {
     for (int l = tp.D; l >= 0; --l) {
       const int ch0 = g->lv.nm_lvl[l], ch1 = g->lv.nm_lvl[l + 1];
@@ -330,7 +365,9 @@ void stns_bwd_impl(tdp_graph g, const double *gout, float *gx, float *gy, hipStr
                            (T *)g->st_adj);
     }
   }
-  st_net_grad_impl<T>(g, g->st_x, g->st_y, (const T *)g->st_adj, (const T *)g->st_adj_nm, s);
+  // (no net wider than a chunk where the sweep was a grid)
+  if (!(flow && star))
+    st_net_grad_impl<T>(g, g->st_x, g->st_y, (const T *)g->st_adj, (const T *)g->st_adj_nm, s);
   hipLaunchKernelGGL(k_st_grad<T>, dim3(nb(tp.N, 256)), dim3(256), 0, s, tp, (const V2<T> *)g->st_gp, gout,
                      gx, gy);
   prof_end(g, TDP_STAGE_STNS, s);
