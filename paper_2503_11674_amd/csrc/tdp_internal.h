@@ -291,7 +291,7 @@ struct tdp_graph_s {
   void *ep_slack = nullptr;      // [E]
   // dataflow sweeps: published words polled by consumers
   uint64_t *flow_w = nullptr;    // [M] {arrival, transition} of a driver (double: two words); all ones = not yet
-  uint64_t *flow_a = nullptr;    // [A] {arrival through an input's arc, tag}, with deviation lists
+  uint64_t *flow_a = nullptr;    // [A] {arrival through an input's arc, number of its pass}, with deviation lists
   int2 *list_turn = nullptr;     // [n_turns] {first cell, cells} of a list wave's turns, level by level
   int32_t n_turns = 0;
   void *flow_r = nullptr;        // [M] required time of a driver (its bits, 4 or 8 bytes); all ones = not yet (PULL)

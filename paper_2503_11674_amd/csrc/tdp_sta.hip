@@ -627,6 +627,16 @@ __global__ void k_backward_big(Topo tp, int i0, int i1, const T *__restrict__ dn
 // time of the slower of the two (200k cells, k = 10: 517 us against 152).
 // Both kinds wait only on lower-numbered chunks or cells and take theirs in
 // increasing order, so the lowest one not yet done can always run.
+//
+// An arrival through an arc, as the arrival waves publish it for the list
+// waves, with the whole number of its pass: passes by level do not write these
+// words, so any number of passes may lie between two that do.
+__device__ __forceinline__ uint64_t pack_arc(float a, uint32_t pass) {
+  return (uint64_t)__float_as_uint(a) | (uint64_t)pass << 32;
+}
+__device__ __forceinline__ uint32_t arc_pass(uint64_t w) { return (uint32_t)(w >> 32); }
+__device__ __forceinline__ float arc_arrival(uint64_t w) { return __uint_as_float((uint32_t)w); }
+
 // Words idx * N .. idx * N + N - 1 of every lane that wants them.  If some are
 // not out yet, one lane first polls the last word of the highest-numbered
 // missing driver (likely to be published last), so that a waiting wave polls
@@ -667,9 +677,10 @@ __device__ __forceinline__ void flow_arrivals(const Topo &tp, const LutView &L, 
                                               const T *__restrict__ load, const T *__restrict__ dnet,
                                               T *__restrict__ at, T *__restrict__ slew, T *__restrict__ darc,
                                               int32_t *__restrict__ crit, uint64_t *__restrict__ node, int words,
-                                              uint64_t *__restrict__ fa, uint64_t *__restrict__ fw, uint32_t tag,
+                                              uint64_t *__restrict__ fa, uint64_t *__restrict__ fw, uint32_t pass,
                                               int32_t *__restrict__ err, int limit) {
   constexpr int N = sizeof(T) / 4;  // words of a driver's {arrival, transition}
+  const uint32_t tag = pass & 3u;
   const int lane = wave_lane();
   const int nch = tp.n_fw_chunks;
   int chunk = w0;
@@ -735,7 +746,7 @@ __device__ __forceinline__ void flow_arrivals(const Topo &tp, const LutView &L, 
     const uint64_t h0 = pack_ids(__shfl(t, argl & 63, 64), __shfl(s, argl & 63, 64), tag);
     const uint64_t h1 = pack_ids(__shfl(ex.x, argl & 63, 64), __shfl(ex.y, argl & 63, 64), tag);
     if constexpr (N == 1) {
-      if (fa && valid) pub_st(&fa[t], pack_dev(a, 0, tag));
+      if (fa && valid) pub_st(&fa[t], pack_arc(a, pass));
     }
     if (is_head) {
       pub_st(node + (size_t)c * words, h0);
@@ -757,14 +768,15 @@ __device__ __forceinline__ void flow_arrivals(const Topo &tp, const LutView &L, 
 template <typename T, int KM>
 __device__ __forceinline__ void flow_lists(const Topo &tp, const int2 *__restrict__ turn, int turns, int w0, int W,
                                            uint32_t *__restrict__ cdep,
-                                           uint64_t *__restrict__ node, const uint64_t *__restrict__ fa, uint32_t tag,
+                                           uint64_t *__restrict__ node, const uint64_t *__restrict__ fa, uint32_t pass,
                                            int32_t *__restrict__ err, int limit) {
   static_assert(KM == 1 || sizeof(T) == 4, "double-precision lists are not published");
   constexpr int LG = list_lanes(KM), NG = 64 / LG, NW = node_words<T>(KM);
+  const uint32_t tag = pass & 3u;
   const int lane = wave_lane(), j = lane & (LG - 1), base = lane & ~(LG - 1), g = lane / LG;
   const unsigned long long group = ((1ull << LG) - 1) << base;
   const uint64_t none = j & 1 ? pack_ids(0, 0, tag) : pack_ids(-1, -1, tag);
-  const uint64_t pad = pack_dev(__builtin_huge_valf(), -1, tag);
+  const uint64_t pad = pack_dev(__builtin_huge_valf(), -1, tag), no_arc = pack_arc(0.f, pass);
   // (spare groups repeat the turn's last cell and store nothing)
   auto cell = [&](int2 u) { return u.x + min(g, u.y - 1); };
   int q = w0;
@@ -805,8 +817,8 @@ __device__ __forceinline__ void flow_lists(const Topo &tp, const int2 *__restric
     // turn's last cell, then all missing words are loaded together
     uint64_t ow = j < 2 ? pub_ld(rec + j) : none;
     const bool own_a = KM > 1 && j < n;
-    uint64_t aw = own_a ? pub_ld(fa + t0 + j) : pad;
-    if (__ballot(tag_lo(ow) != tag || tag_hi(aw) != tag)) {
+    uint64_t aw = own_a ? pub_ld(fa + t0 + j) : no_arc;
+    if (__ballot(tag_lo(ow) != tag || arc_pass(aw) != pass)) {
       const uint64_t *last = node + (size_t)last_c * NW + 1;
       uint64_t lastw = lane == 0 ? pub_ld(last) : none;
       while (again(tag_lo(lastw) != tag)) {
@@ -814,8 +826,8 @@ __device__ __forceinline__ void flow_lists(const Topo &tp, const int2 *__restric
       }
       do {
         if (tag_lo(ow) != tag) ow = pub_ld(rec + j);
-        if (tag_hi(aw) != tag) aw = pub_ld(fa + t0 + j);
-      } while (again(tag_lo(ow) != tag || tag_hi(aw) != tag));
+        if (arc_pass(aw) != pass) aw = pub_ld(fa + t0 + j);
+      } while (again(tag_lo(ow) != tag || arc_pass(aw) != pass));
     }
     const int pred = __shfl((int)(uint32_t)(ow >> 32), base, 64);
     const bool chain = pred >= tp.n_start;
@@ -836,7 +848,7 @@ __device__ __forceinline__ void flow_lists(const Topo &tp, const int2 *__restric
       const int nmax = wave_max_int(n);
       int shift = 0, rank;
       if (nmax <= LG) {
-        const float a = unpack_dev(aw).cost;
+        const float a = arc_arrival(aw);
         const float best = __shfl(a, base + arg, 64);
         const float d = j < n && j != arg && best - a < __builtin_huge_valf() ? best - a : __builtin_huge_valf();
         list_ranks(e.cost, d, j, nmax, group, [&](int i) { return __shfl(d, base + i, 64); }, shift, rank);
@@ -844,8 +856,8 @@ __device__ __forceinline__ void flow_lists(const Topo &tp, const int2 *__restric
       } else {  // a cell with more inputs than lanes: its arrivals one by one
         auto arc = [&](int i) {
           uint64_t w = pub_ld(fa + t0 + i);
-          while (again(tag_hi(w) != tag)) w = pub_ld(fa + t0 + i);
-          return unpack_dev(w).cost;
+          while (again(arc_pass(w) != pass)) w = pub_ld(fa + t0 + i);
+          return arc_arrival(w);
         };
         const float best = arc(arg);
         auto dev = [&](int i) {
@@ -875,13 +887,13 @@ __global__ void __launch_bounds__(256) k_forward_flow(Topo tp, LutView L, int n_
                                                        int32_t *__restrict__ err, int limit) {
   extern __shared__ float4 s_lut4[];
   const int wpb = blockDim.x >> 6, wave = threadIdx.x >> 6;
-  const uint32_t tag = *d_tag & 3u;
+  const uint32_t pass = *d_tag;
   if ((int)blockIdx.x < n_arr)
     flow_arrivals<T>(tp, L, (float *)s_lut4, blockIdx.x * wpb + wave, n_arr * wpb, load, dnet, at, slew, darc, crit,
-                     node, node_words<T>(KM), KM > 1 ? fa : nullptr, fw, tag, err, limit);
+                     node, node_words<T>(KM), KM > 1 ? fa : nullptr, fw, pass, err, limit);
   else
     flow_lists<T, KM>(tp, turn, turns, (blockIdx.x - n_arr) * wpb + wave, ((int)gridDim.x - n_arr) * wpb, cdep, node,
-                      fa, tag, err, limit);
+                      fa, pass, err, limit);
 }
 
 // Backward: chunks from the last.  PULL: a sink lane loads the required time of

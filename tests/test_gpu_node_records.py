@@ -164,3 +164,64 @@ def test_replayed_update(library):
             g.sta_update(*_xy(nl, 50 + s))
             torch.cuda.synchronize()
     g.close()
+
+
+@pytest.mark.parametrize("modes", [(0, 0, 0, 1), (3, 3, 3, 1, 3, 0, 3, 1), (1, 0, 0, 0, 1, 3, 3, 3, 1),
+                                   (1, 1) + 7 * (0,) + (1, 2, 0, 0, 0, 1)])
+@pytest.mark.parametrize("sets", [3, 5])
+def test_grid_passes_after_passes_by_level(library, modes, sets):
+    """Three and seven passes by level between two grid passes, and before a
+    new graph's first: the words that only grid passes write are then four or
+    eight passes old, and of other positions."""
+    from paper_2503_11674_amd import tdp
+    nl = _design(library)
+    k = 10
+    fresh = []
+    for s in range(sets):
+        g = tdp.TimingGraph(nl, library, max_paths=4000, max_k=k)
+        g.set_tuning(sweep_mode=0)
+        g.sta_update(*_xy(nl, 31 + s))
+        fresh.append(_result(g, k))
+        g.close()
+    g = tdp.TimingGraph(nl, library, max_paths=4000, max_k=k)
+    for i, mode in enumerate(modes):
+        g.set_tuning(spin_log2=4 if mode == 2 else 20, sweep_mode=mode)
+        g.sta_update(*_xy(nl, 31 + i % sets))
+        if mode != 2:
+            _same(_result(g, k), fresh[i % sets])
+    g.close()
+
+
+def test_replays_between_passes_by_level(library):
+    """A captured grid pass replayed after every three passes by level."""
+    from paper_2503_11674_amd import tdp
+    nl = _design(library)
+    k = 10
+    g = tdp.TimingGraph(nl, library, max_paths=4000, max_k=k)
+    x, y = _xy(nl)
+    g.sta_update(x, y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        g.sta_update(x, y)
+    for r in range(5):
+        g.set_tuning(sweep_mode=0)
+        for s in range(3):
+            g.sta_update(*_xy(nl, 60 + 3 * r + s))
+        want = _result(g, k)
+        _same(want, _fresh(nl, library, 62 + 3 * r, k))
+        for a, b in zip((x, y), _xy(nl, 80 + r)):
+            a.copy_(b)
+        graph.replay()
+        _same(_result(g, k), _fresh(nl, library, 80 + r, k))
+    g.close()
+
+
+def _fresh(nl, library, seed, k):
+    from paper_2503_11674_amd import tdp
+    g = tdp.TimingGraph(nl, library, max_paths=4000, max_k=k)
+    g.set_tuning(sweep_mode=0)
+    g.sta_update(*_xy(nl, seed))
+    out = _result(g, k)
+    g.close()
+    return out
