@@ -204,7 +204,7 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
        dalloc(g, g->fw_a, T.A, es) &&
        dalloc(g, g->darc, T.A, es) && dalloc(g, g->crit, T.n_comb) &&
        dalloc(g, g->node, (size_t)T.n_comb * (es == 8 ? node_words<double>(g->side_k) : node_words<float>(g->side_k))) &&
-       dalloc(g, g->cdep, T.M) && dalloc(g, g->d_tag, 2) && dalloc(g, g->ep_slack, T.E, es) &&
+       dalloc(g, g->cdep, T.M) && dalloc(g, g->d_tag, 3) && dalloc(g, g->ep_slack, T.E, es) &&
        dalloc(g, g->red_ep, (size_t)3 * T.num_inst * g->ep_chunks) && dalloc(g, g->red_loss, 4096) &&
        dalloc(g, g->red_p2p, 1024) &&
        dalloc(g, g->red_wa, 4096) && dalloc(g, g->summary, (size_t)4 * T.num_inst) &&

@@ -287,7 +287,9 @@ struct tdp_graph_s {
   // node records and chain depths, as tagged words (see NodeRec below)
   uint64_t *node = nullptr;      // [n_comb][node_words]
   uint32_t *cdep = nullptr;      // [M] combinational cells on the critical chain
-  uint32_t *d_tag = nullptr;     // [2] arrival passes so far; the last dataflow sweep gave up
+  // [3] arrival passes so far; the last dataflow sweep gave up; drv_as
+  // (combinational drivers) and fw_a predate the last forward sweep
+  uint32_t *d_tag = nullptr;
   void *ep_slack = nullptr;      // [E]
   // dataflow sweeps: published words polled by consumers
   uint64_t *flow_w = nullptr;    // [M] {arrival, transition} of a driver (double: two words); all ones = not yet
@@ -304,7 +306,6 @@ struct tdp_graph_s {
   bool flow_ok = false;          // the graph can use sweep modes 1-3
   int32_t pos_gen = 0;           // arrival passes so far; d_err[1] == pos_gen: a position was not finite
   bool flow_r_clear = false;     // flow_r holds no published word (the last net pass reset it)
-  bool drv_as_stale = false;     // drv_as (combinational drivers) and fw_a predate the last forward sweep
   double *red_ep = nullptr, *red_loss = nullptr, *red_p2p = nullptr, *red_wa = nullptr;
   double *summary = nullptr;     // [4 * num_inst]: wns, tns, n_fail, 0
   int32_t *d_ep_base = nullptr;

@@ -402,8 +402,9 @@ template Sorted<uint32_t> radix_sort<uint32_t>(uint32_t *, uint32_t *, uint32_t 
 // ------------------------------------------------------ packed positions
 __global__ void k_pack_xy(const float *__restrict__ x, const float *__restrict__ y, float2 *__restrict__ xy, int n,
                           int32_t *__restrict__ bad, int32_t gen, const int32_t *__restrict__ err,
-                          uint32_t *__restrict__ tag) {
+                          uint32_t *__restrict__ tag, uint32_t *__restrict__ note, uint32_t noted) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (note && i == 0) *note = noted;
   if (tag && i == 0) {  // a new arrival pass: its number, and whether the last sweep gave up (bit 1)
     tag[0] = tag[0] + 1;
     tag[1] = (*err & 2) != 0;
@@ -415,8 +416,10 @@ __global__ void k_pack_xy(const float *__restrict__ x, const float *__restrict__
   if (bad && !(__builtin_isfinite(a) && __builtin_isfinite(b))) *bad = gen;
 }
 void pack_xy(const float *x, const float *y, float2 *xy, int n, hipStream_t s, int32_t *bad, int32_t gen,
-             const int32_t *err, uint32_t *tag) {
-  if (n > 0) hipLaunchKernelGGL(k_pack_xy, dim3((n + 255) / 256), dim3(256), 0, s, x, y, xy, n, bad, gen, err, tag);
+             const int32_t *err, uint32_t *tag, uint32_t *note, uint32_t noted) {
+  if (n > 0)
+    hipLaunchKernelGGL(k_pack_xy, dim3((n + 255) / 256), dim3(256), 0, s, x, y, xy, n, bad, gen, err, tag, note,
+                       noted);
 }
 
 // ---------------------------------------------------------- small fills

@@ -1092,11 +1092,13 @@ static void forward_flow(tdp_graph g, hipStream_t s) {
 template <typename T>
 static void netpass_launch(tdp_graph g, const float *x, const float *y, const FlowInit &fl, bool sweep,
                            hipStream_t s) {
+  // (a forward grid publishes through its own words and leaves drv_as and fw_a as they are)
   const Topo &tp = g->topo;
   const NetModel<T> nm = net_model<T>(g);
   const bool tree = g->lut.net_model == 2;
   const T *tree_wl = tree ? (const T *)g->tree.wl : nullptr;
-  pack_xy(x, y, g->xy, tp.N, s, g->d_err + 1, ++g->pos_gen, g->d_err, sweep ? g->d_tag : nullptr);
+  pack_xy(x, y, g->xy, tp.N, s, g->d_err + 1, ++g->pos_gen, g->d_err, sweep ? g->d_tag : nullptr,
+          sweep ? g->d_tag + 2 : nullptr, fl.w ? 1u : 0u);
   const auto k_np = tree ? k_netpass<T, true> : k_netpass<T, false>;
   hipLaunchKernelGGL(k_np, dim3(nblk(tp.n_nm_chunks, 4) + fl.reset_blocks),
                      dim3(256), 0, s, tp, g->lut, g->xy, nm,
@@ -1179,7 +1181,6 @@ void sta_arrivals_impl(tdp_graph g, const float *x, const float *y, bool require
   g->flow_r_clear = bflow;
   prof_end(g, TDP_STAGE_NETPASS, s);
   prof_begin(g, TDP_STAGE_FORWARD, s);
-  g->drv_as_stale = flow;  // the dataflow sweep publishes through its own words
   if (flow) {
     forward_flow<T>(g, s);
   } else {
@@ -1208,14 +1209,16 @@ __global__ void k_inc_maps(Topo tp, int32_t *__restrict__ snk_chunk, int32_t *__
 
 // {arrival, transition} pairs of the combinational drivers from the two
 // arrays, and each input's arrival through its arc (the same sum the
-// arrival job forms), after a forward sweep that kept neither
+// arrival job forms), where the last forward sweep kept neither: the device
+// knows (`stale`), since a captured pass may have run since the host last looked
 template <typename T>
-__global__ void k_pack_as(Topo tp, const T *__restrict__ at, const T *__restrict__ slew, const T *__restrict__ darc,
-                          V2<T> *__restrict__ as, T *__restrict__ fw_a) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int v = tp.n_start + (int)i;
-  if (v < tp.M) as[v] = v2<T>(at[v], slew[v]);
-  if (i < tp.A) fw_a[i] = at[tp.M + i] + darc[i];
+__global__ void k_pack_as(Topo tp, const uint32_t *__restrict__ stale, const T *__restrict__ at,
+                          const T *__restrict__ slew, const T *__restrict__ darc, V2<T> *__restrict__ as,
+                          T *__restrict__ fw_a) {
+  if (!*stale) return;
+  const int nth = gridDim.x * blockDim.x, i0 = blockIdx.x * blockDim.x + threadIdx.x;
+  for (int i = i0; i < tp.n_comb; i += nth) as[tp.n_start + i] = v2<T>(at[tp.n_start + i], slew[tp.n_start + i]);
+  for (int i = i0; i < tp.A; i += nth) fw_a[i] = at[tp.M + i] + darc[i];
 }
 
 // the net chunks that hold a moved cell's pins: its output's net and the nets
@@ -1255,16 +1258,15 @@ void sta_arrivals_incremental_impl(tdp_graph g, const float *x, const float *y, 
   inc.snk_chunk = g->inc_snk_chunk;
   inc.nm = g->inc_nm;
   prof_begin(g, TDP_STAGE_NETPASS, s);
-  if (g->drv_as_stale && tp.n_comb > 0)
-    hipLaunchKernelGGL(k_pack_as<T>, dim3(nblk(std::max(tp.n_comb, tp.A), 256)),
-                       dim3(256), 0, s, tp, (const T *)g->at, (const T *)g->slew, (const T *)g->darc,
+  if (g->fw_flow_ok && tp.n_comb > 0)
+    hipLaunchKernelGGL(k_pack_as<T>, dim3(std::min(2048, nblk(std::max(tp.n_comb, tp.A), 256))),
+                       dim3(256), 0, s, tp, g->d_tag + 2, (const T *)g->at, (const T *)g->slew, (const T *)g->darc,
                        (V2<T> *)g->drv_as, (T *)g->fw_a);
-  g->drv_as_stale = false;
   fill_i32(g->d_err, 1, 0, s);
   if (n > 0)
     hipLaunchKernelGGL(k_inc_mark, dim3(nblk(n, 256)), dim3(256), 0, s, tp, cells, n, g->inc_drv_nm_chunk,
                        g->inc_nm, inc.epoch, g->d_err);
-  pack_xy(x, y, g->xy, tp.N, s, g->d_err + 1, ++g->pos_gen);
+  pack_xy(x, y, g->xy, tp.N, s, g->d_err + 1, ++g->pos_gen, nullptr, nullptr, g->d_tag + 2, 0u);
   // (every net fits a chunk here: graphs with wider nets take full updates)
   const auto k_npm = g->lut.net_model == 2 ? k_netpass_marked<T, true> : k_netpass_marked<T, false>;
   if (n > 0)

@@ -89,3 +89,44 @@ def test_incremental_equals_full(name, precision, moves, modes, library):
     assert e.value.status == 4
     gi.close()
     gf.close()
+
+
+def test_incremental_after_replayed_full_updates(library):
+    """A captured full update replayed before every incremental one, and a
+    captured incremental one replayed after eager full updates."""
+    tdp = _tdp()
+    cfg = netgen.NetlistConfig("i", 3000, ff_frac=0.15, depth=12, fanin_lo=1, fanin_hi=4, fanout_cap=12, die=800.0,
+                               seed=4)
+    nl = with_clock(netgen.make_netlist(cfg), library, 0.4)
+    k, K = 4, 2000
+    dev = torch.device("cuda", 0)
+    movable = np.nonzero(np.asarray(nl["cell_fixed"]) == 0)[0]
+    rng = np.random.default_rng(3)
+    g = tdp.TimingGraph(nl, library, max_paths=K, max_k=k)
+    gf = tdp.TimingGraph(nl, library, max_paths=K, max_k=k)
+    x, y = [torch.tensor(nl[a], device=dev) for a in ("x", "y")]
+    moved = torch.tensor(rng.choice(movable, 3, replace=False), dtype=torch.int32, device=dev)
+    g.sta_update(x, y)
+    g.sta_update_arrivals_incremental(x, y, moved)
+    torch.cuda.synchronize()
+    full, inc = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(full):
+        g.sta_update(x, y)
+    with torch.cuda.graph(inc):
+        g.sta_update_arrivals_incremental(x, y, moved)
+    for rnd in range(6):
+        for a, b in zip((x, y), netgen.jitter_positions(nl, 30.0, 100 + rnd)):
+            a.copy_(torch.tensor(b))
+        if rnd % 2:
+            g.sta_update(x, y)
+        else:
+            full.replay()
+        x[moved.long()] += 15.0
+        if rnd % 3 == 2 or rnd % 2:
+            inc.replay()
+        else:
+            g.sta_update_arrivals_incremental(x, y, moved)
+        gf.sta_update(x, y)
+        _same(_state(g, k, K), _state(gf, k, K))
+    g.close()
+    gf.close()
