@@ -225,7 +225,10 @@ tdp_status tdp_sta_update_arrivals_incremental(tdp_graph, const float *d_x, cons
  * violated endpoints of the last update.  Synchronises the stream.  For a
  * batched graph this is the union's; see tdp_batch_summary.  TDP_E_INVALID
  * when a cell position given to the last arrival pass was NaN or infinite
- * (the timing results of that pass are then meaningless). */
+ * (the timing results of that pass are then meaningless); in a batched graph
+ * such a position spoils its own instance only, and tdp_batch_summary gives the
+ * others' values.  Both return TDP_E_DEVICE after a sweep that gave up waiting
+ * (tdp_set_tuning). */
 tdp_status tdp_sta_summary(tdp_graph, double *wns, double *tns, int32_t *n_fail, hipStream_t);
 tdp_status tdp_batch_summary(tdp_graph, double *wns, double *tns, int32_t *n_fail, hipStream_t);
 

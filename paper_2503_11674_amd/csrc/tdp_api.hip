@@ -435,9 +435,13 @@ tdp_status tdp_batch_summary(tdp_graph g, double *wns, double *tns, int32_t *n_f
   if (!g->updated) return fail(g, TDP_E_STATE, "no timing update yet");
   const int ni = g->topo.num_inst;
   std::vector<double> h(4 * ni);
+  int32_t err = 0;
   if (hipStreamSynchronize(s) != hipSuccess ||
-      hipMemcpy(h.data(), g->summary, sizeof(double) * 4 * ni, hipMemcpyDeviceToHost) != hipSuccess)
+      hipMemcpy(h.data(), g->summary, sizeof(double) * 4 * ni, hipMemcpyDeviceToHost) != hipSuccess ||
+      hipMemcpy(&err, g->d_err, 4, hipMemcpyDeviceToHost) != hipSuccess)
     return fail(g, TDP_E_DEVICE, "summary copy failed");
+  // (a position that is not finite spoils its own instance only: the others' values stand)
+  if (err & 2) return fail(g, TDP_E_DEVICE, "a dataflow sweep gave up waiting (results are invalid)");
   for (int i = 0; i < ni; ++i) {
     if (wns) wns[i] = h[4 * i];
     if (tns) tns[i] = h[4 * i + 1];
