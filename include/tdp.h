@@ -397,7 +397,10 @@ tdp_status tdp_pair_loss_bwd(tdp_graph, int32_t kind, const float *d_x, const fl
  * gamma_ps, value = -gamma * sum over endpoints of softplus(-slack/gamma).
  * fwd overwrites *d_val; bwd (same positions as the last fwd) adds
  * (*d_gout) * gradient into d_gx/d_gy.  d_val and d_gout are single device
- * doubles (d_gout NULL: 1). */
+ * doubles (d_gout NULL: 1).  After a sweep that gave up waiting (see
+ * tdp_set_tuning) the value, and all gradients until the next fwd, are NaN,
+ * and the next tdp_sta_summary, tdp_batch_summary or tdp_paths_count returns
+ * TDP_E_DEVICE, once, whatever updates lie between. */
 tdp_status tdp_stns_fwd(tdp_graph, const float *d_x, const float *d_y, float gamma_ps, double *d_val,
                         hipStream_t);
 tdp_status tdp_stns_bwd(tdp_graph, const double *d_gout, float *d_gx, float *d_gy, hipStream_t);

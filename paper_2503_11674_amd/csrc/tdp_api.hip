@@ -45,6 +45,20 @@ tdp_status fail(tdp_graph g, tdp_status st, const std::string &msg) {
   return st;
 }
 
+// the device's error words, on the host; the stream has been waited for
+bool read_errors(tdp_graph g, int32_t (&err)[4]) {
+  return hipMemcpy(err, g->d_err, sizeof err, hipMemcpyDeviceToHost) == hipSuccess;
+}
+// sweeps that gave up: the timing sweeps' word holds until the next update, the
+// smoothed ones' until it is reported, here
+tdp_status check_sweeps(tdp_graph g, const int32_t (&err)[4]) {
+  if (err[0] & 2) return fail(g, TDP_E_DEVICE, "a dataflow sweep gave up waiting (results are invalid)");
+  if (!err[3]) return TDP_OK;
+  const int32_t none = 0;
+  hipMemcpy(g->d_err + 3, &none, sizeof none, hipMemcpyHostToDevice);
+  return fail(g, TDP_E_DEVICE, "a smoothed-TNS sweep gave up waiting (its value or gradients are invalid)");
+}
+
 tdp_status check_launch(tdp_graph g, const char *what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(g, TDP_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
@@ -409,15 +423,15 @@ tdp_status tdp_sta_summary(tdp_graph g, double *wns, double *tns, int32_t *n_fai
   if (!g->updated) return fail(g, TDP_E_STATE, "no timing update yet");
   const int ni = g->topo.num_inst;
   std::vector<double> h(4 * ni);
-  int32_t errs[2] = {0, 0};
+  int32_t err[4];
   if (hipStreamSynchronize(s) != hipSuccess ||
       hipMemcpy(h.data(), g->summary, sizeof(double) * 4 * ni, hipMemcpyDeviceToHost) != hipSuccess ||
-      hipMemcpy(errs, g->d_err, 8, hipMemcpyDeviceToHost) != hipSuccess)
+      !read_errors(g, err))
     return fail(g, TDP_E_DEVICE, "summary copy failed");
-  const int32_t err = errs[0];
-  if (errs[1] == g->pos_gen) return fail(g, TDP_E_INVALID, "a cell position of the last update is NaN or infinite");
-  if (err & 2) return fail(g, TDP_E_DEVICE, "a dataflow sweep gave up waiting (results are invalid)");
-  if (err & 4) return fail(g, TDP_E_DEVICE, "an incremental update was given a cell id outside [0, num_cells)");
+  if (err[1] == g->pos_gen) return fail(g, TDP_E_INVALID, "a cell position of the last update is NaN or infinite");
+  const tdp_status st = check_sweeps(g, err);
+  if (st != TDP_OK) return st;
+  if (err[0] & 4) return fail(g, TDP_E_DEVICE, "an incremental update was given a cell id outside [0, num_cells)");
   double w = 0, t = 0, n = 0;
   for (int i = 0; i < ni; ++i) {
     w = std::min(w, h[4 * i]);
@@ -435,13 +449,14 @@ tdp_status tdp_batch_summary(tdp_graph g, double *wns, double *tns, int32_t *n_f
   if (!g->updated) return fail(g, TDP_E_STATE, "no timing update yet");
   const int ni = g->topo.num_inst;
   std::vector<double> h(4 * ni);
-  int32_t err = 0;
+  int32_t err[4];
   if (hipStreamSynchronize(s) != hipSuccess ||
       hipMemcpy(h.data(), g->summary, sizeof(double) * 4 * ni, hipMemcpyDeviceToHost) != hipSuccess ||
-      hipMemcpy(&err, g->d_err, 4, hipMemcpyDeviceToHost) != hipSuccess)
+      !read_errors(g, err))
     return fail(g, TDP_E_DEVICE, "summary copy failed");
   // (a position that is not finite spoils its own instance only: the others' values stand)
-  if (err & 2) return fail(g, TDP_E_DEVICE, "a dataflow sweep gave up waiting (results are invalid)");
+  const tdp_status st = check_sweeps(g, err);
+  if (st != TDP_OK) return st;
   for (int i = 0; i < ni; ++i) {
     if (wns) wns[i] = h[4 * i];
     if (tns) tns[i] = h[4 * i + 1];
@@ -760,14 +775,14 @@ tdp_status tdp_report_timing_noalloc(tdp_graph g, int32_t K, float slack_limit, 
 tdp_status tdp_paths_count(tdp_graph g, int32_t *num_paths, int32_t *num_pins, hipStream_t s) {
   GUARD(g);
   if (!g->extracted) return fail(g, TDP_E_STATE, "no extraction yet");
-  int32_t n = 0, pins = 0, err = 0;
+  int32_t n = 0, pins = 0, err[4];
   if (hipStreamSynchronize(s) != hipSuccess ||
       hipMemcpy(&n, g->d_num_paths, 4, hipMemcpyDeviceToHost) != hipSuccess ||
-      hipMemcpy(&pins, g->path_ptr + n, 4, hipMemcpyDeviceToHost) != hipSuccess ||
-      hipMemcpy(&err, g->d_err, 4, hipMemcpyDeviceToHost) != hipSuccess)
+      hipMemcpy(&pins, g->path_ptr + n, 4, hipMemcpyDeviceToHost) != hipSuccess || !read_errors(g, err))
     return fail(g, TDP_E_DEVICE, "count copy failed");
-  if (err & 1) return fail(g, TDP_E_DEVICE, "internal: a path walk did not match its length");
-  if (err & 2) return fail(g, TDP_E_DEVICE, "a dataflow sweep gave up waiting (results are invalid)");
+  if (err[0] & 1) return fail(g, TDP_E_DEVICE, "internal: a path walk did not match its length");
+  const tdp_status st = check_sweeps(g, err);
+  if (st != TDP_OK) return st;
   if (num_paths) *num_paths = n;
   if (num_pins) *num_pins = pins;
   return TDP_OK;

@@ -271,8 +271,9 @@ struct tdp_graph_s {
   bool updated = false, extracted = false, pairs_built = false, stns_ready = false;
   std::vector<void *> allocs;  // every device allocation, freed at destroy
   std::vector<int32_t> h_snk_ext;  // host copy: external pin of each sink
-  // device words: internal consistency errors, the last pass with a position that
-  // was not finite, a smoothed sweep that gave up
+  // device words [4]: internal consistency errors, the last pass with a position
+  // that was not finite, a smoothed sweep that gave up (until the next forward
+  // one), the same until a call has reported it
   int32_t *d_err = nullptr;
   double *consts = nullptr;    // [4] device constants: {1, 0, 0, 0}
 

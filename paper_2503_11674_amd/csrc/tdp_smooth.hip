@@ -32,8 +32,17 @@ namespace tdp {
 
 static inline int nb(long long n, int b) { return n > 0 ? (int)((n + b - 1) / b) : 1; }
 
-// the smoothed sweeps' own error word, behind d_err's
+// the smoothed sweeps' own error words, behind d_err's: this forward pass's and
+// its backward passes', and one that stays set until a call has reported it (the
+// next update clears the timing sweeps' word, and no smoothed call waits for its
+// results)
 constexpr int ST_ERR = 2;
+__device__ __forceinline__ bool st_failed(const int32_t *err) {
+  return pub_ld(reinterpret_cast<const uint32_t *>(err)) != 0;
+}
+__device__ __forceinline__ void st_report(int32_t *err) {
+  if (st_failed(err)) pub_st(reinterpret_cast<uint32_t *>(err + 1), 1u);
+}
 
 template <typename T>
 __device__ __forceinline__ T sgn(T v) {
@@ -119,17 +128,19 @@ __global__ void __launch_bounds__(256) k_st_fwd_flow(Topo tp, T gam, const T *__
     if (valid && lane == head) pub_st(words + tp.n_start + rec.z, pub_bits<T>(c.out));
     if (valid) sa[tp.M + t] = c.share(gam);
   }
-  if (lane == 0 && pub_ld(reinterpret_cast<const uint32_t *>(err)) != 0) atomicOr(err - ST_ERR, 2);
+  if (lane == 0) st_report(err);
 }
 
-// endpoint values and adjoint seeds; the value summed by the last workgroup
+// endpoint values and adjoint seeds; the value summed by the last workgroup (not
+// a number after a sweep that gave up)
 template <typename T>
 __global__ void __launch_bounds__(256) k_st_end(Topo tp, const double *__restrict__ inst_req, T gam,
                                                  const T *__restrict__ dnl, const T *__restrict__ sa,
                                                  T *__restrict__ adj, double *__restrict__ part,
-                                                 uint32_t *__restrict__ ctr, double *__restrict__ val) {
+                                                 uint32_t *__restrict__ ctr, double *__restrict__ val,
+                                                 const int32_t *__restrict__ err) {
   __shared__ double sh[256];
-  double acc = 0.0;
+  double acc = *err ? __builtin_nan("") : 0.0;
   for (int f = blockIdx.x * blockDim.x + threadIdx.x; f < tp.E; f += gridDim.x * blockDim.x) {
     const int t = tp.A + f;
     const T a = sa[tp.snk_drv[t]] + dnl[t];
@@ -226,7 +237,7 @@ __global__ void __launch_bounds__(256) k_st_bwd_flow(Topo tp, const T *__restric
       if (sink) adj_nm[k] = mine;
     }
   }
-  if (lane == 0 && pub_ld(reinterpret_cast<const uint32_t *>(err)) != 0) atomicOr(err - ST_ERR, 2);
+  if (lane == 0) st_report(err);
 }
 
 // the same for nets wider than a chunk, one thread per net
@@ -252,10 +263,12 @@ __global__ void k_st_bwd_big(Topo tp, int i0, int i1, const T *__restrict__ sa, 
 }
 
 // gradient per cell: the sum of its pins' gradients (its output pin, then its
-// input pins), which the net kernels computed per pin
+// input pins), which the net kernels computed per pin (not numbers after a
+// sweep that gave up)
 template <typename T>
 __global__ void __launch_bounds__(256) k_st_grad(Topo tp, const V2<T> *__restrict__ gp, const double *__restrict__ gout,
-                                                  float *__restrict__ gx, float *__restrict__ gy) {
+                                                  float *__restrict__ gx, float *__restrict__ gy,
+                                                  const int32_t *__restrict__ err) {
   const int cell = blockIdx.x * blockDim.x + threadIdx.x;
   if (cell >= tp.N || tp.cell_fixed[cell]) return;
   const int ci = tp.cell_int[cell];
@@ -277,7 +290,7 @@ __global__ void __launch_bounds__(256) k_st_grad(Topo tp, const V2<T> *__restric
     ax += in.x;
     ay += in.y;
   }
-  const T go = (T)*gout;
+  const T go = *err ? (T)__builtin_nan("") : (T)*gout;
   gx[cell] += (float)(go * ax);
   gy[cell] += (float)(go * ay);
 }
@@ -328,7 +341,8 @@ void stns_fwd_impl(tdp_graph g, const float *x, const float *y, float gamma, dou
     }
   }
   hipLaunchKernelGGL(k_st_end<T>, dim3(std::min(128, nb(tp.E, 256))), dim3(256), 0, s, tp, g->d_inst_req, gam,
-                     (const T *)g->st_dnet, (const T *)g->st_at, (T *)g->st_adj, g->red_loss, g->look_ctr + 8, val);
+                     (const T *)g->st_dnet, (const T *)g->st_at, (T *)g->st_adj, g->red_loss, g->look_ctr + 8, val,
+                     g->d_err + ST_ERR);
   g->st_gamma = gamma;
   g->st_x = x;
   g->st_y = y;
@@ -369,7 +383,7 @@ void stns_bwd_impl(tdp_graph g, const double *gout, float *gx, float *gy, hipStr
   if (!(flow && star))
     st_net_grad_impl<T>(g, g->st_x, g->st_y, (const T *)g->st_adj, (const T *)g->st_adj_nm, s);
   hipLaunchKernelGGL(k_st_grad<T>, dim3(nb(tp.N, 256)), dim3(256), 0, s, tp, (const V2<T> *)g->st_gp, gout,
-                     gx, gy);
+                     gx, gy, g->d_err + ST_ERR);
   prof_end(g, TDP_STAGE_STNS, s);
 }
 

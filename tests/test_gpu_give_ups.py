@@ -46,3 +46,43 @@ def test_batch_summary_reports_a_sweep_that_gave_up(library):
     for a, b in zip(want, g.batch_summary()):
         assert np.array_equal(a, b)
     g.close()
+
+
+@pytest.mark.parametrize("model", [0, 1, 2])
+@pytest.mark.parametrize("part", ["forward", "backward"])
+def test_smoothed_sweeps_that_gave_up_are_reported(library, model, part):
+    """The value or the gradients are not numbers, and the next call that waits
+    for results says so once, though an update lies between."""
+    from paper_2503_11674_amd import tdp
+    nl = _design(library, 3000, 40)
+    g = tdp.TimingGraph(nl, dict(library, net_model=model), max_paths=100, max_k=1)
+    x, y = _xy(nl)
+    one = torch.ones((), dtype=torch.float64, device="cuda")
+
+    def bwd():
+        gx, gy = torch.zeros_like(x), torch.zeros_like(y)
+        g.stns_bwd(one, gx, gy)
+        return torch.stack((gx, gy))
+
+    g.sta_update(x, y)
+    want = g.summary()
+    value, grad = float(g.stns_fwd(x, y, 10.0)), bwd()
+    assert np.isfinite(value) and bool(torch.isfinite(grad).all())
+    fixed = torch.tensor(nl["cell_fixed"], device="cuda").bool()
+    for readers in ((g.summary, g.paths_count), (g.batch_summary, g.summary), (g.paths_count, g.summary)):
+        g.extract_paths(n=-1, k=1)
+        if part == "backward":
+            assert float(g.stns_fwd(x, y, 10.0)) == value
+        g.set_tuning(spin_log2=1)
+        if part == "forward":
+            assert np.isnan(float(g.stns_fwd(x, y, 10.0)))
+        assert bool(torch.isnan(bwd()[:, ~fixed]).all())
+        g.set_tuning(spin_log2=20)
+        g.sta_update(x, y)
+        g.extract_paths(n=-1, k=1)
+        _reports(tdp, readers[0])
+        readers[0]()
+        readers[1]()
+        assert g.summary() == want
+        assert float(g.stns_fwd(x, y, 10.0)) == value and torch.equal(bwd(), grad)
+    g.close()
