@@ -535,9 +535,10 @@ tdp_status tdp_profile_read(tdp_graph, double *ms, int32_t *calls);
  *  flow_per_cu: workgroups per compute unit of the resident grids (1..4,
  *    capped by the kernel's occupancy; 0 keeps; default 1): the forward grid
  *    takes that many for the arrivals and three times as many for the
- *    deviation lists, the backward grid twice as many.  The grids must
- *    fit on the GPU beside whatever runs concurrently on other streams; at
- *    the default two such sweeps from different graphs may run at once.
+ *    deviation lists, the backward grid twice as many.  Any number of
+ *    sweeps of different graphs may run at once on different streams, beside
+ *    other kernels: what does not fit on the GPU waits its turn, and a sweep
+ *    that is on it only in part finishes with that part, more slowly.
  *  spin_log2: log2 of the poll budget per wait (0 keeps, 1..30).
  * Results do not depend on the tuning: both sweep forms compute every value
  * with the same operations in the same order. */

@@ -231,6 +231,7 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
   g->flow_ok = prec == TDP_F32 && T.n_big == 0;
   g->sweep_mode = g->flow_ok ? 1 : (g->fw_flow_ok || g->bw_flow_ok ? 4 : 0);
   if (ok && g->bw_flow_ok) ok = dalloc(g, g->flow_r, T.M, es);
+  ok = ok && dalloc(g, g->share, NUM_SWEEPS) && dalloc(g, g->here, (size_t)NUM_SWEEPS * BLOCKS_PER_CU * g->num_cu);
   if (ok && g->fw_flow_ok) {
     std::vector<int2> turns;
     const int ng = CHUNK / list_lanes(g->side_k);
@@ -283,6 +284,13 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
              dalloc(g, b.wl, T.M, es);
     };
     ok = ok && tree_alloc(g->tree) && tree_alloc(g->st_tree);
+  }
+  if (ok) {
+    const SweepArgs args{g->topo,   g->lut,    g->list_turn, g->n_turns, g->crit,   g->d_err,  g->load,      g->dnet,
+                         g->at,     g->slew,   g->rat,       g->darc,    g->dnet_nm, g->flow_r, g->st_at,     g->st_adj,
+                         g->st_dnet, g->st_gp, g->st_adj_nm, g->node,    g->flow_a, g->flow_w, g->cdep,      g->d_tag,
+                         g->xy_st,  g->share,  g->here,      BLOCKS_PER_CU * g->num_cu};
+    ok = upload(g, g->sweep_args, std::vector<SweepArgs>{args});
   }
   if (!ok || hipDeviceSynchronize() != hipSuccess) {
     free_all(g);

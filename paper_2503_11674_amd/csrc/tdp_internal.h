@@ -200,6 +200,36 @@ __host__ __device__ constexpr int list_words() { return (int)sizeof(T) / 4; }
 template <typename T>
 __host__ __device__ constexpr int node_words(int km) { return HOP_WORDS + (km > 1 ? km * list_words<T>() : 0); }
 
+// The resident sweeps of a graph, and what the workgroups of one share in device
+// memory (tdp_flow.h)
+enum Sweep { SWEEP_FORWARD, SWEEP_BACKWARD, SWEEP_ST_FORWARD, SWEEP_ST_BACKWARD, NUM_SWEEPS };
+struct SweepShare {
+  uint32_t ticket[2];  // tickets taken: chunks, and the forward grid's list turns
+  uint32_t number;     // sweeps so far
+  uint32_t ended;      // what has ended its waits
+};
+constexpr uint32_t SWEEP_GAVE_UP = 1, SWEEP_BY_TICKETS = 2;
+// workgroups of a resident sweep per compute unit, at most
+constexpr int BLOCKS_PER_CU = 16;
+
+// the smoothed sweeps' error words in d_err
+constexpr int ST_ERR = 2;
+// The sweeps' arrays in device memory, for code that a sweep hardly ever comes to
+struct SweepArgs {
+  Topo topo;
+  LutView lut;
+  const int2 *turn;
+  int32_t turns;
+  int32_t *crit, *err;
+  void *load, *dnet, *at, *slew, *rat, *darc, *dnet_nm, *flow_r, *st_at, *st_adj, *st_dnet, *st_gp, *st_adj_nm;
+  uint64_t *node, *flow_a, *flow_w;
+  uint32_t *cdep, *d_tag;
+  const float2 *xy_st;
+  SweepShare *share;
+  uint32_t *here;
+  int32_t here_stride;
+};
+
 struct HostLevels {
   std::vector<int32_t> fw_lvl;    // [D+1]: level l input chunks are [fw_lvl[l-1], fw_lvl[l])
   std::vector<int32_t> nm_lvl;    // [D+2]: level l net chunks are [nm_lvl[l], nm_lvl[l+1]) (0 = start points)
@@ -298,6 +328,9 @@ struct tdp_graph_s {
   int2 *list_turn = nullptr;     // [n_turns] {first cell, cells} of a list wave's turns, level by level
   int32_t n_turns = 0;
   void *flow_r = nullptr;        // [M] required time of a driver (its bits, 4 or 8 bytes); all ones = not yet (PULL)
+  tdp::SweepShare *share = nullptr;  // [NUM_SWEEPS]
+  tdp::SweepArgs *sweep_args = nullptr;
+  uint32_t *here = nullptr;      // [NUM_SWEEPS][BLOCKS_PER_CU * num_cu] the sweep that a workgroup last began
   int32_t flow_waves = 4, spin_limit = 1 << 20;
   int32_t flow_per_cu = 1;       // workgroups per compute unit of the resident dataflow grids
   int32_t num_cu = 0;            // compute units of the device

@@ -32,11 +32,10 @@ namespace tdp {
 
 static inline int nb(long long n, int b) { return n > 0 ? (int)((n + b - 1) / b) : 1; }
 
-// the smoothed sweeps' own error words, behind d_err's: this forward pass's and
+// the smoothed sweeps' own error words, ST_ERR behind d_err's: this forward pass's and
 // its backward passes', and one that stays set until a call has reported it (the
 // next update clears the timing sweeps' word, and no smoothed call waits for its
 // results)
-constexpr int ST_ERR = 2;
 __device__ __forceinline__ bool st_failed(const int32_t *err) {
   return pub_ld(reinterpret_cast<const uint32_t *>(err)) != 0;
 }
@@ -60,9 +59,14 @@ __device__ __forceinline__ typename ReqWord<T>::type pub_bits(T v) {
 // adjoint, not yet
 template <typename T>
 __global__ void __launch_bounds__(256) k_st_start(Topo tp, const T *__restrict__ at, T *__restrict__ sa,
-                                                   T *__restrict__ adj, int32_t *__restrict__ err) {
+                                                   T *__restrict__ adj, int32_t *__restrict__ err,
+                                                   SweepShare *__restrict__ share) {
   using RW = typename ReqWord<T>::type;
-  if (blockIdx.x == 0 && threadIdx.x == 0) err[0] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    err[0] = 0;
+    new_sweep(share + SWEEP_ST_FORWARD);
+    new_sweep(share + SWEEP_ST_BACKWARD);
+  }
   for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < tp.M; v += gridDim.x * blockDim.x) {
     reinterpret_cast<RW *>(sa)[v] = v < tp.n_start ? pub_bits<T>(at[v]) : ~(RW)0;
     reinterpret_cast<RW *>(adj)[v] = ~(RW)0;
@@ -106,29 +110,46 @@ __global__ void __launch_bounds__(256) k_st_fwd(Topo tp, int ch0, int ch1, T gam
 // timing pass): wave w takes chunks w, w + W, ... in level order, waits for its
 // drivers' words and publishes its cells'.  Bound by the chain of levels: 156 us
 // at 1M cells, 80 levels, against 312 with a launch per level.
-template <typename T>
-__global__ void __launch_bounds__(256) k_st_fwd_flow(Topo tp, T gam, const T *__restrict__ dnl,
-                                                      const T *__restrict__ darc, T *sa, int32_t *__restrict__ err,
-                                                      int limit) {
+template <typename T, bool TICKETS>
+__device__ __forceinline__ void st_fwd_chunk(const Topo &tp, int4 rec, T gam, const T *__restrict__ dnl,
+                                             const T *__restrict__ darc, T *sa, const Waits<SWEEP_ST_FORWARD> &wt,
+                                             bool &done) {
   using RW = typename ReqWord<T>::type;
   RW *words = reinterpret_cast<RW *>(sa);
+  const int lane = wave_lane();
+  const int t = rec.x;
+  const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
+  const bool valid = t >= 0;
+  const T dn = valid ? dnl[t] : (T)0, da = valid ? darc[t] : (T)0;
+  RW w;
+  done = load_or_leave<false, TICKETS>(words, valid ? rec.y : 0, valid, (RW)~(RW)0, wt, w);
+  if (!done) return;
+  const StCell<T> c(ReqWord<T>::value(w), dn, da, valid, lane, head, tail, gam);
+  if (valid && lane == head) pub_st(words + tp.n_start + rec.z, pub_bits<T>(c.out));
+  if (valid) sa[tp.M + t] = c.share(gam);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_st_fwd_flow(Topo tp, T gam, const T *__restrict__ dnl,
+                                                      const T *__restrict__ darc, T *sa, Waits<SWEEP_ST_FORWARD> wt) {
   const int lane = wave_lane(), wpb = blockDim.x >> 6;
   const int W = gridDim.x * wpb, nch = tp.n_fw_chunks;
-  int q = blockIdx.x * wpb + (threadIdx.x >> 6);
+  int q = blockIdx.x * wpb + wave_id();
   int4 nrec = q < nch ? tp.fw_rec[q * CHUNK + lane] : make_int4(-1, 0, 0, 0);
-  for (; q < nch; q += W) {
+  begin_share(wt);
+  bool done = true;
+  for (; done && q < nch; q += W) {
     const int4 rec = nrec;
     if (q + W < nch) nrec = tp.fw_rec[(q + W) * CHUNK + lane];
-    const int t = rec.x;
-    const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
-    const bool valid = t >= 0;
-    const T dn = valid ? dnl[t] : (T)0, da = valid ? darc[t] : (T)0;
-    const RW w = load_or_wait(words, valid ? rec.y : 0, valid, (RW)~(RW)0, err, limit);
-    const StCell<T> c(ReqWord<T>::value(w), dn, da, valid, lane, head, tail, gam);
-    if (valid && lane == head) pub_st(words + tp.n_start + rec.z, pub_bits<T>(c.out));
-    if (valid) sa[tp.M + t] = c.share(gam);
+    st_fwd_chunk<T, false>(tp, rec, gam, dnl, darc, sa, wt, done);
   }
-  if (lane == 0) st_report(err);
+  if (__syncthreads_or(!done)) {
+    const SweepArgs &c = wt.args();
+    while ((q = take_ticket(&wt.share()->ticket[0])) < c.topo.n_fw_chunks)
+      st_fwd_chunk<T, true>(c.topo, c.topo.fw_rec[q * CHUNK + wave_lane()], gam, (const T *)c.st_dnet, (const T *)c.darc,
+                            (T *)c.st_at, wt, done);
+  }
+  if (lane == 0) st_report(wt.err());
 }
 
 // endpoint values and adjoint seeds; the value summed by the last workgroup (not
@@ -190,54 +211,73 @@ __global__ void __launch_bounds__(256) k_st_bwd(Topo tp, int ch0, int ch1, const
 // gathers and the scatter fits in it (208 us at 1M cells against 147 + 82 in
 // two launches; 46 against 44 + 6 at 50,000).  Otherwise the sinks' adjoints go
 // to adj_nm for the spanning trees' launch.
+template <typename T, bool STAR, bool TICKETS>
+__device__ __forceinline__ void st_bwd_chunk(const Topo &tp, int4 rec, int k, const T *__restrict__ sa, T *adj,
+                                             T *__restrict__ adj_nm, const float2 *__restrict__ xy,
+                                             const NetModel<T> &nm, V2<T> *__restrict__ gp, const Waits<SWEEP_ST_BACKWARD> &wt,
+                                             bool &done) {
+  using RW = typename ReqWord<T>::type;
+  RW *words = reinterpret_cast<RW *>(adj);
+  const int lane = wave_lane();
+  const int p = rec.x, vo = rec.z;
+  const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
+  const bool sink = p >= 0 && lane != head, comb_in = sink && vo >= 0;
+  // a combinational input's share, an endpoint's seed
+  const T share = sink ? (comb_in ? sa : adj)[p] : (T)0;
+  float2 pos = make_float2(0.f, 0.f), off = pos;
+  if constexpr (STAR) {
+    if (rec.y >= 0) pos = xy[rec.y];
+    off = make_float2(tp.nm_ox[k], tp.nm_oy[k]);
+  }
+  RW w;
+  done = load_or_leave<true, TICKETS>(words, comb_in ? vo : 0, comb_in, (RW)~(RW)0, wt, w);
+  if (!done) return;
+  const T mine = comb_in ? ReqWord<T>::value(w) * share : share;
+  const T a = seg_sum(mine, lane, head, tail);
+  if (p >= 0 && lane == head) pub_st(words + p, pub_bits<T>(a));
+  if constexpr (STAR) {
+    // (driver - sink) per axis, a port's position as the base (see the net pass)
+    const bool port = rec.y < 0;
+    const T cx = port ? (T)off.x : (T)pos.x, cy = port ? (T)off.y : (T)pos.y;
+    const T ox = port ? (T)0 : (T)off.x, oy = port ? (T)0 : (T)off.y;
+    const T cxd = __shfl(cx, head, 64), cyd = __shfl(cy, head, 64);
+    const T oxd = __shfl(ox, head, 64), oyd = __shfl(oy, head, 64);
+    const T dx = (cxd - cx) + (oxd - ox), dy = (cyd - cy) + (oyd - oy);
+    const T len = sink ? fabs(dx) + fabs(dy) : (T)0;
+    const T gl = sink ? mine * nm.slope(len, nm.elmore ? (T)tp.type_cap[(rec.w >> 16) & 255] : (T)0) : (T)0;
+    const T ex = gl * sgn(dx), ey = gl * sgn(dy);
+    const T sx = seg_sum(ex, lane, head, tail), sy = seg_sum(ey, lane, head, tail);
+    if (p >= 0) gp[p] = sink ? v2<T>(-ex, -ey) : v2<T>(sx, sy);
+  } else {
+    if (sink) adj_nm[k] = mine;
+  }
+}
+
 template <typename T, bool STAR>
 __global__ void __launch_bounds__(256) k_st_bwd_flow(Topo tp, const T *__restrict__ sa, T *adj,
                                                       T *__restrict__ adj_nm, const float2 *__restrict__ xy,
-                                                      NetModel<T> nm, V2<T> *__restrict__ gp,
-                                                      int32_t *__restrict__ err, int limit) {
-  using RW = typename ReqWord<T>::type;
-  RW *words = reinterpret_cast<RW *>(adj);
+                                                      NetModel<T> nm, V2<T> *__restrict__ gp, Waits<SWEEP_ST_BACKWARD> wt) {
   const int lane = wave_lane(), wpb = blockDim.x >> 6;
   const int W = gridDim.x * wpb, nch = tp.n_nm_chunks;
-  int q = blockIdx.x * wpb + (threadIdx.x >> 6);
+  int q = blockIdx.x * wpb + wave_id();
   int4 nrec = q < nch ? tp.nm_rec[(nch - 1 - q) * CHUNK + lane] : make_int4(-1, -1, -1, 0);
-  for (; q < nch; q += W) {
-    const int k = (nch - 1 - q) * CHUNK + lane;
+  begin_share(wt);
+  bool done = true;
+  for (; done && q < nch; q += W) {
     const int4 rec = nrec;
     if (q + W < nch) nrec = tp.nm_rec[(nch - 1 - q - W) * CHUNK + lane];
-    const int p = rec.x, vo = rec.z;
-    const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
-    const bool sink = p >= 0 && lane != head, comb_in = sink && vo >= 0;
-    // a combinational input's share, an endpoint's seed
-    const T share = sink ? (comb_in ? sa : adj)[p] : (T)0;
-    float2 pos = make_float2(0.f, 0.f), off = pos;
-    if constexpr (STAR) {
-      if (rec.y >= 0) pos = xy[rec.y];
-      off = make_float2(tp.nm_ox[k], tp.nm_oy[k]);
-    }
-    const RW w = load_or_wait<true>(words, comb_in ? vo : 0, comb_in, (RW)~(RW)0, err, limit);
-    const T mine = comb_in ? ReqWord<T>::value(w) * share : share;
-    const T a = seg_sum(mine, lane, head, tail);
-    if (p >= 0 && lane == head) pub_st(words + p, pub_bits<T>(a));
-    if constexpr (STAR) {
-      // (driver - sink) per axis, a port's position as the base (see the net pass)
-      const bool port = rec.y < 0;
-      const T cx = port ? (T)off.x : (T)pos.x, cy = port ? (T)off.y : (T)pos.y;
-      const T ox = port ? (T)0 : (T)off.x, oy = port ? (T)0 : (T)off.y;
-      const T cxd = __shfl(cx, head, 64), cyd = __shfl(cy, head, 64);
-      const T oxd = __shfl(ox, head, 64), oyd = __shfl(oy, head, 64);
-      const T dx = (cxd - cx) + (oxd - ox), dy = (cyd - cy) + (oyd - oy);
-      const T len = sink ? fabs(dx) + fabs(dy) : (T)0;
-      const T gl =
-          sink ? mine * nm.slope(len, nm.elmore ? (T)tp.type_cap[(rec.w >> 16) & 255] : (T)0) : (T)0;
-      const T ex = gl * sgn(dx), ey = gl * sgn(dy);
-      const T sx = seg_sum(ex, lane, head, tail), sy = seg_sum(ey, lane, head, tail);
-      if (p >= 0) gp[p] = sink ? v2<T>(-ex, -ey) : v2<T>(sx, sy);
-    } else {
-      if (sink) adj_nm[k] = mine;
+    st_bwd_chunk<T, STAR, false>(tp, rec, (nch - 1 - q) * CHUNK + lane, sa, adj, adj_nm, xy, nm, gp, wt, done);
+  }
+  if (__syncthreads_or(!done)) {
+    const SweepArgs &c = wt.args();
+    const int cn = c.topo.n_nm_chunks;
+    while ((q = take_ticket(&wt.share()->ticket[0])) < cn) {
+      const int k = (cn - 1 - q) * CHUNK + wave_lane();
+      st_bwd_chunk<T, STAR, true>(c.topo, c.topo.nm_rec[k], k, (const T *)c.st_at, (T *)c.st_adj, (T *)c.st_adj_nm,
+                                  c.xy_st, nm, (V2<T> *)c.st_gp, wt, done);
     }
   }
-  if (lane == 0) st_report(err);
+  if (lane == 0) st_report(wt.err());
 }
 
 // the same for nets wider than a chunk, one thread per net
@@ -325,13 +365,13 @@ void stns_fwd_impl(tdp_graph g, const float *x, const float *y, float gamma, dou
   const T gam = (T)gamma;
   st_net_fwd_impl<T>(g, x, y, (T *)g->st_dnet, s);
   hipLaunchKernelGGL(k_st_start<T>, dim3(std::min(2048, nb(tp.M, 256))), dim3(256), 0, s, tp, (const T *)g->at,
-                     (T *)g->st_at, (T *)g->st_adj, g->d_err + ST_ERR);
+                     (T *)g->st_at, (T *)g->st_adj, g->d_err + ST_ERR, g->share);
   if (g->sweep_mode != 0) {
     const int w = g->flow_waves;
     hipLaunchKernelGGL(k_st_fwd_flow<T>,
                        dim3(st_blocks(g, reinterpret_cast<const void *>(&k_st_fwd_flow<T>), 0, tp.n_fw_chunks)),
                        dim3(64 * w), 0, s, tp, gam, (const T *)g->st_dnet, (const T *)g->darc, (T *)g->st_at,
-                       g->d_err + ST_ERR, g->spin_limit);
+                       sweep_waits<SWEEP_ST_FORWARD>(g));
   } else {
     for (int l = 1; l <= tp.D; ++l) {
       const int ch0 = g->lv.fw_lvl[l - 1], ch1 = g->lv.fw_lvl[l];
@@ -361,12 +401,12 @@ void stns_bwd_impl(tdp_graph g, const double *gout, float *gx, float *gy, hipStr
     const dim3 grid(st_blocks(g, kern, 1, tp.n_nm_chunks)), block(64 * g->flow_waves);
     if (star)
       hipLaunchKernelGGL((k_st_bwd_flow<T, true>), grid, block, 0, s, tp, (const T *)g->st_at, (T *)g->st_adj,
-                         (T *)nullptr, g->xy_st, net_model<T>(g), (V2<T> *)g->st_gp, g->d_err + ST_ERR,
-                         g->spin_limit);
+                         (T *)nullptr, g->xy_st, net_model<T>(g), (V2<T> *)g->st_gp,
+                         sweep_waits<SWEEP_ST_BACKWARD>(g));
     else
       hipLaunchKernelGGL((k_st_bwd_flow<T, false>), grid, block, 0, s, tp, (const T *)g->st_at, (T *)g->st_adj,
-                         (T *)g->st_adj_nm, g->xy_st, net_model<T>(g), (V2<T> *)nullptr, g->d_err + ST_ERR,
-                         g->spin_limit);
+                         (T *)g->st_adj_nm, g->xy_st, net_model<T>(g), (V2<T> *)nullptr,
+                         sweep_waits<SWEEP_ST_BACKWARD>(g));
   } else {
     for (int l = tp.D; l >= 0; --l) {
       const int ch0 = g->lv.nm_lvl[l], ch1 = g->lv.nm_lvl[l + 1];

@@ -42,6 +42,7 @@ struct FlowInit {
   void *r = nullptr;              // the backward sweep's published words and their count
   int nr = 0;
   int32_t *err = nullptr;  // cleared at the start of every update
+  SweepShare *fw = nullptr, *bw = nullptr;  // of the sweeps whose words are reset: a new sweep each
   const uint32_t *tag = nullptr;  // the graph's pass counter and whether the last sweep gave up
   uint64_t *node = nullptr;
   uint32_t *cd = nullptr;
@@ -192,7 +193,11 @@ __global__ void __launch_bounds__(256) k_netpass(Topo tp, LutView L, const float
                                                   T *__restrict__ dnet_nm, float2 *__restrict__ cxy_nm,
                                                   T *__restrict__ at, T *__restrict__ slew,
                                                   V2<T> *__restrict__ as, uint32_t *__restrict__ cdep, FlowInit fl) {
-  if (blockIdx.x == 0 && threadIdx.x == 0 && fl.err) *fl.err = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (fl.err) *fl.err = 0;
+    if (fl.fw) new_sweep(fl.fw);
+    if (fl.bw) new_sweep(fl.bw);
+  }
   const int main_blocks = (int)gridDim.x - fl.reset_blocks;
   if ((int)blockIdx.x >= main_blocks) {
     flow_reset<T>(fl, tp, (int)blockIdx.x - main_blocks);
@@ -596,8 +601,7 @@ __global__ void k_backward_big(Topo tp, int i0, int i1, const T *__restrict__ dn
 // ------------------------------------------------------ dataflow sweeps
 // One launch per sweep on a resident grid: every workgroup of the launch is
 // on the GPU at once (the grid is sized from the occupancy of the kernel, at
-// most a few workgroups per compute unit, so a concurrent kernel on another
-// stream cannot keep part of it waiting), and wave w of the W waves owns
+// most a few workgroups per compute unit), and wave w of the W waves owns
 // chunks w, w + W, w + 2W, ... in dependency order (forward: level order;
 // backward: reverse level order).  For each chunk a wave loads its static
 // data (the next chunk's record is already in flight), waits until the words
@@ -605,8 +609,10 @@ __global__ void k_backward_big(Topo tp, int i0, int i1, const T *__restrict__ dn
 // compute, and publishes its own words.  A chunk waits only on chunks with
 // smaller indices, and every wave takes its chunks in increasing order, so
 // the smallest unfinished chunk always has its inputs and its owner at it:
-// the sweep completes.  The tables are staged in LDS once per workgroup, not
-// once per chunk, and no workgroup is dispatched while the sweep runs.
+// the sweep completes.  Where other streams' kernels keep workgroups out for
+// long, those inside leave their fixed shares and take chunks by tickets
+// (tdp_flow.h): the sweep completes whichever workgroups are inside.  The
+// tables are staged in LDS once per workgroup, not once per chunk.
 // Every wait is also bounded, so a broken assumption ends in a reported
 // error, not a hang.  One lane per wave polls (the word its chunk is likely
 // to see published last) before the others load theirs, which keeps the
@@ -641,48 +647,120 @@ __device__ __forceinline__ float arc_arrival(uint64_t w) { return __uint_as_floa
 // not out yet, one lane first polls the last word of the highest-numbered
 // missing driver (likely to be published last), so that a waiting wave polls
 // one address rather than 64; then all missing words are loaded again
-// together, one round trip per poll.  Bounded as wait_pub.
-template <int N>
-__device__ __forceinline__ void load_words(const uint64_t *base, int idx, bool want, uint64_t (&w)[N], int32_t *err,
-                                           int limit) {
+// together, one round trip per poll.  Bounded and left as load_or_wait.
+template <int N, bool TICKETS>
+__device__ __forceinline__ bool load_words(const uint64_t *base, int idx, bool want, uint64_t (&w)[N],
+                                           const Waits<SWEEP_FORWARD> &wt) {
   bool miss = false;
 #pragma unroll
   for (int q = 0; q < N; ++q) {
     w[q] = want ? pub_ld(base + (size_t)idx * N + q) : 0ull;
     miss = miss || w[q] == W_EMPTY;
   }
-  if (!__ballot(miss)) return;
-  const int rep = wave_max_int(miss ? idx : -1);
-  wait_rep(base + (size_t)rep * N + N - 1, W_EMPTY, err, limit);
-  for (int it = 0; __ballot(miss); ++it) {
-    if (it > limit) {
-      if (wave_lane() == 0) atomicOr(err, 2);
-      return;
-    }
-    if ((it & 31) == 31 && __ballot(__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) return;
-    if (miss) {
-      miss = false;
+  if (!__ballot(miss)) return true;
+  Polls<TICKETS, SWEEP_FORWARD> polls(wt);
+  const uint64_t *const last = base + (size_t)wave_max_int(miss ? idx : -1) * N + N - 1;
+  const bool first = wave_lane() == 0;
+  uint64_t r;
+  do {
+    do r = first ? pub_ld(last) : 0ull;
+    while (polls.missing(r == W_EMPTY));
+    do {
+      if (miss) {
+        miss = false;
 #pragma unroll
-      for (int q = 0; q < N; ++q) {
-        if (w[q] == W_EMPTY) w[q] = pub_ld(base + (size_t)idx * N + q);
-        miss = miss || w[q] == W_EMPTY;
+        for (int q = 0; q < N; ++q) {
+          if (w[q] == W_EMPTY) w[q] = pub_ld(base + (size_t)idx * N + q);
+          miss = miss || w[q] == W_EMPTY;
+        }
       }
+    } while (polls.missing(miss, false));
+  } while (polls.resume(miss));
+  return !polls.leave;
+}
+
+// A chunk's arrivals from its drivers' words, published and stored
+template <typename T, int N>
+__device__ __forceinline__ void arrive(const Topo &tp, const LutView &L, const float *s_lut, int4 rec, int2 ex, T ld, T dn,
+                                       const uint64_t (&w)[N], T *__restrict__ at, T *__restrict__ slew,
+                                       T *__restrict__ darc, int32_t *__restrict__ crit, uint64_t *__restrict__ node,
+                                       int words, uint64_t *__restrict__ fa, uint64_t *__restrict__ fw,
+                                       uint32_t pass) {
+  const int lane = wave_lane();
+  const uint32_t tag = pass & 3u;
+  const int t = rec.x, s = rec.y, c = rec.z, ty = (rec.w >> 16) & 255;
+  const int head = rec.w & 63;
+  const bool valid = t >= 0;
+  T a = -pos_inf<T>(), o = 0, a_in = 0, d = 0;
+  if (valid) {
+    T wa, ws;
+    if constexpr (N == 1) {
+      wa = __uint_as_float((uint32_t)w[0]);
+      ws = __uint_as_float((uint32_t)(w[0] >> 32));
+    } else {
+      wa = __longlong_as_double((long long)w[0]);
+      ws = __longlong_as_double((long long)w[N - 1]);
     }
+    a_in = wa + dn;
+    lut_lds<T>(s_lut, L.nt, L.ns, L.nl, ty, sink_slew<T>(L.net_model, ws, dn), ld, d, o);
+    a = a_in + d;
+  }
+  T best, so;
+  int argl;
+  cell_max<T>(a, o, valid, rec.w, lane, best, so, argl);
+  const bool is_head = valid && lane == head;
+  const int v = tp.n_start + c;
+  if (is_head) {
+    if constexpr (N == 1) {
+      pub_st(&fw[v], pack2(best, so));
+    } else {
+      pub_st(&fw[2 * (size_t)v], (uint64_t)__double_as_longlong(best));
+      pub_st(&fw[2 * (size_t)v + 1], (uint64_t)__double_as_longlong(so));
+    }
+  }
+  const uint64_t h0 = pack_ids(__shfl(t, argl & 63, 64), __shfl(s, argl & 63, 64), tag);
+  const uint64_t h1 = pack_ids(__shfl(ex.x, argl & 63, 64), __shfl(ex.y, argl & 63, 64), tag);
+  if constexpr (N == 1) {
+    if (fa && valid) pub_st(&fa[t], pack_arc(a, pass));
+  }
+  if (is_head) {
+    pub_st(node + (size_t)c * words, h0);
+    pub_st(node + (size_t)c * words + 1, h1);
+    at[v] = best;
+    slew[v] = so;
+    crit[c] = argl - head;
+  }
+  if (valid) {
+    at[tp.M + t] = a_in;
+    darc[t] = d;
   }
 }
 
-// arrivals of chunks w0, w0 + W, ...
-template <typename T>
-__device__ __forceinline__ void flow_arrivals(const Topo &tp, const LutView &L, float *s_lut, int w0, int W,
+// arrivals of chunks w0, w0 + W, ..., or (TICKETS) of those that tickets give;
+// false if the wave left its share
+template <typename T, bool TICKETS>
+__device__ __forceinline__ bool flow_arrivals(const Topo &tp, const LutView &L, float *s_lut, int w0, int W,
                                               const T *__restrict__ load, const T *__restrict__ dnet,
                                               T *__restrict__ at, T *__restrict__ slew, T *__restrict__ darc,
                                               int32_t *__restrict__ crit, uint64_t *__restrict__ node, int words,
                                               uint64_t *__restrict__ fa, uint64_t *__restrict__ fw, uint32_t pass,
-                                              int32_t *__restrict__ err, int limit) {
+                                              const Waits<SWEEP_FORWARD> &wt) {
   constexpr int N = sizeof(T) / 4;  // words of a driver's {arrival, transition}
-  const uint32_t tag = pass & 3u;
   const int lane = wave_lane();
   const int nch = tp.n_fw_chunks;
+  uint64_t w[N];
+  if constexpr (TICKETS) {
+    stage_lut(L, s_lut);
+    for (int chunk; (chunk = take_ticket(&wt.share()->ticket[0])) < nch;) {
+      const int4 rec = tp.fw_rec[chunk * CHUNK + lane];
+      const int2 ex = tp.fw_ext[chunk * CHUNK + lane];
+      const bool valid = rec.x >= 0;
+      const T ld = valid ? load[tp.n_start + rec.z] : (T)0, dn = valid ? dnet[rec.x] : (T)0;
+      load_words<N, true>(fw, rec.y, valid, w, wt);
+      arrive<T, N>(tp, L, s_lut, rec, ex, ld, dn, w, at, slew, darc, crit, node, words, fa, fw, pass);
+    }
+    return true;
+  }
   int chunk = w0;
   const int4 norec = make_int4(-1, 0, 0, 0);
   int4 rec1 = norec, rec2 = norec;  // records of this wave's next two chunks
@@ -702,11 +780,7 @@ __device__ __forceinline__ void flow_arrivals(const Topo &tp, const LutView &L, 
     const int4 rec = rec1;
     const int2 ex = ex1;
     const T ld = ld1, dn = dn1;
-    const int t = rec.x, s = rec.y, c = rec.z, ty = (rec.w >> 16) & 255;
-    const int head = rec.w & 63;
-    const bool valid = t >= 0;
-    uint64_t w[N];
-    load_words<N>(fw, s, valid, w, err, limit);
+    if (!load_words<N, false>(fw, rec.y, rec.x >= 0, w, wt)) return false;
     // the next chunks' static data, in flight behind this one
     rec1 = rec2;
     rec2 = norec;
@@ -716,69 +790,120 @@ __device__ __forceinline__ void flow_arrivals(const Topo &tp, const LutView &L, 
     }
     if (chunk + W < nch) ex1 = tp.fw_ext[(chunk + W) * CHUNK + lane];
     if (chunk + 2 * W < nch) rec2 = tp.fw_rec[(chunk + 2 * W) * CHUNK + lane];
-    T a = -pos_inf<T>(), o = 0, a_in = 0, d = 0;
-    if (valid) {
-      T wa, ws;
-      if constexpr (N == 1) {
-        wa = __uint_as_float((uint32_t)w[0]);
-        ws = __uint_as_float((uint32_t)(w[0] >> 32));
-      } else {
-        wa = __longlong_as_double((long long)w[0]);
-        ws = __longlong_as_double((long long)w[N - 1]);
-      }
-      a_in = wa + dn;
-      lut_lds<T>(s_lut, L.nt, L.ns, L.nl, ty, sink_slew<T>(L.net_model, ws, dn), ld, d, o);
-      a = a_in + d;
-    }
-    T best, so;
-    int argl;
-    cell_max<T>(a, o, valid, rec.w, lane, best, so, argl);
-    const bool is_head = valid && lane == head;
-    const int v = tp.n_start + c;
-    if (is_head) {
-      if constexpr (N == 1) {
-        pub_st(&fw[v], pack2(best, so));
-      } else {
-        pub_st(&fw[2 * (size_t)v], (uint64_t)__double_as_longlong(best));
-        pub_st(&fw[2 * (size_t)v + 1], (uint64_t)__double_as_longlong(so));
-      }
-    }
-    const uint64_t h0 = pack_ids(__shfl(t, argl & 63, 64), __shfl(s, argl & 63, 64), tag);
-    const uint64_t h1 = pack_ids(__shfl(ex.x, argl & 63, 64), __shfl(ex.y, argl & 63, 64), tag);
-    if constexpr (N == 1) {
-      if (fa && valid) pub_st(&fa[t], pack_arc(a, pass));
-    }
-    if (is_head) {
-      pub_st(node + (size_t)c * words, h0);
-      pub_st(node + (size_t)c * words + 1, h1);
-      at[v] = best;
-      slew[v] = so;
-      crit[c] = argl - head;
-    }
-    if (valid) {
-      at[tp.M + t] = a_in;
-      darc[t] = d;
-    }
+    arrive<T, N>(tp, L, s_lut, rec, ex, ld, dn, w, at, slew, darc, crit, node, words, fa, fw, pass);
   }
+  return true;
 }
 
-// node records of the cells of turns w0, w0 + W, ...: turn q takes turn[q].y
-// cells from turn[q].x on, at most 64 / list_lanes, of one level (two cells of
-// one turn never wait for each other)
-template <typename T, int KM>
-__device__ __forceinline__ void flow_lists(const Topo &tp, const int2 *__restrict__ turn, int turns, int w0, int W,
-                                           uint32_t *__restrict__ cdep,
-                                           uint64_t *__restrict__ node, const uint64_t *__restrict__ fa, uint32_t pass,
-                                           int32_t *__restrict__ err, int limit) {
-  static_assert(KM == 1 || sizeof(T) == 4, "double-precision lists are not published");
-  constexpr int LG = list_lanes(KM), NG = 64 / LG, NW = node_words<T>(KM);
+// One turn of a wave's groups: the node record of cell c (c of the turn's cells
+// that share the wave; spare groups repeat the last, last_c, with `on` false, and
+// store nothing), whose inputs are the n from t0 on.  False if the wave left its
+// share.
+template <typename T, int KM, bool TICKETS>
+__device__ __forceinline__ bool list_turn_of(const Topo &tp, int c, bool on, int last_c, int t0, int n,
+                                             uint32_t *__restrict__ cdep, uint64_t *__restrict__ node,
+                                             const uint64_t *__restrict__ fa, uint32_t pass, const Waits<SWEEP_FORWARD> &wt) {
+  constexpr int LG = list_lanes(KM), NW = node_words<T>(KM);
   const uint32_t tag = pass & 3u;
-  const int lane = wave_lane(), j = lane & (LG - 1), base = lane & ~(LG - 1), g = lane / LG;
+  const int lane = wave_lane(), j = lane & (LG - 1), base = lane & ~(LG - 1);
   const unsigned long long group = ((1ull << LG) - 1) << base;
   const uint64_t none = j & 1 ? pack_ids(0, 0, tag) : pack_ids(-1, -1, tag);
   const uint64_t pad = pack_dev(__builtin_huge_valf(), -1, tag), no_arc = pack_arc(0.f, pass);
+  uint64_t *rec = node + (size_t)c * NW;
+  Polls<TICKETS, SWEEP_FORWARD> polls(wt);
+  // own hop: lanes 0 and 1 of the group; arrivals through the arcs: lane j's
+  // input.  Where some are missing, one lane first polls the own hop of the
+  // turn's last cell, then all missing words are loaded together
+  uint64_t ow = j < 2 ? pub_ld(rec + j) : none;
+  const bool own_a = KM > 1 && j < n;
+  uint64_t aw = own_a ? pub_ld(fa + t0 + j) : no_arc;
+  if (__ballot(tag_lo(ow) != tag || arc_pass(aw) != pass)) {
+    const uint64_t *last = node + (size_t)last_c * NW + 1;
+    do {
+      uint64_t lastw;
+      do lastw = lane == 0 ? pub_ld(last) : none;
+      while (polls.missing(tag_lo(lastw) != tag));
+      do {
+        if (tag_lo(ow) != tag) ow = pub_ld(rec + j);
+        if (arc_pass(aw) != pass) aw = pub_ld(fa + t0 + j);
+      } while (polls.missing(tag_lo(ow) != tag || arc_pass(aw) != pass));
+    } while (polls.resume(tag_lo(ow) != tag || arc_pass(aw) != pass));
+    if (polls.leave) return false;
+  }
+  const int pred = __shfl((int)(uint32_t)(ow >> 32), base, 64);
+  const bool chain = pred >= tp.n_start;
+  const uint64_t *p = node + (size_t)(chain ? pred - tp.n_start : 0) * NW;
+  uint64_t hw = chain && j < HOP_WORDS - 2 ? pub_ld(p + j) : none;
+  uint64_t lw = KM > 1 && chain && j < KM ? pub_ld(p + HOP_WORDS + j) : pad;
+  uint32_t cd = j == 0 ? pub_ld(cdep + pred) : tag << 30;
+  do {
+    while (polls.missing(tag_lo(hw) != tag || tag_hi(lw) != tag || cd >> 30 != tag)) {
+      if (tag_lo(hw) != tag) hw = pub_ld(p + j);
+      if (tag_hi(lw) != tag) lw = pub_ld(p + HOP_WORDS + j);
+      if (cd >> 30 != tag) cd = pub_ld(cdep + pred);
+    }
+  } while (polls.resume(tag_lo(hw) != tag || tag_hi(lw) != tag || cd >> 30 != tag));
+  if (polls.leave) return false;
+  if (on && j < HOP_WORDS - 2) pub_st(rec + 2 + j, hw);
+  if (on && j == 0) pub_st(cdep + tp.n_start + c, ((cd + 1) & ID_MASK) | tag << 30);
+  if constexpr (KM > 1) {
+    const Dev<float> e = unpack_dev(lw);
+    const int arg = __shfl(id30((uint32_t)ow), base, 64) - t0;
+    const int nmax = wave_max_int(n);
+    int shift = 0, rank;
+    if (nmax <= LG) {
+      const float a = arc_arrival(aw);
+      const float best = __shfl(a, base + arg, 64);
+      const float d = j < n && j != arg && best - a < __builtin_huge_valf() ? best - a : __builtin_huge_valf();
+      list_ranks(e.cost, d, j, nmax, group, [&](int i) { return __shfl(d, base + i, 64); }, shift, rank);
+      if (on && d < __builtin_huge_valf() && rank < KM) pub_st(rec + HOP_WORDS + rank, pack_dev(d, t0 + j, tag));
+    } else {  // a cell with more inputs than lanes: its arrivals one by one
+      auto arc = [&](int i) {
+        uint64_t w;
+        do {
+          do w = pub_ld(fa + t0 + i);
+          while (polls.missing(arc_pass(w) != pass));
+        } while (polls.resume(arc_pass(w) != pass));
+        return arc_arrival(w);
+      };
+      const float best = arc(arg);
+      auto dev = [&](int i) {
+        const float d = best - arc(min(i, n - 1));
+        return i < n && i != arg && d < __builtin_huge_valf() ? d : __builtin_huge_valf();
+      };
+      for (int b = 0; b < nmax; b += LG) {
+        const float d = dev(b + j);
+        list_ranks(e.cost, d, b + j, nmax, group, dev, shift, rank);
+        if (polls.leave) return false;
+        if (on && d < __builtin_huge_valf() && rank < KM) pub_st(rec + HOP_WORDS + rank, pack_dev(d, t0 + b + j, tag));
+      }
+    }
+    if (on && j < KM && j + shift < KM) pub_st(rec + HOP_WORDS + j + shift, lw);
+  }
+  return true;
+}
+
+// node records of the cells of turns w0, w0 + W, ..., or (TICKETS) of those that
+// tickets give: turn q takes turn[q].y cells from turn[q].x on, at most
+// 64 / list_lanes, of one level (two cells of one turn never wait for each
+// other).  False if the wave left its share.
+template <typename T, int KM, bool TICKETS>
+__device__ __forceinline__ bool flow_lists(const Topo &tp, const int2 *__restrict__ turn, int turns, int w0, int W,
+                                           uint32_t *__restrict__ cdep,
+                                           uint64_t *__restrict__ node, const uint64_t *__restrict__ fa, uint32_t pass,
+                                           const Waits<SWEEP_FORWARD> &wt) {
+  static_assert(KM == 1 || sizeof(T) == 4, "double-precision lists are not published");
+  const int g = wave_lane() / list_lanes(KM);
   // (spare groups repeat the turn's last cell and store nothing)
   auto cell = [&](int2 u) { return u.x + min(g, u.y - 1); };
+  if constexpr (TICKETS) {
+    for (int q; (q = take_ticket(&wt.share()->ticket[1])) < turns;) {
+      const int2 u = turn[q];
+      const int c = cell(u), t0 = tp.comb_inptr[c];
+      list_turn_of<T, KM, true>(tp, c, g < u.y, u.x + u.y - 1, t0, tp.comb_inptr[c + 1] - t0, cdep, node, fa, pass, wt);
+    }
+    return true;
+  }
   int q = w0;
   int2 u1 = make_int2(0, 1), u2 = u1;  // this wave's next two turns
   int nt0 = 0, nt1 = 0;                // the next turn's cells' input ranges
@@ -799,83 +924,14 @@ __device__ __forceinline__ void flow_lists(const Topo &tp, const int2 *__restric
       nt1 = tp.comb_inptr[cell(u1) + 1];
     }
     if (q + 2 * W < turns) u2 = turn[q + 2 * W];
-    uint64_t *rec = node + (size_t)c * NW;
-    int it = 0;
-    // bounded waits: false once the polls run out or another wave gave up
-    auto again = [&](bool miss) {
-      if (!__ballot(miss)) return false;
-      if (++it > limit) {
-        if (lane == 0) atomicOr(err, 2);
-        return false;
-      }
-      if ((it & 31) == 0 && __ballot(__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) return false;
-      __builtin_amdgcn_s_sleep(1);
-      return true;
-    };
-    // own hop: lanes 0 and 1 of the group; arrivals through the arcs: lane j's
-    // input.  Where some are missing, one lane first polls the own hop of the
-    // turn's last cell, then all missing words are loaded together
-    uint64_t ow = j < 2 ? pub_ld(rec + j) : none;
-    const bool own_a = KM > 1 && j < n;
-    uint64_t aw = own_a ? pub_ld(fa + t0 + j) : no_arc;
-    if (__ballot(tag_lo(ow) != tag || arc_pass(aw) != pass)) {
-      const uint64_t *last = node + (size_t)last_c * NW + 1;
-      uint64_t lastw = lane == 0 ? pub_ld(last) : none;
-      while (again(tag_lo(lastw) != tag)) {
-        if (lane == 0) lastw = pub_ld(last);
-      }
-      do {
-        if (tag_lo(ow) != tag) ow = pub_ld(rec + j);
-        if (arc_pass(aw) != pass) aw = pub_ld(fa + t0 + j);
-      } while (again(tag_lo(ow) != tag || arc_pass(aw) != pass));
-    }
-    const int pred = __shfl((int)(uint32_t)(ow >> 32), base, 64);
-    const bool chain = pred >= tp.n_start;
-    const uint64_t *p = node + (size_t)(chain ? pred - tp.n_start : 0) * NW;
-    uint64_t hw = chain && j < HOP_WORDS - 2 ? pub_ld(p + j) : none;
-    uint64_t lw = KM > 1 && chain && j < KM ? pub_ld(p + HOP_WORDS + j) : pad;
-    uint32_t cd = j == 0 ? pub_ld(cdep + pred) : tag << 30;
-    while (again(tag_lo(hw) != tag || tag_hi(lw) != tag || cd >> 30 != tag)) {
-      if (tag_lo(hw) != tag) hw = pub_ld(p + j);
-      if (tag_hi(lw) != tag) lw = pub_ld(p + HOP_WORDS + j);
-      if (cd >> 30 != tag) cd = pub_ld(cdep + pred);
-    }
-    if (on && j < HOP_WORDS - 2) pub_st(rec + 2 + j, hw);
-    if (on && j == 0) pub_st(cdep + tp.n_start + c, ((cd + 1) & ID_MASK) | tag << 30);
-    if constexpr (KM > 1) {
-      const Dev<float> e = unpack_dev(lw);
-      const int arg = __shfl(id30((uint32_t)ow), base, 64) - t0;
-      const int nmax = wave_max_int(n);
-      int shift = 0, rank;
-      if (nmax <= LG) {
-        const float a = arc_arrival(aw);
-        const float best = __shfl(a, base + arg, 64);
-        const float d = j < n && j != arg && best - a < __builtin_huge_valf() ? best - a : __builtin_huge_valf();
-        list_ranks(e.cost, d, j, nmax, group, [&](int i) { return __shfl(d, base + i, 64); }, shift, rank);
-        if (on && d < __builtin_huge_valf() && rank < KM) pub_st(rec + HOP_WORDS + rank, pack_dev(d, t0 + j, tag));
-      } else {  // a cell with more inputs than lanes: its arrivals one by one
-        auto arc = [&](int i) {
-          uint64_t w = pub_ld(fa + t0 + i);
-          while (again(arc_pass(w) != pass)) w = pub_ld(fa + t0 + i);
-          return arc_arrival(w);
-        };
-        const float best = arc(arg);
-        auto dev = [&](int i) {
-          const float d = best - arc(min(i, n - 1));
-          return i < n && i != arg && d < __builtin_huge_valf() ? d : __builtin_huge_valf();
-        };
-        for (int b = 0; b < nmax; b += LG) {
-          const float d = dev(b + j);
-          list_ranks(e.cost, d, b + j, nmax, group, dev, shift, rank);
-          if (on && d < __builtin_huge_valf() && rank < KM) pub_st(rec + HOP_WORDS + rank, pack_dev(d, t0 + b + j, tag));
-        }
-      }
-      if (on && j < KM && j + shift < KM) pub_st(rec + HOP_WORDS + j + shift, lw);
-    }
+    if (!list_turn_of<T, KM, false>(tp, c, on, last_c, t0, n, cdep, node, fa, pass, wt)) return false;
   }
+  return true;
 }
 
-// n_arr workgroups of arrival waves, the rest list waves
+// n_arr workgroups of arrival waves, the rest list waves; where shares are left,
+// every workgroup takes tickets of both kinds, arrivals first (they wait for no
+// list)
 template <typename T, int KM>
 __global__ void __launch_bounds__(256) k_forward_flow(Topo tp, LutView L, int n_arr, const int2 *__restrict__ turn,
                                                        int turns, const T *__restrict__ load,
@@ -884,16 +940,26 @@ __global__ void __launch_bounds__(256) k_forward_flow(Topo tp, LutView L, int n_
                                                        int32_t *__restrict__ crit, uint32_t *__restrict__ cdep,
                                                        uint64_t *__restrict__ node, uint64_t *__restrict__ fa,
                                                        uint64_t *__restrict__ fw, const uint32_t *__restrict__ d_tag,
-                                                       int32_t *__restrict__ err, int limit) {
+                                                       Waits<SWEEP_FORWARD> wt) {
   extern __shared__ float4 s_lut4[];
-  const int wpb = blockDim.x >> 6, wave = threadIdx.x >> 6;
+  float *const s_lut = (float *)s_lut4;
+  const int wpb = blockDim.x >> 6, wave = wave_id();
+  begin_share(wt);
   const uint32_t pass = *d_tag;
+  uint64_t *const arcs = KM > 1 ? fa : nullptr;
+  bool done;
   if ((int)blockIdx.x < n_arr)
-    flow_arrivals<T>(tp, L, (float *)s_lut4, blockIdx.x * wpb + wave, n_arr * wpb, load, dnet, at, slew, darc, crit,
-                     node, node_words<T>(KM), KM > 1 ? fa : nullptr, fw, pass, err, limit);
+    done = flow_arrivals<T, false>(tp, L, s_lut, blockIdx.x * wpb + wave, n_arr * wpb, load, dnet, at, slew, darc, crit,
+                                   node, node_words<T>(KM), arcs, fw, pass, wt);
   else
-    flow_lists<T, KM>(tp, turn, turns, (blockIdx.x - n_arr) * wpb + wave, ((int)gridDim.x - n_arr) * wpb, cdep, node,
-                      fa, pass, err, limit);
+    done = flow_lists<T, KM, false>(tp, turn, turns, (blockIdx.x - n_arr) * wpb + wave,
+                                    ((int)gridDim.x - n_arr) * wpb, cdep, node, fa, pass, wt);
+  if (!__syncthreads_or(!done)) return;
+  const SweepArgs &c = wt.args();
+  const uint32_t again = *c.d_tag;
+  flow_arrivals<T, true>(c.topo, c.lut, s_lut, 0, 0, (const T *)c.load, (const T *)c.dnet, (T *)c.at, (T *)c.slew,
+                         (T *)c.darc, c.crit, c.node, node_words<T>(KM), KM > 1 ? c.flow_a : nullptr, c.flow_w, again, wt);
+  flow_lists<T, KM, true>(c.topo, c.turn, c.turns, 0, 0, c.cdep, c.node, c.flow_a, again, wt);
 }
 
 // Backward: chunks from the last.  PULL: a sink lane loads the required time of
@@ -912,68 +978,94 @@ static bool backward_pushes(const tdp_graph_s *g) {
   return g->topo.n_nm_chunks >= (long long)PUSH_CHUNKS_PER_CU * std::max(1, g->num_cu);
 }
 
+// One net chunk.  A wave that is to leave its share clears `done` and stores
+// nothing (an early return instead costs 4 us at 200k cells).
+template <typename T, bool PUSH, bool TICKETS>
+__device__ __forceinline__ void backward_chunk(const Topo &tp, int4 rec, int k, const T *__restrict__ dnet_nm,
+                                               const T *__restrict__ darc, T *rat, typename ReqWord<T>::type *words,
+                                               const Waits<SWEEP_BACKWARD> &wt, bool &done) {
+  using RW = typename ReqWord<T>::type;
+  const int lane = wave_lane();
+  const T inf = pos_inf<T>();
+  const int p = rec.x;
+  const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
+  const bool sink = p >= 0 && lane != head, driver = p >= 0 && lane == head;
+  const T dn = sink ? dnet_nm[k] : (T)0;
+  T r = inf;
+  if constexpr (PUSH) {
+    const int nin = driver ? rec.w >> 16 : 0;
+    const int t0 = rec.z;
+    T da[FANIN_AHEAD];
+#pragma unroll
+    for (int j = 0; j < FANIN_AHEAD; ++j) da[j] = j < nin ? darc[t0 + j] : (T)0;
+    // input sinks are numbered in level order and published from the top,
+    // so the lowest one missing comes last
+    const RW w = load_or_wait<true, TICKETS>(words, sink ? p : 0, sink, (RW)~(RW)0, wt, done);
+    const T rt = ReqWord<T>::value(w);
+    if (sink && rt != inf) r = rt - dn;
+    r = seg_min(r, lane, head, tail);
+    if (driver && done) {
+      auto publish = [&](int j, T d) {
+        const T ri = r != inf ? r - d : inf;
+        pub_st(words + tp.M + t0 + j, ReqWord<T>::bits(ri == ri ? ri : (T)__builtin_nan("")));
+      };
+#pragma unroll
+      for (int j = 0; j < FANIN_AHEAD; ++j)
+        if (j < nin) publish(j, da[j]);
+      for (int j = FANIN_AHEAD; j < nin; ++j) publish(j, darc[t0 + j]);
+    }
+  } else {
+    const int t = p - tp.M, vo = rec.z;
+    const bool comb_in = sink && vo >= 0;
+    const T da = comb_in ? darc[t] : (T)0;
+    const T rq = sink && !comb_in ? rat[p] : (T)0;  // a D pin's, set at the endpoint
+    // outputs are numbered in production order of the forward sweep, so the
+    // backward sweep publishes the lowest one last
+    const RW w = load_or_wait<true, TICKETS>(words, comb_in ? vo : 0, comb_in, (RW)~(RW)0, wt, done);
+    if (sink && done) {
+      const T rt = comb_in ? sink_required<T>(p, ReqWord<T>::value(w), da, rat) : rq;
+      if (rt != inf) r = rt - dn;
+    }
+    r = seg_min(r, lane, head, tail);
+    if (driver && done) pub_st(&words[p], ReqWord<T>::bits(r));
+  }
+  if (driver && done) rat[p] = r;
+}
+
 template <typename T, bool PUSH>
 __global__ void __launch_bounds__(256) k_backward_flow(Topo tp, const T *__restrict__ dnet_nm,
                                                         const T *__restrict__ darc, T *rat,
-                                                        typename ReqWord<T>::type *fr, int32_t *__restrict__ err,
-                                                        int limit) {
+                                                        typename ReqWord<T>::type *fr, Waits<SWEEP_BACKWARD> wt) {
   using RW = typename ReqWord<T>::type;
   RW *const words = PUSH ? reinterpret_cast<RW *>(rat) : fr;
   const int lane = wave_lane();
-  const T inf = pos_inf<T>();
   const int wpb = blockDim.x >> 6;
   const int W = gridDim.x * wpb;
   const int nch = tp.n_nm_chunks;
-  int q = blockIdx.x * wpb + (threadIdx.x >> 6);
+  int q = blockIdx.x * wpb + wave_id();
   int4 nrec = q < nch ? tp.nm_rec[(nch - 1 - q) * CHUNK + lane] : make_int4(-1, -1, -1, 0);
-  for (; q < nch; q += W) {
-    const int chunk = nch - 1 - q;
+  begin_share(wt);
+  bool done = true;
+  for (; q < nch; q = done ? q + W : nch) {
     const int4 rec = nrec;
     if (q + W < nch) nrec = tp.nm_rec[(nch - 1 - q - W) * CHUNK + lane];
-    const int p = rec.x;
-    const int head = rec.w & 63, tail = (rec.w >> 8) & 63;
-    const bool sink = p >= 0 && lane != head, driver = p >= 0 && lane == head;
-    const T dn = sink ? dnet_nm[chunk * CHUNK + lane] : (T)0;
-    T r = inf;
-    if constexpr (PUSH) {
-      const int nin = driver ? rec.w >> 16 : 0;
-      const int t0 = rec.z;
-      T da[FANIN_AHEAD];
-#pragma unroll
-      for (int j = 0; j < FANIN_AHEAD; ++j) da[j] = j < nin ? darc[t0 + j] : (T)0;
-      // input sinks are numbered in level order and published from the top,
-      // so the lowest one missing comes last
-      const RW w = load_or_wait<true>(words, sink ? p : 0, sink, (RW)~(RW)0, err, limit);
-      const T rt = ReqWord<T>::value(w);
-      if (sink && rt != inf) r = rt - dn;
-      r = seg_min(r, lane, head, tail);
-      if (driver) {
-        auto publish = [&](int j, T d) {
-          const T ri = r != inf ? r - d : inf;
-          pub_st(words + tp.M + t0 + j, ReqWord<T>::bits(ri == ri ? ri : (T)__builtin_nan("")));
-        };
-#pragma unroll
-        for (int j = 0; j < FANIN_AHEAD; ++j)
-          if (j < nin) publish(j, da[j]);
-        for (int j = FANIN_AHEAD; j < nin; ++j) publish(j, darc[t0 + j]);
-      }
-    } else {
-      const int t = p - tp.M, vo = rec.z;
-      const bool comb_in = sink && vo >= 0;
-      const T da = comb_in ? darc[t] : (T)0;
-      const T rq = sink && !comb_in ? rat[p] : (T)0;  // a D pin's, set at the endpoint
-      // outputs are numbered in production order of the forward sweep, so the
-      // backward sweep publishes the lowest one last
-      const RW wr = load_or_wait<true>(words, comb_in ? vo : 0, comb_in, (RW)~(RW)0, err, limit);
-      if (sink) {
-        const T rt = comb_in ? sink_required<T>(p, ReqWord<T>::value(wr), da, rat) : rq;
-        if (rt != inf) r = rt - dn;
-      }
-      r = seg_min(r, lane, head, tail);
-      if (driver) pub_st(&fr[p], ReqWord<T>::bits(r));
-    }
-    if (driver) rat[p] = r;
+    backward_chunk<T, PUSH, false>(tp, rec, (nch - 1 - q) * CHUNK + lane, dnet_nm, darc, rat, words, wt, done);
   }
+  if (!__syncthreads_or(!done)) return;
+  const SweepArgs &c = wt.args();
+  const int cn = c.topo.n_nm_chunks;
+  while ((q = take_ticket(&wt.share()->ticket[0])) < cn) {
+    const int k = (cn - 1 - q) * CHUNK + wave_lane();
+    backward_chunk<T, PUSH, true>(c.topo, c.topo.nm_rec[k], k, (const T *)c.dnet_nm, (const T *)c.darc, (T *)c.rat,
+                                  PUSH ? (RW *)c.rat : (RW *)c.flow_r, wt, done);
+  }
+}
+
+// the backward sweep's words return to "not yet published": a new sweep
+__global__ void k_backward_reset(uint32_t *words, size_t n, SweepShare *sh) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  fill_u32(words, n, ~0u, i, (size_t)gridDim.x * blockDim.x);
+  if (i == 0) new_sweep(sh);
 }
 
 // --------------------------------------------------------------- export
@@ -1070,7 +1162,7 @@ static void launch_forward_flow(tdp_graph g, hipStream_t s) {
   hipLaunchKernelGGL((k_forward_flow<T, KM>), dim3(na + nl), dim3(64 * w), lut_bytes(g->lut), s, tp, g->lut, na,
                      g->list_turn, g->n_turns,
                      (const T *)g->load, (const T *)g->dnet, (T *)g->at, (T *)g->slew, (T *)g->darc, g->crit, g->cdep,
-                     g->node, g->flow_a, g->flow_w, g->d_tag, g->d_err, g->spin_limit);
+                     g->node, g->flow_a, g->flow_w, g->d_tag, sweep_waits<SWEEP_FORWARD>(g));
 }
 
 template <typename T>
@@ -1173,8 +1265,12 @@ void sta_arrivals_impl(tdp_graph g, const float *x, const float *y, bool require
     fl.words = node_words<T>(g->side_k);
     fl.cd = g->cdep;
     fl.seed = g->sweep_mode == 2 ? 0 : 1;
+    fl.fw = g->share + SWEEP_FORWARD;
   }
-  if (bflow) fl.r = backward_words<T>(g, fl.nr);
+  if (bflow) {
+    fl.r = backward_words<T>(g, fl.nr);
+    fl.bw = g->share + SWEEP_BACKWARD;
+  }
   fl.reset_blocks = flow ? 1024 : (bflow ? 64 : 0);
   prof_begin(g, TDP_STAGE_NETPASS, s);
   netpass_launch<T>(g, x, y, fl, true, s);
@@ -1299,7 +1395,9 @@ void sta_required_impl(tdp_graph g, hipStream_t s) {
     // own resets them here
     int nr = 0;
     T *const words = backward_words<T>(g, nr);
-    if (!g->flow_r_clear) fill_i32(reinterpret_cast<int32_t *>(words), nr * (int)(sizeof(T) / 4), -1, s);
+    if (!g->flow_r_clear)
+      hipLaunchKernelGGL(k_backward_reset, dim3(256), dim3(256), 0, s, reinterpret_cast<uint32_t *>(words),
+                         (size_t)nr * (sizeof(T) / 4), g->share + SWEEP_BACKWARD);
     g->flow_r_clear = false;
     // twice flow_per_cu: 346 us against 379 at 2M cells, no difference at 200k
     const int w = g->flow_waves;
@@ -1311,10 +1409,10 @@ void sta_required_impl(tdp_graph g, hipStream_t s) {
     using RW = typename ReqWord<T>::type;
     if (push)
       hipLaunchKernelGGL((k_backward_flow<T, true>), dim3(nb), dim3(64 * w), 0, s, tp, (const T *)g->dnet_nm,
-                         (const T *)g->darc, (T *)g->rat, (RW *)nullptr, g->d_err, g->spin_limit);
+                         (const T *)g->darc, (T *)g->rat, (RW *)nullptr, sweep_waits<SWEEP_BACKWARD>(g));
     else
       hipLaunchKernelGGL((k_backward_flow<T, false>), dim3(nb), dim3(64 * w), 0, s, tp, (const T *)g->dnet_nm,
-                         (const T *)g->darc, (T *)g->rat, (RW *)g->flow_r, g->d_err, g->spin_limit);
+                         (const T *)g->darc, (T *)g->rat, (RW *)g->flow_r, sweep_waits<SWEEP_BACKWARD>(g));
     prof_end(g, TDP_STAGE_BACKWARD, s);
     return;
   }

@@ -66,6 +66,8 @@ __device__ __forceinline__ void store_entry(uint64_t *__restrict__ node, int c, 
 }
 
 __device__ __forceinline__ int wave_lane() { return threadIdx.x & 63; }
+// the wave's number in its workgroup, as a scalar: loops over it need no lane masks
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
 // words that waves of one launch exchange (relaxed device-scope accesses)
 __device__ __forceinline__ uint64_t pub_ld(const uint64_t *p) {

@@ -86,3 +86,82 @@ def test_smoothed_sweeps_that_gave_up_are_reported(library, model, part):
         assert g.summary() == want
         assert float(g.stns_fwd(x, y, 10.0)) == value and torch.equal(bwd(), grad)
     g.close()
+
+
+def _all_results(g, x, y, k):
+    """Everything that the four sweeps make."""
+    out = [v.cpu().numpy() for v in g.export().values()]
+    g.extract_paths(n=-1, k=k)
+    p = g.paths()
+    out += [p[q] for q in ("path_ptr", "path_pins", "path_slack")]
+    value = g.stns_fwd(x, y, 10.0)
+    for _ in range(2):
+        gx, gy = torch.zeros_like(x), torch.zeros_like(y)
+        g.stns_bwd(torch.ones((), dtype=torch.float64, device="cuda"), gx, gy)
+        out += [gx.cpu().numpy(), gy.cpu().numpy()]
+    return out + [float(value), g.summary()]
+
+
+@pytest.mark.parametrize("cells,depth,k,prec,fanin_hi", [(300, 40, 1, "f32", 4), (5000, 60, 3, "f32", 4),
+                                                         (20_000, 50, 20, "f32", 4),
+                                                         (3000, 60, 1, "f64", 4)])
+def test_sweeps_by_tickets(library, cells, depth, k, prec, fanin_hi):
+    """A budget so small that waves soon leave their fixed shares and large
+    enough to end by tickets: the results are the same bits, and no error."""
+    from paper_2503_11674_amd import tdp
+    cfg = netgen.NetlistConfig("t", cells, ff_frac=0.15, depth=depth, fanin_lo=1, fanin_hi=fanin_hi, fanout_cap=20,
+                               die=15.0 * cells ** 0.5, seed=9)
+    nl = with_clock(netgen.make_netlist(cfg), library, 0.3)
+    x, y = _xy(nl)
+    for model in (0, 2):
+        outs = []
+        for form in ("levels", "shares", "tickets"):
+            g = tdp.TimingGraph(nl, dict(library, net_model=model), precision=prec, max_paths=20_000, max_k=k)
+            if form == "levels":
+                g.set_tuning(sweep_mode=0)
+            elif form == "tickets" and prec == "f32":
+                g.set_tuning(spin_log2=12)
+            for i in range(3):
+                if i == 1:
+                    g.sta_update_arrivals(x, y)
+                    g.sta_update_required()
+                    g.sta_update_required()
+                else:
+                    g.sta_update(x, y)
+                outs.append(_all_results(g, x, y, k))
+            g.close()
+        for o in outs[1:]:
+            for a, b in zip(outs[0], o):
+                assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("graphs,k", [(3, 16), (8, 10), (16, 1)])
+def test_sweeps_of_many_graphs_at_once(library, graphs, k):
+    """Graphs on streams of their own, more than their grids fit on the GPU."""
+    from paper_2503_11674_amd import tdp
+    work = []
+    for i in range(graphs):
+        nl = _design(library, 20_000 + 700 * i, 40, seed=i)
+        g = tdp.TimingGraph(nl, library, max_paths=5000, max_k=k)
+        x, y = _xy(nl)
+        g.sta_update(x, y)
+        want = _all_results(g, x, y, k)
+        gx, gy = torch.zeros_like(x), torch.zeros_like(y)
+        work.append((g, x, y, gx, gy, want, torch.cuda.Stream()))
+    one = torch.ones((), dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(30):
+        for g, x, y, gx, gy, _, s in work:
+            with torch.cuda.stream(s):
+                g.sta_update(x, y)
+                g.extract_paths(n=-1, k=k)
+                g.stns_fwd(x, y, 10.0)
+                g.stns_bwd(one, gx, gy)
+    torch.cuda.synchronize()
+    for g, x, y, _, _, want, s in work:
+        with torch.cuda.stream(s):
+            g.summary()
+        torch.cuda.synchronize()
+        for a, b in zip(want, _all_results(g, x, y, k)):
+            assert np.array_equal(a, b)
+        g.close()
