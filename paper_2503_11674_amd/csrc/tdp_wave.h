@@ -69,6 +69,12 @@ __device__ __forceinline__ int wave_lane() { return threadIdx.x & 63; }
 // the wave's number in its workgroup, as a scalar: loops over it need no lane masks
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
+// what the wave's lanes stored to LDS before is seen by all of them after it
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // words that waves of one launch exchange (relaxed device-scope accesses)
 __device__ __forceinline__ uint64_t pub_ld(const uint64_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

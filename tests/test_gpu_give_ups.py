@@ -103,7 +103,7 @@ def _all_results(g, x, y, k):
 
 
 @pytest.mark.parametrize("cells,depth,k,prec,fanin_hi", [(300, 40, 1, "f32", 4), (5000, 60, 3, "f32", 4),
-                                                         (20_000, 50, 20, "f32", 4),
+                                                         (5000, 60, 8, "f32", 20), (20_000, 50, 20, "f32", 4),
                                                          (3000, 60, 1, "f64", 4)])
 def test_sweeps_by_tickets(library, cells, depth, k, prec, fanin_hi):
     """A budget so small that waves soon leave their fixed shares and large
