@@ -173,9 +173,12 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
   g->slot_cap = std::max(1, T.E * max_k);
   g->pin_cap = (int32_t)((int64_t)max_paths * (2 * T.D + 2));
   g->key_bits32 = T.num_inst <= 1 ? 32 : (T.num_inst <= 256 ? 40 : 48);
-  int max_inst_e = 1;
-  for (int i = 0; i < T.num_inst; ++i) max_inst_e = std::max(max_inst_e, H.lv.ep_base[i + 1] - H.lv.ep_base[i]);
-  g->ep_chunks = std::min(256, std::max(1, (max_inst_e + 1023) / 1024));
+  std::vector<int4> ep_jobs;
+  for (int i = 0; i < T.num_inst; ++i) {
+    const int parts = std::min(256, std::max(1, (H.lv.ep_base[i + 1] - H.lv.ep_base[i] + 1023) / 1024));
+    for (int j = 0; j < parts; ++j) ep_jobs.push_back(make_int4(i, parts, j, 0));
+  }
+  g->n_ep_jobs = (int32_t)ep_jobs.size();
 
   bool ok = true;
   // library
@@ -219,7 +222,8 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
        dalloc(g, g->darc, T.A, es) && dalloc(g, g->crit, T.n_comb) &&
        dalloc(g, g->node, (size_t)T.n_comb * (es == 8 ? node_words<double>(g->side_k) : node_words<float>(g->side_k))) &&
        dalloc(g, g->cdep, T.M) && dalloc(g, g->d_tag, 3) && dalloc(g, g->ep_slack, T.E, es) &&
-       dalloc(g, g->red_ep, (size_t)3 * T.num_inst * g->ep_chunks) && dalloc(g, g->red_loss, 4096) &&
+       dalloc(g, g->red_ep, (size_t)3 * g->n_ep_jobs) && upload(g, g->ep_jobs, ep_jobs) &&
+       dalloc(g, g->ep_counts, T.num_inst) && dalloc(g, g->red_loss, 4096) &&
        dalloc(g, g->red_p2p, 1024) &&
        dalloc(g, g->red_wa, 4096) && dalloc(g, g->summary, (size_t)4 * T.num_inst) &&
        dalloc(g, g->d_err, 4) && dalloc(g, g->consts, 4) &&

@@ -295,7 +295,7 @@ struct tdp_graph_s {
   std::vector<double> h_inst_req;
   double *d_inst_req = nullptr;
   int32_t max_paths = 0, max_k = 1, side_k = 1, max_out = 0, max_out_inst = 0, slot_cap = 0, pin_cap = 0;
-  int32_t key_bits32 = 40, ep_chunks = 1;
+  int32_t key_bits32 = 40, n_ep_jobs = 0;
   int32_t tune_block = 256, tune_chunk = 1, sweep_mode = 0;
   std::string last_error;
   bool updated = false, extracted = false, pairs_built = false, stns_ready = false;
@@ -343,6 +343,8 @@ struct tdp_graph_s {
   double *red_ep = nullptr, *red_loss = nullptr, *red_p2p = nullptr, *red_wa = nullptr;
   double *summary = nullptr;     // [4 * num_inst]: wns, tns, n_fail, 0
   int32_t *d_ep_base = nullptr;
+  int4 *ep_jobs = nullptr;       // [n_ep_jobs] of the endpoint summary: {instance, its parts, this part, 0}
+  uint32_t *ep_counts = nullptr; // [num_inst] workgroups done
 
   // extraction
   int32_t *sel_flag = nullptr, *sel_pos = nullptr, *sel_list = nullptr, *d_nsel = nullptr;

@@ -504,22 +504,28 @@ __global__ void __launch_bounds__(256) k_forward(Topo tp, LutView L, int ch0, in
 
 // ------------------------------------------------------------- endpoints
 // Slack at every D pin (SLACK; otherwise ep_slack holds them already), and per
-// instance {min, sum of negatives, count of negatives}: workgroup j of an
-// instance takes the j-th part of its endpoints, and the last workgroup to be
-// done folds the parts, in order.  One launch: 9 us at 20,000 endpoints, 13 at
-// 240,000; as three (slacks, partial sums, one thread's fold) 17 and 23.
+// instance {min, sum of negatives, count of negatives}: a workgroup takes one part
+// of an instance's endpoints (job: the instance, its number of parts, this one),
+// and the last workgroup of the instance to be done folds its parts, in order.
+// One launch: 9 us at 20,000 endpoints, 13 at 240,000; as three (slacks, partial
+// sums, one thread's fold) 17 and 23.  Every instance counts its own workgroups
+// and has no more of them than its own endpoints ask for: with one count, one
+// number of parts and one fold for all, the update of 1,000 designs of 100 cells
+// took 1,070 us, with this 64 (4,000 of 60: 4,111 and 82; 24 of 3,000: 91 and 66).
 template <typename T, bool SLACK>
-__global__ void __launch_bounds__(256) k_endpoint(Topo tp, const int32_t *__restrict__ ep_base, int chunks,
+__global__ void __launch_bounds__(256) k_endpoint(Topo tp, const int32_t *__restrict__ ep_base,
+                                                   const int4 *__restrict__ jobs,
                                                    const double *__restrict__ inst_req, const T *__restrict__ dnet,
                                                    T *__restrict__ at, T *__restrict__ rat, T *__restrict__ ep_slack,
-                                                   double *__restrict__ part, uint32_t *__restrict__ ctr,
+                                                   double *__restrict__ part, uint32_t *__restrict__ counts,
                                                    double *__restrict__ summary) {
   __shared__ double smin[256], ssum[256], scnt[256];
-  const uint32_t launch = ctr[0];
-  const int inst = blockIdx.x / chunks, j = blockIdx.x % chunks;
+  __shared__ int s_last;
+  const int4 job = jobs[blockIdx.x];
+  const int inst = job.x, parts = job.y, j = job.z;
   const int b = ep_base[inst], e = ep_base[inst + 1];
   const int len = e - b;
-  const int lo = b + (int)((long long)len * j / chunks), hi = b + (int)((long long)len * (j + 1) / chunks);
+  const int lo = b + (int)((long long)len * j / parts), hi = b + (int)((long long)len * (j + 1) / parts);
   const T req = SLACK ? (T)inst_req[inst] : (T)0;
   double mn = 0.0, sm = 0.0, ct = 0.0;
   for (int f = lo + threadIdx.x; f < hi; f += blockDim.x) {
@@ -556,28 +562,31 @@ __global__ void __launch_bounds__(256) k_endpoint(Topo tp, const int32_t *__rest
     }
   };
   fold();
-  if (threadIdx.x == 0) {
-    pub_st(part + 3 * blockIdx.x + 0, smin[0]);
-    pub_st(part + 3 * blockIdx.x + 1, ssum[0]);
-    pub_st(part + 3 * blockIdx.x + 2, scnt[0]);
-  }
-  if (!look_done(Look{nullptr, ctr, nullptr}, launch)) return;
-  for (int i = 0; i < tp.num_inst; ++i) {
+  if (parts > 1) {
+    if (threadIdx.x == 0) {
+      pub_st(part + 3 * blockIdx.x + 0, smin[0]);
+      pub_st(part + 3 * blockIdx.x + 1, ssum[0]);
+      pub_st(part + 3 * blockIdx.x + 2, scnt[0]);
+      stores_arrived();
+      s_last = atomicAdd(counts + inst, 1u) == (uint32_t)parts - 1;
+      if (s_last) pub_st(counts + inst, 0u);
+    }
+    __syncthreads();
+    if (!s_last) return;
     mn = sm = ct = 0.0;
-    if ((int)threadIdx.x < chunks) {  // (at most 256)
-      const double *p = part + 3 * ((size_t)i * chunks + threadIdx.x);
+    if ((int)threadIdx.x < parts) {  // (at most 256)
+      const double *p = part + 3 * ((size_t)blockIdx.x - j + threadIdx.x);
       mn = pub_ld(p);
       sm = pub_ld(p + 1);
       ct = pub_ld(p + 2);
     }
     fold();
-    if (threadIdx.x == 0) {
-      summary[4 * i + 0] = smin[0];
-      summary[4 * i + 1] = ssum[0];
-      summary[4 * i + 2] = scnt[0];
-      summary[4 * i + 3] = 0.0;
-    }
-    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    summary[4 * inst + 0] = smin[0];
+    summary[4 * inst + 1] = ssum[0];
+    summary[4 * inst + 2] = scnt[0];
+    summary[4 * inst + 3] = 0.0;
   }
 }
 
@@ -1236,9 +1245,9 @@ static void netpass_launch(tdp_graph g, const float *x, const float *y, const Fl
 template <typename T, bool SLACK>
 static void endpoint_launch(tdp_graph g, hipStream_t s) {
   const Topo &tp = g->topo;
-  hipLaunchKernelGGL((k_endpoint<T, SLACK>), dim3(tp.num_inst * g->ep_chunks), dim3(256), 0, s, tp, g->d_ep_base,
-                     g->ep_chunks, g->d_inst_req, (const T *)g->dnet, (T *)g->at, (T *)g->rat, (T *)g->ep_slack,
-                     g->red_ep, g->look_ctr, g->summary);
+  hipLaunchKernelGGL((k_endpoint<T, SLACK>), dim3(g->n_ep_jobs), dim3(256), 0, s, tp, g->d_ep_base, g->ep_jobs,
+                     g->d_inst_req, (const T *)g->dnet, (T *)g->at, (T *)g->rat, (T *)g->ep_slack,
+                     g->red_ep, g->ep_counts, g->summary);
 }
 
 template <typename T>
