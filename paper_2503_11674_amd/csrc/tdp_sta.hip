@@ -307,11 +307,15 @@ __device__ __forceinline__ void fw_arrivals(const Topo &tp, const LutView &L, fl
     dn = dnet[t];
   }
   // incremental: whether the net pass marked the chunk or an input's driver
-  // changed, and the cell's previous output (issued with the same loads)
+  // changed, and the cell's previous output and hop (issued with the same loads)
+  ulonglong2 old_hop = make_ulonglong2(0, 0);
   bool mark = false;
   if (inc.arr && valid) {
     mark = inc.drv_chg[s] == inc.epoch || inc.arr[chunk] == inc.epoch;
-    if (lane == head) old = as[tp.n_start + c];
+    if (lane == head) {
+      old = as[tp.n_start + c];
+      old_hop = *reinterpret_cast<const ulonglong2 *>(node + (size_t)c * words);
+    }
   }
   stage_lut(L, s_lut);
   if (chunk >= ch1) return;
@@ -342,12 +346,9 @@ __device__ __forceinline__ void fw_arrivals(const Topo &tp, const LutView &L, fl
     slew[v] = so;
     as[v] = v2<T>(best, so);
     crit[c] = argl - head;
-    ulonglong2 *hop = reinterpret_cast<ulonglong2 *>(node + (size_t)c * words);
-    if (inc.arr) {  // the records above copy this hop (the tag is the last full pass's)
-      const ulonglong2 o = *hop;
-      if (o.x != h0 || o.y != h1) inc.drv_lchg[v] = inc.epoch;
-    }
-    *hop = make_ulonglong2(h0, h1);
+    // (the records above copy this hop; the tag is the last full pass's)
+    if (inc.arr && (old_hop.x != h0 || old_hop.y != h1)) inc.drv_lchg[v] = inc.epoch;
+    *reinterpret_cast<ulonglong2 *>(node + (size_t)c * words) = make_ulonglong2(h0, h1);
   }
 }
 
