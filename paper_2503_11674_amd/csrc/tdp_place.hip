@@ -245,9 +245,17 @@ constexpr int DN_STRIP = 4;
 // serial chain, and one of 500 in a strip (cells against the die's edge) took
 // twice as long as all the rest (146 us against 59 and 8 more in k_dn_heavy).
 constexpr int DN_ROW = 64;
+// On a grid of many bins whose rows hold almost that many cells on average, that
+// would make crowded bins of a good part of them, each with a workgroup's fixed
+// cost: there a row may have some more.  500,000 cells evenly over 200 x 200 bins,
+// R = 2 (rows of 62), the whole evaluation: 215 us against 258 (222 with a thread a
+// bin); 256 x 256, R = 3 (53): 211 against 260.  On 128 x 128, R = 1 (91) or where
+// the cells are few for the bins, the lower bound is the better one (165 against
+// 177, clusters 250 against 239).
+constexpr int DN_ROW_FULL = 80, DN_FULL_MEAN = 40, DN_FULL_BINS = 1 << 15;
 
 template <int R>
-__global__ void __launch_bounds__(1024) k_dn_strip(int n, int run, DensityGrid gr, const int32_t *__restrict__ start,
+__global__ void __launch_bounds__(1024) k_dn_strip(int n, int run, int row, DensityGrid gr, const int32_t *__restrict__ start,
                                                     const float *__restrict__ w, float *__restrict__ map,
                                                     int32_t *__restrict__ heavy, int32_t *__restrict__ n_heavy) {
   constexpr int K = 2 * R + 1, ROWS = 16, H = ROWS - 2 * R;
@@ -267,7 +275,7 @@ __global__ void __launch_bounds__(1024) k_dn_strip(int n, int run, DensityGrid g
 #pragma unroll
     for (int k = 0; k <= K; ++k) at[k] = start[sj * gr.gx + min(max(i - R + k, 0), gr.gx)];
     cnt = at[K] - at[0];
-    if (cnt <= DN_ROW) {  // (otherwise every bin that needs the row is crowded)
+    if (cnt <= row) {  // (otherwise every bin that needs the row is crowded)
 #pragma unroll 2
       for (int s = at[0]; s < at[K]; ++s) {
         int col = 2 * R;  // the x weight of a cell k bins along is its (2R - k)-th
@@ -295,7 +303,7 @@ __global__ void __launch_bounds__(1024) k_dn_strip(int n, int run, DensityGrid g
     sum += s_part[q + r][2 * R - r][lane];
   }
   const int b = (j0 + q) * gr.gx + i;
-  if (cnt > DN_HEAVY || most > DN_ROW) heavy[atomicAdd(n_heavy, 1)] = b;  // summed by k_dn_heavy
+  if (cnt > DN_HEAVY || most > row) heavy[atomicAdd(n_heavy, 1)] = b;  // summed by k_dn_heavy
   else map[b] = (float)sum;
 }
 
@@ -510,7 +518,9 @@ static void density_launch(tdp_graph g, const float *x, const float *y, float sc
   float *map = map_out ? map_out : g->dn_map;
   if constexpr (R <= DN_STRIP) {
     const int cols = nbk(gr.gx, 64);
-    hipLaunchKernelGGL(k_dn_strip<R>, dim3(cols * nbk(gr.gy, 16 - 2 * R)), dim3(1024), 0, s, n, 2 * cols, gr,
+    const bool full = G >= DN_FULL_BINS && (long long)n * (2 * R + 1) > (long long)DN_FULL_MEAN * G;
+    const int row = full ? DN_ROW_FULL : DN_ROW;
+    hipLaunchKernelGGL(k_dn_strip<R>, dim3(cols * nbk(gr.gy, 16 - 2 * R)), dim3(1024), 0, s, n, 2 * cols, row, gr,
                        (const int32_t *)g->dn_start, (const float *)g->dn_w, map, g->dn_heavy, g->dn_nheavy);
   } else {
     hipLaunchKernelGGL(k_dn_bins<R>, dim3(nbk(G, DN_BLOCK / DN_LANES)), dim3(DN_BLOCK), 0, s, n,

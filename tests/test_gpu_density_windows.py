@@ -55,3 +55,20 @@ def test_crowded_rows_and_windows(library, row, R):
     y[:] = 50.25
     _check_density(g, nl, x, y, area, grid, 0.5)
     g.close()
+
+
+@pytest.mark.parametrize("gx,gy", [(182, 181), (181, 181)])  # 32,942 and 32,761 bins
+def test_rows_that_are_almost_crowded_on_average(library, gx, gy):
+    """Many bins with rows of 40 to 90 cells: which rows make a bin crowded
+    depends on the mean and on the number of bins."""
+    nl, g = _graph(library, 300_000)
+    n = nl["num_cells"]
+    area = np.full(n, 2.0, np.float32)
+    grid = dict(x0=0.0, y0=0.0, bw=4.0, bh=4.0, gx=gx, gy=gy, R=3, target=0.5)
+    g.density_setup(grid, area)
+    rng = np.random.default_rng(gx)
+    x = rng.uniform(0.0, 4.0 * gx, n).astype(np.float32)
+    y = rng.uniform(0.0, 4.0 * gy, n).astype(np.float32)
+    x[:600], y[:600] = 300.0 + rng.uniform(0.0, 20.0, 600), 305.25
+    _check_density(g, nl, x, y, area, grid, 0.5)
+    g.close()
