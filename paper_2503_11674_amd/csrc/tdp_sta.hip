@@ -1008,10 +1008,13 @@ __global__ void __launch_bounds__(256) k_forward_flow(Topo tp, LutView L, int n_
 // the driver lane publishes its cell's inputs', a consecutive run: one random
 // read a sink where PULL has two and a random write, but three times the
 // published words.  Many chunks per wave are bound by the random accesses and
-// take PUSH (2M cells: 277 us against 345; 1M: 168 against 175), few by the
-// chain and take PULL (200k: 97 against 105; 2k: 26 against 30).
+// take PUSH, few by the chain and take PULL.  The required pass by itself, PUSH
+// and PULL: 2M cells (120,623 chunks) 298 and 359 us, 1.4M (75,479) 215 and 232, 1M
+// of 2 to 4 inputs (60,312) 190 and 200, 1M of 1 to 4 (53,901) 184 and 182, in
+// double precision 193 and 197, 600,000 (32,352) 149 and 140, 200,000 (10,786) 119
+// and 106.
 constexpr int FANIN_AHEAD = 4;         // PUSH: inputs whose arcs are loaded before the wait
-constexpr int PUSH_CHUNKS_PER_CU = 256;  // net chunks from which PUSH is taken
+constexpr int PUSH_CHUNKS_PER_CU = 224;  // net chunks from which PUSH is taken (57,344 on 256 compute units)
 
 static bool backward_pushes(const tdp_graph_s *g) {
   return g->topo.n_nm_chunks >= (long long)PUSH_CHUNKS_PER_CU * std::max(1, g->num_cu);
