@@ -219,31 +219,53 @@ __global__ void k_sel_keys(Topo tp, const T *__restrict__ ep_slack, uint64_t *__
   vals[f] = f;
 }
 
+// first of the ascending keys[0, n) whose low word is >= key, or n: 1,024 places
+// looked at per round by the workgroup's 1,024 threads, two or three rounds
+__device__ __forceinline__ int block_lower_bound(const uint64_t *__restrict__ keys, int n, uint32_t key) {
+  int lo = 0, hi = n;  // the answer lies in [lo, hi]
+  while (lo < hi) {
+    const int step = (hi - lo + 1023) / 1024, at = lo + (int)threadIdx.x * step;
+    const int below = __syncthreads_count(at < hi && (uint32_t)keys[at] < key);  // (the first `below` threads')
+    if (below == 0) return lo;
+    const int next = lo + (below - 1) * step;
+    hi = min(hi, next + step);
+    lo = next + 1;
+  }
+  return lo;
+}
+
+// The sorted keys tell where the finite slacks and the cut's equals begin and end
+// (a count over the slacks themselves took 143 us of 466 for 140,000 of as many
+// endpoints).  A double that rounds to infinity is counted by itself.
 template <typename T>
 __global__ void __launch_bounds__(1024) k_sel_cut_sorted(const int32_t *__restrict__ ep_base,
                                                           const T *__restrict__ ep_slack,
                                                           const uint64_t *__restrict__ keys,
                                                           const uint32_t *__restrict__ perm, int n,
                                                           int32_t *__restrict__ cut) {
-  __shared__ int s_take, s_equal;
+  __shared__ int s_more;
   const int b = ep_base[blockIdx.x], e = ep_base[blockIdx.x + 1];
-  if (threadIdx.x == 0) s_take = s_equal = 0;
+  if (threadIdx.x == 0) s_more = 0;
   __syncthreads();
   const int m = min(n, e - b);
-  int c = 0;
-  for (int j = threadIdx.x; j < m; j += 1024) c += ep_slack[perm[b + j]] < inf_of<T>();
-  if (c) atomicAdd(&s_take, c);
-  __syncthreads();
-  const int take = s_take;
+  const uint32_t inf = (uint32_t)order_key(inf_of<float>());
+  // (below minus infinity there are only NaNs)
+  const int from = block_lower_bound(keys + b, m, (uint32_t)order_key(-inf_of<float>()));
+  const int to = block_lower_bound(keys + b, m, inf);
+  if constexpr (sizeof(T) == 8) {
+    int c = 0;
+    for (int j = to + (int)threadIdx.x; j < m && (uint32_t)keys[b + j] == inf; j += 1024)
+      c += ep_slack[perm[b + j]] < inf_of<T>();
+    if (c) atomicAdd(&s_more, c);
+    __syncthreads();
+  }
+  const int take = to - from + s_more;
   const uint32_t key = take > 0 ? (uint32_t)keys[b + take - 1] : 0u;
-  c = 0;
-  for (int j = threadIdx.x; j < take; j += 1024) c += (uint32_t)keys[b + j] == key;
-  if (c) atomicAdd(&s_equal, c);
-  __syncthreads();
+  const int equal = block_lower_bound(keys + b, take, key);
   if (threadIdx.x == 0) {
     cut[SEL_CUT * blockIdx.x] = (int)key;
     cut[SEL_CUT * blockIdx.x + 1] = take;
-    cut[SEL_CUT * blockIdx.x + 2] = s_equal;
+    cut[SEL_CUT * blockIdx.x + 2] = take - equal;
   }
 }
 
