@@ -11,8 +11,7 @@ namespace tdp {
 // published words of the dataflow sweeps (relaxed device-scope atomics; a
 // consumer polls one word, so no fences are needed)
 constexpr uint64_t W_EMPTY = ~0ull;
-// a published required time: its bits, all ones = not yet (no computed value,
-// NaN included, has that pattern)
+// a published required time or sum: its bits, all ones = not yet
 template <typename T> struct ReqWord;
 template <> struct ReqWord<float> {
   using type = uint32_t;
@@ -24,6 +23,12 @@ template <> struct ReqWord<double> {
   static __device__ __forceinline__ uint64_t bits(double v) { return (uint64_t)__double_as_longlong(v); }
   static __device__ __forceinline__ double value(uint64_t w) { return __longlong_as_double((long long)w); }
 };
+
+// a value as its word (a NaN may have come in with the positions and have any pattern)
+template <typename T>
+__device__ __forceinline__ typename ReqWord<T>::type pub_bits(T v) {
+  return ReqWord<T>::bits(v == v ? v : (T)__builtin_nan(""));
+}
 
 // Shares and tickets.  A resident sweep gives every wave a fixed share of its chunks, which needs all
 // its workgroups on the GPU.  Other streams may keep some of them out for as long

@@ -48,13 +48,6 @@ __device__ __forceinline__ T sgn(T v) {
   return (T)((v > (T)0) - (v < (T)0));
 }
 
-// a value as the word that the dataflow sweeps publish: all ones means not yet,
-// which no NaN made here has
-template <typename T>
-__device__ __forceinline__ typename ReqWord<T>::type pub_bits(T v) {
-  return ReqWord<T>::bits(v == v ? v : (T)__builtin_nan(""));
-}
-
 // start points' arrivals; every other driver's word, and every driver's
 // adjoint, not yet
 template <typename T>

@@ -37,6 +37,17 @@ __device__ __forceinline__ uint64_t pack2(float lo, float hi) {
   return (uint64_t)__float_as_uint(lo) | ((uint64_t)__float_as_uint(hi) << 32);
 }
 
+// A driver's {arrival, transition} as published words.  All ones means "not yet":
+// NaNs that came in with the positions may have that pattern, and get another.
+__device__ __forceinline__ uint64_t flow_word(float a, float s) {
+  const uint64_t w = pack2(a, s);
+  return w != W_EMPTY ? w : pack2(__builtin_nanf(""), __builtin_nanf(""));
+}
+__device__ __forceinline__ uint64_t flow_word(double a) {
+  const uint64_t w = (uint64_t)__double_as_longlong(a);
+  return w != W_EMPTY ? w : (uint64_t)__double_as_longlong(__builtin_nan(""));
+}
+
 struct FlowInit {
   uint64_t *w = nullptr;
   void *r = nullptr;              // the backward sweep's published words and their count
@@ -123,10 +134,10 @@ __device__ __forceinline__ void start_point(const Topo &tp, const LutView &L, in
     // seed the start points' words of the dataflow sweeps
     if (fl.w) {
       if constexpr (sizeof(T) == 4) {
-        fl.w[v] = fl.seed ? pack2(a, s) : W_EMPTY;
+        fl.w[v] = fl.seed ? flow_word(a, s) : W_EMPTY;
       } else {
-        fl.w[2 * (size_t)v] = fl.seed ? (uint64_t)__double_as_longlong(a) : W_EMPTY;
-        fl.w[2 * (size_t)v + 1] = fl.seed ? (uint64_t)__double_as_longlong(s) : W_EMPTY;
+        fl.w[2 * (size_t)v] = fl.seed ? flow_word(a) : W_EMPTY;
+        fl.w[2 * (size_t)v + 1] = fl.seed ? flow_word(s) : W_EMPTY;
       }
     }
   }
@@ -756,10 +767,10 @@ __device__ __forceinline__ void arrive(const Topo &tp, const LutView &L, const f
   const int v = tp.n_start + c;
   if (is_head) {
     if constexpr (N == 1) {
-      pub_st(&fw[v], pack2(best, so));
+      pub_st(&fw[v], flow_word(best, so));
     } else {
-      pub_st(&fw[2 * (size_t)v], (uint64_t)__double_as_longlong(best));
-      pub_st(&fw[2 * (size_t)v + 1], (uint64_t)__double_as_longlong(so));
+      pub_st(&fw[2 * (size_t)v], flow_word(best));
+      pub_st(&fw[2 * (size_t)v + 1], flow_word(so));
     }
   }
   const uint64_t h0 = pack_ids(__shfl(t, argl & 63, 64), __shfl(s, argl & 63, 64), tag);
@@ -1049,7 +1060,7 @@ __device__ __forceinline__ void backward_chunk(const Topo &tp, int4 rec, int k, 
     if (driver && done) {
       auto publish = [&](int j, T d) {
         const T ri = r != inf ? r - d : inf;
-        pub_st(words + tp.M + t0 + j, ReqWord<T>::bits(ri == ri ? ri : (T)__builtin_nan("")));
+        pub_st(words + tp.M + t0 + j, pub_bits<T>(ri));
       };
 #pragma unroll
       for (int j = 0; j < FANIN_AHEAD; ++j)
@@ -1069,7 +1080,7 @@ __device__ __forceinline__ void backward_chunk(const Topo &tp, int4 rec, int k, 
       if (rt != inf) r = rt - dn;
     }
     r = seg_min(r, lane, head, tail);
-    if (driver && done) pub_st(&words[p], ReqWord<T>::bits(r));
+    if (driver && done) pub_st(&words[p], pub_bits<T>(r));
   }
   if (driver && done) rat[p] = r;
 }

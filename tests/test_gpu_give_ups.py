@@ -165,3 +165,34 @@ def test_sweeps_of_many_graphs_at_once(library, graphs, k):
         for a, b in zip(want, _all_results(g, x, y, k)):
             assert np.array_equal(a, b)
         g.close()
+
+
+@pytest.mark.parametrize("bits", [-1, -2, 0x7FFFFFFF, 0x7FC00000, 0x7F800000])
+@pytest.mark.parametrize("k,prec", [(1, "f32"), (4, "f32"), (1, "f64")])
+def test_positions_that_are_not_finite_spoil_their_own_instance(library, bits, k, prec):
+    """NaNs of every payload, the words' "not yet" among them, and infinities in
+    one design of a batch: no wait runs out, and the others' results stand."""
+    from paper_2503_11674_amd import tdp
+    nls = [_design(library, n, 12, seed=n) for n in (300, 700, 500)]
+    if prec == "f64":
+        nls = nls[1:2]
+    g = tdp.TimingGraph(nls if len(nls) > 1 else nls[0], library, precision=prec, max_paths=100, max_k=k)
+    x, y = _xy(*nls)
+    g.sta_update(x, y)
+    want = g.batch_summary()
+    first = g.batch_offsets()[1][1] if len(nls) > 1 else 0
+    bad = [a.clone() for a in (x, y)]
+    for a in bad:
+        a.view(torch.int32)[first:first + nls[-1 if prec == "f64" else 1]["num_cells"]:3] = bits
+    g.sta_update(*bad)
+    got = g.batch_summary()
+    for a, b in zip(want, got):
+        for i in (0, 2) if len(nls) > 1 else ():
+            assert a[i] == b[i]
+    with pytest.raises(tdp.TdpError) as e:
+        g.summary()
+    assert e.value.status == 1
+    g.sta_update(x, y)
+    for a, b in zip(want, g.batch_summary()):
+        assert np.array_equal(a, b)
+    g.close()
