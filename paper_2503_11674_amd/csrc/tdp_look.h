@@ -137,24 +137,27 @@ __device__ __forceinline__ void last_sum(uint32_t *ctr, int n, const double *par
 // (n is small): every workgroup raises its own flag, and one wave of each
 // polls the others' (1 us for up to 32 workgroups; a launch boundary costs 2
 // to 5).  Stores made with pub_st before it are seen by pub_ld after it.
-// Flags count up over launches and are never cleared: `phase` must be
-// larger at every call, `first` + 1, + 2, ... within a launch.
-__device__ __forceinline__ void group_barrier(uint32_t *flags, int n, uint32_t phase, int32_t *err) {
+// Flags count up over launches and are never cleared: `phase` must be larger at
+// every call.  Waits are bounded by `limit` polls: false, with bit 2 of *err set,
+// when one ran out; the workgroup then leaves without using what others store.
+__device__ __forceinline__ bool group_barrier(uint32_t *flags, int n, uint32_t phase, int32_t *err, int limit) {
   stores_arrived();
+  bool out = false;
   __syncthreads();
   if (n > 1 && threadIdx.x < 64) {
     if (threadIdx.x == 0) pub_st(flags + blockIdx.x, phase);
     for (int f = threadIdx.x; f < n; f += 64) {
       int it = 0;
       while ((int)(pub_ld(flags + f) - phase) < 0) {
-        if (++it > LOOK_MAX) {
+        if (++it > limit) {
           atomicOr(err, 2);
+          out = true;
           break;
         }
       }
     }
   }
-  __syncthreads();
+  return __syncthreads_or(out) == 0;
 }
 
 // exclusive sum of one value per thread over the workgroup (at most 16 waves); total in *total

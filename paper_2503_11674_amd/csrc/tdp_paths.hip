@@ -499,8 +499,11 @@ struct OrderBuf {
   uint64_t *w0, *w1;
   uint32_t *hist;   // [ORDER_GROUPS][256]
   uint64_t *total;  // [ORDER_GROUPS] kept slots and their pins
-  uint32_t *flags;  // [ORDER_GROUPS] barrier flags, then the phase reached by the launches so far
+  uint32_t *flags;  // [ORDER_GROUPS] barrier flags, then the phase that the launch's barriers count up from
+  int limit;        // polls per wait
 };
+// phases per launch at most: a barrier more than two a pass of 8 bits
+constexpr uint32_t ORDER_PHASES = 32;
 
 // Slots of instances that have at most RANK_MOST each are put in order by
 // counting, for every slot, the slots of its instance that come before it: no
@@ -521,7 +524,9 @@ __device__ __forceinline__ bool rank_orders(int num_inst, int k, const int32_t *
 
 __global__ void __launch_bounds__(1024) k_rank(Topo tp, int k, int slot_bits, const int32_t *__restrict__ d_nsel,
                                                 const int32_t *__restrict__ sel, const int32_t *__restrict__ inst_selb,
-                                                const float *__restrict__ slot_key, uint64_t *__restrict__ words) {
+                                                const float *__restrict__ slot_key, uint64_t *__restrict__ words,
+                                                uint32_t *__restrict__ order_phase) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *order_phase += ORDER_PHASES;  // (k_order's, which is next)
   __shared__ uint4 s_key[RANK_TILE / 4];
   __shared__ int s_cnt[16][64];
   const int n = *d_nsel * k;
@@ -602,8 +607,7 @@ __global__ void __launch_bounds__(1024) k_order(Topo tp, int k, int K, int key_b
   const int n = *d_nsel * k;
   const int groups = min((int)gridDim.x, max(1, (n + ORDER_RUN - 1) / ORDER_RUN));
   if (me >= groups) return;
-  const uint32_t start = ob.flags[ORDER_GROUPS];
-  uint32_t phase = start;
+  uint32_t phase = ob.flags[ORDER_GROUPS];
   // this workgroup's slots, and this wave's, in rounds of ORDER_ITEMS words a lane
   const int run = ((n + groups - 1) / groups + ORDER_RUN - 1) / ORDER_RUN * ORDER_RUN;
   const int b = min(n, me * run), e = min(n, b + run);
@@ -662,7 +666,7 @@ __global__ void __launch_bounds__(1024) k_order(Topo tp, int k, int K, int key_b
       }
       if (groups > 1) pub_st(ob.hist + me * 256 + tid, mine);
     }
-    group_barrier(ob.flags, groups, ++phase, err);
+    if (!group_barrier(ob.flags, groups, ++phase, err, ob.limit)) return;
     uint32_t before = 0, total = mine;
     if (tid < 256 && groups > 1) {
       total = 0;
@@ -690,7 +694,7 @@ __global__ void __launch_bounds__(1024) k_order(Topo tp, int k, int K, int key_b
         }
       }
     }
-    group_barrier(ob.flags, groups, ++phase, err);
+    if (!group_barrier(ob.flags, groups, ++phase, err, ob.limit)) return;
     uint64_t *t = wa;
     wa = wz;
     wz = t;
@@ -716,7 +720,7 @@ __global__ void __launch_bounds__(1024) k_order(Topo tp, int k, int K, int key_b
     block_exclusive(paths, &c);
     block_exclusive(pins, &p);
     if (tid == 0) pub_st(ob.total + me, (uint64_t)(uint32_t)c | (uint64_t)(uint32_t)p << 32);
-    group_barrier(ob.flags, groups, ++phase, err);
+    if (!group_barrier(ob.flags, groups, ++phase, err, ob.limit)) return;
     for (int g = 0; g < me; ++g) {
       const uint64_t w = pub_ld(ob.total + g);
       q0 += (int)(uint32_t)w;
@@ -740,8 +744,6 @@ __global__ void __launch_bounds__(1024) k_order(Topo tp, int k, int K, int key_b
     *d_num_paths = q0;
     path_ptr[q0] = p0;
   }
-  // (everyone has read the phase: a launch has a barrier, or one workgroup)
-  if (me == 0 && tid == 0) ob.flags[ORDER_GROUPS] = start + 2 * passes + 1;
 }
 
 // the same steps as launches of their own, where a slot's word does not fit
@@ -899,15 +901,21 @@ __global__ void __launch_bounds__(1024) k_order_one(Topo tp, int k, int K, const
 constexpr int WALK_PATHS = 32;  // per workgroup of 128
 
 template <typename T>
-__global__ void __launch_bounds__(128) k_walk(Topo tp, int k, const int32_t *__restrict__ d_num_paths,
+__global__ void __launch_bounds__(128) k_walk(Topo tp, int k, int32_t *__restrict__ d_num_paths,
                                                const int32_t *__restrict__ out_slot, const int32_t *__restrict__ sel,
                                                const int32_t *__restrict__ slot_dev, const int32_t *__restrict__ slot_par,
                                                const T *__restrict__ slot_key, const uint64_t *__restrict__ node,
-                                               int words, const int32_t *__restrict__ path_ptr,
+                                               int words, int32_t *__restrict__ path_ptr,
                                                int32_t *__restrict__ path_pins, int32_t *__restrict__ path_int,
                                                int32_t *__restrict__ path_ep, int32_t *__restrict__ path_epi,
                                                int32_t *__restrict__ path_rank, T *__restrict__ path_slack,
-                                               int32_t *__restrict__ err, int pin_cap) {
+                                               int32_t *__restrict__ err, int pin_cap, int32_t *__restrict__ d_nslots) {
+  // after a wait that ran out the order may be of several calls: no paths, and
+  // reading them reports it
+  if (*err & 2) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *d_num_paths = *d_nslots = path_ptr[0] = 0;
+    return;
+  }
   // a deviation: its sink, cell, driver and both external ids
   __shared__ int32_t s_dev[WALK_PATHS][TDP_MAX_K][5];
   const int lane = wave_lane(), h = lane & 3, first = lane & ~3, mine = threadIdx.x >> 2;
@@ -1102,11 +1110,12 @@ void extract_impl(tdp_graph g, int n, int k, int K, float slack_limit, hipStream
                        (const float *)g->slot_key, g->slot_len, g->d_nslots, g->out_slot, g->slot_out, g->path_ptr,
                        g->d_num_paths);
   } else if (sizeof(T) == 4 && g->key_bits32 + slot_bits <= 64) {
-    const OrderBuf ob{g->sort_k0, g->sort_k1, g->order_hist, g->order_total, g->order_flags};
+    const OrderBuf ob{g->sort_k0, g->sort_k1, g->order_hist, g->order_total, g->order_flags,
+                      (int)std::min<long long>(LOOK_MAX, 4ll * g->spin_limit)};
     // (no more workgroups than it can have slots for: with more slots they leave)
     const long long ranked = std::min(most, (long long)tp.num_inst * RANK_MOST);
     hipLaunchKernelGGL(k_rank, dim3((int)std::min<long long>(1024, (ranked + 63) / 64)), dim3(1024), 0, s, tp, k,
-                       slot_bits, g->d_nsel, g->sel_list, g->inst_selb, (const float *)g->slot_key, ob.w0);
+                       slot_bits, g->d_nsel, g->sel_list, g->inst_selb, (const float *)g->slot_key, ob.w0, ob.flags + ORDER_GROUPS);
     hipLaunchKernelGGL(k_order, dim3((int)std::min<long long>(ORDER_GROUPS, (most + ORDER_RUN - 1) / ORDER_RUN)),
                        dim3(1024), 0, s, tp, k, K, g->key_bits32, slot_bits, g->d_nsel, g->sel_list, g->inst_selb,
                        (const float *)g->slot_key, g->slot_len, ob, g->d_nslots, g->out_slot, g->slot_out, g->path_ptr,
@@ -1125,7 +1134,7 @@ void extract_impl(tdp_graph g, int n, int k, int K, float slack_limit, hipStream
                      g->out_slot,
                      g->sel_list, g->slot_dev, g->slot_par, (const T *)g->slot_key, g->node, node_words<T>(g->side_k),
                      g->path_ptr, g->path_pins, g->path_int, g->path_ep, g->path_epi, g->path_rank,
-                     (T *)g->path_slack, g->d_err, g->pin_cap);
+                     (T *)g->path_slack, g->d_err, g->pin_cap, g->d_nslots);
   prof_end(g, TDP_STAGE_WALK, s);
 }
 

@@ -196,3 +196,40 @@ def test_positions_that_are_not_finite_spoil_their_own_instance(library, bits, k
     for a, b in zip(want, g.batch_summary()):
         assert np.array_equal(a, b)
     g.close()
+
+
+def test_an_ordering_that_gave_up(library):
+    """Barriers of an ordering over several workgroups with a budget of a few
+    polls: the call's paths are right or reported, and the next ones are right."""
+    from paper_2503_11674_amd import tdp
+    cfg = netgen.NetlistConfig("o", 40_000, ff_frac=0.5, depth=6, fanin_lo=1, fanin_hi=4, fanout_cap=12, die=3000.0,
+                               seed=3)
+    nl = with_clock(netgen.make_netlist(cfg), library, 0.4)
+    g = tdp.TimingGraph(nl, library, max_paths=100_000, max_k=4)
+    x, y = _xy(nl)
+    names = ("path_ptr", "path_pins", "path_ep", "path_rank", "path_slack")
+    calls = [(-1, 4), (3000, 1), (10 ** 9, 4), (2000, 2)]
+    want = []
+    g.set_tuning(sweep_mode=0)
+    g.sta_update(x, y)
+    for n, k in calls:
+        g.extract_paths(n=n, k=k)
+        want.append(g.paths())
+    for rnd in range(6):
+        for (n, k), w in zip(calls, want):
+            g.set_tuning(spin_log2=1 + rnd % 3, sweep_mode=0)
+            g.sta_update(x, y)
+            g.extract_paths(n=n, k=k)
+            g.pairs_update()
+            try:
+                p = g.paths()
+            except tdp.TdpError as e:
+                assert e.status == DEVICE_ERROR
+            else:
+                assert all(np.array_equal(p[q], w[q]) for q in names)
+            g.set_tuning(spin_log2=20, sweep_mode=0)
+            g.sta_update(x, y)
+            g.extract_paths(n=n, k=k)
+            p = g.paths()
+            assert all(np.array_equal(p[q], w[q]) for q in names)
+    g.close()
