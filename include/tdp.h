@@ -528,8 +528,9 @@ tdp_status tdp_profile_read(tdp_graph, double *ms, int32_t *calls);
  *    points are never published, so every wait gives up.
  *  sweep_mode 3: arrivals one launch per level, required times on a
  *    resident grid.
- *  A new graph takes mode 1 where it is possible, otherwise a resident grid
- *  for each sweep that its precision, max_k and nets allow, until a mode is set.
+ *  sweep_mode 4: what a new graph takes, and any graph accepts: mode 1 where it
+ *    is possible, otherwise a resident grid for each sweep that the graph's
+ *    precision, max_k and nets allow.
  *  flow_waves: 64-lane waves per workgroup of the resident grids (1, 2 or
  *    4; 0 keeps; default 4);
  *  flow_per_cu: workgroups per compute unit of the resident grids (1..4,
@@ -549,7 +550,8 @@ tdp_status tdp_set_tuning(tdp_graph, int32_t flow_waves, int32_t flow_per_cu, in
  * extract_paths(n, k, K) (k = 0: the update alone) under every sweep
  * configuration the graph supports (per-level launches; resident dataflow
  * grids for both sweeps or for the required times only, with 1, 2 or 4
- * waves per workgroup and 1, 2 or 4 workgroups per compute unit), one
+ * waves per workgroup and 1, 2 or 4 workgroups per compute unit; for a graph
+ * that modes 1 to 3 do not take, per-level launches and mode 4), one
  * warm-up and `reps` timed runs each (1..1000), and keeps the fastest.
  * Choices are kept for the life of the process by graph signature (device,
  * precision, pin / cell / net / endpoint counts, depth, instances,

@@ -106,6 +106,9 @@ static double required_time(tdp_precision prec, float period, float setup) {
   return prec == TDP_F32 ? (double)(period - setup) : (double)period - (double)setup;
 }
 
+// the sweep mode of a new graph: both sweeps as grids, or each that it allows
+static int own_sweep_mode(const tdp_graph_s *g) { return g->flow_ok ? 1 : (g->fw_flow_ok || g->bw_flow_ok ? 4 : 0); }
+
 // state words of the one-launch prefix sums: the most tiles any of them has, times its values
 static size_t look_words(const Topo &T, int slots) {
   const size_t t = 4096;
@@ -233,7 +236,7 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
   g->fw_flow_ok = prec == TDP_F32 || g->side_k == 1;
   g->bw_flow_ok = T.n_big == 0;
   g->flow_ok = prec == TDP_F32 && T.n_big == 0;
-  g->sweep_mode = g->flow_ok ? 1 : (g->fw_flow_ok || g->bw_flow_ok ? 4 : 0);
+  g->sweep_mode = own_sweep_mode(g);
   if (ok && g->bw_flow_ok) ok = dalloc(g, g->flow_r, T.M, es);
   ok = ok && dalloc(g, g->share, NUM_SWEEPS) && dalloc(g, g->here, (size_t)NUM_SWEEPS * BLOCKS_PER_CU * g->num_cu);
   if (ok && g->fw_flow_ok) {
@@ -1100,13 +1103,13 @@ tdp_status tdp_set_tuning(tdp_graph g, int32_t flow_waves, int32_t flow_per_cu, 
     return fail(g, TDP_E_INVALID, "flow_waves must be 0, 1, 2 or 4");
   if (flow_per_cu < 0 || flow_per_cu > 4) return fail(g, TDP_E_INVALID, "flow_per_cu must be 0..4");
   if (spin_log2 != 0 && (spin_log2 < 1 || spin_log2 > 30)) return fail(g, TDP_E_INVALID, "spin_log2 out of range");
-  if (sweep_mode < 0 || sweep_mode > 3) return fail(g, TDP_E_INVALID, "sweep_mode must be 0..3");
-  if (sweep_mode >= 1 && !g->flow_ok)
+  if (sweep_mode < 0 || sweep_mode > 4) return fail(g, TDP_E_INVALID, "sweep_mode must be 0..4");
+  if (sweep_mode >= 1 && sweep_mode <= 3 && !g->flow_ok)
     return fail(g, TDP_E_UNSUPPORTED, "dataflow sweeps need single precision and nets of at most 63 sinks");
   if (flow_waves) g->flow_waves = flow_waves;
   if (flow_per_cu) g->flow_per_cu = flow_per_cu;
   if (spin_log2) g->spin_limit = 1 << spin_log2;
-  g->sweep_mode = sweep_mode;
+  g->sweep_mode = sweep_mode == 4 ? own_sweep_mode(g) : sweep_mode;
   return TDP_OK;
 }
 
@@ -1135,7 +1138,7 @@ tdp_status tdp_autotune(tdp_graph g, const float *x, const float *y, int32_t n, 
       g->flow_waves = it->second.waves;
       g->flow_per_cu = it->second.per_cu;
       if (choice) {
-        choice[0] = it->second.mode == 4 ? 0 : it->second.mode;
+        choice[0] = it->second.mode;
         choice[1] = it->second.waves;
         choice[2] = it->second.per_cu;
         choice[3] = it->second.us;
@@ -1148,7 +1151,8 @@ tdp_status tdp_autotune(tdp_graph g, const float *x, const float *y, int32_t n, 
   struct Cand {
     int mode, waves, per_cu;
   };
-  std::vector<Cand> cands = {{g->flow_ok ? 0 : g->sweep_mode, g->flow_waves, g->flow_per_cu}};
+  std::vector<Cand> cands = {{0, g->flow_waves, g->flow_per_cu}};
+  if (own_sweep_mode(g) == 4) cands.push_back({4, g->flow_waves, g->flow_per_cu});
   if (g->flow_ok)
     for (int w : {1, 2, 4})
       for (int pc : {1, 2, 4})
@@ -1204,7 +1208,7 @@ tdp_status tdp_autotune(tdp_graph g, const float *x, const float *y, int32_t n, 
   if (st != TDP_OK) return st;
   const int us = std::isfinite(best) ? (int32_t)std::lround(best * 1000.0f) : -1;
   if (choice) {
-    choice[0] = best_c.mode == 4 ? 0 : best_c.mode;
+    choice[0] = best_c.mode;
     choice[1] = best_c.waves;
     choice[2] = best_c.per_cu;
     choice[3] = us;

@@ -577,7 +577,8 @@ class TimingGraph:
     def set_tuning(self, flow_waves: int = 0, spin_log2: int = 0, sweep_mode: int = 1, flow_per_cu: int = 0):
         """sweep_mode 0: one launch per level; 1: dataflow sweeps on a resident
         grid; 2: self-test of the dataflow sweeps' bounded waits; 3: the
-        backward sweep as a dataflow grid, the forward one per level.  flow_waves:
+        backward sweep as a dataflow grid, the forward one per level; 4: what a
+        new graph takes.  flow_waves:
         waves per workgroup of the resident grids (1, 2, 4; 0 keeps);
         flow_per_cu: their workgroups per compute unit (1..4; 0 keeps)."""
         _check(tdp_set_tuning(self.h, flow_waves, flow_per_cu, spin_log2, sweep_mode), self.h)

@@ -225,3 +225,32 @@ def _fresh(nl, library, seed, k):
     out = _result(g, k)
     g.close()
     return out
+
+
+@pytest.mark.parametrize("prec,k", [("f64", 1), ("f64", 5), ("f32", 5)])
+def test_a_graphs_own_choice_can_be_had_back(library, prec, k):
+    """Mode 4 after another one, and by the autotuner: results as by level, and
+    the choice it reports is one that can be set."""
+    from paper_2503_11674_amd import tdp
+    nl = _design(library, cells=900 + k)
+    g = tdp.TimingGraph(nl, library, precision=prec, max_paths=4000, max_k=k)
+    g.set_tuning(sweep_mode=0)
+    x, y = _xy(nl)
+    g.sta_update(x, y)
+    want = _result(g, k)
+    if prec == "f64":
+        with pytest.raises(tdp.TdpError):
+            g.set_tuning(sweep_mode=1)
+    g.set_tuning(sweep_mode=4)
+    g.sta_update(x, y)
+    _same(_result(g, k), want)
+    g.set_tuning(sweep_mode=0)
+    ch = g.autotune(x, y, n=-1, k=k, reps=5)
+    assert ch["sweep_mode"] in ((0, 4) if prec == "f64" else (0, 1, 3))
+    _same(_result(g, k), want)
+    g.set_tuning(sweep_mode=ch["sweep_mode"])
+    assert g.autotune(x, y, n=-1, k=k, reps=5) == ch
+    _same(_result(g, k), want)
+    with pytest.raises(tdp.TdpError):
+        g.set_tuning(sweep_mode=5)
+    g.close()
