@@ -6,22 +6,24 @@
 //              (kappa * L^2 with L Manhattan, or the sink's Elmore delay),
 //              the driver's load (star model, a segmented sum); start points
 //              get arrival and transition.
-//   forward    one launch per level; one lane per combinational input pin,
-//              a cell's inputs adjacent: arrival = segmented max over inputs of
-//              (driver arrival + net delay + table delay at the input's
-//              transition, under the Elmore model the driver's degraded by the
-//              wire, and the output load), output transition =
-//              segmented max of the table transitions, the critical input =
-//              lowest lane attaining the max; the cell's head lane writes the
-//              output and, with deviation lists on, merges the cell's own
-//              deviations into the critical driver's list.
+//   forward    one lane per combinational input pin, a cell's inputs adjacent:
+//              arrival = segmented max over inputs of (driver arrival + net
+//              delay + table delay at the input's transition, under the Elmore
+//              model the driver's degraded by the wire, and the output load),
+//              output transition = segmented max of the table transitions, the
+//              critical input = lowest lane attaining the max; the cell's head
+//              lane writes the output.  Some lanes per cell then make its node
+//              record: hops up the critical chain and, with deviation lists on,
+//              the cell's own deviations merged into the critical driver's list.
 //   endpoint   slack at every D pin; WNS / TNS / count per instance in a
 //              fixed-order two-level reduction.
-//   backward   one launch per level from the top; one lane per net pin:
-//              required time of a driver = segmented min over its sinks of
-//              (sink required time - net delay); the driver lane then gives
-//              its cell's inputs their required time (output's minus the arc
-//              delay) and slack.
+//   backward   from the top; one lane per net pin: required time of a driver =
+//              segmented min over its sinks of (sink required time - net delay);
+//              a cell's inputs' are its output's minus the arc delays.
+// Either sweep runs in one launch on a resident grid, its waves waiting for the
+// words they read (the dataflow sweeps below), or in one launch per level:
+// incremental updates, deviation lists in double precision, required times with
+// a net wider than a chunk, and wherever sweep_mode asks for it.
 // Tables live in LDS for the forward sweep.  Nets with more than 63 sinks
 // take a one-thread-per-net path.
 #include "tdp_flow.h"
