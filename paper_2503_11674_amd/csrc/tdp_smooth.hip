@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(256) k_st_fwd(Topo tp, int ch0, int ch1, T gam
 
 // The whole forward sweep on a resident grid (see the dataflow sweeps of the
 // timing pass): wave w takes chunks w, w + W, ... in level order, waits for its
-// drivers' words and publishes its cells'.  Bound by the chain of levels: 156 us
+// drivers' words and publishes its cells'.  Bound by the chain of levels: 157 us
 // at 1M cells, 80 levels, against 312 with a launch per level.
 template <typename T, bool TICKETS>
 __device__ __forceinline__ void st_fwd_chunk(const Topo &tp, int4 rec, T gam, const T *__restrict__ dnl,
@@ -201,7 +201,7 @@ __global__ void __launch_bounds__(256) k_st_bwd(Topo tp, int ch0, int ch1, const
 // which also gathered the arc, both arrivals and the exponential of each share.
 // STAR: the pins' gradients under the star models as well, after the driver's
 // adjoint is out: the waves wait for most of a level's time, and part of the
-// gathers and the scatter fits in it (208 us at 1M cells against 147 + 82 in
+// gathers and the scatter fits in it (191 us at 1M cells against 147 + 82 in
 // two launches; 46 against 44 + 6 at 50,000).  Otherwise the sinks' adjoints go
 // to adj_nm for the spanning trees' launch.
 template <typename T, bool STAR, bool TICKETS>

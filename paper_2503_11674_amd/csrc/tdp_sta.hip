@@ -687,7 +687,7 @@ __global__ void k_backward_big(Topo tp, int i0, int i1, const T *__restrict__ dn
 // and no fence is needed.  Arrivals never wait for lists, so the arrival chain
 // runs at its own pace and the list chain trails it; in one wave that did
 // both (lists of a chunk after the arrivals of its next) each level took the
-// time of the slower of the two (200k cells, k = 10: 517 us against 152).
+// time of the slower of the two (200k cells, k = 10: 517 us against 149).
 // Both kinds wait only on lower-numbered chunks or cells and take theirs in
 // increasing order, so the lowest one not yet done can always run.
 //
@@ -1286,8 +1286,8 @@ void netpass_impl(tdp_graph g, const float *x, const float *y, hipStream_t s) {
 // A published deviation is one word, so lists in double precision stay with
 // the per-level launches; so do required times where a net is wider than a
 // chunk.  The grids win at every size measured (forward / backward us: 2k
-// cells, k = 10, 48 / 28 against 81 / 58; 200k 152 / 99 against 268 / 199; 2M,
-// k = 8, 457 / 277 against 682 / 557): no kernel boundary per level, static data
+// cells, k = 10, 45 / 28 against 81 / 58; 200k 149 / 98 against 268 / 199; 2M,
+// k = 8, 462 / 286 against 682 / 557): no kernel boundary per level, static data
 // loaded ahead, and lists off the arrivals' way.
 static bool flow_forward(const tdp_graph_s *g) {
   return g->sweep_mode == 1 || g->sweep_mode == 2 || (g->sweep_mode == 4 && g->fw_flow_ok);
