@@ -489,8 +489,8 @@ __global__ void k_slot_keys(Topo tp, int k, const int32_t *__restrict__ d_nsel, 
 // goes through device-scope stores and loads.  Bound by the barriers (two a
 // pass) and the round trips around them.  10,000 slots (200k cells): 50 us,
 // against 65 in nine launches and 103 in 22 (and 85 with 11-bit digits: more to
-// clear, add up and read per pass than a pass saves); 96,000 (2M cells): 71
-// against 78 and 105.  Without passes, behind k_rank: 12 us for 10,000.
+// clear, add up and read per pass than a pass saves); 96,000 (2M cells): 86
+// against 115 in eleven launches.  Without passes, behind k_rank: 12 us for 10,000.
 constexpr int ORDER_GROUPS = 64;
 constexpr int ORDER_ITEMS = 2;  // words per thread and round
 constexpr int ORDER_RUN = 1024 * ORDER_ITEMS;
