@@ -228,7 +228,7 @@ tdp_status tdp_sta_update_arrivals_incremental(tdp_graph, const float *d_x, cons
  * (the timing results of that pass are then meaningless); in a batched graph
  * such a position spoils its own instance only, and tdp_batch_summary gives the
  * others' values.  Both return TDP_E_DEVICE after a sweep that gave up waiting
- * (tdp_set_tuning). */
+ * (tdp_set_tuning), until the next full update. */
 tdp_status tdp_sta_summary(tdp_graph, double *wns, double *tns, int32_t *n_fail, hipStream_t);
 tdp_status tdp_batch_summary(tdp_graph, double *wns, double *tns, int32_t *n_fail, hipStream_t);
 

@@ -1372,6 +1372,10 @@ __global__ void k_pack_as(Topo tp, const uint32_t *__restrict__ stale, const T *
   for (int i = i0; i < tp.A; i += nth) fw_a[i] = at[tp.M + i] + darc[i];
 }
 
+// the error word of an incremental update: as it starts from the values of the
+// last pass, a sweep that gave up there stays noted until a full update
+__global__ void k_inc_begin(int32_t *err) { *err &= 2; }
+
 // the net chunks that hold a moved cell's pins: its output's net and the nets
 // of its inputs (bit 2 of err: an id outside [0, N))
 __global__ void k_inc_mark(Topo tp, const int32_t *__restrict__ cells, int n, const int32_t *__restrict__ drv_nm_chunk,
@@ -1413,7 +1417,7 @@ void sta_arrivals_incremental_impl(tdp_graph g, const float *x, const float *y, 
     hipLaunchKernelGGL(k_pack_as<T>, dim3(std::min(2048, nblk(std::max(tp.n_comb, tp.A), 256))),
                        dim3(256), 0, s, tp, g->d_tag + 2, (const T *)g->at, (const T *)g->slew, (const T *)g->darc,
                        (V2<T> *)g->drv_as, (T *)g->fw_a);
-  fill_i32(g->d_err, 1, 0, s);
+  hipLaunchKernelGGL(k_inc_begin, dim3(1), dim3(1), 0, s, g->d_err);
   if (n > 0)
     hipLaunchKernelGGL(k_inc_mark, dim3(nblk(n, 256)), dim3(256), 0, s, tp, cells, n, g->inc_drv_nm_chunk,
                        g->inc_nm, inc.epoch, g->d_err);

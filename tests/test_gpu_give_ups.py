@@ -233,3 +233,31 @@ def test_an_ordering_that_gave_up(library):
             p = g.paths()
             assert all(np.array_equal(p[q], w[q]) for q in names)
     g.close()
+
+
+def test_an_incremental_update_after_a_give_up(library):
+    """It starts from values that are not right, so the error stays until a full
+    update."""
+    from paper_2503_11674_amd import tdp
+    nl = _design(library, 3000, 12)
+    g = tdp.TimingGraph(nl, library, max_paths=100, max_k=4)
+    x, y = _xy(nl)
+    moved = torch.nonzero(torch.tensor(nl["cell_fixed"]) == 0)[:3, 0].to(torch.int32).cuda()
+    for spin in (4, 1):
+        g.set_tuning(spin_log2=20, sweep_mode=1)
+        g.sta_update(x, y)
+        want = g.summary()
+        g.sta_update_arrivals_incremental(x, y, moved)
+        g.sta_update_required()
+        assert g.summary() == want
+        g.set_tuning(spin_log2=spin, sweep_mode=2)
+        g.sta_update(x, y)
+        g.set_tuning(spin_log2=20, sweep_mode=1)
+        for _ in range(2):
+            g.sta_update_arrivals_incremental(x, y, moved)
+            g.sta_update_required()
+            _reports(tdp, g.summary)
+            _reports(tdp, g.batch_summary)
+        g.sta_update(x, y)
+        assert g.summary() == want
+    g.close()
