@@ -224,7 +224,7 @@ tdp_status build_common(const tdp_netlist *const *nls, int32_t count, const tdp_
        dalloc(g, g->fw_a, T.A, es) &&
        dalloc(g, g->darc, T.A, es) && dalloc(g, g->crit, T.n_comb) &&
        dalloc(g, g->node, (size_t)T.n_comb * (es == 8 ? node_words<double>(g->side_k) : node_words<float>(g->side_k))) &&
-       dalloc(g, g->cdep, T.M) && dalloc(g, g->d_tag, 3) && dalloc(g, g->ep_slack, T.E, es) &&
+       dalloc(g, g->cdep, T.M) && dalloc(g, g->d_tag, 4) && dalloc(g, g->ep_slack, T.E, es) &&
        dalloc(g, g->red_ep, (size_t)3 * g->n_ep_jobs) && upload(g, g->ep_jobs, ep_jobs) &&
        dalloc(g, g->ep_counts, T.num_inst) && dalloc(g, g->red_loss, 4096) &&
        dalloc(g, g->red_p2p, 1024) &&

@@ -318,8 +318,9 @@ struct tdp_graph_s {
   // node records and chain depths, as tagged words (see NodeRec below)
   uint64_t *node = nullptr;      // [n_comb][node_words]
   uint32_t *cdep = nullptr;      // [M] combinational cells on the critical chain
-  // [3] arrival passes so far; the last dataflow sweep gave up; drv_as
-  // (combinational drivers) and fw_a predate the last forward sweep
+  // [4] arrival passes so far; a dataflow sweep gave up before the last one; drv_as
+  // (combinational drivers) and fw_a predate the last forward sweep; a sweep gave
+  // up, kept by a net pass without an arrival pass
   uint32_t *d_tag = nullptr;
   void *ep_slack = nullptr;      // [E]
   // dataflow sweeps: published words polled by consumers

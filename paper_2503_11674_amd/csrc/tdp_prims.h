@@ -22,8 +22,8 @@ int sort_hist_size(int cap, int digit_bits);
 void fill_i32(int32_t *p, int n, int32_t v, hipStream_t s);
 // xy[i] = (x[i], y[i]): one 8-byte gather per random position lookup; where
 // a coordinate is NaN or infinite, *bad = gen (if bad is given); tag (if
-// given) counts the arrival passes and notes whether err has bit 1 set; *note
-// (if given) = noted
+// given) notes whether err has bit 1 set and, with a note, counts the arrival
+// passes; *note (if given) = noted
 void pack_xy(const float *x, const float *y, float2 *xy, int n, hipStream_t s, int32_t *bad = nullptr,
              int32_t gen = 0, const int32_t *err = nullptr, uint32_t *tag = nullptr, uint32_t *note = nullptr,
              uint32_t noted = 0);

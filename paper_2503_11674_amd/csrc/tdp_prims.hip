@@ -405,9 +405,14 @@ __global__ void k_pack_xy(const float *__restrict__ x, const float *__restrict__
                           uint32_t *__restrict__ tag, uint32_t *__restrict__ note, uint32_t noted) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (note && i == 0) *note = noted;
-  if (tag && i == 0) {  // a new arrival pass: its number, and whether the last sweep gave up (bit 1)
-    tag[0] = tag[0] + 1;
-    tag[1] = (*err & 2) != 0;
+  if (tag && i == 0) {
+    // whether a sweep gave up (bit 1) since the last arrival pass began: the word is cleared after this
+    const uint32_t gave_up = tag[3] | (*err & 2) >> 1;
+    if (note) {  // a new arrival pass
+      tag[0] = tag[0] + 1;
+      tag[1] = gave_up;
+    }
+    tag[3] = note ? 0 : gave_up;
   }
   if (i >= n) return;
   const float a = x[i], b = y[i];

@@ -1244,7 +1244,7 @@ static void netpass_launch(tdp_graph g, const float *x, const float *y, const Fl
   const NetModel<T> nm = net_model<T>(g);
   const bool tree = g->lut.net_model == 2;
   const T *tree_wl = tree ? (const T *)g->tree.wl : nullptr;
-  pack_xy(x, y, g->xy, tp.N, s, g->d_err + 1, ++g->pos_gen, g->d_err, sweep ? g->d_tag : nullptr,
+  pack_xy(x, y, g->xy, tp.N, s, g->d_err + 1, ++g->pos_gen, g->d_err, g->d_tag,
           sweep ? g->d_tag + 2 : nullptr, fl.w ? 1u : 0u);
   const auto k_np = tree ? k_netpass<T, true> : k_netpass<T, false>;
   hipLaunchKernelGGL(k_np, dim3(nblk(tp.n_nm_chunks, 4) + fl.reset_blocks),

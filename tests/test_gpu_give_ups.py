@@ -261,3 +261,44 @@ def test_an_incremental_update_after_a_give_up(library):
         g.sta_update(x, y)
         assert g.summary() == want
     g.close()
+
+
+@pytest.mark.parametrize("between", ["rise_fall", "incremental"])
+@pytest.mark.parametrize("give_ups", [1, 2, 3, 4])
+def test_give_ups_with_other_updates_between(library, between, give_ups):
+    """Records of the last good pass, four numbers old after three passes that
+    gave up, are not taken for the new pass's, also where another kind of
+    update has cleared the error word between them."""
+    from paper_2503_11674_amd import tdp
+    nl = _design(library, 3000, 12)
+    k = 4
+    sets = [[torch.tensor(a, device="cuda") for a in netgen.jitter_positions(nl, 30.0, s)] for s in (1, 2)]
+    moved = torch.arange(3, dtype=torch.int32, device="cuda")
+
+    def result(g):
+        g.extract_paths(n=-1, k=k)
+        p = g.paths()
+        return g.summary(), [p[key] for key in ("path_ptr", "path_pins", "path_ep", "path_slack")]
+
+    fresh = tdp.TimingGraph(nl, library, max_paths=4000, max_k=k)
+    fresh.set_tuning(sweep_mode=0)
+    fresh.sta_update(*sets[1])
+    want = result(fresh)
+    fresh.close()
+    g = tdp.TimingGraph(nl, library, max_paths=4000, max_k=k)
+    g.rf_setup(netgen.make_rf_library(library))
+    g.sta_update(*sets[0])
+    for _ in range(give_ups):
+        g.set_tuning(spin_log2=4, sweep_mode=2)
+        g.sta_update(*sets[0])
+        if between == "rise_fall":
+            g.sta_update_rf(*sets[0])
+        else:
+            g.sta_update_arrivals_incremental(*sets[0], moved)
+    g.set_tuning(spin_log2=20, sweep_mode=1)
+    g.sta_update(*sets[1])
+    got = result(g)
+    assert got[0] == want[0]
+    for a, b in zip(got[1], want[1]):
+        assert np.array_equal(a, b)
+    g.close()
